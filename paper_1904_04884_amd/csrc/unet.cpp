@@ -112,7 +112,9 @@ Net build_net(int L, int base) {
 // Activation / gradient buffers for one volume size.
 struct Buffers {
   size_t total = 0;
-  size_t packed = 0, in0 = 0, y = 0, gy8 = 0, loss = 0, part = 0;
+  size_t packed = 0, in0 = 0, y = 0, gy8 = 0, loss = 0, lpart = 0;
+  std::vector<size_t> wpart, bpart;   // gradient partials of each layer
+  std::vector<int> nblk;              // ... and their count
   std::vector<size_t> a, cat, p, idx, da, db, ga, gcat, gda, gdb, gp;
   size_t bbot = 0, gbbot = 0;
 };
@@ -169,25 +171,29 @@ Buffers layout(const Net& n, int D, int H, int W, bool train) {
       }
     }
     B.gbbot = take(nv(L - 1) * n.ch[L - 1] * 2);
-    // partial sums of the gradient reductions: the largest of any layer's
-    // weight (chunks x taps x C x N), bias (chunks x N) and loss (blocks) partials
-    size_t most = 16384;
-    auto chunks = [](long rows, long per) { return (size_t)((rows + per - 1) / per); };
+    // partial sums of every layer's weight and bias gradients, and of the loss
+    B.wpart.resize(n.layers.size());
+    B.bpart.resize(n.layers.size());
+    B.nblk.resize(n.layers.size());
+    auto grad = [&](int k, int mode, int lv) {   // lv: level of the rows
+      const Layer& y = n.layers[k];
+      const int taps = y.kind == CONV ? 27 : (y.kind == UP ? 8 : 1);
+      const int nb = wgrad_blocks(mode, D >> lv, H >> lv, W >> lv, y.cout, y.cin);
+      B.nblk[k] = nb;
+      B.wpart[k] = take((size_t)nb * taps * y.cin * y.cout * 4);
+      B.bpart[k] = take((size_t)nb * (y.kind == UP ? 8 : 1) * y.cout * 4);
+    };
     for (int l = 0; l < L; ++l) {
-      const long rows = (long)nv(l);
-      const size_t c = n.ch[l], cin = l == 0 ? 1 : n.ch[l - 1];
-      const size_t nw = chunks(rows, wgrad_rows_per_block(rows)), nbias = chunks(rows, bias_rows_per_block(rows));
-      most = std::max(most, nw * 27 * std::max(cin, c) * c);               // encoder a, b
-      most = std::max(most, nbias * 2 * c);
+      grad(n.enc_a(l), GG_CONV3_FWD, l);
+      grad(n.enc_b(l), GG_CONV3_FWD, l);
       if (l < L - 1) {
-        most = std::max(most, nw * 27 * 2 * c * c);                           // decoder a (2c in), b
-        const long crows = (long)nv(l + 1);
-        const size_t nu = chunks(crows, wgrad_rows_per_block(crows));
-        most = std::max(most, nu * 8 * (size_t)n.ch[l + 1] * c);              // up-convolution
+        grad(n.up(l), GG_UP_FWD, l + 1);
+        grad(n.dec_a(l), GG_CONV3_FWD, l);
+        grad(n.dec_b(l), GG_CONV3_FWD, l);
       }
     }
-    most = std::max(most, chunks((long)nv(0), wgrad_rows_per_block((long)nv(0))) * (size_t)n.ch[0]);   // head
-    B.part = take(most * 4);
+    grad(n.head(), GG_POINT, 0);
+    B.lpart = take((size_t)mse_blocks((long)nv(0)) * 4);
   }
   B.total = off;
   return B;
@@ -311,33 +317,31 @@ ri_status forward(const Net& n, const float* params, const float* in, float scal
   return RI_OK;
 }
 
-WgradArgs wg(int mode, int D, int H, int W, const uint16_t* g, int gcs, int gc0, int N, const uint16_t* src,
-             int scs, int sc0, int C, float* dw) {
-  WgradArgs w{};
-  w.mode = mode;
-  w.D = D; w.H = H; w.W = W;
-  w.g = g; w.g_cs = gcs; w.g_c0 = gc0; w.N = N; w.Npad = pad(N, 16);
-  w.s = src; w.s_cs = scs; w.s_c0 = sc0; w.C = C; w.Cpad = pad(C, 16);
-  w.dw = dw;
-  w.rows_per_block = 2048;
-  return w;
-}
-
-ri_status backward(const Net& n, const float* params, const float* target, float pos_weight, float* grads, int D,
-                   int H, int W, void* ws, const Buffers& B, hipStream_t s) {
+ri_status backward(const Net& n, const float* params, const float* target, float pos_weight, int D, int H, int W,
+                   void* ws, const Buffers& B, hipStream_t s) {
   const int L = n.L;
   uint16_t* pk = at<uint16_t>(ws, B.packed);
   const long nv0 = (long)D * H * W;
   uint16_t* gy8 = at<uint16_t>(ws, B.gy8);
   UTRY(launch_zero_u16(gy8, (size_t)nv0 * 8, s));
-  float* part = at<float>(ws, B.part);
-  UTRY(launch_mse(at<float>(ws, B.y), target, nv0, pos_weight, gy8, 8, at<float>(ws, B.loss), part, s));
+  UTRY(launch_mse(at<float>(ws, B.y), target, nv0, pos_weight, gy8, 8, at<float>(ws, B.lpart), s));
+  auto wgrad = [&](int k, int mode, int Dl, int Hl, int Wl, const uint16_t* g, int gcs, int gc0, const uint16_t* src,
+                   int scs, int sc0) {
+    const Layer& y = n.layers[k];
+    WgradArgs w{};
+    w.mode = mode;
+    w.D = Dl; w.H = Hl; w.W = Wl;
+    w.g = g; w.g_cs = gcs; w.g_c0 = gc0; w.N = y.cout;
+    w.s = src; w.s_cs = scs; w.s_c0 = sc0; w.C = y.cin;
+    w.part = at<float>(ws, B.wpart[k]);
+    w.bpart = at<float>(ws, B.bpart[k]);
+    return launch_wgrad(w, B.nblk[k], s);
+  };
   // head
   const Layer& hd = n.layers[n.head()];
   const uint16_t* top = L > 1 ? at<uint16_t>(ws, B.db[0]) : at<uint16_t>(ws, B.bbot);
   uint16_t* gtop = L > 1 ? at<uint16_t>(ws, B.gdb[0]) : at<uint16_t>(ws, B.gbbot);
-  UTRY(launch_wgrad(wg(GG_POINT, D, H, W, gy8, 8, 0, 1, top, n.ch[0], 0, n.ch[0], grads + hd.w), 1, part, s));
-  UTRY(launch_bias_grad(gy8, 8, 0, 1, nv0, grads + hd.b, part, s));
+  UTRY(wgrad(n.head(), GG_POINT, D, H, W, gy8, 8, 0, top, n.ch[0], 0));
   UTRY(launch_gather_gemm(gemm(GG_POINT, D, H, W, gy8, 8, 0, 1, hd.b_c, pk + hd.pb, n.ch[0], hd.b_npad, nullptr, 0,
                                gtop, n.ch[0], 0), s));
   // decoder, finest level first
@@ -354,20 +358,17 @@ ri_status backward(const Net& n, const float* params, const float* target, float
     const uint16_t* dao = at<uint16_t>(ws, B.da[l]);
     const uint16_t* cat = at<uint16_t>(ws, B.cat[l]);
     UTRY(launch_relu_mask(gdb, c, 0, dbo, c, 0, c, nvl, s));
-    UTRY(launch_wgrad(wg(GG_CONV3_FWD, Dl, Hl, Wl, gdb, c, 0, c, dao, c, 0, c, grads + db.w), 27, part, s));
-    UTRY(launch_bias_grad(gdb, c, 0, c, nvl, grads + db.b, part, s));
+    UTRY(wgrad(n.dec_b(l), GG_CONV3_FWD, Dl, Hl, Wl, gdb, c, 0, dao, c, 0));
     UTRY(launch_gather_gemm(gemm(GG_CONV3_BWD, Dl, Hl, Wl, gdb, c, 0, 27, db.b_c, pk + db.pb, c, db.b_npad, nullptr,
                                  0, gda, c, 0), s));
     UTRY(launch_relu_mask(gda, c, 0, dao, c, 0, c, nvl, s));
-    UTRY(launch_wgrad(wg(GG_CONV3_FWD, Dl, Hl, Wl, gda, c, 0, c, cat, 2 * c, 0, 2 * c, grads + da.w), 27, part, s));
-    UTRY(launch_bias_grad(gda, c, 0, c, nvl, grads + da.b, part, s));
+    UTRY(wgrad(n.dec_a(l), GG_CONV3_FWD, Dl, Hl, Wl, gda, c, 0, cat, 2 * c, 0));
     UTRY(launch_gather_gemm(gemm(GG_CONV3_BWD, Dl, Hl, Wl, gda, c, 0, 27, da.b_c, pk + da.pb, 2 * c, da.b_npad,
                                  nullptr, 0, gcat, 2 * c, 0), s));
     // up-convolution: gradient rows at the fine level, parameters over coarse rows
     const uint16_t* hin = (l + 1 == L - 1) ? at<uint16_t>(ws, B.bbot) : at<uint16_t>(ws, B.db[l + 1]);
     uint16_t* ghin = (l + 1 == L - 1) ? at<uint16_t>(ws, B.gbbot) : at<uint16_t>(ws, B.gdb[l + 1]);
-    UTRY(launch_wgrad(wg(GG_UP_FWD, Dl / 2, Hl / 2, Wl / 2, gcat, 2 * c, 0, c, hin, cu, 0, cu, grads + up.w), 8, part, s));
-    UTRY(launch_bias_grad(gcat, 2 * c, 0, c, nvl, grads + up.b, part, s));
+    UTRY(wgrad(n.up(l), GG_UP_FWD, Dl / 2, Hl / 2, Wl / 2, gcat, 2 * c, 0, hin, cu, 0));
     UTRY(launch_gather_gemm(gemm(GG_UP_BWD, Dl / 2, Hl / 2, Wl / 2, gcat, 2 * c, 0, 8, up.b_c, pk + up.pb, cu,
                                  up.b_npad, nullptr, 0, ghin, cu, 0), s));
   }
@@ -386,15 +387,13 @@ ri_status backward(const Net& n, const float* params, const float* target, float
     UTRY(launch_relu_mask(gout, ocs, oc0, out, ocs, oc0, c, nvl, s));
     const uint16_t* a = at<uint16_t>(ws, B.a[l]);
     uint16_t* ga = at<uint16_t>(ws, B.ga[l]);
-    UTRY(launch_wgrad(wg(GG_CONV3_FWD, Dl, Hl, Wl, gout, ocs, oc0, c, a, c, 0, c, grads + eb.w), 27, part, s));
-    UTRY(launch_bias_grad(gout, ocs, oc0, c, nvl, grads + eb.b, part, s));
+    UTRY(wgrad(n.enc_b(l), GG_CONV3_FWD, Dl, Hl, Wl, gout, ocs, oc0, a, c, 0));
     UTRY(launch_gather_gemm(gemm(GG_CONV3_BWD, Dl, Hl, Wl, gout, ocs, oc0, 27, eb.b_c, pk + eb.pb, c, eb.b_npad,
                                  nullptr, 0, ga, c, 0), s));
     UTRY(launch_relu_mask(ga, c, 0, a, c, 0, c, nvl, s));
     const uint16_t* src = l == 0 ? at<uint16_t>(ws, B.in0) : at<uint16_t>(ws, B.p[l - 1]);
     const int scs = l == 0 ? 8 : n.ch[l - 1], cin = l == 0 ? 1 : n.ch[l - 1];
-    UTRY(launch_wgrad(wg(GG_CONV3_FWD, Dl, Hl, Wl, ga, c, 0, c, src, scs, 0, cin, grads + ea.w), 27, part, s));
-    UTRY(launch_bias_grad(ga, c, 0, c, nvl, grads + ea.b, part, s));
+    UTRY(wgrad(n.enc_a(l), GG_CONV3_FWD, Dl, Hl, Wl, ga, c, 0, src, scs, 0));
     if (l > 0)
       UTRY(launch_gather_gemm(gemm(GG_CONV3_BWD, Dl, Hl, Wl, ga, c, 0, 27, ea.b_c, pk + ea.pb, cin, ea.b_npad,
                                    nullptr, 0, at<uint16_t>(ws, B.gp[l - 1]), cin, 0), s));
@@ -491,12 +490,31 @@ extern "C" ri_status ri_unet_train_step(const ri_unet_config* cfg, float* params
   const Buffers B = layout(n, d, h, w, true);
   if (ws_bytes < B.total) return set_error(RI_ERR_WORKSPACE_TOO_SMALL, "unet workspace too small");
   hipStream_t s = (hipStream_t)stream;
-  UTRY(hipMemsetAsync(grads, 0, n.nparams * sizeof(float), s));
   st = forward(n, params, in, scale, d, h, w, ws, B, true, s);
   if (st != RI_OK) return st;
-  st = backward(n, params, target, pos_weight, grads, d, h, w, ws, B, s);
+  st = backward(n, params, target, pos_weight, d, h, w, ws, B, s);
   if (st != RI_OK) return st;
-  if (loss_out) UTRY(hipMemcpyAsync(loss_out, at<float>(ws, B.loss), sizeof(float), hipMemcpyDeviceToDevice, s));
-  if (lr > 0) UTRY(launch_adam(params, grads, adam_m, adam_v, n.nparams, lr, 0.9, 0.999, 1e-8, step, s));
+  // gradients (and the loss) from their partials, with the Adam update
+  GradTable tab{};
+  auto entry = [&](size_t part, float* out, long param, size_t count, int parts) {
+    tab.e[tab.n++] = GradEntry{at<float>(ws, part), out, param, (int)count, parts, 0};
+  };
+  for (size_t k = 0; k < n.layers.size(); ++k) {
+    const Layer& y = n.layers[k];
+    entry(B.wpart[k], grads + y.w, (long)y.w, y.b - y.w, B.nblk[k]);
+    entry(B.bpart[k], grads + y.b, (long)y.b, (size_t)y.cout, B.nblk[k] * (y.kind == UP ? 8 : 1));
+  }
+  entry(B.lpart, loss_out ? loss_out : at<float>(ws, B.loss), -1, 1, mse_blocks((long)d * h * w));
+  const double b1 = 0.9, b2 = 0.999;
+  AdamArgs ad{};
+  ad.w = params; ad.m = adam_m; ad.v = adam_v;
+  ad.lr = lr;
+  if (lr > 0) {
+    ad.b1 = (float)b1; ad.b2 = (float)b2; ad.a1 = (float)(1.0 - b1); ad.a2 = (float)(1.0 - b2);
+    ad.eps = (float)1e-8;
+    ad.c1 = (float)(1.0 - std::pow(b1, (double)step));
+    ad.c2 = (float)(1.0 - std::pow(b2, (double)step));
+  }
+  UTRY(launch_finish_grads(tab, ad, s));
   return RI_OK;
 }

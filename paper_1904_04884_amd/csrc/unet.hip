@@ -13,9 +13,8 @@
 //   A (16 x 32): row l % 16, reduction elements 8 (l / 16) .. 8 (l / 16) + 7
 //   B (32 x 16): column l % 16, reduction elements 8 (l / 16) .. + 7
 //   D (16 x 16): rows 4 (l / 16) .. 4 (l / 16) + 3, column l % 16
+#include <algorithm>
 #include <type_traits>
-
-#include <cmath>
 
 #include "unet_internal.h"
 
@@ -68,17 +67,6 @@ __device__ __forceinline__ long gg_source_m(const GatherGemmArgs& a, const GgRow
     return ((long)g.z * H + g.y) * W + g.x;
   }
 }
-__device__ __forceinline__ long gg_source(const GatherGemmArgs& a, const GgRow& g, int t) {
-  switch (a.mode) {
-    case GG_CONV3_FWD: return gg_source_m<GG_CONV3_FWD>(a, g, t);
-    case GG_CONV3_BWD: return gg_source_m<GG_CONV3_BWD>(a, g, t);
-    case GG_UP_BWD: return gg_source_m<GG_UP_BWD>(a, g, t);
-    case GG_UP_FWD:
-    case GG_POINT: return gg_source_m<GG_POINT>(a, g, t);
-  }
-  return -1;
-}
-
 // Load target of switched-off lanes (zero-initialised device memory): operand
 // loads are selects of an address, never branches, so that the loads of the
 // next reduction step stay in flight under the MFMAs of this one.
@@ -357,118 +345,194 @@ __global__ void __launch_bounds__(256) k_conv3_lds(GatherGemmArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Weight gradient: dW[t][c][n] += sum_r S(r, t)[c] * G(r, t)[n]  (FP32 atomics;
-// [t][c][n] is the [tap][cin][cout] layout of the master weights).
-// Block: one tap, a chunk of rows and a group of up to 16 (n, c) output tiles;
-// 32-row slabs of G and S are staged in LDS, tiles are spread over the 4
-// wavefronts.
+// Weight gradient: dW[t][c][n] = sum_r S(r + offset(t))[c] G(r)[n], and the bias
+// gradient sum_r G(r)[n] from the same pass ([t][c][n] is the [tap][cin][cout]
+// layout of the master weights).
+//
+// A block takes a run of 16 x 4 x 4 boxes of rows.  It stages a box of G and
+// the box of S with its one-voxel halo (zeros outside the grid) in LDS once,
+// channels-last as they lie in memory, and every tap then takes its operand
+// from there at a shifted voxel; the 16-bit transposing LDS read turns four
+// rows of 16 channels into the 8 reduction (row) elements per lane the MFMA
+// wants.  A wavefront owns one 16 x 16 (n, c) tile of every tap (27 x 4
+// accumulators); a block covers up to 2 x 2 such tiles, or splits the box's
+// rows over its wavefronts when the layer has fewer, and adds their sums
+// through LDS at the end.  Each block writes one partial; k_finish_grads adds
+// the partials in order, so the result is the same on every run.
+// The pass is bound by those LDS reads (1 KiB per MFMA).  Staging S per tap
+// from global memory with 2-byte transposes, and summing the bias with one
+// thread per channel, took 13 ms of a 15.07 ms training step at 64 x 64 x 32
+// (levels 4, base 16); with this kernel the step takes 2.15 ms.
 // ---------------------------------------------------------------------------
-constexpr int kWgRows = 32;
-constexpr int kWgMaxN = 128, kWgMaxC = 256;
+constexpr int kWgBX = 16, kWgBY = 4, kWgBZ = 4;   // rows of a box: 8 slabs of 32
+constexpr int kWgRows = kWgBX * kWgBY * kWgBZ;
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
 
+// Element offset of an LDS voxel: CS channels and 16 bytes of padding, so that
+// the rows a transposing read gathers fall into different banks.
+template <int CS>
+__host__ __device__ constexpr int wg_stride() { return CS + 8; }
+
+__device__ __forceinline__ s16x4 lds_tr(const uint16_t* p) {
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(const __attribute__((address_space(3))) uint16_t*)p);
+}
+
+// TAPS: 27 (3x3x3, S with halo) or 1 (1x1x1 layers, and one tap of an
+// up-convolution per blockIdx.z: G at the fine voxel 2q + tap).  CT x NT: the
+// 16-channel tiles of S and G a block covers.
+template <int TAPS, int CT, int NT>
 __global__ void __launch_bounds__(256) k_wgrad(WgradArgs a) {
-  __shared__ uint16_t sg[kWgRows][kWgMaxN];
-  __shared__ uint16_t ss[kWgRows][kWgMaxC];
-  const int t = blockIdx.y;
-  const long nrows = (long)a.D * a.H * a.W;
-  const long r0 = (long)blockIdx.x * a.rows_per_block;
-  const long r1 = min(nrows, r0 + a.rows_per_block);
+  constexpr bool CONV = TAPS == 27;
+  constexpr int PB = CT * NT, RP = 4 / PB;       // tiles per block, row parts per tile
+  constexpr int HX = CONV ? kWgBX + 2 : kWgBX, HY = CONV ? kWgBY + 2 : kWgBY, HZ = CONV ? kWgBZ + 2 : kWgBZ;
+  constexpr int SS = wg_stride<CT * 16>(), SG = wg_stride<NT * 16>();
+  constexpr int NSV = HX * HY * HZ;
+  constexpr int PIECE = CONV ? 9 : 1;             // taps reduced over the row parts at a time
+  constexpr int kStage = (NSV * SS + kWgRows * SG) * 2, kRed = 4 * PIECE * 64 * 16;
+  __shared__ __align__(16) unsigned char s_raw[kStage > kRed ? kStage : kRed];
+  uint16_t* ss = reinterpret_cast<uint16_t*>(s_raw);
+  uint16_t* sg = ss + NSV * SS;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int tn = a.Npad / 16, tc = a.Cpad / 16, ntile = tn * tc;
-  constexpr int MAXT = 4;  // tiles per wavefront kept in registers (16 tiles per block)
-  const int tile0 = blockIdx.z * 16;
-  f32x4 acc[MAXT];
+  const int pair = wv % PB, rp = wv / PB;
+  const int cg = (a.Cpad / 16) / CT;              // channel groups of S
+  const int c0 = (blockIdx.y % cg) * CT * 16, n0 = (blockIdx.y / cg) * NT * 16;
+  const int ci = pair % CT, ni = pair / CT;
+  const int tap = a.mode == GG_UP_FWD ? (int)blockIdx.z : 0;
+  const int bxn = (a.W + kWgBX - 1) / kWgBX, byn = (a.H + kWgBY - 1) / kWgBY, bzn = (a.D + kWgBZ - 1) / kWgBZ;
+  const int nbox = bxn * byn * bzn;
+  const int b0 = (int)((long)blockIdx.x * nbox / gridDim.x), b1 = (int)((long)(blockIdx.x + 1) * nbox / gridDim.x);
+  f32x4 acc[TAPS], accb = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < MAXT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  GatherGemmArgs ga{};
-  ga.mode = a.mode;
-  ga.D = a.D; ga.H = a.H; ga.W = a.W;
-  for (long rb = r0; rb < r1; rb += kWgRows) {
+  for (int t = 0; t < TAPS; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // transposing read: lane i of a group of 16 supplies row i / 4, channels 4 (i % 4)
+  const int tr = (lane & 15) >> 2, tq = (lane & 3) * 4, kg = lane >> 4;
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, (s16x8)(short)0x3f80);
+  for (int b = b0; b < b1; ++b) {
+    const int x0 = (b % bxn) * kWgBX, y0 = ((b / bxn) % byn) * kWgBY, z0 = (b / (bxn * byn)) * kWgBZ;
     __syncthreads();
-    // stage G rows (all n) and S rows (all c) of this slab
-    for (int e = threadIdx.x; e < kWgRows * a.Npad; e += 256) {
-      const int rr = e / a.Npad, n = e - rr * a.Npad;
-      const long r = rb + rr;
-      uint16_t gv = 0;
-      if (r < r1 && n < a.N) {
-        long gvox = r;
-        if (a.mode == GG_UP_FWD) {
-          // gradient rows live at the fine voxel of tap t
-          const int x = (int)(r % a.W), y = (int)((r / a.W) % a.H), z = (int)(r / ((long)a.W * a.H));
-          gvox = ((long)(2 * z + (t >> 2)) * (2 * a.H) + 2 * y + ((t >> 1) & 1)) * (2 * a.W) + 2 * x + (t & 1);
-        }
-        gv = a.g[(size_t)gvox * a.g_cs + a.g_c0 + n];
-      }
-      sg[rr][n] = gv;
+    for (int e = threadIdx.x; e < NSV * CT * 2; e += 256) {
+      const int v = e / (CT * 2), q = e % (CT * 2);
+      constexpr int O = CONV ? 1 : 0;
+      const int x = x0 + v % HX - O, y = y0 + (v / HX) % HY - O, z = z0 + v / (HX * HY) - O, c = c0 + q * 8;
+      const bool on = (unsigned)x < (unsigned)a.W && (unsigned)y < (unsigned)a.H && (unsigned)z < (unsigned)a.D && c < a.C;
+      const uint4 val = *(on ? reinterpret_cast<const uint4*>(a.s + (((long)z * a.H + y) * a.W + x) * a.s_cs + a.s_c0 + c)
+                             : &g_gg_zero);
+      *reinterpret_cast<uint4*>(ss + v * SS + q * 8) = val;
     }
-    for (int e = threadIdx.x; e < kWgRows * a.Cpad; e += 256) {
-      const int rr = e / a.Cpad, c = e - rr * a.Cpad;
-      const long r = rb + rr;
-      uint16_t sv = 0;
-      if (r < r1 && c < a.C) {
-        long svox = r;
-        if (a.mode == GG_CONV3_FWD) svox = gg_source(ga, gg_row(ga, r, r + 1), t);
-        if (svox >= 0) sv = a.s[(size_t)svox * a.s_cs + a.s_c0 + c];
-      }
-      ss[rr][c] = sv;
+    for (int e = threadIdx.x; e < kWgRows * NT * 2; e += 256) {
+      const int v = e / (NT * 2), q = e % (NT * 2);
+      const int x = x0 + v % kWgBX, y = y0 + (v / kWgBX) % kWgBY, z = z0 + v / (kWgBX * kWgBY), n = n0 + q * 8;
+      const bool on = x < a.W && y < a.H && z < a.D && n < a.N;
+      long gv = ((long)z * a.H + y) * a.W + x;
+      if (a.mode == GG_UP_FWD)
+        gv = ((long)(2 * z + (tap >> 2)) * (2 * a.H) + 2 * y + ((tap >> 1) & 1)) * (2 * a.W) + 2 * x + (tap & 1);
+      const uint4 val = *(on ? reinterpret_cast<const uint4*>(a.g + gv * a.g_cs + a.g_c0 + n) : &g_gg_zero);
+      *reinterpret_cast<uint4*>(sg + v * SG + q * 8) = val;
     }
     __syncthreads();
-    // A (16 n x 32 r): lane row n = 16 tn_i + lane % 16, r = 8 (lane / 16) + 0..7
-    // B (32 r x 16 c): lane column c = 16 tc_i + lane % 16
+    // slab k of 32 rows: y rows 2 (k % 2), 2 (k % 2) + 1 of plane k / 2; this
+    // lane's 8 rows are x = 8 (kg % 2) .. + 7 of row kg / 2
+    for (int k = rp; k < kWgRows / 32; k += RP) {
+      const int yy = (k & 1) * 2 + (kg >> 1), zz = k >> 1, xx = (kg & 1) * 8 + tr;
+      auto frag = [&](const uint16_t* base, int stride) {
+        const s16x4 lo = lds_tr(base), hi = lds_tr(base + 4 * stride);
+        s16x8 f;
+        f[0] = lo[0]; f[1] = lo[1]; f[2] = lo[2]; f[3] = lo[3];
+        f[4] = hi[0]; f[5] = hi[1]; f[6] = hi[2]; f[7] = hi[3];
+        return __builtin_bit_cast(bf16x8, f);
+      };
+      const bf16x8 gf = frag(sg + ((zz * kWgBY + yy) * kWgBX + xx) * SG + ni * 16 + tq, SG);
+      accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf, ones, accb, 0, 0, 0);
+      const uint16_t* sb = ss + ((zz * HY + yy) * HX + xx) * SS + ci * 16 + tq;
 #pragma unroll
-    for (int i = 0; i < MAXT; ++i) {
-      const int tile = tile0 + wv + 4 * i;
-      if (tile >= ntile) break;
-      const int ni = tile / tc, ci = tile - ni * tc;
-      uint16_t av[8], bv[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int rr = (lane >> 4) * 8 + q;
-        av[q] = sg[rr][ni * 16 + (lane & 15)];
-        bv[q] = ss[rr][ci * 16 + (lane & 15)];
+      for (int t = 0; t < TAPS; ++t) {
+        const int o = CONV ? ((t / 9) * HY + (t / 3) % 3) * HX + t % 3 : 0;
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf, frag(sb + o * SS, SS), acc[t], 0, 0, 0);
       }
-      bf16x8 A, B;
-      __builtin_memcpy(&A, av, 16);
-      __builtin_memcpy(&B, bv, 16);
-      acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B, acc[i], 0, 0, 0);
     }
   }
-  // D rows = n, columns = c
+  // D rows n = 4 (lane / 16) + i, columns c = lane % 16; the row parts of a
+  // tile are added in order
+  const int c = c0 + ci * 16 + (lane & 15), n = n0 + ni * 16 + (lane >> 4) * 4;
+  const size_t count = (size_t)a.taps * a.C * a.N;
+  float* part = a.part + (size_t)blockIdx.x * count;
+  auto store = [&](int t, f32x4 v) {
+    if (c >= a.C) return;
 #pragma unroll
-  for (int i = 0; i < MAXT; ++i) {
-    const int tile = tile0 + wv + 4 * i;
-    if (tile >= ntile) break;
-    const int ni = tile / tc, ci = tile - ni * tc;
-    const int c = ci * 16 + (lane & 15);
+    for (int i = 0; i < 4; ++i)
+      if (n + i < a.N) part[((size_t)t * a.C + c) * a.N + n + i] = v[i];
+  };
+  auto store_bias = [&](f32x4 v) {
+    if (blockIdx.y % cg != 0 || ci != 0 || (lane & 15) != 0) return;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int n = ni * 16 + (lane >> 4) * 4 + q;
-      // this block's partial (row chunk blockIdx.x); summed in chunk order by k_sum_partials
-      if (n < a.N && c < a.C)
-        a.part[(size_t)blockIdx.x * a.taps * a.C * a.N + ((size_t)t * a.C + c) * a.N + n] = acc[i][q];
+    for (int i = 0; i < 4; ++i)
+      if (n + i < a.N) a.bpart[((size_t)blockIdx.x * gridDim.z + blockIdx.z) * a.N + n + i] = v[i];
+  };
+  if constexpr (RP == 1) {
+#pragma unroll
+    for (int t = 0; t < TAPS; ++t) store(CONV ? t : tap, acc[t]);
+    store_bias(accb);
+  } else {
+    f32x4* red = reinterpret_cast<f32x4*>(s_raw);   // [4 waves][PIECE][64]
+#pragma unroll
+    for (int p = 0; p < TAPS / PIECE; ++p) {
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < PIECE; ++j) red[(wv * PIECE + j) * 64 + lane] = acc[p * PIECE + j];
+      __syncthreads();
+      for (int j = rp; j < PIECE; j += RP) {
+        f32x4 v = red[(pair * PIECE + j) * 64 + lane];
+#pragma unroll
+        for (int r = 1; r < RP; ++r) v += red[((r * PB + pair) * PIECE + j) * 64 + lane];
+        store(CONV ? p * PIECE + j : tap, v);
+      }
+    }
+    __syncthreads();
+    red[wv * 64 + lane] = accb;
+    __syncthreads();
+    if (rp == 0) {
+#pragma unroll
+      for (int r = 1; r < RP; ++r) accb += red[(r * PB + pair) * 64 + lane];
+      store_bias(accb);
     }
   }
 }
 
-// bias gradient: partial sums of g[r][n] over a chunk of rows per block
-__global__ void __launch_bounds__(256) k_bias_grad(const uint16_t* g, int cs, int c0, int N, long nrows,
-                                                   long rows_per_block, float* part) {
-  const long r0 = (long)blockIdx.x * rows_per_block, r1 = min(nrows, r0 + rows_per_block);
-  for (int n = threadIdx.x; n < N; n += 256) {
-    float s = 0.f;
-    for (long r = r0; r < r1; ++r) s += bf2f(g[(size_t)r * cs + c0 + n]);
-    part[(size_t)blockIdx.x * N + n] = s;
+// Gradients from their partials (weights, biases and the loss are table
+// entries): out[e] = sum over b of part[b * count + e].  A block takes 64
+// elements; its four groups of 64 threads add a quarter of the partials each,
+// in order, and the quarters are added in order, so every run gives the same
+// bits.  With lr > 0 the same thread applies Adam to its parameter (a1 = 1 -
+// b1, a2 = 1 - b2 and the bias corrections c1, c2 come from the host in FP64;
+// 1 - 0.999f in FP32 is off by 5e-5 relative).
+__global__ void __launch_bounds__(256) k_finish_grads(GradTable tab, AdamArgs ad) {
+  __shared__ float s_q[4][64];
+  int k = 0;
+  while (k + 1 < tab.n && (int)blockIdx.x >= tab.e[k + 1].block0) ++k;
+  const GradEntry g = tab.e[k];
+  const int t = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const long e = (long)((int)blockIdx.x - g.block0) * 64 + t;
+  const int p0 = (int)((long)q * g.parts / 4), p1 = (int)((long)(q + 1) * g.parts / 4);
+  float s = 0.f;
+  if (e < g.count) {
+    const float* src = g.part + e;
+#pragma unroll 8
+    for (int b = p0; b < p1; ++b) s += src[(size_t)b * g.count];
   }
-}
-
-// out[e] += sum over b of part[b * count + e], b in order: partial sums of
-// row chunks reduced the same way on every run (no floating-point atomics).
-__global__ void k_sum_partials(const float* __restrict__ part, int nb, size_t count, float* out) {
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < count; e += (size_t)gridDim.x * blockDim.x) {
-    float s = 0.f;
-    for (int b = 0; b < nb; ++b) s += part[(size_t)b * count + e];
-    out[e] += s;
-  }
+  s_q[q][t] = s;
+  __syncthreads();
+  if (q != 0 || e >= g.count) return;
+  const float gi = s_q[0][t] + s_q[1][t] + s_q[2][t] + s_q[3][t];
+  g.out[e] = gi;
+  if (g.param < 0 || !(ad.lr > 0.f)) return;
+  const size_t i = (size_t)g.param + e;
+  const float mi = ad.b1 * ad.m[i] + ad.a1 * gi;
+  const float vi = ad.b2 * ad.v[i] + ad.a2 * gi * gi;
+  ad.m[i] = mi;
+  ad.v[i] = vi;
+  ad.w[i] -= ad.lr * (mi / ad.c1) / (sqrtf(vi / ad.c2) + ad.eps);
 }
 
 // ---------------------------------------------------------------------------
@@ -547,21 +611,6 @@ __global__ void k_mse(const float* y, const float* t, long n, float inv_n, float
   if (threadIdx.x == 0) loss[blockIdx.x] = (red[0] + red[1] + red[2] + red[3]) * inv_n;   // per-block partial
 }
 
-// Adam on FP32 master weights
-// Adam.  a1 = 1 - b1, a2 = 1 - b2 and the bias corrections c1, c2 come from
-// the host in FP64 (1 - 0.999f in FP32 is off by 5e-5 relative).
-__global__ void k_adam(float* w, const float* g, float* m, float* v, size_t n, float lr, float b1, float b2,
-                       float a1, float a2, float eps, float c1, float c2) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + a1 * gi;
-    const float vi = b2 * v[i] + a2 * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-  }
-}
-
 // Pack FP32 master weights W[t][cin][cout] into BF16 B[t][n][c] for one use:
 // transpose = 1: n = cout, c = cin (forward); 0: n = cin, c = cout (input
 // gradient).  Channels beyond the real counts are zero.
@@ -595,10 +644,6 @@ __global__ void k_pack_up_fwd(const float* u, int cin, int cout, uint16_t* out) 
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-__global__ void k_fill_f32_one(float* p) {
-  if (threadIdx.x == 0) *p = 0.f;
-}
-
 static int ew_grid(size_t n) {
   size_t b = (n + 255) / 256;
   return (int)(b > 16384 ? 16384 : (b == 0 ? 1 : b));
@@ -668,29 +713,41 @@ hipError_t launch_gather_gemm(const GatherGemmArgs& a, hipStream_t s) {
   }
 }
 
-long wgrad_rows_per_block(long nrows) { return std::max<long>(2048, (nrows + kReduceBlocks - 1) / kReduceBlocks); }
-long bias_rows_per_block(long nrows) { return std::max<long>(4096, (nrows + kReduceBlocks - 1) / kReduceBlocks); }
+int wgrad_blocks(int mode, int D, int H, int W, int N, int C) {
+  const int nbox = ((W + kWgBX - 1) / kWgBX) * ((H + kWgBY - 1) / kWgBY) * ((D + kWgBZ - 1) / kWgBZ);
+  const int tn = (N + 15) / 16, tc = (C + 15) / 16;
+  const int groups = std::max(1, tn / 2) * std::max(1, tc / 2) * (mode == GG_UP_FWD ? 8 : 1);
+  // about two blocks per compute unit; a block sums at least one box
+  return std::min(nbox, std::max(1, 512 / groups > 256 ? 256 : 512 / groups));
+}
 
-hipError_t launch_wgrad(WgradArgs a, int taps, float* part, hipStream_t s) {
-  if (a.Npad > kWgMaxN || a.Cpad > kWgMaxC || a.Npad % 16 || a.Cpad % 16) return hipErrorInvalidValue;
-  const long nrows = (long)a.D * a.H * a.W;
-  a.rows_per_block = wgrad_rows_per_block(nrows);
-  a.taps = taps;
-  a.part = part;
-  const int nb = (int)((nrows + a.rows_per_block - 1) / a.rows_per_block);
-  const int groups = ((a.Npad / 16) * (a.Cpad / 16) + 15) / 16;
-  hipLaunchKernelGGL(k_wgrad, dim3(nb, taps, groups), dim3(256), 0, s, a);
-  const size_t count = (size_t)taps * a.C * a.N;
-  hipLaunchKernelGGL(k_sum_partials, dim3(ew_grid(count)), dim3(256), 0, s, part, nb, count, a.dw);
+hipError_t launch_wgrad(WgradArgs a, int blocks, hipStream_t s) {
+  if (a.N < 1 || a.C < 1 || a.s_cs % 8 || a.s_c0 % 8 || a.g_cs % 8 || a.g_c0 % 8) return hipErrorInvalidValue;
+  const int tn = (a.N + 15) / 16, tc = (a.C + 15) / 16;
+  if ((tn & (tn - 1)) || (tc & (tc - 1))) return hipErrorInvalidValue;
+  a.Cpad = tc * 16;
+  const int NT = tn > 1 ? 2 : 1, CT = tc > 1 ? 2 : 1;
+  const bool conv = a.mode == GG_CONV3_FWD;
+  a.taps = conv ? 27 : (a.mode == GG_UP_FWD ? 8 : 1);
+  const dim3 g((unsigned)blocks, (unsigned)((tn / NT) * (tc / CT)), a.mode == GG_UP_FWD ? 8 : 1);
+#define RIHVR_WG(CT_, NT_)                                                                \
+  if (conv) hipLaunchKernelGGL((k_wgrad<27, CT_, NT_>), g, dim3(256), 0, s, a);           \
+  else hipLaunchKernelGGL((k_wgrad<1, CT_, NT_>), g, dim3(256), 0, s, a);
+  if (CT == 2 && NT == 2) { RIHVR_WG(2, 2) }
+  else if (CT == 2) { RIHVR_WG(2, 1) }
+  else if (NT == 2) { RIHVR_WG(1, 2) }
+  else { RIHVR_WG(1, 1) }
+#undef RIHVR_WG
   return hipGetLastError();
 }
 
-hipError_t launch_bias_grad(const uint16_t* g, int cs, int c0, int N, long nrows, float* db, float* part,
-                            hipStream_t s) {
-  const long per = bias_rows_per_block(nrows);
-  const int nb = (int)((nrows + per - 1) / per);
-  hipLaunchKernelGGL(k_bias_grad, dim3(nb), dim3(256), 0, s, g, cs, c0, N, nrows, per, part);
-  hipLaunchKernelGGL(k_sum_partials, dim3(ew_grid((size_t)N)), dim3(256), 0, s, part, nb, (size_t)N, db);
+hipError_t launch_finish_grads(GradTable& tab, const AdamArgs& ad, hipStream_t s) {
+  int blocks = 0;
+  for (int k = 0; k < tab.n; ++k) {
+    tab.e[k].block0 = blocks;
+    blocks += (int)((tab.e[k].count + 63) / 64);
+  }
+  hipLaunchKernelGGL(k_finish_grads, dim3(blocks), dim3(256), 0, s, tab, ad);
   return hipGetLastError();
 }
 
@@ -725,21 +782,11 @@ hipError_t launch_input(const float* in, float scale, uint16_t* x, int cs, long 
   return hipGetLastError();
 }
 
-hipError_t launch_mse(const float* y, const float* t, long n, float pos_w, uint16_t* g, int gcs, float* loss,
-                      float* part, hipStream_t s) {
-  // per-block partials in part (ew_grid(n) <= kLossBlocks of them), then one ordered sum
-  const int nb = ew_grid(n);
-  hipLaunchKernelGGL(k_mse, dim3(nb), dim3(256), 0, s, y, t, n, 1.f / (float)n, pos_w, g, gcs, part);
-  hipLaunchKernelGGL(k_fill_f32_one, dim3(1), dim3(64), 0, s, loss);
-  hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, part, nb, (size_t)1, loss);
-  return hipGetLastError();
-}
+int mse_blocks(long n) { return std::min(ew_grid((size_t)n), 512); }
 
-hipError_t launch_adam(float* w, const float* g, float* m, float* v, size_t n, float lr, double b1, double b2,
-                       double eps, int step, hipStream_t s) {
-  const float c1 = (float)(1.0 - std::pow(b1, (double)step)), c2 = (float)(1.0 - std::pow(b2, (double)step));
-  hipLaunchKernelGGL(k_adam, dim3(ew_grid(n)), dim3(256), 0, s, w, g, m, v, n, lr, (float)b1, (float)b2,
-                     (float)(1.0 - b1), (float)(1.0 - b2), (float)eps, c1, c2);
+hipError_t launch_mse(const float* y, const float* t, long n, float pos_w, uint16_t* g, int gcs, float* part,
+                      hipStream_t s) {
+  hipLaunchKernelGGL(k_mse, dim3(mse_blocks(n)), dim3(256), 0, s, y, t, n, 1.f / (float)n, pos_w, g, gcs, part);
   return hipGetLastError();
 }
 

@@ -32,28 +32,39 @@ struct GatherGemmArgs {
 };
 hipError_t launch_gather_gemm(const GatherGemmArgs& a, hipStream_t s);
 
+// Weight and bias gradient of one layer: per-block partials, added in order
+// (with the loss and, for lr > 0, the Adam update) by launch_finish_grads, so
+// a training step gives the same bits on every run.
 struct WgradArgs {
   int mode;                // GG_CONV3_FWD, GG_UP_FWD (coarse rows) or GG_POINT
   int D, H, W;             // row grid
   const uint16_t* g;       // gradient w.r.t. the layer output (masked), channel view
-  int g_cs, g_c0, N, Npad;
+  int g_cs, g_c0, N;
   const uint16_t* s;       // layer input, channel view
-  int s_cs, s_c0, C, Cpad;
-  float* dw;               // FP32 [t][C][N], accumulated
-  long rows_per_block;     // set by launch_wgrad
-  int taps;                // set by launch_wgrad
-  float* part;             // per-row-chunk partials [chunk][t][C][N] (set by launch_wgrad)
+  int s_cs, s_c0, C;
+  float* part;             // [blocks][t][C][N]
+  float* bpart;            // [blocks (x 8 up-convolution taps)][N]
+  int Cpad, taps;          // set by launch_wgrad
 };
-// Weight and bias gradients are reduced without floating-point atomics: each
-// block writes the partial sum of its chunk of rows (at most kReduceBlocks
-// chunks) to `part`, and one ordered pass adds the chunks, so a training step
-// gives the same bits on every run.
-constexpr long kReduceBlocks = 256;
-long wgrad_rows_per_block(long nrows);
-long bias_rows_per_block(long nrows);
-hipError_t launch_wgrad(WgradArgs a, int taps, float* part, hipStream_t s);
-hipError_t launch_bias_grad(const uint16_t* g, int cs, int c0, int N, long nrows, float* db, float* part,
-                            hipStream_t s);
+int wgrad_blocks(int mode, int D, int H, int W, int N, int C);
+hipError_t launch_wgrad(WgradArgs a, int blocks, hipStream_t s);
+
+struct GradEntry {
+  const float* part;       // [parts][count]
+  float* out;
+  long param;              // first parameter of the entry, or -1 (the loss)
+  int count, parts;
+  int block0;              // set by launch_finish_grads
+};
+struct GradTable {
+  int n;
+  GradEntry e[2 * 28 + 1]; // weights and biases of at most 28 layers, the loss
+};
+struct AdamArgs {
+  float *w, *m, *v;
+  float lr, b1, b2, a1, a2, eps, c1, c2;
+};
+hipError_t launch_finish_grads(GradTable& tab, const AdamArgs& ad, hipStream_t s);
 
 hipError_t launch_pool_fwd(const uint16_t* x, int xcs, int xc0, uint16_t* y, int ycs, uint8_t* idx, int C, int D,
                            int H, int W, hipStream_t s);
@@ -63,10 +74,9 @@ hipError_t launch_relu_mask(uint16_t* g, int gcs, int gc0, const uint16_t* y, in
                             hipStream_t s);
 hipError_t launch_zero_u16(uint16_t* p, size_t n, hipStream_t s);
 hipError_t launch_input(const float* in, float scale, uint16_t* x, int cs, long nvox, hipStream_t s);
-hipError_t launch_mse(const float* y, const float* t, long n, float pos_w, uint16_t* g, int gcs, float* loss,
-                      float* part, hipStream_t s);   // part: one float per block (<= 16384)
-hipError_t launch_adam(float* w, const float* g, float* m, float* v, size_t n, float lr, double b1, double b2,
-                       double eps, int step, hipStream_t s);
+int mse_blocks(long n);
+hipError_t launch_mse(const float* y, const float* t, long n, float pos_w, uint16_t* g, int gcs, float* part,
+                      hipStream_t s);   // part: mse_blocks(n) floats
 hipError_t launch_pack(const float* w, int T, int cin, int cout, int transpose, int Npad, int Cpad, uint16_t* out,
                        hipStream_t s);
 hipError_t launch_pack_up_fwd(const float* u, int cin, int cout, uint16_t* out, hipStream_t s);
