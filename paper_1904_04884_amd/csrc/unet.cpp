@@ -249,6 +249,20 @@ GatherGemmArgs gemm(int mode, int D, int H, int W, const uint16_t* src, int cs, 
   return g;
 }
 
+// 3x3x3 layer of a channel view (channels contiguous)
+ConvArgs conv(int bwd, int D, int H, int W, const uint16_t* src, int cs, int C, const uint16_t* wt, int N, int Npad,
+              const float* bias, int relu, uint16_t* dst, int dcs) {
+  ConvArgs a{};
+  a.bwd = bwd;
+  a.D = D; a.H = H; a.W = W;
+  a.src = src; a.src2 = src + C / 2; a.src_cs = cs;
+  a.C = C;
+  a.wt = wt; a.N = N; a.Npad = Npad;
+  a.bias = bias; a.relu = relu;
+  a.dst = dst; a.dst2 = dst; a.nsplit = a.Npad; a.dst_cs = dcs;
+  return a;
+}
+
 ri_status pack_all(const Net& n, const float* params, uint16_t* packed, bool with_bwd, hipStream_t s) {
   for (const Layer& y : n.layers) {
     if (y.kind == CONV) {
@@ -280,12 +294,11 @@ ri_status forward(const Net& n, const float* params, const float* in, float scal
     const uint16_t* src = l == 0 ? in0 : at<uint16_t>(ws, B.p[l - 1]);
     const int scs = l == 0 ? 8 : n.ch[l - 1];
     uint16_t* a = at<uint16_t>(ws, B.a[l]);
-    UTRY(launch_gather_gemm(gemm(GG_CONV3_FWD, Dl, Hl, Wl, src, scs, 0, 27, ea.f_c, pk + ea.pf, c, ea.f_npad,
-                                 params + ea.b, 1, a, c, 0), s));
+    UTRY(launch_conv3(conv(0, Dl, Hl, Wl, src, scs, ea.f_c, pk + ea.pf, c, ea.f_npad, params + ea.b, 1, a, c), s));
     uint16_t* bo = l < L - 1 ? at<uint16_t>(ws, B.cat[l]) : at<uint16_t>(ws, B.bbot);
     const int bcs = l < L - 1 ? 2 * c : c, bc0 = l < L - 1 ? c : 0;
-    UTRY(launch_gather_gemm(gemm(GG_CONV3_FWD, Dl, Hl, Wl, a, c, 0, 27, eb.f_c, pk + eb.pf, c, eb.f_npad,
-                                 params + eb.b, 1, bo, bcs, bc0), s));
+    UTRY(launch_conv3(conv(0, Dl, Hl, Wl, a, c, eb.f_c, pk + eb.pf, c, eb.f_npad, params + eb.b, 1, bo + bc0, bcs),
+                      s));
     if (l < L - 1)
       UTRY(launch_pool_fwd(bo, bcs, bc0, at<uint16_t>(ws, B.p[l]), c, at<uint8_t>(ws, B.idx[l]), c, Dl / 2, Hl / 2,
                            Wl / 2, s));
@@ -302,11 +315,9 @@ ri_status forward(const Net& n, const float* params, const float* in, float scal
     g.up_cout = c;
     UTRY(launch_gather_gemm(g, s));
     uint16_t* dao = at<uint16_t>(ws, B.da[l]);
-    UTRY(launch_gather_gemm(gemm(GG_CONV3_FWD, Dl, Hl, Wl, cat, 2 * c, 0, 27, da.f_c, pk + da.pf, c, da.f_npad,
-                                 params + da.b, 1, dao, c, 0), s));
+    UTRY(launch_conv3(conv(0, Dl, Hl, Wl, cat, 2 * c, da.f_c, pk + da.pf, c, da.f_npad, params + da.b, 1, dao, c), s));
     uint16_t* dbo = at<uint16_t>(ws, B.db[l]);
-    UTRY(launch_gather_gemm(gemm(GG_CONV3_FWD, Dl, Hl, Wl, dao, c, 0, 27, db.f_c, pk + db.pf, c, db.f_npad,
-                                 params + db.b, 1, dbo, c, 0), s));
+    UTRY(launch_conv3(conv(0, Dl, Hl, Wl, dao, c, db.f_c, pk + db.pf, c, db.f_npad, params + db.b, 1, dbo, c), s));
     h = dbo;
   }
   // head: ReLU output for inference; training keeps the pre-activation (the
@@ -359,12 +370,10 @@ ri_status backward(const Net& n, const float* params, const float* target, float
     const uint16_t* cat = at<uint16_t>(ws, B.cat[l]);
     UTRY(launch_relu_mask(gdb, c, 0, dbo, c, 0, c, nvl, s));
     UTRY(wgrad(n.dec_b(l), GG_CONV3_FWD, Dl, Hl, Wl, gdb, c, 0, dao, c, 0));
-    UTRY(launch_gather_gemm(gemm(GG_CONV3_BWD, Dl, Hl, Wl, gdb, c, 0, 27, db.b_c, pk + db.pb, c, db.b_npad, nullptr,
-                                 0, gda, c, 0), s));
+    UTRY(launch_conv3(conv(1, Dl, Hl, Wl, gdb, c, db.b_c, pk + db.pb, c, db.b_npad, nullptr, 0, gda, c), s));
     UTRY(launch_relu_mask(gda, c, 0, dao, c, 0, c, nvl, s));
     UTRY(wgrad(n.dec_a(l), GG_CONV3_FWD, Dl, Hl, Wl, gda, c, 0, cat, 2 * c, 0));
-    UTRY(launch_gather_gemm(gemm(GG_CONV3_BWD, Dl, Hl, Wl, gda, c, 0, 27, da.b_c, pk + da.pb, 2 * c, da.b_npad,
-                                 nullptr, 0, gcat, 2 * c, 0), s));
+    UTRY(launch_conv3(conv(1, Dl, Hl, Wl, gda, c, da.b_c, pk + da.pb, 2 * c, da.b_npad, nullptr, 0, gcat, 2 * c), s));
     // up-convolution: gradient rows at the fine level, parameters over coarse rows
     const uint16_t* hin = (l + 1 == L - 1) ? at<uint16_t>(ws, B.bbot) : at<uint16_t>(ws, B.db[l + 1]);
     uint16_t* ghin = (l + 1 == L - 1) ? at<uint16_t>(ws, B.gbbot) : at<uint16_t>(ws, B.gdb[l + 1]);
@@ -388,15 +397,14 @@ ri_status backward(const Net& n, const float* params, const float* target, float
     const uint16_t* a = at<uint16_t>(ws, B.a[l]);
     uint16_t* ga = at<uint16_t>(ws, B.ga[l]);
     UTRY(wgrad(n.enc_b(l), GG_CONV3_FWD, Dl, Hl, Wl, gout, ocs, oc0, a, c, 0));
-    UTRY(launch_gather_gemm(gemm(GG_CONV3_BWD, Dl, Hl, Wl, gout, ocs, oc0, 27, eb.b_c, pk + eb.pb, c, eb.b_npad,
-                                 nullptr, 0, ga, c, 0), s));
+    UTRY(launch_conv3(conv(1, Dl, Hl, Wl, gout + oc0, ocs, eb.b_c, pk + eb.pb, c, eb.b_npad, nullptr, 0, ga, c), s));
     UTRY(launch_relu_mask(ga, c, 0, a, c, 0, c, nvl, s));
     const uint16_t* src = l == 0 ? at<uint16_t>(ws, B.in0) : at<uint16_t>(ws, B.p[l - 1]);
     const int scs = l == 0 ? 8 : n.ch[l - 1], cin = l == 0 ? 1 : n.ch[l - 1];
     UTRY(wgrad(n.enc_a(l), GG_CONV3_FWD, Dl, Hl, Wl, ga, c, 0, src, scs, 0));
     if (l > 0)
-      UTRY(launch_gather_gemm(gemm(GG_CONV3_BWD, Dl, Hl, Wl, ga, c, 0, 27, ea.b_c, pk + ea.pb, cin, ea.b_npad,
-                                   nullptr, 0, at<uint16_t>(ws, B.gp[l - 1]), cin, 0), s));
+      UTRY(launch_conv3(conv(1, Dl, Hl, Wl, ga, c, ea.b_c, pk + ea.pb, cin, ea.b_npad, nullptr, 0,
+                             at<uint16_t>(ws, B.gp[l - 1]), cin), s));
   }
   return RI_OK;
 }

@@ -2,12 +2,13 @@
 // accumulation on the matrix cores (v_mfma_f32_16x16x32_bf16).
 //
 // Activations are channels-last, [z][y][x][c] with a channel stride (so a
-// concatenation is two views of one buffer).  Every convolution-like layer is
-// one "gather GEMM": row r is an output voxel, the reduction index k = t*C + c
-// runs over taps t and input channels c, and the operand row of tap t is read
-// from a source voxel chosen by the layer's gather mode.  Weights are packed as
-// B[t][n][c] (n the GEMM column, c contiguous) so each lane loads 8 consecutive
-// reduction values with one 16-byte load.
+// concatenation is two views of one buffer).  Every convolution-like layer is a
+// matrix product: row r is an output voxel, the reduction index k = t*C + c runs
+// over taps t and input channels c.  The 3x3x3 layers read their operand from a
+// haloed box in LDS (k_conv3); the others gather it from a source voxel chosen by
+// the layer's mode (k_gather_gemm).  Weights are packed as B[t][n][c] (n the
+// output channel, c contiguous) so each lane loads 8 consecutive reduction values
+// with one 16-byte load.
 //
 // MFMA 16x16x32 operand layout (per wavefront of 64 lanes, lane l):
 //   A (16 x 32): row l % 16, reduction elements 8 (l / 16) .. 8 (l / 16) + 7
@@ -16,12 +17,15 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "rihvr_internal.h"
 #include "unet_internal.h"
 
 namespace rihvr {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float bf2f(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
 __device__ __forceinline__ uint16_t f2bf(float f) {
@@ -29,6 +33,30 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
   uint32_t u = __float_as_uint(f);
   u += 0x7fffu + ((u >> 16) & 1u);
   return (uint16_t)(u >> 16);
+}
+
+// Two values rounded and packed (the first in the low half).
+__device__ __forceinline__ uint32_t bf_pack(float a, float b) {
+  uint32_t u = __float_as_uint(a), v = __float_as_uint(b);
+  u += 0x7fffu + ((u >> 16) & 1u);
+  v += 0x7fffu + ((v >> 16) & 1u);
+  return __builtin_amdgcn_perm(v, u, 0x07060302u);
+}
+// Four packed values, zero where the mask's is not > 0.
+__device__ __forceinline__ u32x2 bf_mask(u32x2 o, u32x2 m) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const uint32_t lo = bf2f((uint16_t)m[k]) > 0.f ? 0xffffu : 0u, hi = bf2f((uint16_t)(m[k] >> 16)) > 0.f ? 0xffff0000u : 0u;
+    o[k] &= lo | hi;
+  }
+  return o;
+}
+
+// Planes as buffer resources: a read past the given bytes returns 0, a store
+// there is dropped (kBufOff lies past every plane).
+constexpr uint32_t kBufOff = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
 }
 
 // Row coordinates of one lane, computed once: the source voxel of a tap is
@@ -52,14 +80,8 @@ __device__ __forceinline__ GgRow gg_row(const GatherGemmArgs& a, long r, long nr
 // Source voxel (linear index at the source resolution) of a row for tap t, or -1.
 template <int MODE>
 __device__ __forceinline__ long gg_source_m(const GatherGemmArgs& a, const GgRow& g, int t) {
-  const int D = a.D, H = a.H, W = a.W;  // row grid
-  if constexpr (MODE == GG_CONV3_FWD || MODE == GG_CONV3_BWD) {
-    int dz = t / 9 - 1, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;  // tap t of the 3x3x3 stencil
-    if constexpr (MODE == GG_CONV3_BWD) { dz = -dz; dy = -dy; dx = -dx; }
-    const int zz = g.z + dz, yy = g.y + dy, xx = g.x + dx;
-    if (zz < 0 || zz >= D || yy < 0 || yy >= H || xx < 0 || xx >= W) return -1;
-    return ((long)zz * H + yy) * W + xx;
-  } else if constexpr (MODE == GG_UP_BWD) {
+  const int H = a.H, W = a.W;  // row grid
+  if constexpr (MODE == GG_UP_BWD) {
     // row (z, y, x) is a coarse voxel; tap t = dz*4 + dy*2 + dx selects the fine voxel
     const int zz = 2 * g.z + (t >> 2), yy = 2 * g.y + ((t >> 1) & 1), xx = 2 * g.x + (t & 1);
     return ((long)zz * (2 * H) + yy) * (2 * W) + xx;
@@ -111,46 +133,10 @@ __global__ void __launch_bounds__(256) k_gather_gemm(GatherGemmArgs a) {
     st.kin = st.t * a.C + st.c < K;
     return st;
   };
-  // 3x3x3 modes: per row, the address of its own voxel and a mask of the taps
-  // whose source voxel lies inside the grid, so that a step costs one shared
-  // tap offset per lane and a bit test and an add per row
-  constexpr bool CONV3 = MODE == GG_CONV3_FWD || MODE == GG_CONV3_BWD;
-  constexpr int SGN = MODE == GG_CONV3_BWD ? -1 : 1;
-  const uint16_t* rbase[RT];
-  uint32_t tmask[RT];
-  if constexpr (CONV3) {
-#pragma unroll
-    for (int i = 0; i < RT; ++i) {
-      const GgRow& g = rows[i];
-      rbase[i] = src + (((long)g.z * a.H + g.y) * a.W + g.x) * a.src_cs;
-      uint32_t mz = 0, my = 0, mx = 0;  // bit d + 1 set: offset d in -1..1 stays inside
-#pragma unroll
-      for (int d = -1; d <= 1; ++d) {
-        const int e = SGN * d;
-        mz |= (g.z + e >= 0 && g.z + e < a.D) ? 1u << (d + 1) : 0u;
-        my |= (g.y + e >= 0 && g.y + e < a.H) ? 1u << (d + 1) : 0u;
-        mx |= (g.x + e >= 0 && g.x + e < a.W) ? 1u << (d + 1) : 0u;
-      }
-      uint32_t m = 0;
-#pragma unroll
-      for (int t = 0; t < 27; ++t)
-        if (((mz >> (t / 9)) & (my >> ((t / 3) % 3)) & (mx >> (t % 3)) & 1u) != 0) m |= 1u << t;
-      tmask[i] = g.ok ? m : 0u;
-    }
-  }
-  auto tap_offset = [&](int t) -> long {  // source voxel of tap t relative to the row's voxel, in elements
-    const int dz = t / 9 - 1, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
-    return (long)(SGN * ((dz * a.H + dy) * a.W + dx)) * a.src_cs;
-  };
-  auto ld_a = [&](int i, const Step& st, long toff) -> uint4 {
-    if constexpr (CONV3) {
-      const bool on = st.kin && ((tmask[i] >> (st.t & 31)) & 1u) != 0;   // kin implies t < 27
-      return *(on ? reinterpret_cast<const uint4*>(rbase[i] + toff + st.c) : zero);
-    } else {
-      const long sv = gg_source_m<MODE>(a, rows[i], st.t);
-      const bool on = st.kin && rows[i].ok && sv >= 0;
-      return *(on ? reinterpret_cast<const uint4*>(src + sv * a.src_cs + st.c) : zero);
-    }
+  auto ld_a = [&](int i, const Step& st) -> uint4 {
+    const long sv = gg_source_m<MODE>(a, rows[i], st.t);
+    const bool on = st.kin && rows[i].ok && sv >= 0;
+    return *(on ? reinterpret_cast<const uint4*>(src + sv * a.src_cs + st.c) : zero);
   };
   auto ld_b = [&](int j, const Step& st) -> uint4 {
     return *(st.kin ? reinterpret_cast<const uint4*>(wt + ((size_t)st.t * a.Npad + j * 16 + (lane & 15)) * a.C + st.c)
@@ -159,9 +145,8 @@ __global__ void __launch_bounds__(256) k_gather_gemm(GatherGemmArgs a) {
   // set X holds the operands of the current step, set Y those of the next
   uint4 xa[RT], ya[RT], xb[NBP], yb[NBP];
   auto load = [&](uint4 (&sa)[RT], uint4 (&sb)[NBP], const Step& st) {
-    const long toff = CONV3 ? tap_offset(st.t) : 0;
 #pragma unroll
-    for (int i = 0; i < RT; ++i) sa[i] = ld_a(i, st, toff);
+    for (int i = 0; i < RT; ++i) sa[i] = ld_a(i, st);
     if constexpr (PB) {
 #pragma unroll
       for (int j = 0; j < NB; ++j) sb[j] = ld_b(j, st);
@@ -225,120 +210,253 @@ __global__ void __launch_bounds__(256) k_gather_gemm(GatherGemmArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// 3x3x3 layers from an LDS halo tile.  A block's rows are a 16 x 4 x RT box of
-// output voxels (x fastest; wavefront w takes y0 + w, row tile i takes z0 + i,
-// MFMA row m takes x0 + m).  The input box with a one-voxel halo, 18 x 6 x
-// (RT + 2) voxels of all C channels with zeros outside the grid, is staged in
-// LDS once, and every tap reads its A operand there at a fixed offset, instead
-// of gathering it from global memory nine to 27 times per voxel.
+// 3x3x3 layers.  A block's rows are a 16 x 4 x RT box of output voxels (x
+// fastest; wavefront w takes y0 + w % 4, MFMA column m takes x0 + m, row tile i
+// takes z0 + i); NH = 2 puts two wavefronts on a row, each with its own NT
+// column tiles of 16 output channels.  The input box with its one-voxel halo
+// (zeros outside the grid) is staged in LDS once, all C channels, and every tap
+// reads its operand there at a fixed offset.  The block marches along z: the
+// next box is loaded into registers while the MFMAs of this one run where its
+// LDS leaves one block per CU; below that the other blocks of the CU hide the
+// loads.  Weights stay in registers for the whole march where they are at most
+// 28 fragments (C <= 32 at NT = 1), else each tap's are loaded two taps ahead.  Voxels of 32 channels and more are padded by 16 bytes in LDS, so that
+// the eight voxels of one read phase fall into different banks.
+//
+// The MFMA takes the weights as its A operand, so a lane ends up with four
+// consecutive output channels of one voxel and stores 8 bytes; the reduction
+// runs over k = t C + c in steps of 32, taps first.
+//
+// Bound by LDS reads (1 KiB per NT MFMAs) and, at 16 channels, by HBM: the
+// 16 -> 16 layer moves 64 B per voxel, 3.6 TB/s at 512 x 512 x 128.  Times at
+// that volume, first with one box per block, 64-bit addresses formed per load
+// and 2-byte stores (64 -> 32 and wider: gathered from global memory): 1 -> 16
+// channels 1.08 -> 0.45 ms, 16 -> 16 1.59 -> 0.59, 32 -> 16 3.81 -> 1.04,
+// 64 -> 32 (256 x 256 x 64) 2.32 -> 1.06, 128 -> 64 (128 x 128 x 32) 1.15 -> 0.90.
 // ---------------------------------------------------------------------------
 constexpr int kHbX = 18, kHbY = 6;  // halo box extent in x and y
 
-template <int NB, int RT, int MODE>
-__global__ void __launch_bounds__(256) k_conv3_lds(GatherGemmArgs a) {
-  extern __shared__ uint4 s_box4[];
-  uint16_t* s_box = reinterpret_cast<uint16_t*>(s_box4);  // [RT + 2][6][18][C]
-  constexpr int BZ = RT + 2;
-  constexpr int SGN = MODE == GG_CONV3_BWD ? -1 : 1;
+template <int C>
+__host__ __device__ constexpr int conv_stride() { return C >= 32 ? C + 8 : C; }  // elements per LDS voxel
+
+template <int C, int NT, int NH, int RT, int MODE, bool IN32>
+__global__ void __launch_bounds__(256 * NH, NH == 1 && (RT + 2) * 108 * conv_stride<C>() * 2 > 80 * 1024 ? 1 : 2)
+k_conv3(ConvArgs a) {
+  constexpr int BZ = RT + 2, NV = kHbX * kHbY * BZ, CCH = C / 8, VS = conv_stride<C>();
+  constexpr int ZS = kHbY * kHbX * VS;                      // one plane of the box
+  // threads and 16-byte chunks per voxel of one staging half, chunks per thread and plane
+  constexpr int NTHR = 256 * NH, NTH = C > 8 ? NTHR / 2 : NTHR, CCT = C > 8 ? CCH / 2 : 1;
+  constexpr int NCP = (kHbX * kHbY * CCT + NTH - 1) / NTH;
+  constexpr int NSTEP = (27 * C + 31) / 32, KC = C >= 32 ? C / 32 : 1;
+  constexpr bool PRE = NSTEP * NT <= 28;                    // weights in registers
+  static_assert(PRE || C >= 32, "weights of several taps per step stay in registers");
+  constexpr bool PF = NV * VS * 2 > 64 * 1024;              // one block per CU: next box prefetched
+  __shared__ __align__(16) uint16_t s_box[NV * VS];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int C = a.C;
-  const int x0 = blockIdx.x * 16, y0 = blockIdx.y * 4, z0 = blockIdx.z * RT;
-  const int cch = C / 8;  // 16-byte chunks per voxel
-  const int nchunk = kHbX * kHbY * BZ * cch;
-  for (int e = threadIdx.x; e < nchunk; e += 256) {
-    const int v = e / cch, q = e - v * cch;
-    const int bx = v % kHbX, by = (v / kHbX) % kHbY, bz = v / (kHbX * kHbY);
-    const int gx = x0 + bx - 1, gy = y0 + by - 1, gz = z0 + bz - 1;
-    uint4 val = make_uint4(0, 0, 0, 0);
-    if (gx >= 0 && gx < a.W && gy >= 0 && gy < a.H && gz >= 0 && gz < a.D)
-      val = *reinterpret_cast<const uint4*>(a.src + (((long)gz * a.H + gy) * a.W + gx) * a.src_cs + a.src_c0 +
-                                            q * 8);
-    s_box4[e] = val;  // chunk e is voxel v, channels 8q .. 8q + 7
+  const int wy = wv & 3, nh = wv >> 2;
+  const int lx = lane & 15, g = lane >> 4;
+  // block -> (column group, x, y, z run): column groups share the input box
+  uint32_t id = xcd_tile(blockIdx.x, gridDim.x);
+  const int ngrp = a.Npad / (16 * NT * NH);
+  const int n0 = ((int)(id % ngrp) * NH + nh) * NT * 16;
+  id /= ngrp;
+  const int xt = (a.W + 15) / 16, yt = (a.H + 3) / 4, zt = (a.D + RT - 1) / RT;
+  const int x0 = (int)(id % xt) * 16;
+  id /= xt;
+  const int y0 = (int)(id % yt) * 4;
+  const int zb = (int)(id / yt) * a.zrun, ze = min(zt, zb + a.zrun);
+
+  // Staging: half of the wavefronts load channels [0, C/2) from src, the other
+  // half [C/2, C) from src2 (all of them the one chunk of C = 8).  A thread's
+  // chunks sit at the same offsets in every plane, computed once; the six rows
+  // of a plane are a buffer descriptor, empty for planes outside the grid, and
+  // chunks outside it in x or y take an offset past every one: both read 0.
+  const uint32_t half = C > 8 ? __builtin_amdgcn_readfirstlane(threadIdx.x / (NTHR / 2)) : 0u;
+  const int th = (int)threadIdx.x - (int)half * (NTHR / 2);
+  const uint32_t esz = IN32 ? 4u : (uint32_t)a.src_cs * 2u;   // bytes per source voxel
+  const uint32_t rowb = (uint32_t)a.W * esz;
+  uint32_t goff[NCP];
+  int loff[NCP];   // LDS element offset, or -1
+#pragma unroll
+  for (int i = 0; i < NCP; ++i) {
+    const int e = th + i * NTH, v = e / CCT, q = e % CCT;
+    const int x = x0 + v % kHbX - 1, y = y0 + v / kHbX - 1;
+    const bool in = e < kHbX * kHbY * CCT;
+    goff[i] = in && (unsigned)x < (unsigned)a.W && (unsigned)y < (unsigned)a.H
+                  ? (uint32_t)(v / kHbX) * rowb + x * esz + (IN32 ? 0u : q * 16u) : kBufOff;
+    loff[i] = in ? v * VS + (int)(half * CCT + q) * 8 : -1;
   }
-  __syncthreads();
-  const int lx = lane & 15;
-  const int kq = (lane >> 4) * 8;
-  const int K = 27 * C;
-  const uint16_t* __restrict__ wt = a.wt;
-  const uint4* zero = &g_gg_zero;
-  f32x4 acc[RT][NB];
+  const char* gsrc = IN32 ? reinterpret_cast<const char*>(a.src32)
+                          : reinterpret_cast<const char*>(half ? a.src2 : a.src);
+  u32x4 st[BZ][NCP];
+  float st32[BZ][NCP];
+  auto load_box = [&](int z0) {
 #pragma unroll
-  for (int i = 0; i < RT; ++i)
+    for (int b = 0; b < BZ; ++b) {
+      const int z = z0 + b - 1;
+      const __amdgpu_buffer_rsrc_t r =
+          buf_rsrc(gsrc + ((long)z * a.H + y0 - 1) * rowb, (unsigned)z < (unsigned)a.D ? kHbY * rowb : 0u);
 #pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // the weights of step k + 32 are loaded while the MFMAs of step k run (two
-  // register sets used in turn); a trailing step past K reads zeros
-  struct Step {
-    int t, c;
-    bool kin;
-  };
-  auto next = [&](Step st) {
-    st.c += 32;
-    while (st.c >= C) {
-      st.c -= C;
-      ++st.t;
-    }
-    st.kin = st.t * C + st.c < K;  // t < 27
-    return st;
-  };
-  auto ld_b = [&](uint4 (&sb)[NB], const Step& st) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-      sb[j] = *(st.kin ? reinterpret_cast<const uint4*>(wt + ((size_t)st.t * a.Npad + j * 16 + lx) * C + st.c) : zero);
-  };
-  auto mma = [&](const uint4 (&sb)[NB], const Step& st) {
-    const int tt = st.kin ? st.t : 13;  // the centre tap keeps the LDS index inside the box
-    const int dz = SGN * (tt / 9 - 1), dy = SGN * ((tt / 3) % 3 - 1), dx = SGN * (tt % 3 - 1);
-    bf16x8 av[RT];
-#pragma unroll
-    for (int i = 0; i < RT; ++i) {
-      const int vi = ((i + 1 + dz) * kHbY + (wv + 1 + dy)) * kHbX + (lx + 1 + dx);
-      const uint4 raw = *reinterpret_cast<const uint4*>(s_box + (size_t)vi * C + st.c);
-      av[i] = __builtin_bit_cast(bf16x8, st.kin ? raw : make_uint4(0, 0, 0, 0));
-    }
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const bf16x8 bv = __builtin_bit_cast(bf16x8, sb[j]);
-#pragma unroll
-      for (int i = 0; i < RT; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv, acc[i][j], 0, 0, 0);
+      for (int i = 0; i < NCP; ++i) {
+        if constexpr (IN32) st32[b][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)goff[i], 0, 0));
+        else st[b][i] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)goff[i], 0, 0);
+      }
     }
   };
-  uint4 xb[NB], yb[NB];
-  Step cur{kq / C, kq - (kq / C) * C, kq < K};
-  ld_b(xb, cur);
-  for (int k0 = 0; k0 < K; k0 += 64) {
-    const Step s1 = next(cur);
-    ld_b(yb, s1);
-    mma(xb, cur);
-    const Step s2 = next(s1);
-    ld_b(xb, s2);
-    mma(yb, s1);
-    cur = s2;
+  auto store_box = [&]() {
+#pragma unroll
+    for (int i = 0; i < NCP; ++i) {
+      if (loff[i] < 0) continue;
+#pragma unroll
+      for (int b = 0; b < BZ; ++b) {
+        u32x4 v;
+        if constexpr (IN32) v = u32x4{f2bf(a.scale * st32[b][i]), 0u, 0u, 0u};
+        else v = st[b][i];
+        *reinterpret_cast<u32x4*>(s_box + loff[i] + b * ZS) = v;
+      }
+    }
+  };
+  // weight fragment of the reduction elements k = 8 g .. 8 g + 7 of a step
+  const uint16_t* wt = a.wt;
+  auto ld_w = [&](int t, int c, int j) -> bf16x8 {
+    const bool on = C >= 32 || t < 27;
+    return __builtin_bit_cast(
+        bf16x8, *(on ? reinterpret_cast<const u32x4*>(wt + ((size_t)t * a.Npad + n0 + j * 16 + lx) * C + c)
+                     : reinterpret_cast<const u32x4*>(&g_gg_zero)));
+  };
+  // LDS element offset of tap t relative to this lane's voxel at (0, 0, 0)
+  auto tap = [&](int t) -> int {
+    const int dz = MODE == GG_CONV3_BWD ? 2 - t / 9 : t / 9, dy = MODE == GG_CONV3_BWD ? 2 - (t / 3) % 3 : (t / 3) % 3,
+              dx = MODE == GG_CONV3_BWD ? 2 - t % 3 : t % 3;
+    return ((dz * kHbY + dy) * kHbX + dx) * VS;
+  };
+  const uint16_t* lane_box = s_box + (wy * kHbX + lx) * VS + (C >= 32 ? g * 8 : (C == 16 ? (g & 1) * 8 : 0));
+
+  // PRE: every fragment; else a ring of three taps, loaded two taps ahead
+  bf16x8 wr[PRE ? NSTEP : 3 * KC][NT];
+  if constexpr (PRE) {
+#pragma unroll
+    for (int k = 0; k < NSTEP; ++k)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        if constexpr (C == 8) wr[k][j] = ld_w(4 * k + g, 0, j);
+        else if constexpr (C == 16) wr[k][j] = ld_w(2 * k + (g >> 1), (g & 1) * 8, j);
+        else wr[k][j] = ld_w(k / KC, (k % KC) * 32 + g * 8, j);
+      }
   }
-  // epilogue: D row m = 4 (lane / 16) + i is voxel (x0 + m, y0 + wv, z0 + rt)
-  const int y = y0 + wv;
+  auto ld_tap = [&](int t, int slot) {
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    const int z = z0 + rt;
+    for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int n = j * 16 + lx;
-      if (n >= a.N) continue;
+      for (int j = 0; j < NT; ++j) wr[PRE ? 0 : slot * KC + kc][j] = ld_w(t, kc * 32 + g * 8, j);
+  };
+  // output offsets of this lane's voxel and channels in the four rows of a
+  // plane (kBufOff: not stored)
+  const uint32_t drow = (uint32_t)a.W * a.dst_cs * 2u, mrow = (uint32_t)a.W * a.mask_cs * 2u;
+  uint32_t doff[NT], doff2[NT], moff[NT];
+  float bs[NT][4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int x = x0 + (lane >> 4) * 4 + i;
-        if (x >= a.W || y >= a.H || z >= a.D) continue;
-        float v = acc[rt][j][i];
-        if (a.bias) v += a.bias[n];
-        if (a.relu) v = fmaxf(v, 0.f);
-        const size_t o = (size_t)(((long)z * a.H + y) * a.W + x) * a.dst_cs + a.dst_c0 + n;
-        if (a.out_f32) {
-          float* d = reinterpret_cast<float*>(a.dst);
-          d[o] = a.accumulate ? d[o] + v : v;
+  for (int j = 0; j < NT; ++j) {
+    const int x = x0 + lx, n = n0 + j * 16 + g * 4;
+    const bool on = x < a.W && y0 + wy < a.H && n < a.N;
+    const uint32_t o = wy * drow + (uint32_t)x * a.dst_cs * 2u;
+    doff[j] = on && n < a.nsplit ? o + n * 2u : kBufOff;
+    doff2[j] = on && n >= a.nsplit ? o + (n - a.nsplit) * 2u : kBufOff;
+    moff[j] = on ? wy * mrow + ((uint32_t)x * a.mask_cs + n) * 2u : kBufOff;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bs[j][r] = a.bias && n < a.N ? a.bias[n + r] : 0.f;
+  }
+  if (PF && zb < ze) load_box(zb * RT);
+  for (int zi = zb; zi < ze; ++zi) {
+    const int z0 = zi * RT;
+    if (!PF) load_box(z0);
+    __syncthreads();   // the previous box has been read
+    store_box();
+    __syncthreads();
+    if (PF && zi + 1 < ze) load_box(z0 + RT);
+    f32x4 acc[RT][NT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (PRE) {
+#pragma unroll
+      for (int k = 0; k < NSTEP; ++k) {
+        int off;
+        bool in = true;   // the last step of C < 32 has taps past 26
+        if constexpr (C >= 32) {
+          off = tap(k);
+        } else if constexpr (C == 16) {
+          const int o0 = tap(2 * k), o1 = 2 * k + 1 < 27 ? tap(2 * k + 1) : 0;
+          off = (g >> 1) ? o1 : o0;
+          in = 2 * k + 1 < 27 || (g >> 1) == 0;
         } else {
-          uint16_t* d = reinterpret_cast<uint16_t*>(a.dst);
-          d[o] = f2bf(a.accumulate ? bf2f(d[o]) + v : v);
+          const int o0 = tap(4 * k), o1 = tap(4 * k + 1), o2 = tap(4 * k + 2), o3 = 4 * k + 3 < 27 ? tap(4 * k + 3) : 0;
+          off = g < 2 ? (g == 0 ? o0 : o1) : (g == 2 ? o2 : o3);
+          in = 4 * k + 3 < 27 || g < 3;
         }
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+          u32x4 raw = *reinterpret_cast<const u32x4*>(lane_box + off + i * ZS);
+          if (C < 32 && k == NSTEP - 1 && !in) raw = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+          for (int j = 0; j < NT; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[k][j], __builtin_bit_cast(bf16x8, raw), acc[i][j], 0, 0, 0);
+        }
+      }
+    } else {
+      // a fresh pointer per box: the loads of all taps would otherwise be
+      // hoisted out of the march into registers it does not have
+      asm volatile("" : "+s"(wt));
+      ld_tap(0, 0);
+      ld_tap(1, 1);
+#pragma unroll 1
+      for (int dz = 0; dz < 3; ++dz) {
+        const uint16_t* zbox = lane_box + (MODE == GG_CONV3_BWD ? 2 - dz : dz) * ZS;
+#pragma unroll
+        for (int u = 0; u < 9; ++u) {
+          ld_tap(min(dz * 9 + u + 2, 26), (u + 2) % 3);   // past the last tap: not used
+          const int uu = MODE == GG_CONV3_BWD ? 8 - u : u;
+          const int off = ((uu / 3) * kHbX + uu % 3) * VS;
+#pragma unroll
+          for (int kc = 0; kc < KC; ++kc) {
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+              const bf16x8 xv = *reinterpret_cast<const bf16x8*>(zbox + off + i * ZS + kc * 32);
+#pragma unroll
+              for (int j = 0; j < NT; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[(u % 3) * KC + kc][j], xv, acc[i][j], 0, 0, 0);
+            }
+          }
+        }
+      }
+    }
+    // D row 4 g + r is an output channel, column lx a voxel
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i) {
+        const int z = z0 + i;
+        if (z >= a.D) break;
+        float v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          v[r] = acc[i][j][r];
+          if (a.bias) v[r] += bs[j][r];
+          if (a.relu) v[r] = fmaxf(v[r], 0.f);
+        }
+        u32x2 o = {bf_pack(v[0], v[1]), bf_pack(v[2], v[3])};
+        if (a.mask) {
+          const __amdgpu_buffer_rsrc_t rm =
+              buf_rsrc(reinterpret_cast<const char*>(a.mask) + ((long)z * a.H + y0) * mrow, 4 * mrow);
+          o = bf_mask(o, __builtin_amdgcn_raw_buffer_load_b64(rm, (int)moff[j], 0, 0));
+        }
+        const long row = ((long)z * a.H + y0) * drow;
+        if (n0 + j * 16 < a.nsplit)
+          __builtin_amdgcn_raw_buffer_store_b64(o, buf_rsrc(reinterpret_cast<char*>(a.dst) + row, 4 * drow),
+                                                (int)doff[j], 0, 0);
+        if (n0 + j * 16 + 16 > a.nsplit)
+          __builtin_amdgcn_raw_buffer_store_b64(o, buf_rsrc(reinterpret_cast<char*>(a.dst2) + row, 4 * drow),
+                                                (int)doff2[j], 0, 0);
       }
     }
   }
@@ -649,39 +767,64 @@ static int ew_grid(size_t n) {
   return (int)(b > 16384 ? 16384 : (b == 0 ? 1 : b));
 }
 
-// Halo-box bytes of k_conv3_lds, or 0 when a layer does not take it (other
-// modes, more than 8 column tiles, rows narrower than a tile, or a box above
-// 64 KiB, which would leave fewer than two blocks per CU).
-static size_t conv3_lds_bytes(const GatherGemmArgs& a, int rt) {
-  if (a.mode != GG_CONV3_FWD && a.mode != GG_CONV3_BWD) return 0;
-  if (a.Npad / 16 > 8 || a.W < 16 || a.C % 8 != 0 || a.src_cs % 8 != 0 || a.src_c0 % 8 != 0) return 0;
-  const size_t bytes = (size_t)kHbX * kHbY * (rt + 2) * a.C * sizeof(uint16_t);
-  return bytes <= 64 * 1024 ? bytes : 0;
+// Blocks and z run of a 3x3x3 layer.  Big grids take boxes of RT planes and
+// march along z in runs that leave about 2048 blocks; grids of fewer boxes than
+// compute units (the coarse levels of a training crop) take one plane and 16
+// output channels per block, which spreads them over more of the chip.
+template <int C, int NT, int NH, int RT, bool IN32>
+static hipError_t launch_conv3_t(ConvArgs a, hipStream_t s) {
+  const long xy = (long)((a.W + 15) / 16) * ((a.H + 3) / 4), zt = (a.D + RT - 1) / RT;
+  const long groups = a.Npad / (16 * NT * NH);
+  a.zrun = (int)std::max<long>(1, std::min<long>(zt, xy * zt * groups / 2048));
+  const dim3 g((unsigned)(xy * groups * ((zt + a.zrun - 1) / a.zrun)));
+  if constexpr (!IN32) {
+    if (a.bwd) {
+      hipLaunchKernelGGL((k_conv3<C, NT, NH, RT, GG_CONV3_BWD, false>), g, dim3(256 * NH), 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_conv3<C, NT, NH, RT, GG_CONV3_FWD, IN32>), g, dim3(256 * NH), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_conv3(ConvArgs a, hipStream_t s) {
+  if (a.N % 8 || a.Npad % 16 || a.src_cs % 8 || a.dst_cs % 4 || a.mask_cs % 4 || (a.src32 && (a.bwd || a.C != 8)))
+    return hipErrorInvalidValue;
+  // six rows of a plane are addressed with 31 bits
+  if ((double)a.W * std::max(a.src_cs, std::max(a.dst_cs, a.mask_cs)) * 2 * kHbY >= 2147483648.0) return hipErrorInvalidValue;
+  const int nt = a.Npad / 16;
+  const bool in32 = a.src32 != nullptr;
+  const int rt = a.C <= 64 ? 4 : 2;
+  const long boxes = (long)((a.W + 15) / 16) * ((a.H + 3) / 4) * ((a.D + rt - 1) / rt) * ((nt + 3) / 4);
+  const bool small = boxes < 256;
+  if (in32) {
+    if (small || nt == 1) return small ? launch_conv3_t<8, 1, 1, 1, true>(a, s) : launch_conv3_t<8, 1, 1, 4, true>(a, s);
+    return nt == 2 ? launch_conv3_t<8, 2, 1, 4, true>(a, s) : launch_conv3_t<8, 2, 2, 4, true>(a, s);
+  }
+  switch (a.C) {
+    case 8: return small || nt > 1 ? launch_conv3_t<8, 1, 1, 1, false>(a, s) : launch_conv3_t<8, 1, 1, 4, false>(a, s);
+    case 16:
+      if (!small && nt == 1) return launch_conv3_t<16, 1, 1, 4, false>(a, s);
+      if (!small && nt == 2) return launch_conv3_t<16, 2, 1, 4, false>(a, s);
+      return launch_conv3_t<16, 1, 1, 1, false>(a, s);
+    case 32:
+      if (!small && nt == 1) return launch_conv3_t<32, 1, 1, 4, false>(a, s);
+      if (!small && nt == 2) return launch_conv3_t<32, 2, 1, 4, false>(a, s);
+      if (!small && nt % 4 == 0) return launch_conv3_t<32, 2, 2, 4, false>(a, s);
+      return launch_conv3_t<32, 1, 1, 1, false>(a, s);
+    case 64:
+      if (!small && nt == 2) return launch_conv3_t<64, 2, 1, 4, false>(a, s);
+      if (!small && nt % 4 == 0) return launch_conv3_t<64, 2, 2, 4, false>(a, s);
+      return launch_conv3_t<64, 1, 1, 1, false>(a, s);
+    case 128:
+      if (!small && nt % 4 == 0) return launch_conv3_t<128, 2, 2, 2, false>(a, s);
+      return launch_conv3_t<128, 1, 1, 1, false>(a, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 hipError_t launch_gather_gemm(const GatherGemmArgs& a, hipStream_t s) {
   const long nrows = (long)a.D * a.H * a.W;
-  {
-    const int nb = a.Npad / 16;
-    const int rt = nb <= 2 ? 4 : (nb == 4 ? 2 : 1);
-    const size_t lds = conv3_lds_bytes(a, rt);
-    if (lds > 0) {
-      const dim3 g((unsigned)((a.W + 15) / 16), (unsigned)((a.H + 3) / 4), (unsigned)((a.D + rt - 1) / rt));
-      const bool bwd = a.mode == GG_CONV3_BWD;
-#define RIHVR_CONV3(NB, RT)                                                                                    \
-  if (bwd) hipLaunchKernelGGL((k_conv3_lds<NB, RT, GG_CONV3_BWD>), g, dim3(256), lds, s, a);                   \
-  else hipLaunchKernelGGL((k_conv3_lds<NB, RT, GG_CONV3_FWD>), g, dim3(256), lds, s, a);
-      switch (nb) {
-        case 1: RIHVR_CONV3(1, 4) break;
-        case 2: RIHVR_CONV3(2, 4) break;
-        case 4: RIHVR_CONV3(4, 2) break;
-        case 8: RIHVR_CONV3(8, 1) break;
-        default: return hipErrorInvalidValue;
-      }
-#undef RIHVR_CONV3
-      return hipGetLastError();
-    }
-  }
   // row tiles per wave: enough MFMAs per loaded fragment without exceeding the
   // accumulator budget (RT * NB <= 8 tiles of 16 x 16)
   auto grid = [&](int rt) { return dim3((unsigned)((nrows + 64 * rt - 1) / (64 * rt))); };
@@ -689,8 +832,6 @@ hipError_t launch_gather_gemm(const GatherGemmArgs& a, hipStream_t s) {
     constexpr int NB = decltype(nb)::value, RT = decltype(rt)::value;
     const dim3 g = grid(RT);
     switch (a.mode) {
-      case GG_CONV3_FWD: hipLaunchKernelGGL((k_gather_gemm<NB, RT, GG_CONV3_FWD>), g, dim3(256), 0, s, a); break;
-      case GG_CONV3_BWD: hipLaunchKernelGGL((k_gather_gemm<NB, RT, GG_CONV3_BWD>), g, dim3(256), 0, s, a); break;
       case GG_UP_BWD: hipLaunchKernelGGL((k_gather_gemm<NB, RT, GG_UP_BWD>), g, dim3(256), 0, s, a); break;
       case GG_UP_FWD:
       case GG_POINT: hipLaunchKernelGGL((k_gather_gemm<NB, RT, GG_POINT>), g, dim3(256), 0, s, a); break;

@@ -7,7 +7,7 @@
 
 namespace rihvr {
 
-// Gather modes of the convolution-like GEMM (see unet.hip).
+// Layer modes (see unet.hip); the 3x3x3 ones run k_conv3, the others the gather GEMM.
 enum GatherMode {
   GG_CONV3_FWD = 0,  // rows: voxels; tap t reads voxel r + offset(t) (zero outside)
   GG_CONV3_BWD = 1,  // rows: voxels; tap t reads voxel r - offset(t)
@@ -31,6 +31,29 @@ struct GatherGemmArgs {
   int dst_cs, dst_c0;
 };
 hipError_t launch_gather_gemm(const GatherGemmArgs& a, hipStream_t s);
+
+// 3x3x3 layer (forward, or its input gradient with the per-tap transposed weights).
+struct ConvArgs {
+  int bwd;
+  int D, H, W;
+  const uint16_t* src;     // channels [0, C/2) of the input (all of them when C = 8), stride src_cs
+  const uint16_t* src2;    // channels [C/2, C)
+  int src_cs;
+  const float* src32;      // instead of src, C = 8: channel 0 is scale * src32 rounded to BF16, the others 0
+  float scale;
+  int C;                   // input channels: 8, 16, 32, 64 or 128
+  const uint16_t* wt;      // packed BF16 B[27][Npad][C]
+  int N, Npad;             // real (multiple of 8) and padded output channels
+  const float* bias;       // nullable
+  int relu;
+  const uint16_t* mask;    // nullable: outputs where mask <= 0 become 0 (same voxel and channel)
+  int mask_cs;
+  uint16_t* dst;           // channels [0, nsplit)
+  uint16_t* dst2;          // channels [nsplit, N)
+  int nsplit, dst_cs;
+  int zrun;                // set by the launcher
+};
+hipError_t launch_conv3(ConvArgs a, hipStream_t s);
 
 // Weight and bias gradient of one layer: per-block partials, added in order
 // (with the loss and, for lr > 0, the Adam update) by launch_finish_grads, so
