@@ -112,10 +112,10 @@ Net build_net(int L, int base) {
 // Activation / gradient buffers for one volume size.
 struct Buffers {
   size_t total = 0;
-  size_t packed = 0, in0 = 0, y = 0, gy8 = 0, loss = 0, lpart = 0;
+  size_t packed = 0, y = 0, gy8 = 0, loss = 0, lpart = 0;
   std::vector<size_t> wpart, bpart;   // gradient partials of each layer
   std::vector<int> nblk;              // ... and their count
-  std::vector<size_t> a, cat, p, idx, da, db, ga, gcat, gda, gdb, gp;
+  std::vector<size_t> a, up, skip, p, idx, da, db, ga, gup, gskip, gda, gdb, gp;
   size_t bbot = 0, gbbot = 0;
 };
 
@@ -132,15 +132,16 @@ Buffers layout(const Net& n, int D, int H, int W, bool train) {
   };
   auto nv = [&](int l) { return (size_t)(D >> l) * (H >> l) * (W >> l); };
   B.packed = take(n.npacked * 2);
-  B.in0 = take(nv(0) * 8 * 2);
   B.a.resize(L);
-  B.cat.resize(L);
+  B.up.resize(L);
+  B.skip.resize(L);
   B.p.resize(L);
   B.idx.resize(L);
   B.da.resize(L);
   B.db.resize(L);
   B.ga.resize(L);
-  B.gcat.resize(L);
+  B.gup.resize(L);
+  B.gskip.resize(L);
   B.gda.resize(L);
   B.gdb.resize(L);
   B.gp.resize(L);
@@ -148,23 +149,25 @@ Buffers layout(const Net& n, int D, int H, int W, bool train) {
     const size_t c = n.ch[l];
     B.a[l] = take(nv(l) * c * 2);
     if (l < L - 1) {
-      B.cat[l] = take(nv(l) * 2 * c * 2);
+      B.up[l] = take(nv(l) * c * 2);
+      B.skip[l] = take(nv(l) * c * 2);
       B.p[l] = take(nv(l + 1) * c * 2);
-      B.idx[l] = take(nv(l + 1) * c);
+      if (train) B.idx[l] = take(nv(l + 1) * c);
       B.da[l] = take(nv(l) * c * 2);
       B.db[l] = take(nv(l) * c * 2);
     }
   }
   B.bbot = take(nv(L - 1) * n.ch[L - 1] * 2);
-  B.y = take(nv(0) * 4);
   if (train) {
+    B.y = take(nv(0) * 4);
     B.gy8 = take(nv(0) * 8 * 2);
     B.loss = take(4);
     for (int l = 0; l < L; ++l) {
       const size_t c = n.ch[l];
       B.ga[l] = take(nv(l) * c * 2);
       if (l < L - 1) {
-        B.gcat[l] = take(nv(l) * 2 * c * 2);
+        B.gup[l] = take(nv(l) * c * 2);
+        B.gskip[l] = take(nv(l) * c * 2);
         B.gda[l] = take(nv(l) * c * 2);
         B.gdb[l] = take(nv(l) * c * 2);
         B.gp[l] = take(nv(l + 1) * c * 2);
@@ -233,74 +236,59 @@ ri_status check_dims(const ri_unet_config* c, int D, int H, int W) {
     }                                                                   \
   } while (0)
 
-GatherGemmArgs gemm(int mode, int D, int H, int W, const uint16_t* src, int cs, int c0, int T, int C,
-                    const uint16_t* wt, int N, int Npad, const float* bias, int relu, void* dst, int dcs, int dc0,
-                    int out_f32 = 0) {
-  GatherGemmArgs g{};
-  g.mode = mode;
-  g.D = D; g.H = H; g.W = W;
-  g.src = src; g.src_cs = cs; g.src_c0 = c0;
-  g.T = T; g.C = C;
-  g.wt = wt; g.N = N; g.Npad = Npad;
-  g.bias = bias;
-  g.relu = relu;
-  g.out_f32 = out_f32;
-  g.dst = dst; g.dst_cs = dcs; g.dst_c0 = dc0;
-  return g;
-}
-
-// 3x3x3 layer of a channel view (channels contiguous)
-ConvArgs conv(int bwd, int D, int H, int W, const uint16_t* src, int cs, int C, const uint16_t* wt, int N, int Npad,
-              const float* bias, int relu, uint16_t* dst, int dcs) {
+// 3x3x3 layer on contiguous channels
+ConvArgs conv(int bwd, int D, int H, int W, const uint16_t* src, int C, const uint16_t* wt, int N, int Npad,
+              const float* bias, int relu, uint16_t* dst) {
   ConvArgs a{};
   a.bwd = bwd;
   a.D = D; a.H = H; a.W = W;
-  a.src = src; a.src2 = src + C / 2; a.src_cs = cs;
+  a.src = src; a.src2 = src + C / 2; a.src_cs = C;
   a.C = C;
   a.wt = wt; a.N = N; a.Npad = Npad;
   a.bias = bias; a.relu = relu;
-  a.dst = dst; a.dst2 = dst; a.nsplit = a.Npad; a.dst_cs = dcs;
+  a.dst = dst; a.dst2 = dst; a.nsplit = Npad; a.dst_cs = N;
   return a;
 }
 
 ri_status pack_all(const Net& n, const float* params, uint16_t* packed, bool with_bwd, hipStream_t s) {
+  PackTable tab{};
+  auto entry = [&](const Layer& y, int T, int kind, int Npad, int Cpad, size_t out) {
+    tab.e[tab.n++] = PackEntry{params + y.w, packed + out, T, y.cin, y.cout, kind, Npad, Cpad, 0};
+  };
   for (const Layer& y : n.layers) {
-    if (y.kind == CONV) {
-      UTRY(launch_pack(params + y.w, 27, y.cin, y.cout, 1, y.f_npad, y.f_c, packed + y.pf, s));
-      if (with_bwd) UTRY(launch_pack(params + y.w, 27, y.cin, y.cout, 0, y.b_npad, y.b_c, packed + y.pb, s));
-    } else if (y.kind == UP) {
-      UTRY(launch_pack_up_fwd(params + y.w, y.cin, y.cout, packed + y.pf, s));
-      if (with_bwd) UTRY(launch_pack(params + y.w, 8, y.cin, y.cout, 0, y.b_npad, y.b_c, packed + y.pb, s));
-    } else {
-      UTRY(launch_pack(params + y.w, 1, y.cin, 1, 1, y.f_npad, y.f_c, packed + y.pf, s));
-      if (with_bwd) UTRY(launch_pack(params + y.w, 1, y.cin, 1, 0, y.b_npad, y.b_c, packed + y.pb, s));
-    }
+    const int T = y.kind == CONV ? 27 : (y.kind == UP ? 8 : 1);
+    if (y.kind == UP) entry(y, 1, 2, y.f_npad, y.f_c, y.pf);
+    else entry(y, T, 1, y.f_npad, y.f_c, y.pf);
+    if (with_bwd) entry(y, T, 0, y.b_npad, y.b_c, y.pb);
   }
+  UTRY(launch_pack(tab, s));
   return RI_OK;
 }
 
-ri_status forward(const Net& n, const float* params, const float* in, float scale, int D, int H, int W, void* ws,
-                  const Buffers& B, bool train, hipStream_t s) {
+// Network output (training: the head's pre-activation) to `out`.
+ri_status forward(const Net& n, const float* params, const float* in, float scale, float* out, int D, int H, int W,
+                  void* ws, const Buffers& B, bool train, hipStream_t s) {
   const int L = n.L;
   uint16_t* pk = at<uint16_t>(ws, B.packed);
   ri_status st = pack_all(n, params, pk, train, s);
   if (st != RI_OK) return st;
-  uint16_t* in0 = at<uint16_t>(ws, B.in0);
-  UTRY(launch_input(in, scale, in0, 8, (long)D * H * W, s));
   for (int l = 0; l < L; ++l) {
     const int Dl = D >> l, Hl = H >> l, Wl = W >> l, c = n.ch[l];
     const Layer& ea = n.layers[n.enc_a(l)];
     const Layer& eb = n.layers[n.enc_b(l)];
-    const uint16_t* src = l == 0 ? in0 : at<uint16_t>(ws, B.p[l - 1]);
-    const int scs = l == 0 ? 8 : n.ch[l - 1];
     uint16_t* a = at<uint16_t>(ws, B.a[l]);
-    UTRY(launch_conv3(conv(0, Dl, Hl, Wl, src, scs, ea.f_c, pk + ea.pf, c, ea.f_npad, params + ea.b, 1, a, c), s));
-    uint16_t* bo = l < L - 1 ? at<uint16_t>(ws, B.cat[l]) : at<uint16_t>(ws, B.bbot);
-    const int bcs = l < L - 1 ? 2 * c : c, bc0 = l < L - 1 ? c : 0;
-    UTRY(launch_conv3(conv(0, Dl, Hl, Wl, a, c, eb.f_c, pk + eb.pf, c, eb.f_npad, params + eb.b, 1, bo + bc0, bcs),
-                      s));
+    ConvArgs ca = conv(0, Dl, Hl, Wl, l == 0 ? nullptr : at<uint16_t>(ws, B.p[l - 1]), ea.f_c, pk + ea.pf, c, ea.f_npad,
+                       params + ea.b, 1, a);
+    if (l == 0) {
+      ca.src = ca.src2 = nullptr;
+      ca.src32 = in;
+      ca.scale = scale;
+    }
+    UTRY(launch_conv3(ca, s));
+    uint16_t* bo = l < L - 1 ? at<uint16_t>(ws, B.skip[l]) : at<uint16_t>(ws, B.bbot);
+    UTRY(launch_conv3(conv(0, Dl, Hl, Wl, a, eb.f_c, pk + eb.pf, c, eb.f_npad, params + eb.b, 1, bo), s));
     if (l < L - 1)
-      UTRY(launch_pool_fwd(bo, bcs, bc0, at<uint16_t>(ws, B.p[l]), c, at<uint8_t>(ws, B.idx[l]), c, Dl / 2, Hl / 2,
+      UTRY(launch_pool_fwd(bo, at<uint16_t>(ws, B.p[l]), train ? at<uint8_t>(ws, B.idx[l]) : nullptr, c, Dl / 2, Hl / 2,
                            Wl / 2, s));
   }
   const uint16_t* h = at<uint16_t>(ws, B.bbot);
@@ -309,102 +297,111 @@ ri_status forward(const Net& n, const float* params, const float* in, float scal
     const Layer& up = n.layers[n.up(l)];
     const Layer& da = n.layers[n.dec_a(l)];
     const Layer& db = n.layers[n.dec_b(l)];
-    uint16_t* cat = at<uint16_t>(ws, B.cat[l]);
-    GatherGemmArgs g = gemm(GG_UP_FWD, Dl / 2, Hl / 2, Wl / 2, h, cu, 0, 1, up.f_c, pk + up.pf, 8 * c, up.f_npad,
-                            params + up.b, 0, cat, 2 * c, 0);
-    g.up_cout = c;
-    UTRY(launch_gather_gemm(g, s));
+    uint16_t* uo = at<uint16_t>(ws, B.up[l]);
+    UTRY(launch_up_fwd(UpArgs{Dl / 2, Hl / 2, Wl / 2, h, cu, c, pk + up.pf, params + up.b, uo}, s));
     uint16_t* dao = at<uint16_t>(ws, B.da[l]);
-    UTRY(launch_conv3(conv(0, Dl, Hl, Wl, cat, 2 * c, da.f_c, pk + da.pf, c, da.f_npad, params + da.b, 1, dao, c), s));
+    ConvArgs ca = conv(0, Dl, Hl, Wl, uo, da.f_c, pk + da.pf, c, da.f_npad, params + da.b, 1, dao);
+    ca.src2 = at<uint16_t>(ws, B.skip[l]);   // concatenation [up, skip]
+    ca.src_cs = c;
+    UTRY(launch_conv3(ca, s));
     uint16_t* dbo = at<uint16_t>(ws, B.db[l]);
-    UTRY(launch_conv3(conv(0, Dl, Hl, Wl, dao, c, db.f_c, pk + db.pf, c, db.f_npad, params + db.b, 1, dbo, c), s));
+    UTRY(launch_conv3(conv(0, Dl, Hl, Wl, dao, db.f_c, pk + db.pf, c, db.f_npad, params + db.b, 1, dbo), s));
     h = dbo;
   }
   // head: ReLU output for inference; training keeps the pre-activation (the
   // loss is taken on it, so a voxel below zero still passes gradient)
   const Layer& hd = n.layers[n.head()];
-  UTRY(launch_gather_gemm(gemm(GG_POINT, D, H, W, h, n.ch[0], 0, 1, hd.f_c, pk + hd.pf, 1, hd.f_npad, params + hd.b,
-                               train ? 0 : 1, at<float>(ws, B.y), 1, 0, 1), s));
+  UTRY(launch_head(h, n.ch[0], pk + hd.pf, params + hd.b, train ? 0 : 1, out, (long)D * H * W, s));
   return RI_OK;
 }
 
-ri_status backward(const Net& n, const float* params, const float* target, float pos_weight, int D, int H, int W,
-                   void* ws, const Buffers& B, hipStream_t s) {
+// Gradients from the loss down; every ReLU mask is applied where the gradient
+// is written.
+ri_status backward(const Net& n, const float* params, const float* in, float scale, const float* target,
+                   float pos_weight, int D, int H, int W, void* ws, const Buffers& B, hipStream_t s) {
   const int L = n.L;
   uint16_t* pk = at<uint16_t>(ws, B.packed);
-  const long nv0 = (long)D * H * W;
   uint16_t* gy8 = at<uint16_t>(ws, B.gy8);
-  UTRY(launch_zero_u16(gy8, (size_t)nv0 * 8, s));
-  UTRY(launch_mse(at<float>(ws, B.y), target, nv0, pos_weight, gy8, 8, at<float>(ws, B.lpart), s));
-  auto wgrad = [&](int k, int mode, int Dl, int Hl, int Wl, const uint16_t* g, int gcs, int gc0, const uint16_t* src,
-                   int scs, int sc0) {
+  UTRY(launch_mse(at<float>(ws, B.y), target, (long)D * H * W, pos_weight, gy8, at<float>(ws, B.lpart), s));
+  auto wgrad = [&](int k, int mode, int Dl, int Hl, int Wl, const uint16_t* g, int gcs, const uint16_t* src,
+                   const uint16_t* src2 = nullptr) {
     const Layer& y = n.layers[k];
     WgradArgs w{};
     w.mode = mode;
     w.D = Dl; w.H = Hl; w.W = Wl;
-    w.g = g; w.g_cs = gcs; w.g_c0 = gc0; w.N = y.cout;
-    w.s = src; w.s_cs = scs; w.s_c0 = sc0; w.C = y.cin;
+    w.g = g; w.g_cs = gcs; w.N = y.cout;
+    w.s = src; w.s_cs = y.cin; w.ssplit = pad(y.cin, 8); w.C = y.cin;
+    if (src2) {          // concatenation of two buffers of cin / 2 channels
+      w.s_cs = w.ssplit = y.cin / 2;
+      w.s2 = src2 - y.cin / 2;
+    }
+    if (!src) {          // the first layer
+      w.s32 = in;
+      w.scale = scale;
+      w.s_cs = 8;
+    }
     w.part = at<float>(ws, B.wpart[k]);
     w.bpart = at<float>(ws, B.bpart[k]);
     return launch_wgrad(w, B.nblk[k], s);
+  };
+  auto gemm = [&](int mode, int Dl, int Hl, int Wl, const uint16_t* src, int cs, int T, const Layer& y,
+                  const uint16_t* mask, uint16_t* dst) {
+    return launch_gather_gemm(GatherGemmArgs{mode, Dl, Hl, Wl, src, cs, T, y.b_c, pk + y.pb, y.cin, y.b_npad, mask, dst},
+                              s);
   };
   // head
   const Layer& hd = n.layers[n.head()];
   const uint16_t* top = L > 1 ? at<uint16_t>(ws, B.db[0]) : at<uint16_t>(ws, B.bbot);
   uint16_t* gtop = L > 1 ? at<uint16_t>(ws, B.gdb[0]) : at<uint16_t>(ws, B.gbbot);
-  UTRY(wgrad(n.head(), GG_POINT, D, H, W, gy8, 8, 0, top, n.ch[0], 0));
-  UTRY(launch_gather_gemm(gemm(GG_POINT, D, H, W, gy8, 8, 0, 1, hd.b_c, pk + hd.pb, n.ch[0], hd.b_npad, nullptr, 0,
-                               gtop, n.ch[0], 0), s));
+  UTRY(wgrad(n.head(), GG_POINT, D, H, W, gy8, 8, top));
+  UTRY(gemm(GG_POINT, D, H, W, gy8, 8, 1, hd, top, gtop));
   // decoder, finest level first
   for (int l = 0; l <= L - 2; ++l) {
-    const int Dl = D >> l, Hl = H >> l, Wl = W >> l, c = n.ch[l], cu = n.ch[l + 1];
-    const long nvl = (long)Dl * Hl * Wl;
+    const int Dl = D >> l, Hl = H >> l, Wl = W >> l, c = n.ch[l];
     const Layer& up = n.layers[n.up(l)];
     const Layer& da = n.layers[n.dec_a(l)];
     const Layer& db = n.layers[n.dec_b(l)];
     uint16_t* gdb = at<uint16_t>(ws, B.gdb[l]);
     uint16_t* gda = at<uint16_t>(ws, B.gda[l]);
-    uint16_t* gcat = at<uint16_t>(ws, B.gcat[l]);
-    const uint16_t* dbo = at<uint16_t>(ws, B.db[l]);
+    uint16_t* gup = at<uint16_t>(ws, B.gup[l]);
     const uint16_t* dao = at<uint16_t>(ws, B.da[l]);
-    const uint16_t* cat = at<uint16_t>(ws, B.cat[l]);
-    UTRY(launch_relu_mask(gdb, c, 0, dbo, c, 0, c, nvl, s));
-    UTRY(wgrad(n.dec_b(l), GG_CONV3_FWD, Dl, Hl, Wl, gdb, c, 0, dao, c, 0));
-    UTRY(launch_conv3(conv(1, Dl, Hl, Wl, gdb, c, db.b_c, pk + db.pb, c, db.b_npad, nullptr, 0, gda, c), s));
-    UTRY(launch_relu_mask(gda, c, 0, dao, c, 0, c, nvl, s));
-    UTRY(wgrad(n.dec_a(l), GG_CONV3_FWD, Dl, Hl, Wl, gda, c, 0, cat, 2 * c, 0));
-    UTRY(launch_conv3(conv(1, Dl, Hl, Wl, gda, c, da.b_c, pk + da.pb, 2 * c, da.b_npad, nullptr, 0, gcat, 2 * c), s));
+    UTRY(wgrad(n.dec_b(l), GG_CONV3_FWD, Dl, Hl, Wl, gdb, c, dao));
+    ConvArgs cb = conv(1, Dl, Hl, Wl, gdb, db.b_c, pk + db.pb, c, db.b_npad, nullptr, 0, gda);
+    cb.mask = dao;
+    cb.mask_cs = c;
+    UTRY(launch_conv3(cb, s));
+    UTRY(wgrad(n.dec_a(l), GG_CONV3_FWD, Dl, Hl, Wl, gda, c, at<uint16_t>(ws, B.up[l]), at<uint16_t>(ws, B.skip[l])));
+    ConvArgs ca = conv(1, Dl, Hl, Wl, gda, da.b_c, pk + da.pb, 2 * c, da.b_npad, nullptr, 0, gup);
+    ca.dst2 = at<uint16_t>(ws, B.gskip[l]);
+    ca.nsplit = c;
+    ca.dst_cs = c;
+    UTRY(launch_conv3(ca, s));
     // up-convolution: gradient rows at the fine level, parameters over coarse rows
     const uint16_t* hin = (l + 1 == L - 1) ? at<uint16_t>(ws, B.bbot) : at<uint16_t>(ws, B.db[l + 1]);
     uint16_t* ghin = (l + 1 == L - 1) ? at<uint16_t>(ws, B.gbbot) : at<uint16_t>(ws, B.gdb[l + 1]);
-    UTRY(wgrad(n.up(l), GG_UP_FWD, Dl / 2, Hl / 2, Wl / 2, gcat, 2 * c, 0, hin, cu, 0));
-    UTRY(launch_gather_gemm(gemm(GG_UP_BWD, Dl / 2, Hl / 2, Wl / 2, gcat, 2 * c, 0, 8, up.b_c, pk + up.pb, cu,
-                                 up.b_npad, nullptr, 0, ghin, cu, 0), s));
+    UTRY(wgrad(n.up(l), GG_UP_FWD, Dl / 2, Hl / 2, Wl / 2, gup, c, hin));
+    UTRY(gemm(GG_UP_BWD, Dl / 2, Hl / 2, Wl / 2, gup, c, 8, up, hin, ghin));
   }
   // encoder, coarsest level first
   for (int l = L - 1; l >= 0; --l) {
     const int Dl = D >> l, Hl = H >> l, Wl = W >> l, c = n.ch[l];
-    const long nvl = (long)Dl * Hl * Wl;
     const Layer& ea = n.layers[n.enc_a(l)];
     const Layer& eb = n.layers[n.enc_b(l)];
-    uint16_t* gout = l == L - 1 ? at<uint16_t>(ws, B.gbbot) : at<uint16_t>(ws, B.gcat[l]);
-    const uint16_t* out = l == L - 1 ? at<uint16_t>(ws, B.bbot) : at<uint16_t>(ws, B.cat[l]);
-    const int ocs = l == L - 1 ? c : 2 * c, oc0 = l == L - 1 ? 0 : c;
+    uint16_t* gout = l == L - 1 ? at<uint16_t>(ws, B.gbbot) : at<uint16_t>(ws, B.gskip[l]);
     if (l < L - 1)
-      UTRY(launch_pool_bwd(at<uint16_t>(ws, B.gp[l]), c, at<uint8_t>(ws, B.idx[l]), gout, ocs, oc0, c, Dl / 2,
-                           Hl / 2, Wl / 2, s));
-    UTRY(launch_relu_mask(gout, ocs, oc0, out, ocs, oc0, c, nvl, s));
+      UTRY(launch_pool_bwd(at<uint16_t>(ws, B.gp[l]), at<uint8_t>(ws, B.idx[l]), at<uint16_t>(ws, B.skip[l]), gout, c,
+                           Dl / 2, Hl / 2, Wl / 2, s));
     const uint16_t* a = at<uint16_t>(ws, B.a[l]);
     uint16_t* ga = at<uint16_t>(ws, B.ga[l]);
-    UTRY(wgrad(n.enc_b(l), GG_CONV3_FWD, Dl, Hl, Wl, gout, ocs, oc0, a, c, 0));
-    UTRY(launch_conv3(conv(1, Dl, Hl, Wl, gout + oc0, ocs, eb.b_c, pk + eb.pb, c, eb.b_npad, nullptr, 0, ga, c), s));
-    UTRY(launch_relu_mask(ga, c, 0, a, c, 0, c, nvl, s));
-    const uint16_t* src = l == 0 ? at<uint16_t>(ws, B.in0) : at<uint16_t>(ws, B.p[l - 1]);
-    const int scs = l == 0 ? 8 : n.ch[l - 1], cin = l == 0 ? 1 : n.ch[l - 1];
-    UTRY(wgrad(n.enc_a(l), GG_CONV3_FWD, Dl, Hl, Wl, ga, c, 0, src, scs, 0));
+    UTRY(wgrad(n.enc_b(l), GG_CONV3_FWD, Dl, Hl, Wl, gout, c, a));
+    ConvArgs cb = conv(1, Dl, Hl, Wl, gout, eb.b_c, pk + eb.pb, c, eb.b_npad, nullptr, 0, ga);
+    cb.mask = a;
+    cb.mask_cs = c;
+    UTRY(launch_conv3(cb, s));
+    UTRY(wgrad(n.enc_a(l), GG_CONV3_FWD, Dl, Hl, Wl, ga, c, l == 0 ? nullptr : at<uint16_t>(ws, B.p[l - 1])));
     if (l > 0)
-      UTRY(launch_conv3(conv(1, Dl, Hl, Wl, ga, c, ea.b_c, pk + ea.pb, cin, ea.b_npad, nullptr, 0,
-                             at<uint16_t>(ws, B.gp[l - 1]), cin), s));
+      UTRY(launch_conv3(conv(1, Dl, Hl, Wl, ga, ea.b_c, pk + ea.pb, n.ch[l - 1], ea.b_npad, nullptr, 0,
+                             at<uint16_t>(ws, B.gp[l - 1])), s));
   }
   return RI_OK;
 }
@@ -475,10 +472,7 @@ extern "C" ri_status ri_unet_forward(const ri_unet_config* cfg, const float* par
   const Buffers B = layout(n, d, h, w, false);
   if (ws_bytes < B.total) return set_error(RI_ERR_WORKSPACE_TOO_SMALL, "unet workspace too small");
   hipStream_t s = (hipStream_t)stream;
-  st = forward(n, params, in, scale, d, h, w, ws, B, false, s);
-  if (st != RI_OK) return st;
-  UTRY(hipMemcpyAsync(out, at<float>(ws, B.y), (size_t)d * h * w * sizeof(float), hipMemcpyDeviceToDevice, s));
-  return RI_OK;
+  return forward(n, params, in, scale, out, d, h, w, ws, B, false, s);
 }
 
 extern "C" ri_status ri_unet_train_step(const ri_unet_config* cfg, float* params, float* grads, float* adam_m,
@@ -498,9 +492,9 @@ extern "C" ri_status ri_unet_train_step(const ri_unet_config* cfg, float* params
   const Buffers B = layout(n, d, h, w, true);
   if (ws_bytes < B.total) return set_error(RI_ERR_WORKSPACE_TOO_SMALL, "unet workspace too small");
   hipStream_t s = (hipStream_t)stream;
-  st = forward(n, params, in, scale, d, h, w, ws, B, true, s);
+  st = forward(n, params, in, scale, at<float>(ws, B.y), d, h, w, ws, B, true, s);
   if (st != RI_OK) return st;
-  st = backward(n, params, target, pos_weight, d, h, w, ws, B, s);
+  st = backward(n, params, in, scale, target, pos_weight, d, h, w, ws, B, s);
   if (st != RI_OK) return st;
   // gradients (and the loss) from their partials, with the Adam update
   GradTable tab{};

@@ -1,8 +1,8 @@
 // Warm-start 3D U-Net kernels for gfx950: BF16 activations and weights, FP32
 // accumulation on the matrix cores (v_mfma_f32_16x16x32_bf16).
 //
-// Activations are channels-last, [z][y][x][c] with a channel stride (so a
-// concatenation is two views of one buffer).  Every convolution-like layer is a
+// Activations are channels-last, [z][y][x][c]; the two halves of a
+// concatenation are buffers of their own.  Every convolution-like layer is a
 // matrix product: row r is an output voxel, the reduction index k = t*C + c runs
 // over taps t and input channels c.  The 3x3x3 layers read their operand from a
 // haloed box in LDS (k_conv3); the others gather it from a source voxel chosen by
@@ -68,12 +68,11 @@ struct GgRow {
 __device__ __forceinline__ GgRow gg_row(const GatherGemmArgs& a, long r, long nrows) {
   GgRow g;
   g.ok = r < nrows;
-  const long rr = g.ok ? r : 0;
-  const long hw = (long)a.W * a.H;
-  g.z = (int)(rr / hw);
-  const int rem = (int)(rr - (long)g.z * hw);
-  g.y = rem / a.W;
-  g.x = rem - g.y * a.W;
+  const uint32_t rr = g.ok ? (uint32_t)r : 0u;   // fewer than 2^31 rows (launch_gather_gemm)
+  const uint32_t zy = rr / (uint32_t)a.W;
+  g.x = (int)(rr - zy * a.W);
+  g.z = (int)(zy / (uint32_t)a.H);
+  g.y = (int)(zy - g.z * (uint32_t)a.H);
   return g;
 }
 
@@ -85,7 +84,7 @@ __device__ __forceinline__ long gg_source_m(const GatherGemmArgs& a, const GgRow
     // row (z, y, x) is a coarse voxel; tap t = dz*4 + dy*2 + dx selects the fine voxel
     const int zz = 2 * g.z + (t >> 2), yy = 2 * g.y + ((t >> 1) & 1), xx = 2 * g.x + (t & 1);
     return ((long)zz * (2 * H) + yy) * (2 * W) + xx;
-  } else {  // GG_UP_FWD, GG_POINT
+  } else {  // GG_POINT
     return ((long)g.z * H + g.y) * W + g.x;
   }
 }
@@ -115,7 +114,7 @@ __global__ void __launch_bounds__(256) k_gather_gemm(GatherGemmArgs a) {
   for (int i = 0; i < RT; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const uint16_t* __restrict__ src = a.src + a.src_c0;
+  const uint16_t* __restrict__ src = a.src;
   const uint16_t* __restrict__ wt = a.wt;
   const uint4* zero = &g_gg_zero;
   constexpr bool PB = NB <= 4;   // B prefetched with A
@@ -184,26 +183,8 @@ __global__ void __launch_bounds__(256) k_gather_gemm(GatherGemmArgs a) {
       for (int i = 0; i < 4; ++i) {
         const long r = row0 + rt * 16 + (lane >> 4) * 4 + i;
         if (r >= nrows) continue;
-        float v = acc[rt][j][i];
-        long dvox = r;
-        int dch = n;
-        if (a.mode == GG_UP_FWD) {
-          // column n = d * Cout + co writes fine voxel 2 q + d, channel co
-          const int d = n / a.up_cout, co = n - d * a.up_cout;
-          const GgRow g = gg_row(a, r, nrows);
-          dvox = ((long)(2 * g.z + (d >> 2)) * (2 * a.H) + 2 * g.y + ((d >> 1) & 1)) * (2 * a.W) + 2 * g.x + (d & 1);
-          dch = co;
-        }
-        if (a.bias) v += a.bias[dch];
-        if (a.relu) v = fmaxf(v, 0.f);
-        const size_t o = (size_t)dvox * a.dst_cs + a.dst_c0 + dch;
-        if (a.out_f32) {
-          float* d = reinterpret_cast<float*>(a.dst);
-          d[o] = a.accumulate ? d[o] + v : v;
-        } else {
-          uint16_t* d = reinterpret_cast<uint16_t*>(a.dst);
-          d[o] = f2bf(a.accumulate ? bf2f(d[o]) + v : v);
-        }
+        const bool on = a.mask == nullptr || bf2f(a.mask[(size_t)r * a.N + n]) > 0.f;
+        a.dst[(size_t)r * a.N + n] = on ? f2bf(acc[rt][j][i]) : (uint16_t)0;
       }
     }
   }
@@ -535,8 +516,10 @@ __global__ void __launch_bounds__(256) k_wgrad(WgradArgs a) {
       constexpr int O = CONV ? 1 : 0;
       const int x = x0 + v % HX - O, y = y0 + (v / HX) % HY - O, z = z0 + v / (HX * HY) - O, c = c0 + q * 8;
       const bool on = (unsigned)x < (unsigned)a.W && (unsigned)y < (unsigned)a.H && (unsigned)z < (unsigned)a.D && c < a.C;
-      const uint4 val = *(on ? reinterpret_cast<const uint4*>(a.s + (((long)z * a.H + y) * a.W + x) * a.s_cs + a.s_c0 + c)
-                             : &g_gg_zero);
+      const long vox = ((long)z * a.H + y) * a.W + x;
+      uint4 val;
+      if (a.s32) val = make_uint4(on ? f2bf(a.scale * a.s32[vox]) : 0u, 0u, 0u, 0u);
+      else val = *(on ? reinterpret_cast<const uint4*>((c < a.ssplit ? a.s : a.s2) + vox * a.s_cs + c) : &g_gg_zero);
       *reinterpret_cast<uint4*>(ss + v * SS + q * 8) = val;
     }
     for (int e = threadIdx.x; e < kWgRows * NT * 2; e += 256) {
@@ -546,7 +529,7 @@ __global__ void __launch_bounds__(256) k_wgrad(WgradArgs a) {
       long gv = ((long)z * a.H + y) * a.W + x;
       if (a.mode == GG_UP_FWD)
         gv = ((long)(2 * z + (tap >> 2)) * (2 * a.H) + 2 * y + ((tap >> 1) & 1)) * (2 * a.W) + 2 * x + (tap & 1);
-      const uint4 val = *(on ? reinterpret_cast<const uint4*>(a.g + gv * a.g_cs + a.g_c0 + n) : &g_gg_zero);
+      const uint4 val = *(on ? reinterpret_cast<const uint4*>(a.g + gv * a.g_cs + n) : &g_gg_zero);
       *reinterpret_cast<uint4*>(sg + v * SG + q * 8) = val;
     }
     __syncthreads();
@@ -654,74 +637,192 @@ __global__ void __launch_bounds__(256) k_finish_grads(GradTable tab, AdamArgs ad
 }
 
 // ---------------------------------------------------------------------------
-// Max pooling 2x2x2 (forward with argmax, backward accumulating)
+// Up-convolution (2x2x2, stride 2): the coarse voxels times [cu] x [8 c]
+// weights; column d c + co is channel co of the fine voxel 2 q + d.  A
+// wavefront takes 64 coarse voxels and every column tile (or the share of
+// blockIdx.y); the weights are the MFMA's A operand, so a lane stores four
+// channels of one fine voxel.  Bound by the stores: 16 c bytes per coarse voxel,
+// whole lines as the skip connection lies in a buffer of its own (32 -> 16
+// channels at 512 x 512 x 128: 1.60 ms with 2-byte stores into half of each
+// voxel's line, now 0.55, 4.3 TB/s of stores and loads).
 // ---------------------------------------------------------------------------
-__global__ void k_pool_fwd(const uint16_t* x, int xcs, int xc0, uint16_t* y, int ycs, uint8_t* idx, int C,
-                           int D, int H, int W) {  // D, H, W: coarse dims
-  const long n = (long)D * H * W * C;
-  for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long)gridDim.x * blockDim.x) {
-    const int c = (int)(e % C);
-    const long q = e / C;
-    const int qx = (int)(q % W), qy = (int)((q / W) % H), qz = (int)(q / ((long)W * H));
-    float best = 0.f;
-    int bi = 0;
-    for (int d = 0; d < 8; ++d) {
-      const long f = ((long)(2 * qz + (d >> 2)) * (2 * H) + 2 * qy + ((d >> 1) & 1)) * (2 * W) + 2 * qx + (d & 1);
-      const float v = bf2f(x[(size_t)f * xcs + xc0 + c]);
-      if (d == 0 || v > best) { best = v; bi = d; }
+template <int KS>
+__global__ void __launch_bounds__(256) k_up_fwd(UpArgs a) {
+  const int lane = threadIdx.x & 63, lx = lane & 15, g = lane >> 4;
+  const long nrows = (long)a.D * a.H * a.W;
+  const long r0 = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  bf16x8 xv[4][KS];
+  long fv[4];   // fine voxel 2 q of each tile's column, or -1
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const long r = r0 + i * 16 + lx;
+    const bool on = r < nrows;   // nrows < 2^31
+    const uint32_t zy = (uint32_t)r / (uint32_t)a.W, x = (uint32_t)r - zy * a.W, z = zy / (uint32_t)a.H, y = zy - z * a.H;
+    fv[i] = on ? ((long)(2 * z) * (2 * a.H) + 2 * y) * (2 * a.W) + 2 * x : -1;
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      const int c = k * 32 + g * 8;
+      xv[i][k] = __builtin_bit_cast(
+          bf16x8, on && c < a.cu ? *reinterpret_cast<const u32x4*>(a.src + r * a.cu + c) : zero);
     }
-    y[(size_t)q * ycs + c] = f2bf(best);
-    idx[(size_t)q * C + c] = (uint8_t)bi;
+  }
+  const int tiles = 8 * a.c / 16, per = tiles / (int)gridDim.y, j0 = (int)blockIdx.y * per;
+  auto ld_w = [&](int j, int k) {
+    const int c = k * 32 + g * 8;
+    return __builtin_bit_cast(
+        bf16x8, c < a.cu ? *reinterpret_cast<const u32x4*>(a.wt + ((size_t)j * 16 + lx) * a.cu + c) : zero);
+  };
+  bf16x8 wn[KS];
+#pragma unroll
+  for (int k = 0; k < KS; ++k) wn[k] = ld_w(j0, k);
+  for (int j = j0; j < j0 + per; ++j) {
+    bf16x8 w[KS];
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      w[k] = wn[k];
+      wn[k] = ld_w(min(j + 1, tiles - 1), k);
+    }
+    const int n = j * 16 + g * 4, d = n / a.c, co = n - d * a.c;
+    float b[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) b[r] = a.bias[co + r];
+    const long off = ((long)(d >> 2) * (2 * a.H) + ((d >> 1) & 1)) * (2 * a.W) + (d & 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < KS; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[k], xv[i][k], acc, 0, 0, 0);
+      if (fv[i] >= 0)
+        *reinterpret_cast<u32x2*>(a.dst + (fv[i] + off) * a.c + co) =
+            u32x2{bf_pack(acc[0] + b[0], acc[1] + b[1]), bf_pack(acc[2] + b[2], acc[3] + b[3])};
+    }
   }
 }
 
-__global__ void k_pool_bwd(const uint16_t* gy, int gycs, const uint8_t* idx, uint16_t* gx, int gxcs, int gxc0,
-                           int C, int D, int H, int W) {  // coarse dims; gx accumulates
-  const long n = (long)D * H * W * C;
-  for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long)gridDim.x * blockDim.x) {
-    const int c = (int)(e % C);
-    const long q = e / C;
-    const int qx = (int)(q % W), qy = (int)((q / W) % H), qz = (int)(q / ((long)W * H));
-    const int d = idx[(size_t)q * C + c];
-    const long f = ((long)(2 * qz + (d >> 2)) * (2 * H) + 2 * qy + ((d >> 1) & 1)) * (2 * W) + 2 * qx + (d & 1);
-    const size_t o = (size_t)f * gxcs + gxc0 + c;
-    gx[o] = f2bf(bf2f(gx[o]) + bf2f(gy[(size_t)q * gycs + c]));
+// Head (1x1x1, one output channel, FP32): row 0 of the weight operand is real.
+template <int KS>
+__global__ void __launch_bounds__(256) k_head(const uint16_t* __restrict__ src, int C, const uint16_t* __restrict__ wt,
+                                              const float* bias, int relu, float* __restrict__ out, long nvox) {
+  const int lane = threadIdx.x & 63, lx = lane & 15, g = lane >> 4;
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  bf16x8 w[KS];
+#pragma unroll
+  for (int k = 0; k < KS; ++k) {
+    const int c = k * 32 + g * 8;
+    w[k] = __builtin_bit_cast(bf16x8, c < C ? *reinterpret_cast<const u32x4*>(wt + (size_t)lx * C + c) : zero);
+  }
+  const float b = bias[0];
+  for (long r0 = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64; r0 < nvox; r0 += (long)gridDim.x * 256) {
+    u32x4 xv[4][KS];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const long r = r0 + i * 16 + lx;
+        const int c = k * 32 + g * 8;
+        xv[i][k] = r < nvox && c < C ? *reinterpret_cast<const u32x4*>(src + r * C + c) : zero;
+      }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < KS; ++k)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[k], __builtin_bit_cast(bf16x8, xv[i][k]), acc, 0, 0, 0);
+      const long r = r0 + i * 16 + lx;
+      const float v = acc[0] + b;
+      if (g == 0 && r < nvox) out[r] = relu ? fmaxf(v, 0.f) : v;
+    }
   }
 }
 
-// g <- g * (y > 0) over a channel view
-__global__ void k_relu_mask(uint16_t* g, int gcs, int gc0, const uint16_t* y, int ycs, int yc0, int C, long nvox) {
-  const long n = nvox * C;
-  for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long)gridDim.x * blockDim.x) {
-    const int c = (int)(e % C);
-    const long v = e / C;
-    if (!(bf2f(y[(size_t)v * ycs + yc0 + c]) > 0.f)) g[(size_t)v * gcs + gc0 + c] = 0;
-  }
+// ---------------------------------------------------------------------------
+// Max pooling 2x2x2, eight channels per thread (C is a multiple of 8, channels
+// contiguous).  Forward: the first largest value of the window and, for
+// training, its index.
+// ---------------------------------------------------------------------------
+// f(coarse voxel, first fine voxel of its window, channel) for every coarse
+// voxel and chunk of 8 channels: x and channels over blockIdx.x, rows and planes
+// over blockIdx.y and .z
+template <class F>
+__device__ __forceinline__ void for_pool(int C, int D, int H, int W, F f) {
+  const uint32_t cc = (uint32_t)C / 8, e = blockIdx.x * 256u + threadIdx.x, x = e / cc;
+  if (x >= (uint32_t)W) return;
+  for (int z = blockIdx.z; z < D; z += gridDim.z)
+    for (int y = blockIdx.y; y < H; y += gridDim.y)
+      f(((long)z * H + y) * W + x, ((long)(2 * z) * (2 * H) + 2 * y) * (2 * W) + 2 * x, (int)(e - x * cc) * 8);
 }
 
-__global__ void k_fill_u16(uint16_t* p, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0;
+__global__ void __launch_bounds__(256) k_pool_fwd(const uint16_t* __restrict__ x, uint16_t* __restrict__ y,
+                                                  uint8_t* __restrict__ idx, int C, int D, int H, int W) {
+  for_pool(C, D, H, W, [&](long q, long f0, int c) {
+    u32x4 v[8];
+#pragma unroll
+    for (int d = 0; d < 8; ++d)
+      v[d] = *reinterpret_cast<const u32x4*>(x + (f0 + ((long)(d >> 2) * (2 * H) + ((d >> 1) & 1)) * (2 * W) + (d & 1)) * C + c);
+    u32x4 best = v[0], bi = {0u, 0u, 0u, 0u};   // bi: per channel the index, 16 bits each
+#pragma unroll
+    for (int d = 1; d < 8; ++d)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t b = best[k], w = v[d][k];
+        const bool lo = __uint_as_float(w << 16) > __uint_as_float(b << 16);
+        const bool hi = __uint_as_float(w & 0xffff0000u) > __uint_as_float(b & 0xffff0000u);
+        best[k] = (lo ? w & 0xffffu : b & 0xffffu) | (hi ? w & 0xffff0000u : b & 0xffff0000u);
+        bi[k] = (lo ? (uint32_t)d : bi[k] & 0xffffu) | (hi ? (uint32_t)d << 16 : bi[k] & 0xffff0000u);
+      }
+    *reinterpret_cast<u32x4*>(y + q * C + c) = best;
+    if (idx != nullptr) {
+      u32x2 o;
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        o[k] = (bi[2 * k] & 7u) | ((bi[2 * k] >> 16) << 8) | ((bi[2 * k + 1] & 7u) << 16) | ((bi[2 * k + 1] >> 16) << 24);
+      *reinterpret_cast<u32x2*>(idx + q * C + c) = o;
+    }
+  });
 }
 
-// input: x_bf16[v][0] = scale * in[v], channels 1..cs-1 zero
-__global__ void k_input(const float* in, float scale, uint16_t* x, int cs, long nvox) {
-  for (long v = (long)blockIdx.x * blockDim.x + threadIdx.x; v < nvox; v += (long)gridDim.x * blockDim.x) {
-    x[(size_t)v * cs] = f2bf(scale * in[v]);
-    for (int c = 1; c < cs; ++c) x[(size_t)v * cs + c] = 0;
-  }
+// Backward, onto the gradient that came through the skip connection: g at the
+// window's winner grows by the pooled gradient (rounded), and the ReLU of the
+// pooled layer (y) masks every voxel.
+__global__ void __launch_bounds__(256) k_pool_bwd(const uint16_t* __restrict__ gy, const uint8_t* __restrict__ idx,
+                                                  const uint16_t* __restrict__ y, uint16_t* __restrict__ g, int C,
+                                                  int D, int H, int W) {
+  for_pool(C, D, H, W, [&](long q, long f0, int c) {
+    const u32x4 gv = *reinterpret_cast<const u32x4*>(gy + q * C + c);
+    const u32x2 iv = *reinterpret_cast<const u32x2*>(idx + q * C + c);
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+      const long o = (f0 + ((long)(d >> 2) * (2 * H) + ((d >> 1) & 1)) * (2 * W) + (d & 1)) * C + c;
+      const u32x4 yv = *reinterpret_cast<const u32x4*>(y + o);
+      u32x4 gg = *reinterpret_cast<const u32x4*>(g + o);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float r[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t w = (iv[k >> 1] >> (16 * (k & 1) + 8 * h)) & 0xffu;
+          const float a = bf2f((uint16_t)(gg[k] >> (16 * h))), b = bf2f((uint16_t)(gv[k] >> (16 * h)));
+          r[h] = w == (uint32_t)d ? a + b : a;
+          if (!(bf2f((uint16_t)(yv[k] >> (16 * h))) > 0.f)) r[h] = 0.f;
+        }
+        gg[k] = bf_pack(r[0], r[1]);
+      }
+      *reinterpret_cast<u32x4*>(g + o) = gg;
+    }
+  });
 }
 
 // Weighted MSE of the head's pre-activation y (FP32) against t, weight pos_w
-// where t > 0 and 1 elsewhere; gradient 2 w (y - t) / n into g[v][0]
-__global__ void k_mse(const float* y, const float* t, long n, float inv_n, float pos_w, uint16_t* g, int gcs,
-                      float* loss) {
+// where t > 0 and 1 elsewhere; gradient 2 w (y - t) / n into channel 0 of g[v][8], zeros in the others
+__global__ void k_mse(const float* y, const float* t, long n, float inv_n, float pos_w, uint16_t* g, float* loss) {
   __shared__ float red[4];
   float s = 0.f;
   for (long v = (long)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (long)gridDim.x * blockDim.x) {
     const float d = y[v] - t[v];
     const float w = t[v] > 0.f ? pos_w : 1.f;
     s += w * d * d;
-    g[(size_t)v * gcs] = f2bf(2.f * w * d * inv_n);
+    *reinterpret_cast<u32x4*>(g + v * 8) = u32x4{f2bf(2.f * w * d * inv_n), 0u, 0u, 0u};
   }
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
@@ -729,34 +830,27 @@ __global__ void k_mse(const float* y, const float* t, long n, float inv_n, float
   if (threadIdx.x == 0) loss[blockIdx.x] = (red[0] + red[1] + red[2] + red[3]) * inv_n;   // per-block partial
 }
 
-// Pack FP32 master weights W[t][cin][cout] into BF16 B[t][n][c] for one use:
-// transpose = 1: n = cout, c = cin (forward); 0: n = cin, c = cout (input
-// gradient).  Channels beyond the real counts are zero.
-__global__ void k_pack(const float* w, int T, int cin, int cout, int transpose, int Npad, int Cpad, uint16_t* out) {
-  const size_t n = (size_t)T * Npad * Cpad;
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x) {
-    const int c = (int)(e % Cpad);
-    const int nn = (int)((e / Cpad) % Npad);
-    const int t = (int)(e / ((size_t)Cpad * Npad));
-    float v = 0.f;
-    if (transpose) {
-      if (nn < cout && c < cin) v = w[((size_t)t * cin + c) * cout + nn];
-    } else {
-      if (nn < cin && c < cout) v = w[((size_t)t * cin + nn) * cout + c];
-    }
-    out[e] = f2bf(v);
+// Pack FP32 master weights W[t][cin][cout] into BF16 B[t][n][c], every layer
+// and use in one launch (a table entry each).  kind 1: n = cout, c = cin
+// (forward); 0: n = cin, c = cout (input gradient); 2, the up-convolution
+// forward: one tap, n = t cout + co, c = cin.  Channels beyond the real counts
+// are zero.
+__global__ void __launch_bounds__(256) k_pack(PackTable tab) {
+  int k = 0;
+  while (k + 1 < tab.n && (int)blockIdx.x >= tab.e[k + 1].block0) ++k;
+  const PackEntry p = tab.e[k];
+  const uint32_t e = (blockIdx.x - (uint32_t)p.block0) * 256u + threadIdx.x;
+  if (e >= (uint32_t)p.T * p.Npad * p.Cpad) return;
+  const uint32_t c = e % p.Cpad, r = e / p.Cpad, nn = r % p.Npad, t = r / p.Npad;
+  float v = 0.f;
+  if (p.kind == 1) {
+    if (nn < (uint32_t)p.cout && c < (uint32_t)p.cin) v = p.w[(t * p.cin + c) * p.cout + nn];
+  } else if (p.kind == 0) {
+    if (nn < (uint32_t)p.cin && c < (uint32_t)p.cout) v = p.w[(t * p.cin + nn) * p.cout + c];
+  } else {
+    v = p.w[((nn / p.cout) * p.cin + c) * p.cout + nn % p.cout];
   }
-}
-
-// Up-convolution forward packing: B[0][n = d*cout + co][c = ci] = U[d][ci][co].
-__global__ void k_pack_up_fwd(const float* u, int cin, int cout, uint16_t* out) {
-  const size_t n = (size_t)8 * cout * cin;
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x) {
-    const int ci = (int)(e % cin);
-    const int col = (int)(e / cin);
-    const int d = col / cout, co = col - d * cout;
-    out[e] = f2bf(u[((size_t)d * cin + ci) * cout + co]);
-  }
+  p.out[e] = f2bf(v);
 }
 
 // ---------------------------------------------------------------------------
@@ -825,6 +919,7 @@ hipError_t launch_conv3(ConvArgs a, hipStream_t s) {
 
 hipError_t launch_gather_gemm(const GatherGemmArgs& a, hipStream_t s) {
   const long nrows = (long)a.D * a.H * a.W;
+  if (nrows >= (1l << 31)) return hipErrorInvalidValue;
   // row tiles per wave: enough MFMAs per loaded fragment without exceeding the
   // accumulator budget (RT * NB <= 8 tiles of 16 x 16)
   auto grid = [&](int rt) { return dim3((unsigned)((nrows + 64 * rt - 1) / (64 * rt))); };
@@ -833,7 +928,6 @@ hipError_t launch_gather_gemm(const GatherGemmArgs& a, hipStream_t s) {
     const dim3 g = grid(RT);
     switch (a.mode) {
       case GG_UP_BWD: hipLaunchKernelGGL((k_gather_gemm<NB, RT, GG_UP_BWD>), g, dim3(256), 0, s, a); break;
-      case GG_UP_FWD:
       case GG_POINT: hipLaunchKernelGGL((k_gather_gemm<NB, RT, GG_POINT>), g, dim3(256), 0, s, a); break;
       default: return hipErrorInvalidValue;
     }
@@ -847,9 +941,6 @@ hipError_t launch_gather_gemm(const GatherGemmArgs& a, hipStream_t s) {
     case 2: return by_mode(I2{}, I4{});
     case 4: return by_mode(I4{}, I2{});
     case 8: return by_mode(std::integral_constant<int, 8>{}, I1{});
-    case 16: return by_mode(std::integral_constant<int, 16>{}, I1{});
-    case 32: return by_mode(std::integral_constant<int, 32>{}, I1{});
-    case 64: return by_mode(std::integral_constant<int, 64>{}, I1{});
     default: return hipErrorInvalidValue;
   }
 }
@@ -863,7 +954,7 @@ int wgrad_blocks(int mode, int D, int H, int W, int N, int C) {
 }
 
 hipError_t launch_wgrad(WgradArgs a, int blocks, hipStream_t s) {
-  if (a.N < 1 || a.C < 1 || a.s_cs % 8 || a.s_c0 % 8 || a.g_cs % 8 || a.g_c0 % 8) return hipErrorInvalidValue;
+  if (a.N < 1 || a.C < 1 || a.s_cs % 8 || a.ssplit % 8 || a.g_cs % 8 || (a.s32 && a.C != 1)) return hipErrorInvalidValue;
   const int tn = (a.N + 15) / 16, tc = (a.C + 15) / 16;
   if ((tn & (tn - 1)) || (tc & (tc - 1))) return hipErrorInvalidValue;
   a.Cpad = tc * 16;
@@ -892,54 +983,67 @@ hipError_t launch_finish_grads(GradTable& tab, const AdamArgs& ad, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_pool_fwd(const uint16_t* x, int xcs, int xc0, uint16_t* y, int ycs, uint8_t* idx, int C, int D,
-                           int H, int W, hipStream_t s) {
-  hipLaunchKernelGGL(k_pool_fwd, dim3(ew_grid((size_t)D * H * W * C)), dim3(256), 0, s, x, xcs, xc0, y, ycs, idx, C,
-                     D, H, W);
+static dim3 pool_grid(int C, int D, int H, int W) {
+  return dim3((unsigned)(((long)W * (C / 8) + 255) / 256), (unsigned)std::min(H, 65535), (unsigned)std::min(D, 65535));
+}
+
+hipError_t launch_pool_fwd(const uint16_t* x, uint16_t* y, uint8_t* idx, int C, int D, int H, int W, hipStream_t s) {
+  hipLaunchKernelGGL(k_pool_fwd, pool_grid(C, D, H, W), dim3(256), 0, s, x, y, idx, C, D, H, W);
   return hipGetLastError();
 }
 
-hipError_t launch_pool_bwd(const uint16_t* gy, int gycs, const uint8_t* idx, uint16_t* gx, int gxcs, int gxc0, int C,
-                           int D, int H, int W, hipStream_t s) {
-  hipLaunchKernelGGL(k_pool_bwd, dim3(ew_grid((size_t)D * H * W * C)), dim3(256), 0, s, gy, gycs, idx, gx, gxcs,
-                     gxc0, C, D, H, W);
+hipError_t launch_pool_bwd(const uint16_t* gy, const uint8_t* idx, const uint16_t* y, uint16_t* g, int C, int D, int H,
+                           int W, hipStream_t s) {
+  hipLaunchKernelGGL(k_pool_bwd, pool_grid(C, D, H, W), dim3(256), 0, s, gy, idx, y, g, C, D, H, W);
   return hipGetLastError();
 }
 
-hipError_t launch_relu_mask(uint16_t* g, int gcs, int gc0, const uint16_t* y, int ycs, int yc0, int C, long nvox,
-                            hipStream_t s) {
-  hipLaunchKernelGGL(k_relu_mask, dim3(ew_grid((size_t)nvox * C)), dim3(256), 0, s, g, gcs, gc0, y, ycs, yc0, C,
-                     nvox);
+hipError_t launch_up_fwd(const UpArgs& a, hipStream_t s) {
+  const long nrows = (long)a.D * a.H * a.W;
+  if (nrows >= (1l << 31)) return hipErrorInvalidValue;
+  const unsigned gx = (unsigned)((nrows + 255) / 256);
+  // few coarse voxels: the column tiles are shared out so that more blocks run
+  unsigned gy = 1;
+  while (gx * gy < 512 && gy < (unsigned)a.c / 2) gy *= 2;
+  const dim3 g(gx, gy);
+  switch (a.cu) {
+    case 16:
+    case 32: hipLaunchKernelGGL(k_up_fwd<1>, g, dim3(256), 0, s, a); break;
+    case 64: hipLaunchKernelGGL(k_up_fwd<2>, g, dim3(256), 0, s, a); break;
+    case 128: hipLaunchKernelGGL(k_up_fwd<4>, g, dim3(256), 0, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_zero_u16(uint16_t* p, size_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_fill_u16, dim3(ew_grid(n)), dim3(256), 0, s, p, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_input(const float* in, float scale, uint16_t* x, int cs, long nvox, hipStream_t s) {
-  hipLaunchKernelGGL(k_input, dim3(ew_grid(nvox)), dim3(256), 0, s, in, scale, x, cs, nvox);
+hipError_t launch_head(const uint16_t* src, int C, const uint16_t* wt, const float* bias, int relu, float* out, long n,
+                       hipStream_t s) {
+  const dim3 g((unsigned)std::min<long>((n + 255) / 256, 4096));
+  switch (C) {
+    case 8:
+    case 16:
+    case 32: hipLaunchKernelGGL(k_head<1>, g, dim3(256), 0, s, src, C, wt, bias, relu, out, n); break;
+    case 64: hipLaunchKernelGGL(k_head<2>, g, dim3(256), 0, s, src, C, wt, bias, relu, out, n); break;
+    case 128: hipLaunchKernelGGL(k_head<4>, g, dim3(256), 0, s, src, C, wt, bias, relu, out, n); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
 int mse_blocks(long n) { return std::min(ew_grid((size_t)n), 512); }
 
-hipError_t launch_mse(const float* y, const float* t, long n, float pos_w, uint16_t* g, int gcs, float* part,
-                      hipStream_t s) {
-  hipLaunchKernelGGL(k_mse, dim3(mse_blocks(n)), dim3(256), 0, s, y, t, n, 1.f / (float)n, pos_w, g, gcs, part);
+hipError_t launch_mse(const float* y, const float* t, long n, float pos_w, uint16_t* g, float* part, hipStream_t s) {
+  hipLaunchKernelGGL(k_mse, dim3(mse_blocks(n)), dim3(256), 0, s, y, t, n, 1.f / (float)n, pos_w, g, part);
   return hipGetLastError();
 }
 
-hipError_t launch_pack(const float* w, int T, int cin, int cout, int transpose, int Npad, int Cpad, uint16_t* out,
-                       hipStream_t s) {
-  hipLaunchKernelGGL(k_pack, dim3(ew_grid((size_t)T * Npad * Cpad)), dim3(256), 0, s, w, T, cin, cout, transpose,
-                     Npad, Cpad, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_pack_up_fwd(const float* u, int cin, int cout, uint16_t* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_pack_up_fwd, dim3(ew_grid((size_t)8 * cin * cout)), dim3(256), 0, s, u, cin, cout, out);
+hipError_t launch_pack(PackTable& tab, hipStream_t s) {
+  int blocks = 0;
+  for (int k = 0; k < tab.n; ++k) {
+    tab.e[k].block0 = blocks;
+    blocks += (tab.e[k].T * tab.e[k].Npad * tab.e[k].Cpad + 255) / 256;
+  }
+  hipLaunchKernelGGL(k_pack, dim3(blocks), dim3(256), 0, s, tab);
   return hipGetLastError();
 }
 

@@ -11,26 +11,36 @@ namespace rihvr {
 enum GatherMode {
   GG_CONV3_FWD = 0,  // rows: voxels; tap t reads voxel r + offset(t) (zero outside)
   GG_CONV3_BWD = 1,  // rows: voxels; tap t reads voxel r - offset(t)
-  GG_UP_FWD = 2,     // rows: coarse voxels; one tap; column d*Cout + co writes fine voxel 2q + d
+  GG_UP_FWD = 2,     // rows: coarse voxels; column d*Cout + co is fine voxel 2q + d
   GG_UP_BWD = 3,     // rows: coarse voxels; tap d reads fine voxel 2q + d
   GG_POINT = 4,      // rows: voxels; one tap, same voxel (1x1x1 convolution)
 };
 
+// Input gradients of the up-convolution and the head (GG_UP_BWD, GG_POINT).
 struct GatherGemmArgs {
   int mode;
-  int D, H, W;             // grid of the rows (coarse grid for the up modes)
+  int D, H, W;             // grid of the rows (coarse grid for GG_UP_BWD)
   const uint16_t* src;     // BF16 channels-last source
-  int src_cs, src_c0;      // channel stride / offset of the source view
+  int src_cs;              // its channel stride
   int T, C;                // taps, channels per tap (multiple of 8)
   const uint16_t* wt;      // packed BF16 B[t][Npad][C]
   int N, Npad;             // real and padded (multiple of 16) output columns
-  int up_cout;             // GG_UP_FWD: output channels (N = 8 * up_cout)
-  const float* bias;       // nullable, indexed by output channel
-  int relu, out_f32, accumulate;
-  void* dst;               // BF16 or FP32 channels-last destination
-  int dst_cs, dst_c0;
+  const uint16_t* mask;    // nullable: outputs where mask <= 0 become 0
+  uint16_t* dst;           // BF16 [rows][N]
 };
 hipError_t launch_gather_gemm(const GatherGemmArgs& a, hipStream_t s);
+
+struct UpArgs {
+  int D, H, W;             // coarse grid
+  const uint16_t* src;     // [voxels][cu]
+  int cu, c;               // input and output channels
+  const uint16_t* wt;      // packed BF16 [8 c][cu]
+  const float* bias;
+  uint16_t* dst;           // [fine voxels][c]
+};
+hipError_t launch_up_fwd(const UpArgs& a, hipStream_t s);
+hipError_t launch_head(const uint16_t* src, int C, const uint16_t* wt, const float* bias, int relu, float* out, long n,
+                       hipStream_t s);
 
 // 3x3x3 layer (forward, or its input gradient with the per-tap transposed weights).
 struct ConvArgs {
@@ -61,10 +71,13 @@ hipError_t launch_conv3(ConvArgs a, hipStream_t s);
 struct WgradArgs {
   int mode;                // GG_CONV3_FWD, GG_UP_FWD (coarse rows) or GG_POINT
   int D, H, W;             // row grid
-  const uint16_t* g;       // gradient w.r.t. the layer output (masked), channel view
-  int g_cs, g_c0, N;
-  const uint16_t* s;       // layer input, channel view
-  int s_cs, s_c0, C;
+  const uint16_t* g;       // gradient w.r.t. the layer output (masked)
+  int g_cs, N;
+  const uint16_t* s;       // layer input, channels [0, ssplit)
+  const uint16_t* s2;      // channels [ssplit, C): channel c at s2 + c
+  int ssplit, s_cs, C;
+  const float* s32;        // instead of s, C = 1: scale * s32 rounded to BF16
+  float scale;
   float* part;             // [blocks][t][C][N]
   float* bpart;            // [blocks (x 8 up-convolution taps)][N]
   int Cpad, taps;          // set by launch_wgrad
@@ -89,19 +102,23 @@ struct AdamArgs {
 };
 hipError_t launch_finish_grads(GradTable& tab, const AdamArgs& ad, hipStream_t s);
 
-hipError_t launch_pool_fwd(const uint16_t* x, int xcs, int xc0, uint16_t* y, int ycs, uint8_t* idx, int C, int D,
-                           int H, int W, hipStream_t s);
-hipError_t launch_pool_bwd(const uint16_t* gy, int gycs, const uint8_t* idx, uint16_t* gx, int gxcs, int gxc0, int C,
-                           int D, int H, int W, hipStream_t s);
-hipError_t launch_relu_mask(uint16_t* g, int gcs, int gc0, const uint16_t* y, int ycs, int yc0, int C, long nvox,
-                            hipStream_t s);
-hipError_t launch_zero_u16(uint16_t* p, size_t n, hipStream_t s);
-hipError_t launch_input(const float* in, float scale, uint16_t* x, int cs, long nvox, hipStream_t s);
+hipError_t launch_pool_fwd(const uint16_t* x, uint16_t* y, uint8_t* idx, int C, int D, int H, int W, hipStream_t s);
+hipError_t launch_pool_bwd(const uint16_t* gy, const uint8_t* idx, const uint16_t* y, uint16_t* g, int C, int D, int H,
+                           int W, hipStream_t s);   // D, H, W: coarse dims
 int mse_blocks(long n);
-hipError_t launch_mse(const float* y, const float* t, long n, float pos_w, uint16_t* g, int gcs, float* part,
-                      hipStream_t s);   // part: mse_blocks(n) floats
-hipError_t launch_pack(const float* w, int T, int cin, int cout, int transpose, int Npad, int Cpad, uint16_t* out,
-                       hipStream_t s);
-hipError_t launch_pack_up_fwd(const float* u, int cin, int cout, uint16_t* out, hipStream_t s);
+// g: [n][8]; part: mse_blocks(n) floats
+hipError_t launch_mse(const float* y, const float* t, long n, float pos_w, uint16_t* g, float* part, hipStream_t s);
+
+struct PackEntry {
+  const float* w;
+  uint16_t* out;
+  int T, cin, cout, kind, Npad, Cpad;
+  int block0;              // set by launch_pack
+};
+struct PackTable {
+  int n;
+  PackEntry e[2 * 28];     // forward and input-gradient weights of at most 28 layers
+};
+hipError_t launch_pack(PackTable& tab, hipStream_t s);
 
 }  // namespace rihvr
