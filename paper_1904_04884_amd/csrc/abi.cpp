@@ -1621,11 +1621,11 @@ extern "C" ri_status ri_solve_batched(int32_t n, ri_plan* const* plans, const ri
     g = grid_obj(p->g.nx, ny, nz);             it[i].obj.gx = g.x; it[i].obj.gy = g.y;
     g = grid_rows(m, ny * nz);                 it[i].fwd_rows.gx = g.x; it[i].fwd_rows.gy = g.y;
     g = grid_cols(ny, m, ctx[i].L.nchunk);     it[i].fwd_cols.gx = g.x; it[i].fwd_cols.gy = g.y;
-    g = grid_cols(ny, m, 1);                   it[i].holo_inv.gx = g.x; it[i].holo_inv.gy = g.y;
+    g = grid_holo(m);                          it[i].holo_inv.gx = g.x; it[i].holo_inv.gy = g.y;
     g = grid_rows(m, ny);                      it[i].holo_c2r.gx = g.x; it[i].holo_c2r.gy = g.y;
     it[i].scal.gx = 1; it[i].scal.gy = 1;
     g = grid_rows(m, ny);                      it[i].resid.gx = g.x; it[i].resid.gy = g.y;
-    g = grid_cols(ny, m, ctx[i].L.nchunk);     it[i].adj_cols.gx = g.x; it[i].adj_cols.gy = g.y;
+    g = grid_adj_cols(ny, m, ctx[i].L.nchunk); it[i].adj_cols.gx = g.x; it[i].adj_cols.gy = g.y;
     g = grid_rows(m, ny * nz);                 it[i].adj_rows.gx = g.x; it[i].adj_rows.gy = g.y;
     npass[i] = prox_pass_count(p, params[i]);
     tv[i].resize(tv_pass_args_size() * npass[i]);

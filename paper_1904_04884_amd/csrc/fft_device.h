@@ -1,14 +1,17 @@
 // Device-side FFT building blocks for gfx950: self-sorting (Stockham) radix
-// 2/3/4/8 passes over transforms held in LDS, complex helpers, and the
-// compile-time radix plan.  A transform of length L is processed by T = L/P
-// threads, each owning P points per pass (P divisible by every radix used).
+// 2/3/4/8/12 passes, complex helpers, and the compile-time radix plan.  A
+// transform of length L is processed by T = L/P threads, each owning P points
+// per pass (P divisible by every radix used).
 //
 // Stockham pass with radix R and span p (product of the radices already
 // applied), for butterfly i in [0, L/R), k = i mod p:
 //     u_r = a[i + r L/R] * w^(r k / (p R)),  r = 0..R-1,  w = exp(-+2 pi i)
 //     U   = DFT_R(u)
 //     b[(i - k) R + k + r p] = U_r
-// After the last pass the data are in natural order.
+// After the last pass the data are in natural order.  With thread t taking the
+// butterflies i = t + b T, the first pass's inputs and the last pass's outputs
+// are the elements t + s T, s = 0..P-1, so a transform starts and ends in
+// registers and only the exchanges between passes go through LDS.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -93,12 +96,36 @@ template <bool INV> struct Dft<8, INV> {
   }
 };
 
+// 12 = 3 x 4 without twiddles (Good-Thomas): with input n = (4 n1 + 3 n2) mod 12
+// and output q = (4 q1 + 9 q2) mod 12 the transform is a 3-point one over n1 and
+// a 4-point one over n2.
+template <bool INV> struct Dft<12, INV> {
+  __device__ __forceinline__ static void run(float2* v) {
+    float2 a[3][4];
+#pragma unroll
+    for (int n1 = 0; n1 < 3; ++n1) {
+#pragma unroll
+      for (int n2 = 0; n2 < 4; ++n2) a[n1][n2] = v[(4 * n1 + 3 * n2) % 12];
+      Dft<4, INV>::run(a[n1]);
+    }
+#pragma unroll
+    for (int q2 = 0; q2 < 4; ++q2) {
+      float2 c[3] = {a[0][q2], a[1][q2], a[2][q2]};
+      Dft<3, INV>::run(c);
+#pragma unroll
+      for (int q1 = 0; q1 < 3; ++q1) v[(4 * q1 + 9 * q2) % 12] = c[q1];
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------
-// Compile-time radix plan.  L = 2^a or 3 * 2^a.  A radix-3 pass comes first,
-// then radix 8 while it divides both the remaining length and P, then 4 / 2.
+// Compile-time radix plan.  L = 2^a or 3 * 2^a.  A pass with the factor 3 comes
+// first (radix 12 where P allows), then radix 8 while it divides both the
+// remaining length and P, then 4 / 2.
 // ---------------------------------------------------------------------------
 __host__ __device__ constexpr int next_radix(int rem, int P) {
-  return (rem % 3 == 0) ? 3
+  return (rem % 12 == 0 && P % 12 == 0) ? 12
+       : (rem % 3 == 0) ? 3
        : (rem % 8 == 0 && P % 8 == 0) ? 8
        : (rem % 4 == 0 && P % 4 == 0) ? 4
        : 2;
@@ -132,56 +159,69 @@ __device__ __forceinline__ void lds_sync() {
   }
 }
 
-// One Stockham pass.  `buf` holds the transform with element e at buf[e*S].
-// `tw` is a table exp(-2 pi i m / (L*TWS)), m in [0, L*TWS), read with stride TWS.
-template <int R, int L, int P, int S, int TWS, int p, bool INV, bool WAVE>
-__device__ __forceinline__ void stockham_pass(float2* buf, int t, const float2* __restrict__ tw) {
-  constexpr int T = L / P;
-  constexpr int NB = P / R;
+// The first pass writes its R outputs side by side, so threads write R elements
+// apart: on the same banks for even R.  That exchange therefore skips one element
+// in every fft_pad (0: none).
+__host__ __device__ constexpr int fft_pad(int L, int P) {
+  const int R = next_radix(L, P);
+  return R == L ? 0 : (R == 8 ? 8 : (R == 12 || R == 4 ? 4 : 0));
+}
+// Elements (times the stride S) of the LDS buffer of a transform.
+__host__ __device__ constexpr int fft_buf_len(int L, int P) { return L + (fft_pad(L, P) > 0 ? L / fft_pad(L, P) : 0); }
+
+// One pass and the ones after it.  v holds the elements t + s T on entry and
+// on return.  An exchange waits before it writes (the one before may still be
+// read) and before it reads; two buffers in turn, with one barrier per exchange,
+// measured no faster in the column kernels at 1024 and 512 points.
+template <int L, int P, int S, int TWS, int p, int rem, bool INV, bool WAVE>
+__device__ __forceinline__ void fft_passes(float2 (&v)[P], float2* buf, int t, const float2* __restrict__ tw) {
+  constexpr int R = next_radix(rem, P), T = L / P, NB = P / R;
   static_assert(P % R == 0, "radix must divide the points per thread");
-  float2 v[NB][R];
+  float2 u[NB][R];
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const int i = t + b * T;
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[b][r] = buf[(i + r * (L / R)) * S];
-  }
-  lds_sync<WAVE>();
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const int i = t + b * T;
-    const int k = i % p;
-    if (p > 1) {
+    for (int r = 0; r < R; ++r) u[b][r] = v[b + r * NB];
+    if constexpr (p > 1) {
+      const int k = (t + b * T) % p;
 #pragma unroll
       for (int r = 1; r < R; ++r) {
-        float2 w = tw[(r * k * (L / (p * R))) * TWS];
-        v[b][r] = INV ? cmulc(v[b][r], w) : cmul(v[b][r], w);
+        const float2 w = tw[(r * k * (L / (p * R))) * TWS];
+        u[b][r] = INV ? cmulc(u[b][r], w) : cmul(u[b][r], w);
       }
     }
-    Dft<R, INV>::run(v[b]);
-    const int j = (i - k) * R + k;
+    Dft<R, INV>::run(u[b]);
+  }
+  if constexpr (rem == R) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) buf[(j + r * p) * S] = v[b][r];
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[b + r * NB] = u[b][r];
+  } else {
+    constexpr int PAD = p == 1 ? fft_pad(L, P) : 0;
+    auto at = [](int e) { return (PAD > 0 ? e + e / (PAD > 0 ? PAD : 1) : e) * S; };
+    lds_sync<WAVE>();
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int i = t + b * T, k = i % p, j = (i - k) * R + k;
+#pragma unroll
+      for (int r = 0; r < R; ++r) buf[at(j + r * p)] = u[b][r];
+    }
+    lds_sync<WAVE>();
+#pragma unroll
+    for (int s = 0; s < P; ++s) v[s] = buf[at(t + s * T)];
+    fft_passes<L, P, S, TWS, p * R, rem / R, INV, WAVE>(v, buf, t, tw);
   }
-  lds_sync<WAVE>();
 }
 
-template <int L, int P, int S, int TWS, int p, int rem, bool INV, bool WAVE>
-__device__ __forceinline__ void stockham_rest(float2* buf, int t, const float2* __restrict__ tw) {
-  if constexpr (rem > 1) {
-    constexpr int R = next_radix(rem, P);
-    stockham_pass<R, L, P, S, TWS, p, INV, WAVE>(buf, t, tw);
-    stockham_rest<L, P, S, TWS, p * R, rem / R, INV, WAVE>(buf, t, tw);
-  }
-}
-
-// Full in-LDS transform of length L (unscaled).  Every thread of the block (of
-// the wave, with WAVE) must call it; thread t in [0, L/P) of each transform
-// owns P points per pass.
-template <int L, int P, int S, int TWS, bool INV, bool WAVE = false>
-__device__ __forceinline__ void fft_lds(float2* buf, int t, const float2* __restrict__ tw) {
+// Transform of length L (unscaled) of the elements t + s T in v, in place.
+// Every thread of the block (of the wave, with WAVE) must call it.  Element e
+// of an exchange sits at buf[e S] (plus padding); `tw` is a table
+// exp(-2 pi i m / (L TWS)) read with stride TWS.
+template <int L, int P, int S, int TWS, bool INV, bool WAVE>
+__device__ __forceinline__ void fft_reg(float2 (&v)[P], float2* buf, int t, const float2* __restrict__ tw) {
   static_assert(valid_len(L), "length must be 2^a or 3*2^a");
-  stockham_rest<L, P, S, TWS, 1, L, INV, WAVE>(buf, t, tw);
+  fft_passes<L, P, S, TWS, 1, L, INV, WAVE>(v, buf, t, tw);
 }
 
 }  // namespace rihvr

@@ -37,13 +37,24 @@ __host__ __device__ constexpr int kRowsPerBlock(int m) {
 // passes order LDS within the wave, with no block barrier.
 __host__ __device__ constexpr bool kRowWave(int m) { return kRowThreads(m) <= 64; }
 // Column transforms: points per thread, and columns per tile such that a block
-// has at most 512 threads (256 VGPRs per lane available, no spills) and the tile
-// plus three column-sized tables (a column buffer, the twiddles, the Nyquist
-// column's theta) and 4 KiB of flags fit the 160 KiB of LDS.
+// has at most 512 threads (256 VGPRs per lane available, no spills) and one
+// exchange buffer (padded), the twiddles and 4 KiB of flags fit the 160 KiB of LDS.
 __host__ __device__ constexpr int kColP(int ny) { return (ny % 3 == 0) ? 12 : (ny >= 2048 ? 16 : 8); }
 __host__ __device__ constexpr int kColW(int ny) {
   int w = 16;
   while (w > 1 && ((ny / kColP(ny)) * w > 512 || (size_t)ny * (w + 3) * 8 + 4096 > 160 * 1024)) w /= 2;
+  return w;
+}
+
+// Columns per tile of the adjoint's column pass: wider where 8 points per thread
+// leave the registers for blocks of 1024 threads, since it stores 8 W bytes of
+// every row of its tile: A^T at 1024^2 x 256 took 1048 us with 32-byte stores,
+// 908 with 64.  The forward pass, which loads, lost by it (1048 -> 1099 us), and
+// 128-byte stores at 512 points spill (110 -> 118 us).
+__host__ __device__ constexpr int kAdjW(int ny) {
+  int w = kColW(ny);
+  if (kColP(ny) <= 8)
+    while (w < 8 && (ny / kColP(ny)) * w * 2 <= 1024) w *= 2;
   return w;
 }
 
@@ -95,7 +106,7 @@ template <int M>
 __device__ __forceinline__ void rows_r2c_body(const RowsR2CArgs& a, int bx, int by) {
   const float2* __restrict__ tw = a.pt.tw_row;
   constexpr int P = points_per_thread(M), T = M / P, ROWS = kRowsPerBlock(M);
-  __shared__ float2 lds[ROWS][M];
+  __shared__ float2 lds[ROWS][fft_buf_len(M, P)];
   if (solve_done(a.st)) return;
   constexpr bool WAVE = kRowWave(M);
   const int r = threadIdx.x / T, t = threadIdx.x % T;
@@ -107,6 +118,7 @@ __device__ __forceinline__ void rows_r2c_body(const RowsR2CArgs& a, int bx, int 
     if (!__syncthreads_or(active)) return;
   }
   float2* buf = lds[r];
+  float2 v[P];
   if (a.mode != 1) {
     const float2* src = nullptr;
     if (a.mode == 2 && a.rs.on) {
@@ -118,10 +130,7 @@ __device__ __forceinline__ void rows_r2c_body(const RowsR2CArgs& a, int bx, int 
       src = reinterpret_cast<const float2*>(xin) + (size_t)row * M;
     }
 #pragma unroll
-    for (int s = 0; s < P; ++s) {
-      const int e = t + s * T;
-      buf[e] = (active && src != nullptr) ? src[e] : make_float2(0.f, 0.f);
-    }
+    for (int s = 0; s < P; ++s) v[s] = (active && src != nullptr) ? src[t + s * T] : make_float2(0.f, 0.f);
   } else {
     const SolveState* st = a.st;
     const float beta = (float)st->beta;
@@ -131,23 +140,26 @@ __device__ __forceinline__ void rows_r2c_body(const RowsR2CArgs& a, int bx, int 
 #pragma unroll
     for (int s = 0; s < P; ++s) {
       const int e = t + s * T;
-      float2 v = make_float2(0.f, 0.f);
+      v[s] = make_float2(0.f, 0.f);
       if (active) {
         float2 xc = c0[e], xp = c1[e], bv = bb[e];
-        v.x = xc.x + beta * (xc.x - xp.x) - bv.x;
-        v.y = xc.y + beta * (xc.y - xp.y) - bv.y;
+        v[s].x = xc.x + beta * (xc.x - xp.x) - bv.x;
+        v[s].y = xc.y + beta * (xc.y - xp.y) - bv.y;
       }
-      buf[e] = v;
     }
   }
+  fft_reg<M, P, 1, 2, false, WAVE>(v, buf, t, tw);
+  // the partner Z[M - k] of every k comes through LDS
   lds_sync<WAVE>();
-  fft_lds<M, P, 1, 2, false, WAVE>(buf, t, tw);
+#pragma unroll
+  for (int s = 0; s < P; ++s) buf[t + s * T] = v[s];
+  lds_sync<WAVE>();
   if (!active) return;  // no barriers below
   float2* dst = a.out + (size_t)row * M;
 #pragma unroll
   for (int s = 0; s < P; ++s) {
     const int k = t + s * T;
-    const float2 zk = buf[k];
+    const float2 zk = v[s];
     float2 o;
     if (k == 0) {
       o = make_float2(zk.x + zk.y, zk.x - zk.y);
@@ -165,34 +177,35 @@ __device__ __forceinline__ void rows_r2c_body(const RowsR2CArgs& a, int bx, int 
 // ---------------------------------------------------------------------------
 // Packed C2R of rows (scaled).  Inverse of k_rows_r2c up to the scale.
 // ---------------------------------------------------------------------------
+// v: the packed spectrum's elements t + s T; returned ready for the inverse
+// transform (the partners X[M - k] come through LDS).
 template <int M, bool WAVE>
-__device__ __forceinline__ void c2r_prepare(float2* buf, int t, const float2* __restrict__ tw) {
+__device__ __forceinline__ void c2r_prepare(float2 (&v)[points_per_thread(M)], float2* buf, int t,
+                                            const float2* __restrict__ tw) {
   constexpr int P = points_per_thread(M), T = M / P;
-  float2 zt[P];
+#pragma unroll
+  for (int s = 0; s < P; ++s) buf[t + s * T] = v[s];
+  lds_sync<WAVE>();
 #pragma unroll
   for (int s = 0; s < P; ++s) {
     const int k = t + s * T;
-    const float2 xk = buf[k];
+    const float2 xk = v[s];
     if (k == 0) {
-      zt[s] = make_float2(xk.x + xk.y, xk.x - xk.y);
+      v[s] = make_float2(xk.x + xk.y, xk.x - xk.y);
     } else {
       const float2 xc = cconj(buf[M - k]);
       const float2 sum = cadd(xk, xc), dif = csub(xk, xc);
       const float2 wd = cmulc(dif, tw[k]);             // exp(+2 pi i k / nx) * dif
-      zt[s] = make_float2(sum.x - wd.y, sum.y + wd.x);  // sum + i wd
+      v[s] = make_float2(sum.x - wd.y, sum.y + wd.x);  // sum + i wd
     }
   }
-  lds_sync<WAVE>();
-#pragma unroll
-  for (int s = 0; s < P; ++s) buf[t + s * T] = zt[s];
-  lds_sync<WAVE>();
 }
 
 template <int M>
 __device__ __forceinline__ void rows_c2r_body(const RowsC2RArgs& a, int bx, int by) {
   const float2* __restrict__ tw = a.pt.tw_row;
   constexpr int P = points_per_thread(M), T = M / P, ROWS = kRowsPerBlock(M), NT = ROWS * T;
-  __shared__ float2 lds[ROWS][M];
+  __shared__ float2 lds[ROWS][fft_buf_len(M, P)];
   __shared__ double red[16];
   if (solve_done(a.st)) return;
   const int r = threadIdx.x / T, t = threadIdx.x % T;
@@ -200,19 +213,16 @@ __device__ __forceinline__ void rows_c2r_body(const RowsC2RArgs& a, int bx, int 
   const bool active = row < a.nrows;
   float2* buf = lds[r];
   const float2* src = a.in + (size_t)row * M;
+  float2 v[P];
 #pragma unroll
-  for (int s = 0; s < P; ++s) {
-    const int e = t + s * T;
-    buf[e] = active ? src[e] : make_float2(0.f, 0.f);
-  }
-  lds_sync<kRowWave(M)>();
-  c2r_prepare<M, kRowWave(M)>(buf, t, tw);
-  fft_lds<M, P, 1, 2, true, kRowWave(M)>(buf, t, tw);
+  for (int s = 0; s < P; ++s) v[s] = active ? src[t + s * T] : make_float2(0.f, 0.f);
+  c2r_prepare<M, kRowWave(M)>(v, buf, t, tw);
+  fft_reg<M, P, 1, 2, true, kRowWave(M)>(v, buf, t, tw);
   if (a.mode == 0) {
     if (!active) return;
     float2* dst = reinterpret_cast<float2*>(a.out) + (size_t)row * M;
 #pragma unroll
-    for (int s = 0; s < P; ++s) dst[t + s * T] = cscale(buf[t + s * T], a.scale);
+    for (int s = 0; s < P; ++s) dst[t + s * T] = cscale(v[s], a.scale);
     return;
   }
   double acc = 0.0;
@@ -223,10 +233,10 @@ __device__ __forceinline__ void rows_c2r_body(const RowsC2RArgs& a, int bx, int 
 #pragma unroll
     for (int s = 0; s < P; ++s) {
       const int e = t + s * T;
-      const float2 v = cscale(buf[e], a.scale);
-      dst[e] = v;
+      const float2 ax = cscale(v[s], a.scale);
+      dst[e] = ax;
       const float2 bv = bb[e];
-      const double dx = (double)v.x - (double)bv.x, dy = (double)v.y - (double)bv.y;
+      const double dx = (double)ax.x - (double)bv.x, dy = (double)ax.y - (double)bv.y;
       acc += dx * dx + dy * dy;
     }
   }
@@ -253,112 +263,96 @@ __device__ __forceinline__ float2 buf_ld2(__amdgpu_buffer_rsrc_t r, unsigned off
   const auto u = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
   return make_float2(__uint_as_float(u[0]), __uint_as_float(u[1]));
 }
-template <int NY>
-__device__ __forceinline__ void stage_twiddles(float2* s_tw, const float2* __restrict__ tw) {
-  for (int i = threadIdx.x; i < NY; i += blockDim.x) s_tw[i] = tw[i];
+// LDS of the column kernels.  The block that holds the packed column 0 also
+// needs, for that column, the filter of the Nyquist column (cn) and the column's
+// own values at -ky (c0).  Its threads share out the NY filter values of a plane
+// instead of evaluating them in the lanes of column 0, where every wavefront
+// would run a second phase for each of its points: the grid is only about two
+// blocks per CU, so these blocks set its end (A at 512^2 x 128: 156 us with the
+// second phase in the lanes, 148 shared out).  theta is read once into registers
+// (a global load in the loop would wait for the next plane's tile in flight:
+// 177 us).
+template <int NY, int W>
+struct ColLds {
+  float2 buf[fft_buf_len(NY, kColP(NY)) * W];
+  float2 tw[NY];
+  float2 c0[NY];
+  float cn[NY];
+};
+template <int NY, int W, bool INV>
+__device__ __forceinline__ void col_fft(float2 (&v)[kColP(NY)], ColLds<NY, W>& l, int w, int q) {
+  fft_reg<NY, kColP(NY), W, 1, INV, false>(v, l.buf + w, q, l.tw);
 }
-// theta of the Nyquist column (kx = m), which column 0 pairs with; only the
-// block holding column 0 needs it.
-template <int NY>
-__device__ __forceinline__ void stage_theta_nyquist(double* s_thn, const double* __restrict__ theta, int m,
-                                                    bool needed) {
-  if (needed)
-    for (int i = threadIdx.x; i < NY; i += blockDim.x) s_thn[i] = theta[(size_t)i * (m + 1) + m];
+// Column 0 (the lanes w == 0 of its block) into LDS.
+template <int NY, int W>
+__device__ __forceinline__ void col0_put(const float2 (&v)[kColP(NY)], ColLds<NY, W>& l, int w, int q) {
+  constexpr int P = kColP(NY), TC = NY / P;
+#pragma unroll
+  for (int s = 0; s < P; ++s)
+    if (w == 0) l.c0[q + s * TC] = v[s];
+}
+// A thread's share of the Nyquist column: theta, and the filter of a plane.
+template <int NY, int W>
+struct NyquistShare {
+  static constexpr int NT = W * NY / kColP(NY), N = (NY + NT - 1) / NT;
+  double th[N];
+  __device__ __forceinline__ void load(const PlanTables& pt, int m) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int y = threadIdx.x + i * NT;
+      th[i] = y < NY ? pt.theta[(size_t)y * (m + 1) + m] : 0.0;
+    }
+  }
+  __device__ __forceinline__ void put(ColLds<NY, W>& l, double2 zc) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int y = threadIdx.x + i * NT;
+      if (y < NY) l.cn[y] = phase_cos(zc.x, zc.y, th[i]);
+    }
+  }
+};
+// The filtered value of column 0 at y: c its own filter there.
+template <int NY, int W>
+__device__ __forceinline__ float2 col0_filter(const ColLds<NY, W>& l, int y, float c, float2 v) {
+  const float2 vn = cconj(l.c0[(NY - y) % NY]);
+  const float ca = 0.5f * (c + l.cn[y]), cb = 0.5f * (c - l.cn[y]);
+  return make_float2(ca * v.x + cb * vn.x, ca * v.y + cb * vn.y);
+}
+template <int NY, int W>
+__device__ __forceinline__ void stage_twiddles(ColLds<NY, W>& l, const float2* __restrict__ tw) {
+  for (int i = threadIdx.x; i < NY; i += blockDim.x) l.tw[i] = tw[i];
 }
 
 // ---------------------------------------------------------------------------
 // Forward column pass with the propagation filter and the sum over planes.
-// Block: W columns x TC threads per column (TC = NY / P).
+// Block: W columns x TC threads per column (TC = NY / P).  A tile goes from
+// global memory into the first pass's registers and from the last pass's
+// registers into the sums; only the exchanges between passes touch LDS (two of
+// 512 points, where the transform held in LDS made four round trips and eight
+// barriers per plane).  768 x 384 x 75, with radix 12 in place of two passes of
+// radix 3 and 4: 90 -> 54 us; frames of 768 x 768: 626 -> 369 us; 1024^2 x 256
+// (512 blocks) stays at 0.55 ms: its tiles are four columns wide, 32 bytes of
+// every row.
 // ---------------------------------------------------------------------------
 //
 // Software pipeline over the planes of the chunk: the tile of the next
-// non-empty plane is requested right after the barrier that precedes the
-// transform of the current one, so its loads run under the transform; the row
-// flags that decide which rows of that tile are read are themselves staged
-// into LDS one plane earlier still (one dword of flags per thread).
-// Direct form (no prefetch) for the transform sizes whose pipelined form would
-// not fit the register file: every row flag is read from global memory.
-template <int NY>
-__device__ __forceinline__ void fwd_cols_body_direct(const FwdColsArgs& a, int bx, int by) {
-  const PlanTables& pt = a.pt;
-  constexpr int P = kColP(NY), TC = NY / P, W = kColW(NY);
-  __shared__ float2 lds[NY * W];
-  __shared__ float2 s_tw[NY];
-  __shared__ double s_thn[NY];
-  if (solve_done(a.st)) return;
-  const int w = threadIdx.x % W, q = threadIdx.x / W;
-  const int m = a.m;
-  const int kx = bx * W + w;
-  const bool colok = kx < m;           // tiles may overhang the last column
-  const bool col0 = (kx == 0);
-  // first read after the loop's first barrier
-  stage_twiddles<NY>(s_tw, pt.tw_col);
-  stage_theta_nyquist<NY>(s_thn, pt.theta, m, bx == 0);
-  double th[P];
-#pragma unroll
-  for (int s = 0; s < P; ++s) th[s] = colok ? pt.theta[(size_t)(q + s * TC) * (m + 1) + kx] : 0.0;
-  float2 acc[P];
-#pragma unroll
-  for (int s = 0; s < P; ++s) acc[s] = make_float2(0.f, 0.f);
-  const int j0 = by * a.planes_per_chunk;
-  const int j1 = min(a.nz, j0 + a.planes_per_chunk);
-  for (int j = j0; j < j1; ++j) {
-    if (a.planeflag != nullptr && a.planeflag[j] == 0) continue;
-    const float2* src = a.t + (size_t)j * NY * m + kx;
-#pragma unroll
-    for (int s = 0; s < P; ++s) {
-      const int y = q + s * TC;
-      const bool on = colok && (a.rowflag == nullptr || a.rowflag[(size_t)j * NY + y] != 0);
-      lds[y * W + w] = on ? src[(size_t)y * m] : make_float2(0.f, 0.f);
-    }
-    __syncthreads();
-    fft_lds<NY, P, W, 1, false>(lds + w, q, s_tw);
-    const double2 zc = pt.zc[j];
-#pragma unroll
-    for (int s = 0; s < P; ++s) {
-      const int y = q + s * TC;
-      const float2 v = lds[y * W + w];
-      const float c = phase_cos(zc.x, zc.y, th[s]);
-      if (!col0) {
-        acc[s].x += c * v.x;
-        acc[s].y += c * v.y;
-      } else {
-        const float cn = phase_cos(zc.x, zc.y, s_thn[y]);
-        const float2 vn = cconj(lds[((NY - y) % NY) * W]);
-        const float ca = 0.5f * (c + cn), cb = 0.5f * (c - cn);
-        acc[s].x += ca * v.x + cb * vn.x;
-        acc[s].y += ca * v.y + cb * vn.y;
-      }
-    }
-    __syncthreads();
-  }
-  if (!colok) return;
-  float2* dst = a.gp + (size_t)by * NY * m + kx;
-#pragma unroll
-  for (int s = 0; s < P; ++s) dst[(size_t)(q + s * TC) * m] = acc[s];
-}
-
-template <int NY>
-__device__ __forceinline__ void fwd_cols_body(const FwdColsArgs& a, int bx, int by) {
-  if constexpr (kColP(NY) > 8) {
-    fwd_cols_body_direct<NY>(a, bx, by);
-    return;
-  }
+// non-empty plane is requested right after the first barrier of the transform of
+// the current one, so its loads run under the transform; the row flags that
+// decide which rows of that tile are read are themselves staged into LDS one
+// plane earlier still (one dword of flags per thread).  PF = false: no prefetch,
+// for the transform sizes whose pipelined form would not fit the register file;
+// every row flag is read from global memory.  COL0: the block holding column 0.
+template <int NY, bool PF, bool COL0>
+__device__ __forceinline__ void fwd_cols_planes(const FwdColsArgs& a, int bx, int by, ColLds<NY, kColW(NY)>& l, uint32_t* lds_fl,
+                                                uint8_t* s_pf) {
   const PlanTables& pt = a.pt;
   constexpr int P = kColP(NY), TC = NY / P, W = kColW(NY);
   constexpr int NFW = NY / 4;          // dwords of row flags per plane
-  static_assert(W * TC >= NFW, "one flag dword per thread");
-  __shared__ float2 lds[NY * W];
-  __shared__ uint32_t lds_fl[NFW];
-  __shared__ float2 s_tw[NY];
-  __shared__ double s_thn[NY];
-  __shared__ uint8_t s_pf[kColPlaneFlags];
-  if (solve_done(a.st)) return;
+  static_assert(!PF || W * TC >= NFW, "one flag dword per thread");
   const int w = threadIdx.x % W, q = threadIdx.x / W;
   const int m = a.m;
   const int kx = bx * W + w;
   const bool colok = kx < m;           // tiles may overhang the last column
-  const bool col0 = (kx == 0);
   const bool flags = a.rowflag != nullptr;
   const uint8_t* fl8 = reinterpret_cast<const uint8_t*>(lds_fl);
   double th[P];
@@ -373,8 +367,9 @@ __device__ __forceinline__ void fwd_cols_body(const FwdColsArgs& a, int bx, int 
   const bool pflags = a.planeflag != nullptr;
   if (pflags)
     for (int i = threadIdx.x; i < min(j1 - j0, kColPlaneFlags); i += blockDim.x) s_pf[i] = a.planeflag[j0 + i];
-  stage_twiddles<NY>(s_tw, pt.tw_col);
-  stage_theta_nyquist<NY>(s_thn, pt.theta, m, bx == 0);
+  stage_twiddles(l, pt.tw_col);
+  NyquistShare<NY, W> ny;
+  if constexpr (COL0) ny.load(pt, m);
   __syncthreads();
   auto next_plane = [&](int j) {
     if (pflags)
@@ -384,62 +379,77 @@ __device__ __forceinline__ void fwd_cols_body(const FwdColsArgs& a, int bx, int 
   auto load_flagword = [&](int j) -> uint32_t {
     return reinterpret_cast<const uint32_t*>(a.rowflag + (size_t)j * NY)[threadIdx.x];
   };
-  float2 nv[P];  // tile of the next plane, in flight
   const size_t plane_bytes = (size_t)NY * m * sizeof(float2);
-  auto load_tile = [&](int j) {
+  auto load_tile = [&](int j, float2 (&nv)[P]) {
     const __amdgpu_buffer_rsrc_t r = spec_rsrc(a.t + (size_t)j * NY * m, plane_bytes);
     // offsets first (the flag bytes are read even when unused), then the loads
     unsigned o[P];
 #pragma unroll
     for (int s = 0; s < P; ++s) {
       const int y = q + s * TC;
-      const bool on = colok & (!flags | (fl8[y] != 0));
+      const bool on = PF ? colok & (!flags | (fl8[y] != 0))
+                         : colok && (!flags || a.rowflag[(size_t)j * NY + y] != 0);
       o[s] = on ? (unsigned)((y * m + kx) * sizeof(float2)) : kColOff;
     }
 #pragma unroll
     for (int s = 0; s < P; ++s) nv[s] = buf_ld2(r, o[s]);
   };
-  int j = next_plane(j0);
-  int jn = j < j1 ? next_plane(j + 1) : j1;
-  uint32_t flw = 0;  // flag dword of plane jn (threads < NFW)
-  if (j < j1) {
-    if (flags) {
-      if (threadIdx.x < NFW) lds_fl[threadIdx.x] = load_flagword(j);
+  // the plane's tile transformed, filtered, and added to the sums
+  auto accumulate = [&](int j, float2 (&v)[P]) {
+    const double2 zc = pt.zc[j];
+    if constexpr (COL0) ny.put(l, zc);   // the last reads are a barrier or more back
+    col_fft<NY, W, false>(v, l, w, q);
+    if constexpr (COL0) {
+      col0_put(v, l, w, q);
       __syncthreads();
     }
-    load_tile(j);
-    if (flags && jn < j1 && threadIdx.x < NFW) flw = load_flagword(jn);
-    __syncthreads();  // the flags of j are read before the loop overwrites them
-  }
-  while (j < j1) {
-#pragma unroll
-    for (int s = 0; s < P; ++s) lds[(q + s * TC) * W + w] = nv[s];
-    if (flags && jn < j1 && threadIdx.x < NFW) lds_fl[threadIdx.x] = flw;
-    const int jnn = jn < j1 ? next_plane(jn + 1) : j1;
-    if (flags && jnn < j1 && threadIdx.x < NFW) flw = load_flagword(jnn);
-    __syncthreads();
-    if (jn < j1) load_tile(jn);
-    fft_lds<NY, P, W, 1, false>(lds + w, q, s_tw);
-    const double2 zc = pt.zc[j];
 #pragma unroll
     for (int s = 0; s < P; ++s) {
-      const int y = q + s * TC;
-      const float2 v = lds[y * W + w];
       const float c = phase_cos(zc.x, zc.y, th[s]);
-      if (!col0) {
-        acc[s].x += c * v.x;
-        acc[s].y += c * v.y;
+      if (COL0 && kx == 0) {
+        const float2 f = col0_filter(l, q + s * TC, c, v[s]);
+        acc[s].x += f.x;
+        acc[s].y += f.y;
       } else {
-        const float cn = phase_cos(zc.x, zc.y, s_thn[y]);
-        const float2 vn = cconj(lds[((NY - y) % NY) * W]);
-        const float ca = 0.5f * (c + cn), cb = 0.5f * (c - cn);
-        acc[s].x += ca * v.x + cb * vn.x;
-        acc[s].y += ca * v.y + cb * vn.y;
+        acc[s].x += c * v[s].x;
+        acc[s].y += c * v[s].y;
       }
     }
-    __syncthreads();
-    j = jn;
-    jn = jnn;
+    if constexpr (COL0) __syncthreads();   // cn and c0 are written again for the next plane
+  };
+  if constexpr (!PF) {
+    for (int j = next_plane(j0); j < j1; j = next_plane(j + 1)) {
+      float2 v[P];
+      load_tile(j, v);
+      accumulate(j, v);
+    }
+  } else {
+    float2 nv[P];  // tile of the next plane, in flight
+    int j = next_plane(j0);
+    int jn = j < j1 ? next_plane(j + 1) : j1;
+    uint32_t flw = 0;  // flag dword of plane jn (threads < NFW)
+    if (j < j1) {
+      if (flags) {
+        if (threadIdx.x < NFW) lds_fl[threadIdx.x] = load_flagword(j);
+        __syncthreads();
+      }
+      load_tile(j, nv);
+      if (flags && jn < j1 && threadIdx.x < NFW) flw = load_flagword(jn);
+      __syncthreads();  // the flags of j are read before the loop overwrites them
+    }
+    while (j < j1) {
+      float2 v[P];
+#pragma unroll
+      for (int s = 0; s < P; ++s) v[s] = nv[s];
+      if (flags && jn < j1 && threadIdx.x < NFW) lds_fl[threadIdx.x] = flw;
+      const int jnn = jn < j1 ? next_plane(jn + 1) : j1;
+      if (flags && jnn < j1 && threadIdx.x < NFW) flw = load_flagword(jnn);
+      __syncthreads();
+      if (jn < j1) load_tile(jn, nv);
+      accumulate(j, v);
+      j = jn;
+      jn = jnn;
+    }
   }
   if (!colok) return;
   float2* dst = a.gp + (size_t)by * NY * m + kx;
@@ -447,105 +457,129 @@ __device__ __forceinline__ void fwd_cols_body(const FwdColsArgs& a, int bx, int 
   for (int s = 0; s < P; ++s) dst[(size_t)(q + s * TC) * m] = acc[s];
 }
 
+template <int NY>
+__device__ __forceinline__ void fwd_cols_body(const FwdColsArgs& a, int bx, int by) {
+  constexpr bool PF = kColP(NY) <= 8;
+  __shared__ ColLds<NY, kColW(NY)> l;
+  __shared__ uint32_t lds_fl[PF ? NY / 4 : 1];
+  __shared__ uint8_t s_pf[kColPlaneFlags];
+  if (solve_done(a.st)) return;
+  if (bx == 0) fwd_cols_planes<NY, PF, true>(a, bx, by, l, lds_fl, s_pf);
+  else fwd_cols_planes<NY, PF, false>(a, bx, by, l, lds_fl, s_pf);
+}
+
 // ---------------------------------------------------------------------------
-// Sum of partial spectra and inverse column FFT (hologram sized).
+// Sum of partial spectra and inverse column FFT (hologram sized).  A block
+// takes kHoloW columns; its G thread groups each add every G-th partial and
+// the groups' sums meet in LDS, where group 0 (the others on zeros) runs the
+// transform.  The sum of nchunk partials per point is the work here, so it
+// wants loads in flight: one thread per point of a 16-column tile, adding all
+// partials in turn, took 77 us at 128^2 (32 partials, 4 blocks), 74 us at
+// 768 x 384 (19 partials) and 207 us for frames of 256^2; now 10, 24 and 47 us.
 // ---------------------------------------------------------------------------
+constexpr int kHoloW = 4;
+__host__ __device__ constexpr int kHoloG(int ny) {   // groups: blocks of up to 512 threads
+  int g = 1;
+  while (g < 16 && (ny / kColP(ny)) * kHoloW * g * 2 <= 512) g *= 2;
+  return g;
+}
+__host__ __device__ constexpr int kHoloThreads(int ny) { return (ny / kColP(ny)) * kHoloW * kHoloG(ny); }
+
 template <int NY>
 __device__ __forceinline__ void holo_cols_inv_body(const HoloColsInvArgs& a, int bx, int by) {
   const PlanTables& pt = a.pt;
-  constexpr int P = kColP(NY), TC = NY / P, W = kColW(NY);
-  __shared__ float2 lds[NY * W];
+  constexpr int P = kColP(NY), TC = NY / P, W = kHoloW, G = kHoloG(NY), LEN = fft_buf_len(NY, P) * W;
+  __shared__ float2 lds[G][LEN];
   if (solve_done(a.st)) return;
-  const int w = threadIdx.x % W, q = threadIdx.x / W;
+  const int g = threadIdx.x / (TC * W), tt = threadIdx.x % (TC * W);
+  const int w = tt % W, q = tt / W;
   const int m = a.m;
   const int kx = bx * W + w;
+  float2 v[P];
 #pragma unroll
-  for (int s = 0; s < P; ++s) {
-    const int y = q + s * TC;
-    float2 v = make_float2(0.f, 0.f);
-    if (kx < m)
-      for (int c = 0; c < a.nchunk; ++c) v = cadd(v, a.gp[((size_t)c * NY + y) * m + kx]);
-    lds[y * W + w] = v;
-  }
-  __syncthreads();
-  fft_lds<NY, P, W, 1, true>(lds + w, q, pt.tw_col);
-  if (kx >= m) return;
+  for (int s = 0; s < P; ++s) v[s] = make_float2(0.f, 0.f);
+  if (kx < m) {
+    const float2* src = a.gp + (size_t)q * m + kx;
+#pragma unroll 4
+    for (int c = g; c < a.nchunk; c += G)
 #pragma unroll
-  for (int s = 0; s < P; ++s) {
-    const int y = q + s * TC;
-    a.gi[(size_t)y * m + kx] = lds[y * W + w];
+      for (int s = 0; s < P; ++s) v[s] = cadd(v[s], src[((size_t)c * NY + s * TC) * m]);
   }
+  if constexpr (G > 1) {
+#pragma unroll
+    for (int s = 0; s < P; ++s) lds[g][(q + s * TC) * W + w] = v[s];
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < P; ++s) {
+      if (g == 0) {
+#pragma unroll
+        for (int k = 1; k < G; ++k) v[s] = cadd(v[s], lds[k][(q + s * TC) * W + w]);
+      }
+    }
+    __syncthreads();
+  }
+  fft_reg<NY, P, W, 1, true, false>(v, lds[g] + w, q, pt.tw_col);
+  if (kx >= m || g != 0) return;
+#pragma unroll
+  for (int s = 0; s < P; ++s) a.gi[(size_t)(q + s * TC) * m + kx] = v[s];
 }
 
 // ---------------------------------------------------------------------------
 // Adjoint column pass.  The residual spectrum of the tile is computed once
 // (column FFT of its packed row spectra) and kept in registers; every plane of
-// the chunk multiplies it by cos(phase_j) and inverse-transforms the columns.
+// the chunk multiplies it by cos(phase_j) and inverse-transforms the columns
+// (from and to registers, as the forward pass: 67 -> 48 us at 512^2 x 128,
+// 460 -> 411 us at 1024^2 x 256 and 512 blocks).
 // ---------------------------------------------------------------------------
-template <int NY>
-__device__ __forceinline__ void adj_cols_body(const AdjColsArgs& a, int bx, int by) {
+template <int NY, bool COL0>
+__device__ __forceinline__ void adj_cols_planes(const AdjColsArgs& a, int bx, int by, ColLds<NY, kAdjW(NY)>& l) {
   const PlanTables& pt = a.pt;
-  constexpr int P = kColP(NY), TC = NY / P, W = kColW(NY);
-  __shared__ float2 lds[NY * W];
-  __shared__ float2 r0[NY];
-  __shared__ float2 s_tw[NY];
-  __shared__ double s_thn[NY];
-  if (solve_done(a.st)) return;
+  constexpr int P = kColP(NY), TC = NY / P, W = kAdjW(NY);
   const int w = threadIdx.x % W, q = threadIdx.x / W;
   const int m = a.m;
   const int kx = bx * W + w;
   const bool colok = kx < m;
-  const bool col0 = (kx == 0);
-  stage_twiddles<NY>(s_tw, pt.tw_col);
-  stage_theta_nyquist<NY>(s_thn, pt.theta, m, bx == 0);
-#pragma unroll
-  for (int s = 0; s < P; ++s) {
-    const int y = q + s * TC;
-    lds[y * W + w] = colok ? a.th[(size_t)y * m + kx] : make_float2(0.f, 0.f);
-  }
-  __syncthreads();
-  fft_lds<NY, P, W, 1, false>(lds + w, q, s_tw);
+  stage_twiddles(l, pt.tw_col);
+  NyquistShare<NY, W> ny;
+  if constexpr (COL0) ny.load(pt, m);
   float2 rh[P];
+#pragma unroll
+  for (int s = 0; s < P; ++s) rh[s] = colok ? a.th[(size_t)(q + s * TC) * m + kx] : make_float2(0.f, 0.f);
+  __syncthreads();
+  col_fft<NY, W, false>(rh, l, w, q);
+  if constexpr (COL0) col0_put(rh, l, w, q);
   double th[P];
 #pragma unroll
-  for (int s = 0; s < P; ++s) {
-    const int y = q + s * TC;
-    rh[s] = lds[y * W + w];
-    if (w == 0) r0[y] = rh[s];
-    th[s] = colok ? pt.theta[(size_t)y * (m + 1) + kx] : 0.0;
-  }
-  __syncthreads();
+  for (int s = 0; s < P; ++s) th[s] = colok ? pt.theta[(size_t)(q + s * TC) * (m + 1) + kx] : 0.0;
   const int j0 = by * a.planes_per_chunk;
   const int j1 = min(a.nz, j0 + a.planes_per_chunk);
   for (int j = j0; j < j1; ++j) {
     const double2 zc = pt.zc[j];
+    if constexpr (COL0) {
+      ny.put(l, zc);
+      __syncthreads();   // (the next put comes after the transform's barriers)
+    }
+    float2 v[P];
 #pragma unroll
     for (int s = 0; s < P; ++s) {
-      const int y = q + s * TC;
       const float c = phase_cos(zc.x, zc.y, th[s]);
-      float2 v;
-      if (!col0) {
-        v = cscale(rh[s], c);
-      } else {
-        const float cn = phase_cos(zc.x, zc.y, s_thn[y]);
-        const float2 vn = cconj(r0[(NY - y) % NY]);
-        const float ca = 0.5f * (c + cn), cb = 0.5f * (c - cn);
-        v = make_float2(ca * rh[s].x + cb * vn.x, ca * rh[s].y + cb * vn.y);
-      }
-      lds[y * W + w] = v;
+      v[s] = COL0 && kx == 0 ? col0_filter(l, q + s * TC, c, rh[s]) : cscale(rh[s], c);
     }
-    __syncthreads();
-    fft_lds<NY, P, W, 1, true>(lds + w, q, s_tw);
+    col_fft<NY, W, true>(v, l, w, q);
     float2* dst = a.u + (size_t)j * NY * m + kx;
     if (colok) {
 #pragma unroll
-      for (int s = 0; s < P; ++s) {
-        const int y = q + s * TC;
-        dst[(size_t)y * m] = lds[y * W + w];
-      }
+      for (int s = 0; s < P; ++s) dst[(size_t)(q + s * TC) * m] = v[s];
     }
-    __syncthreads();
   }
+}
+
+template <int NY>
+__device__ __forceinline__ void adj_cols_body(const AdjColsArgs& a, int bx, int by) {
+  __shared__ ColLds<NY, kAdjW(NY)> l;
+  if (solve_done(a.st)) return;
+  if (bx == 0) adj_cols_planes<NY, true>(a, bx, by, l);
+  else adj_cols_planes<NY, false>(a, bx, by, l);
 }
 
 // ---------------------------------------------------------------------------
@@ -556,7 +590,7 @@ template <int M>
 __device__ __forceinline__ void adj_rows_body(const AdjRowsArgs& a, int bx, int by) {
   const float2* __restrict__ tw = a.pt.tw_row;
   constexpr int P = points_per_thread(M), T = M / P, ROWS = kRowsPerBlock(M);
-  __shared__ float2 lds[ROWS][M];
+  __shared__ float2 lds[ROWS][fft_buf_len(M, P)];
   if (solve_done(a.st)) return;
   const int r = threadIdx.x / T, t = threadIdx.x % T;
   const int row = bx * ROWS + r;
@@ -570,19 +604,16 @@ __device__ __forceinline__ void adj_rows_body(const AdjRowsArgs& a, int bx, int 
   }
   float2* buf = lds[r];
   const float2* src = a.u + (size_t)row * M;
+  float2 w[P];
 #pragma unroll
-  for (int s = 0; s < P; ++s) {
-    const int e = t + s * T;
-    buf[e] = active ? src[e] : make_float2(0.f, 0.f);
-  }
-  lds_sync<kRowWave(M)>();
-  c2r_prepare<M, kRowWave(M)>(buf, t, tw);
-  fft_lds<M, P, 1, 2, true, kRowWave(M)>(buf, t, tw);
+  for (int s = 0; s < P; ++s) w[s] = active ? src[t + s * T] : make_float2(0.f, 0.f);
+  c2r_prepare<M, kRowWave(M)>(w, buf, t, tw);
+  fft_reg<M, P, 1, 2, true, kRowWave(M)>(w, buf, t, tw);
   if (!active) return;
   if (a.mode == 0) {
     float2* dst = reinterpret_cast<float2*>(a.out) + (size_t)row * M;
 #pragma unroll
-    for (int s = 0; s < P; ++s) dst[t + s * T] = cscale(buf[t + s * T], a.scale);
+    for (int s = 0; s < P; ++s) dst[t + s * T] = cscale(w[s], a.scale);
     return;
   }
   const SolveState* st = a.st;
@@ -604,7 +635,7 @@ __device__ __forceinline__ void adj_rows_body(const AdjRowsArgs& a, int bx, int 
 #pragma unroll
   for (int s = 0; s < P; ++s) {
     const int e = t + s * T;
-    const float2 g = buf[e];
+    const float2 g = w[s];
     const float2 c = xc != nullptr ? xc[e] : make_float2(0.f, 0.f);
     const float2 p = xpr != nullptr ? xpr[e] : make_float2(0.f, 0.f);
     float2 v;
@@ -1082,8 +1113,8 @@ __host__ __device__ constexpr int kColWavesPerSimd(int ny) { return kColP(ny) <=
     BODY<TP>(a, bx, by);                                                                          \
   }
 RIHVR_ENTRY_COLS(k_fwd_cols, fwd_cols_body, FwdColsArgs, NY, kColW(NY) * (NY / kColP(NY)))
-RIHVR_ENTRY_T(k_holo_cols_inv, holo_cols_inv_body, HoloColsInvArgs, NY, kColW(NY) * (NY / kColP(NY)))
-RIHVR_ENTRY_COLS(k_adj_cols, adj_cols_body, AdjColsArgs, NY, kColW(NY) * (NY / kColP(NY)))
+RIHVR_ENTRY_T(k_holo_cols_inv, holo_cols_inv_body, HoloColsInvArgs, NY, kHoloThreads(NY))
+RIHVR_ENTRY_COLS(k_adj_cols, adj_cols_body, AdjColsArgs, NY, kAdjW(NY) * (NY / kColP(NY)))
 #undef RIHVR_ENTRY_T
 #undef RIHVR_ENTRY_COLS
 
@@ -1135,7 +1166,13 @@ dim3 grid_cols(int ny, int m, int nchunk) {
   const int w = kColW(ny);
   return dim3((m + w - 1) / w, nchunk);
 }
+dim3 grid_holo(int m) { return dim3((m + kHoloW - 1) / kHoloW); }
 static int row_threads(int m) { return kRowsPerBlock(m) * kRowThreads(m); }
+dim3 grid_adj_cols(int ny, int m, int nchunk) {
+  const int w = kAdjW(ny);
+  return dim3((m + w - 1) / w, nchunk);
+}
+static int adj_threads(int ny) { return kAdjW(ny) * (ny / kColP(ny)); }
 static int col_threads(int ny) { return kColW(ny) * (ny / kColP(ny)); }
 
 #define RIHVR_DISPATCH(SIZES, VAR, SINGLE_OR_BATCH)                                          \
@@ -1193,27 +1230,27 @@ hipError_t launch_fwd_cols_batched(int ny, const FwdColsArgs* args, BatchMap map
 #undef C
 }
 hipError_t launch_holo_cols_inv(int ny, HoloColsInvArgs a, hipStream_t s) {
-  const dim3 g = grid_cols(ny, a.m, 1);
+  const dim3 g = grid_holo(a.m);
   a.gx = g.x; a.gy = g.y;
-#define C(NY) case NY: hipLaunchKernelGGL(k_holo_cols_inv<NY>, g, dim3(col_threads(NY)), 0, s, a); return hipGetLastError();
+#define C(NY) case NY: hipLaunchKernelGGL(k_holo_cols_inv<NY>, g, dim3(kHoloThreads(NY)), 0, s, a); return hipGetLastError();
   RIHVR_DISPATCH(RIHVR_COL_SIZES, ny, C)
 #undef C
 }
 hipError_t launch_holo_cols_inv_batched(int ny, const HoloColsInvArgs* args, BatchMap map, int nb,
                                         hipStream_t s) {
-#define C(NY) case NY: hipLaunchKernelGGL(k_holo_cols_inv_b<NY>, dim3(nb), dim3(col_threads(NY)), 0, s, args, map); return hipGetLastError();
+#define C(NY) case NY: hipLaunchKernelGGL(k_holo_cols_inv_b<NY>, dim3(nb), dim3(kHoloThreads(NY)), 0, s, args, map); return hipGetLastError();
   RIHVR_DISPATCH(RIHVR_COL_SIZES, ny, C)
 #undef C
 }
 hipError_t launch_adj_cols(int ny, int nchunk, AdjColsArgs a, hipStream_t s) {
-  const dim3 g = grid_cols(ny, a.m, nchunk);
+  const dim3 g = grid_adj_cols(ny, a.m, nchunk);
   a.gx = g.x; a.gy = g.y;
-#define C(NY) case NY: hipLaunchKernelGGL(k_adj_cols<NY>, g, dim3(col_threads(NY)), 0, s, a); return hipGetLastError();
+#define C(NY) case NY: hipLaunchKernelGGL(k_adj_cols<NY>, g, dim3(adj_threads(NY)), 0, s, a); return hipGetLastError();
   RIHVR_DISPATCH(RIHVR_COL_SIZES, ny, C)
 #undef C
 }
 hipError_t launch_adj_cols_batched(int ny, const AdjColsArgs* args, BatchMap map, int nb, hipStream_t s) {
-#define C(NY) case NY: hipLaunchKernelGGL(k_adj_cols_b<NY>, dim3(nb), dim3(col_threads(NY)), 0, s, args, map); return hipGetLastError();
+#define C(NY) case NY: hipLaunchKernelGGL(k_adj_cols_b<NY>, dim3(nb), dim3(adj_threads(NY)), 0, s, args, map); return hipGetLastError();
   RIHVR_DISPATCH(RIHVR_COL_SIZES, ny, C)
 #undef C
 }

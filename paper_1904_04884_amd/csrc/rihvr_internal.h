@@ -167,6 +167,8 @@ struct FwdColsArgs {
   int gx, gy;
 };
 dim3 grid_cols(int ny, int m, int nchunk);
+dim3 grid_adj_cols(int ny, int m, int nchunk);
+dim3 grid_holo(int m);
 hipError_t launch_fwd_cols(int ny, int nchunk, FwdColsArgs a, hipStream_t s);
 hipError_t launch_fwd_cols_batched(int ny, const FwdColsArgs* args, BatchMap map, int nblocks, hipStream_t s);
 
