@@ -509,7 +509,7 @@ static void prox_duals(const ri_plan* p, const Layout& L, void* ws, ProxArgs* a)
   a->tv2 = (p->g.flags & RI_TV2D) ? 1 : 0;
   a->dual_bf16 = (p->g.flags & RI_TV_DUAL_BF16) ? 1 : 0;
   a->fgp = (p->g.flags & RI_TV_FGP) ? 1 : 0;
-  a->cus = p->cus;
+  a->cus = a->fill = p->cus;
   a->group_planes = plane_group(p) ? p->dual_planes : 0;
 }
 
@@ -1033,6 +1033,14 @@ struct IterArgs {
   ProxArgs prox;
 };
 
+// Objective partials of a solve's final TV pass, whose grid is cut to reach `fill` blocks.
+static int final_partials(const ri_plan* p, int fill) {
+  const int nx = p->g.nx, ny = p->g.ny, nz = p->g.nz;
+  const ri_tuning& t = p->tune;
+  return plane_group(p) ? tv_group_final_blocks(nx, ny, nz, p->dual_planes, t.tv_levels, t.tv_blocks, p->cus, fill)
+                        : tv_final_blocks(nx, ny, nz, t.tv_levels, t.tv_blocks, p->cus, fill);
+}
+
 static IterArgs iteration_args(const SolveCtx& c) {
   ri_plan* p = c.p;
   const Layout& L = c.L;
@@ -1099,9 +1107,7 @@ static IterArgs iteration_args(const SolveCtx& c) {
   sa.n_obj = L.n_obj;
   sa.qsum = at<double>(c.ws, L.qsum);
   sa.qtv = at<double>(c.ws, L.qtv);
-  sa.n_prox = plane_group(p) ? tv_group_final_blocks(nx, ny, nz, p->dual_planes, p->tune.tv_levels,
-                                                      p->tune.tv_blocks, p->cus)
-                             : tv_final_blocks(nx, ny, nz, p->tune.tv_levels, p->tune.tv_blocks, p->cus);
+  sa.n_prox = final_partials(p, p->cus);
   sa.hist = at<double>(c.ws, L.hist);
   if (p->cplx) sa.qsum = sa.qtv = nullptr;   // the objective kernel runs every iteration
   sa.overflow = c.rs.on ? c.rs.overflow : nullptr;
@@ -1615,6 +1621,8 @@ extern "C" ri_status ri_solve_batched(int32_t n, ri_plan* const* plans, const ri
   std::vector<int> npass(n);
   for (int i = 0; i < n; ++i) {
     it[i] = iteration_args(ctx[i]);
+    it[i].prox.fill = std::max(1, plans[i]->cus / n);   // the frames fill the device together
+    it[i].scal.n_prox = final_partials(plans[i], it[i].prox.fill);
     const ri_plan* p = plans[i];
     const int ny = p->g.ny, nz = p->g.nz, m = p->m;
     dim3 g;
@@ -2044,7 +2052,7 @@ extern "C" ri_status ri_plan_autotune(ri_plan* p, int32_t inner_iters, const cha
   for (int H = kTvLevelsMin; H <= kTvLevelsMax; ++H) {
     for (int b : kTvBlockCands) {
       const bool is_dflt = H == dflt.tv_levels && b == dflt.tv_blocks;
-      const std::pair<int, int> g{H, tv_pass_zchunk(nx, ny, nz, H, b)};
+      const std::pair<int, int> g{H, tv_pass_zchunk(nx, ny, nz, H, b, p->cus)};
       if (std::find(seen_tv.begin(), seen_tv.end(), g) != seen_tv.end() && !is_dflt) continue;
       seen_tv.push_back(g);
       ProxArgs a{};

@@ -1,0 +1,6 @@
+// TV pass kernels of fusion depth 4.
+#include "tv_device.h"
+
+namespace rihvr {
+template void launch_tv_depth<4>(const TvSelect&, dim3, const TvPassArgs*, const BatchMap&, hipStream_t);
+}  // namespace rihvr
