@@ -609,6 +609,7 @@ static Prox64Args prox64_args(const ri_plan* p, const Layout64& L, void* ws, int
   a.step = step;
   a.l1 = l1;
   a.tv = tv;
+  a.cus = p->cus;
   return a;
 }
 

@@ -1,4 +1,4 @@
-// Gradient-projection TV prox (one step per launch) and objective partials, templated on the
+// Gradient-projection TV prox and objective partials, templated on the
 // element type T (float, double) and the number of parts NP (1: real object,
 // 2: complex object).  They serve the complex object in FP32 and every FP64
 // plan.
@@ -15,15 +15,12 @@
 // the soft threshold of Eq. (8) shrinks the modulus and keeps the phase.
 //
 // The TV prox is gradient projection on the dual, one value per part and
-// direction, projected jointly on the unit ball.  One launch takes one step,
-// streamed along z with the dual staged in LDS and u formed once per voxel,
-// and writes the other of two dual sets, so the sets alternate step by step.
+// direction, projected jointly on the unit ball.  One launch takes up to two
+// (FP64) or three (FP32) steps, streamed along z, and writes the other of two
+// dual sets, so the sets alternate launch by launch.
 // The last launch forms u once more and writes the threshold (real: max(u -
 // thr, 0) or the signed form; complex: the shrinkage of the modulus), with the
-// occupancy flags.  A step streams v, one dual set in and the other out (56 B
-// per complex voxel, plus the tile halo); there is no temporal blocking: these
-// kernels are the complex-object and FP64 paths, not the benchmark's real
-// FP32 path.
+// occupancy flags.
 #include <hip/hip_runtime.h>
 
 #include <utility>
@@ -50,6 +47,8 @@ struct GpArgs {
   int tv2;
   int nonneg;            // real object: x >= 0
   int first;             // the dual is zero (no step taken yet)
+  int levels;            // steps of this launch
+  int gx, gy, zchunk;    // tiles along x and y, planes per block
   T tau, c, thr;
 };
 
@@ -85,434 +84,263 @@ __device__ __forceinline__ T neg_div(const GpArgs<T>& a, size_t i, size_t o, int
   return d;
 }
 
-// One gradient-projection step, streamed along z.  A block of 512 threads
-// owns a 64 x 8 tile of every plane and walks the planes upward (a 64 x 16
-// tile in FP32, two rows per thread, measured 3% slower: half the blocks fit
-// a CU by LDS).  For each plane it stages in LDS the dual it needs (p_x with
-// its -x halo column, p_y with its -y halo row, p_z of this plane and of the
-// one below, all on the tile and its +x / +y halo), forms u = v - tau D^T p
-// once per voxel of the tile and its halo, and then writes the new dual of the
-// plane below, q = p + c D u, p' = q / max(1, |q|), from u at the voxel and
-// its +x, +y and +z neighbours.  The loads of a plane (its dual stage and v)
-// go to registers two planes ahead and into LDS when the plane's turn comes,
-// so they are in flight while the plane before is computed (132 -> 87 ms per
-// outer iteration at 1024^2 x 256 complex).  It reads the dual set a.p and
-// writes the other set a.q.  FP32 runs it only for an odd last step
-// (k_gp_zstep2 takes the steps in pairs); FP64 runs every step with it.
-constexpr int kZX = 64, kZT = 512;
-template <class T>
-constexpr int zstep_rows() { return 8; }
+// Up to LV gradient-projection steps in one launch, streamed along z.  A
+// wavefront holds 64 points along x (a lane each) of Q rows, NW wavefronts a
+// 64 x 16 tile; step l works one plane behind step l - 1 and keeps, per point,
+// its previous plane's dual and u in registers.  Neighbours along x come by DPP
+// wave shifts, along y from the lane's other row or through LDS rows, one
+// barrier per step and plane.  Points within LV of the tile's edge are computed
+// but not stored, and a chunk of planes has LV planes of margin; a chunk's
+// planes are read through buffer descriptors (0 outside the volume), one plane
+// ahead.  State below the volume starts at zero and the dual's component along
+// an axis is exactly zero on that axis' last plane, so z needs no masks; x / y
+// masks are compiled only into tiles at the volume's edge (EDGE).
+//
+// Bound by the latency of its loads and of the exchange at each barrier, at
+// large sizes by memory: v and the dual in and out once per LV steps, 56 B per
+// complex FP32 voxel, the reads 16 / (16 - 2 LV) times over for the halo.  Two
+// blocks of eight wavefronts a compute unit hide that best: 512 x 384 x 48
+// complex, 20 steps, 1588 us with LV = 3, 1743 with 2 (1024^2 x 64: 9.2 and 14.7
+// ms); one block of sixteen wavefronts and 32 rows 1613 (9.1 ms), LV = 4 spills
+// (2626).  FP64 has registers for LV = 2.  Against a pair of steps through LDS
+// with six stages and five barriers a plane (FP64: a step): 2934 us; FP64 real
+// 192 x 128 x 24, 10 steps, 450 -> 154 us; 256^2 x 48 complex FP64, 11 steps,
+// 1708 -> 763.
+constexpr unsigned kGpOff = 0x40000000u;   // past every plane, also when two are added
 
-template <class T, int NP>
-__global__ void __launch_bounds__(kZT) k_gp_zstep(GpArgs<T> a) {
-  if (done(a.st)) return;
-  constexpr int NT = kZT, kZY = zstep_rows<T>(), RY = kZY / (kZT / kZX);   // rows of the tile, per thread
-  constexpr int UW = kZX + 1, UH = kZY + 1, UA = UW * UH;      // u and p_z: tile + forward halo
-  constexpr int XW = kZX + 2, XA = XW * UH;                      // p_x: also the -x column
-  constexpr int YA = UW * (kZY + 2);                             // p_y: also the -y row
-  __shared__ T us[2][NP][UA];
-  __shared__ T pxs[NP][XA];
-  __shared__ T pys[NP][YA];
-  __shared__ T pzs[2][NP][UA];
-  const int nx = a.nx, ny = a.ny, nz = a.nz;
-  const size_t plane = (size_t)nx * ny, n = plane * nz;
-  const int tx = threadIdx.x % kZX, ty0 = threadIdx.x / kZX;   // rows ty0 + r * (kZT / kZX)
-  const int x0 = blockIdx.x * kZX, y0 = blockIdx.y * kZY;
-  const int x = x0 + tx;
-  const bool tv3 = !a.tv2;
-  const bool pre = !a.first;   // the dual is read (zero on the first step)
-  const T* __restrict__ v = in_of(a);
-  // What a thread loads of plane z: its points of the p_x, p_y and p_z stages
-  // (tile and halo, as laid out in LDS) and of v on the u region, held in
-  // registers so that plane z + 2 is in flight while plane z is computed.
-  constexpr int NXR = (XA + NT - 1) / NT, NYR = (YA + NT - 1) / NT, NUR = (UA + NT - 1) / NT;
-  struct Plane {
-    T px[NXR][NP], py[NYR][NP], pz[NUR][NP], v[NUR][NP];
-  };
-  auto fetch = [&](int z, Plane& r) {
-    const size_t base = (size_t)z * plane;
-#pragma unroll
-    for (int i = 0; i < NXR; ++i) {
-      const int k = threadIdx.x + i * NT, xx = x0 - 1 + k % XW, yy = y0 + k / XW;
-      const bool ok = pre && k < XA && xx >= 0 && xx < nx && yy < ny;
-#pragma unroll
-      for (int part = 0; part < NP; ++part)
-        r.px[i][part] = ok ? a.p[0][part * n + base + (size_t)yy * nx + xx] : T(0);
-    }
-#pragma unroll
-    for (int i = 0; i < NYR; ++i) {
-      const int k = threadIdx.x + i * NT, xx = x0 + k % UW, yy = y0 - 1 + k / UW;
-      const bool ok = pre && k < YA && xx < nx && yy >= 0 && yy < ny;
-#pragma unroll
-      for (int part = 0; part < NP; ++part)
-        r.py[i][part] = ok ? a.p[1][part * n + base + (size_t)yy * nx + xx] : T(0);
-    }
-#pragma unroll
-    for (int i = 0; i < NUR; ++i) {
-      const int k = threadIdx.x + i * NT, xx = x0 + k % UW, yy = y0 + k / UW;
-      const bool ok = k < UA && xx < nx && yy < ny;
-      const size_t o = base + (size_t)yy * nx + xx;
-#pragma unroll
-      for (int part = 0; part < NP; ++part) {
-        r.pz[i][part] = (ok && pre && tv3) ? a.p[2][part * n + o] : T(0);
-        r.v[i][part] = ok ? v[part * n + o] : T(0);
-      }
-    }
-  };
-  // the dual of plane z into LDS (p_z into parity slot z & 1)
-  auto commit = [&](int z, const Plane& r) {
-    if (!pre) return;
-#pragma unroll
-    for (int i = 0; i < NXR; ++i) {
-      const int k = threadIdx.x + i * NT;
-      if (k < XA)
-#pragma unroll
-        for (int part = 0; part < NP; ++part) pxs[part][k] = r.px[i][part];
-    }
-#pragma unroll
-    for (int i = 0; i < NYR; ++i) {
-      const int k = threadIdx.x + i * NT;
-      if (k < YA)
-#pragma unroll
-        for (int part = 0; part < NP; ++part) pys[part][k] = r.py[i][part];
-    }
-    if (tv3) {
-#pragma unroll
-      for (int i = 0; i < NUR; ++i) {
-        const int k = threadIdx.x + i * NT;
-        if (k < UA)
-#pragma unroll
-          for (int part = 0; part < NP; ++part) pzs[z & 1][part][k] = r.pz[i][part];
-      }
-    }
-  };
-  // u of plane z on the tile and its forward halo into slot z & 1 (v from the
-  // registers, the dual from LDS)
-  auto form_u = [&](int z, const Plane& r) {
-#pragma unroll
-    for (int i = 0; i < NUR; ++i) {
-      const int k = threadIdx.x + i * NT;
-      if (k >= UA) continue;
-      const int lx = k % UW, ly = k / UW, xx = x0 + lx, yy = y0 + ly;
-      const bool ok = xx < nx && yy < ny;
-#pragma unroll
-      for (int part = 0; part < NP; ++part) {
-        T u = r.v[i][part];
-        if (ok && pre) {
-          T d = (xx + 1 < nx ? pxs[part][ly * XW + lx + 1] : T(0)) - (xx > 0 ? pxs[part][ly * XW + lx] : T(0));
-          d += (yy + 1 < ny ? pys[part][(ly + 1) * UW + lx] : T(0)) - (yy > 0 ? pys[part][ly * UW + lx] : T(0));
-          if (tv3)
-            d += (z + 1 < nz ? pzs[z & 1][part][k] : T(0)) - (z > 0 ? pzs[(z & 1) ^ 1][part][k] : T(0));
-          u = fmaT(a.tau, d, u);
-        }
-        us[z & 1][part][k] = u;
-      }
-    }
-  };
-  Plane R;
-  fetch(0, R);
-  commit(0, R);
-  __syncthreads();
-  form_u(0, R);
-  if (nz > 1) fetch(1, R);
-  for (int z = 0; z < nz; ++z) {
-    const int s0 = z & 1, s1 = s0 ^ 1;
-    // this thread's dual of plane z, read before plane z + 1 is staged over it
-    T p0[RY][3][NP];
-#pragma unroll
-    for (int r = 0; r < RY; ++r) {
-      const int ty = ty0 + r * (kZT / kZX), ko = ty * UW + tx;
-#pragma unroll
-      for (int part = 0; part < NP; ++part) {
-        p0[r][0][part] = pre ? pxs[part][ty * XW + tx + 1] : T(0);
-        p0[r][1][part] = pre ? pys[part][(ty + 1) * UW + tx] : T(0);
-        p0[r][2][part] = (pre && tv3) ? pzs[s0][part][ko] : T(0);
-      }
-    }
-    __syncthreads();
-    if (z + 1 < nz) {
-      commit(z + 1, R);
-      __syncthreads();
-      form_u(z + 1, R);
-      if (z + 2 < nz) fetch(z + 2, R);   // in flight while plane z is computed
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < RY; ++r) {
-      const int ty = ty0 + r * (kZT / kZX), ko = ty * UW + tx, y = y0 + ty;
-      if (x < nx && y < ny) {
-        const size_t i = (size_t)z * plane + (size_t)y * nx + x;
-        const bool hx = x + 1 < nx, hy = y + 1 < ny, hz = tv3 && z + 1 < nz;
-        const int nd = tv3 ? 3 : 2;
-        T q[3][NP];
-        T n2 = T(0);
-#pragma unroll
-        for (int part = 0; part < NP; ++part) {
-          const T uc = us[s0][part][ko];
-          const T g[3] = {hx ? us[s0][part][ko + 1] - uc : T(0), hy ? us[s0][part][ko + UW] - uc : T(0),
-                          hz ? us[s1][part][ko] - uc : T(0)};
-          for (int d = 0; d < nd; ++d) {
-            q[d][part] = fmaT(a.c, g[d], p0[r][d][part]);
-            n2 = fmaT(q[d][part], q[d][part], n2);
-          }
-        }
-        const T sc = n2 > T(1) ? sqrtT(n2) : T(1);
-        for (int d = 0; d < nd; ++d)
-#pragma unroll
-          for (int part = 0; part < NP; ++part) a.q[d][part * n + i] = q[d][part] / sc;
-      }
-    }
+__device__ __forceinline__ int dpp_left(int v) { return __builtin_amdgcn_mov_dpp(v, 0x138, 0xf, 0xf, true); }
+__device__ __forceinline__ int dpp_right(int v) { return __builtin_amdgcn_mov_dpp(v, 0x130, 0xf, 0xf, true); }
+__device__ __forceinline__ int dpp_same(int v) { return __builtin_amdgcn_mov_dpp(v, 0xE4, 0xf, 0xf, false); }
+#define RIHVR_LANES(name, op)                                                            \
+  __device__ __forceinline__ float name(float v) { return __int_as_float(op(__float_as_int(v))); } \
+  __device__ __forceinline__ double name(double v) {                                     \
+    return __hiloint2double(op(__double2hiint(v)), op(__double2loint(v)));               \
   }
+RIHVR_LANES(from_left, dpp_left)     // lane i <- lane i - 1 (0 at lane 0)
+RIHVR_LANES(from_right, dpp_right)   // lane i <- lane i + 1 (0 at lane 63)
+RIHVR_LANES(kept_copy, dpp_same)     // a copy that the compiler keeps: the loaded registers are free for the next plane
+#undef RIHVR_LANES
+
+template <class T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t gp_rsrc(const T* base, size_t plane, size_t sz, bool on) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base) + plane * sz, (short)0, on ? (int)(sz * sizeof(T)) : 0,
+                                           0x00020000);
+}
+typedef unsigned int gp_u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void gp_ld(float& v, __amdgpu_buffer_rsrc_t r, unsigned off) {
+  v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
+__device__ __forceinline__ void gp_ld(double& v, __amdgpu_buffer_rsrc_t r, unsigned off) {
+  const gp_u32x2 u = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
+  v = __hiloint2double((int)u.y, (int)u.x);
+}
+__device__ __forceinline__ void gp_st(float v, __amdgpu_buffer_rsrc_t r, unsigned off) {
+  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)off, 0, 0);
+}
+__device__ __forceinline__ void gp_st(double v, __amdgpu_buffer_rsrc_t r, unsigned off) {
+  const gp_u32x2 u = {(unsigned)__double2loint(v), (unsigned)__double2hiint(v)};
+  __builtin_amdgcn_raw_buffer_store_b64(u, r, (int)off, 0, 0);
 }
 
-// Two gradient-projection steps in one launch, streamed along z like
-// k_gp_zstep: the first step's dual p' never leaves LDS, so a pair of steps
-// reads p and v once and writes p'' once (56 B per complex voxel per two
-// steps instead of per step).  The second step needs p' on the tile and a
-// one-voxel ring around it, which needs u on the tile and a ring of two on the
-// +x / +y side and one on the other sides, which needs p on a ring of two on
-// the -x / -y side.  Regions, relative to the tile origin:
-//   p_x staged  x in [-2, 65], y in [-1, 9]     u, v, p_z   x in [-1, 65], y in [-1, 9]
-//   p_y staged  x in [-1, 65], y in [-2, 9]     p'          x in [-1, 64], y in [-1, 8]
-//   u' = v - tau D^T p'   x in [0, 64], y in [0, 8]          p''   the 64 x 8 tile
-// At plane z the block stages p(z + 1), forms u(z + 1), steps p'(z), forms
-// u'(z) and steps p''(z - 1), with every plane's loads issued into registers
-// two planes ahead.  FP32 only (its LDS, 78 KB, holds two blocks per CU):
-// 87 -> 69 ms per outer iteration at 1024^2 x 256 complex.
+// 1 / max(1, sqrt(n2)).  FP32: the hardware's reciprocal square root (1 ulp)
+// with one Newton step (not where n2 is infinite: 0, as 1 / sqrt(n2)).
+__device__ __forceinline__ float proj_scale(float n2) {
+  const float r = __builtin_amdgcn_rsqf(n2);
+  const float e = fmaf(-n2 * r, r, 1.f);
+  const float q = fmaf(0.5f * r, e, r);
+  return n2 > 1.f ? (n2 < __builtin_huge_valf() ? q : r) : 1.f;
+}
+__device__ __forceinline__ double proj_scale(double n2) { return n2 > 1.0 ? 1.0 / sqrt(n2) : 1.0; }
+
+// Rows of a lane and wavefronts of a tile (FP64 complex: a row per lane), steps per launch.
 template <class T, int NP>
-__global__ void __launch_bounds__(kZT) k_gp_zstep2(GpArgs<T> a) {
-  if (done(a.st)) return;
-  constexpr int NT = kZT, TW = kZX, TH = kZT / kZX;
-  constexpr int AW = TW + 3, AH = TH + 3, AA = AW * AH;    // u, v, p_z
-  constexpr int XW = TW + 4, XA = XW * AH;                 // p_x
-  constexpr int YW = AW, YH = TH + 4, YA = YW * YH;        // p_y
-  constexpr int BW = TW + 2, BH = TH + 2, BA = BW * BH;    // p'
-  constexpr int CW = TW + 1, CH = TH + 1, CA = CW * CH;    // u'
-  __shared__ T pxs[NP][XA];
-  __shared__ T pys[NP][YA];
-  __shared__ T pzs[2][NP][AA];
-  __shared__ T vs[2][NP][AA];
-  __shared__ T us[2][NP][AA];
-  __shared__ T qxs[NP][BA];
-  __shared__ T qys[NP][BA];
-  __shared__ T qzs[2][NP][BA];
-  __shared__ T ws[2][NP][CA];
+constexpr int gp_q() { return sizeof(T) * NP > 8 ? 1 : 2; }
+template <class T, int NP>
+constexpr int gp_waves() { return sizeof(T) * NP > 8 ? 16 : 8; }
+template <class T, int NP>
+constexpr int gp_rows() { return gp_q<T, NP>() * gp_waves<T, NP>(); }
+template <class T>
+constexpr int gp_levels() { return sizeof(T) == 4 ? 3 : 2; }
+
+template <class T, int NP, int LV, bool EDGE>
+__device__ __forceinline__ void gp_pass_body(const GpArgs<T>& a, int bx, int by, int zb, int ze,
+                                             T (*s_py)[2][NP][gp_waves<T, NP>()][64],
+                                             T (*s_ut)[2][NP][gp_waves<T, NP>()][64]) {
+  constexpr int NW = gp_waves<T, NP>(), Q = gp_q<T, NP>(), RY = gp_rows<T, NP>(), H = LV;
   const int nx = a.nx, ny = a.ny, nz = a.nz;
-  const size_t plane = (size_t)nx * ny, n = plane * nz;
-  const int x0 = blockIdx.x * TW, y0 = blockIdx.y * TH;
-  const bool tv3 = !a.tv2;
-  const bool pre = !a.first;   // p is read (zero before the first step)
+  const size_t sz = (size_t)nx * ny;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool tv3 = !a.tv2, pre = !a.first;
+  const int L = a.levels;
   const T tau = a.tau, cc = a.c;
-  const T* __restrict__ v = in_of(a);
-  auto inside = [&](int gx, int gy) { return gx >= 0 && gx < nx && gy >= 0 && gy < ny; };
-  // a plane's loads, in registers until its turn
-  constexpr int NXR = (XA + NT - 1) / NT, NYR = (YA + NT - 1) / NT, NAR = (AA + NT - 1) / NT;
+  const T* v = in_of(a);
+  const int x = bx * (64 - 2 * H) - H + lane;
+  const bool inx = !EDGE || (x >= 0 && x < nx);
+  const bool xlo = !EDGE || x > 0, xhi = !EDGE || x + 1 < nx;
+  bool ylo[Q], yhi[Q];
+  unsigned offl[Q], offs[Q];   // in-plane byte offsets of loads and stores (kGpOff and above: none)
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int r = wv * Q + q, y = by * (RY - 2 * H) - H + r;
+    const bool iny = !EDGE || (y >= 0 && y < ny);
+    ylo[q] = !EDGE || y > 0;
+    yhi[q] = !EDGE || y + 1 < ny;
+    offl[q] = inx && iny ? (unsigned)(y * nx + x) * (unsigned)sizeof(T) : kGpOff;
+    offs[q] = inx && iny && lane >= H && lane < 64 - H && r >= H && r < RY - H ? offl[q] : kGpOff;
+  }
+  const int M = tv3 ? L : 0;
+  const int zs = max(0, zb - M), zl = min(nz, ze + M);
+
   struct Plane {
-    T px[NXR][NP], py[NYR][NP], pz[NAR][NP], v[NAR][NP];
+    T v[Q][NP], p[Q][3][NP];
   };
-  auto fetch = [&](int z, Plane& r) {
-    const size_t base = (size_t)z * plane;
-#pragma unroll
-    for (int i = 0; i < NXR; ++i) {
-      const int k = threadIdx.x + i * NT, gx = x0 + k % XW - 2, gy = y0 + k / XW - 1;
-      const bool ok = pre && k < XA && inside(gx, gy);
-#pragma unroll
-      for (int part = 0; part < NP; ++part)
-        r.px[i][part] = ok ? a.p[0][part * n + base + (size_t)gy * nx + gx] : T(0);
-    }
-#pragma unroll
-    for (int i = 0; i < NYR; ++i) {
-      const int k = threadIdx.x + i * NT, gx = x0 + k % YW - 1, gy = y0 + k / YW - 2;
-      const bool ok = pre && k < YA && inside(gx, gy);
-#pragma unroll
-      for (int part = 0; part < NP; ++part)
-        r.py[i][part] = ok ? a.p[1][part * n + base + (size_t)gy * nx + gx] : T(0);
-    }
-#pragma unroll
-    for (int i = 0; i < NAR; ++i) {
-      const int k = threadIdx.x + i * NT, gx = x0 + k % AW - 1, gy = y0 + k / AW - 1;
-      const bool ok = k < AA && inside(gx, gy);
-      const size_t o = base + (size_t)(ok ? gy : 0) * nx + (ok ? gx : 0);
-#pragma unroll
-      for (int part = 0; part < NP; ++part) {
-        r.pz[i][part] = (ok && pre && tv3) ? a.p[2][part * n + o] : T(0);
-        r.v[i][part] = ok ? v[part * n + o] : T(0);
-      }
-    }
-  };
-  auto commit = [&](int z, const Plane& r) {
-    const int sl = z & 1;
-#pragma unroll
-    for (int i = 0; i < NXR; ++i) {
-      const int k = threadIdx.x + i * NT;
-      if (k < XA)
-#pragma unroll
-        for (int part = 0; part < NP; ++part) pxs[part][k] = r.px[i][part];
-    }
-#pragma unroll
-    for (int i = 0; i < NYR; ++i) {
-      const int k = threadIdx.x + i * NT;
-      if (k < YA)
-#pragma unroll
-        for (int part = 0; part < NP; ++part) pys[part][k] = r.py[i][part];
-    }
-#pragma unroll
-    for (int i = 0; i < NAR; ++i) {
-      const int k = threadIdx.x + i * NT;
-      if (k < AA)
-#pragma unroll
-        for (int part = 0; part < NP; ++part) {
-          pzs[sl][part][k] = r.pz[i][part];
-          vs[sl][part][k] = r.v[i][part];
-        }
-    }
-  };
-  // u(z) = v - tau D^T p on the u region
-  auto form_u = [&](int z) {
-    const int sl = z & 1;
-#pragma unroll
-    for (int i = 0; i < NAR; ++i) {
-      const int k = threadIdx.x + i * NT;
-      if (k >= AA) continue;
-      const int lx = k % AW - 1, ly = k / AW - 1, gx = x0 + lx, gy = y0 + ly;
-      const bool in = inside(gx, gy);
-#pragma unroll
-      for (int part = 0; part < NP; ++part) {
-        T u = vs[sl][part][k];
-        if (in && pre) {
-          const int ix = (ly + 1) * XW + lx + 2, iy = (ly + 2) * YW + lx + 1;
-          T d = (gx + 1 < nx ? pxs[part][ix] : T(0)) - (gx > 0 ? pxs[part][ix - 1] : T(0));
-          d += (gy + 1 < ny ? pys[part][iy] : T(0)) - (gy > 0 ? pys[part][iy - YW] : T(0));
-          if (tv3) d += (z + 1 < nz ? pzs[sl][part][k] : T(0)) - (z > 0 ? pzs[sl ^ 1][part][k] : T(0));
-          u = fmaT(tau, d, u);
-        }
-        us[sl][part][k] = in ? u : T(0);
-      }
-    }
-  };
-  constexpr int NBR = (BA + NT - 1) / NT, NCR = (CA + NT - 1) / NT;
-  Plane R;
-  fetch(0, R);
-  commit(0, R);
-  __syncthreads();
-  form_u(0);
-  if (nz > 1) fetch(1, R);
-  // this thread's p' of the plane below on the tile (second step's input)
-  const int tx = threadIdx.x % TW, ty = threadIdx.x / TW, gxt = x0 + tx, gyt = y0 + ty;
-  const bool int_ = inside(gxt, gyt);
-  T pp1[3][NP];
-  // p''(m) on the tile from u'(m) (slot m & 1), u'(m + 1) (the other slot, when
-  // hz) and pp1 = p'(m); stored to a.q
-  auto step2_out = [&](int m, bool hz) {
-    const int sl = m & 1;
-    const int kc = ty * CW + tx;
-    T q[3][NP];
-    T n2 = T(0);
+  auto load_plane = [&](Plane& r, int z) __attribute__((always_inline)) {
 #pragma unroll
     for (int part = 0; part < NP; ++part) {
-      const T wc = ws[sl][part][kc];
-      const T g[3] = {gxt + 1 < nx ? ws[sl][part][kc + 1] - wc : T(0), gyt + 1 < ny ? ws[sl][part][kc + CW] - wc : T(0),
-                      hz ? ws[sl ^ 1][part][kc] - wc : T(0)};
+      const __amdgpu_buffer_rsrc_t rv = gp_rsrc(v, (size_t)part * nz + z, sz, true);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) gp_ld(r.v[q][part], rv, offl[q]);
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
-        q[d][part] = (d < 2 || tv3) ? fmaT(cc, g[d], pp1[d][part]) : T(0);
-        n2 = fmaT(q[d][part], q[d][part], n2);
-      }
-    }
-    if (int_) {
-      const T sc = n2 > T(1) ? sqrtT(n2) : T(1);
-      const size_t i = (size_t)m * plane + (size_t)gyt * nx + gxt;
-      const int nd = tv3 ? 3 : 2;
-      for (int d = 0; d < nd; ++d)
+        const __amdgpu_buffer_rsrc_t rp = gp_rsrc<T>(a.p[d], (size_t)part * nz + z, sz, pre && (d < 2 || tv3));
 #pragma unroll
-        for (int part = 0; part < NP; ++part) a.q[d][part * n + i] = q[d][part] / sc;
+        for (int q = 0; q < Q; ++q) gp_ld(r.p[q][d][part], rp, offl[q]);
+      }
     }
   };
-  for (int z = 0; z < nz; ++z) {
-    const int sl = z & 1;
-    // p(z) on the p' region, read before plane z + 1 is staged over it
-    T p0[NBR][3][NP];
+  // per step: the previous plane's dual and u; v of the planes that steps 1.. are at
+  T Pp[LV][Q][3][NP], Up[LV][Q][NP], V[LV][Q][NP];
 #pragma unroll
-    for (int i = 0; i < NBR; ++i) {
-      const int k = threadIdx.x + i * NT, lx = k % BW - 1, ly = k / BW - 1;
-      const bool ok = pre && k < BA;
+  for (int l = 0; l < LV; ++l)
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
 #pragma unroll
       for (int part = 0; part < NP; ++part) {
-        p0[i][0][part] = ok ? pxs[part][(ly + 1) * XW + lx + 2] : T(0);
-        p0[i][1][part] = ok ? pys[part][(ly + 2) * YW + lx + 1] : T(0);
-        p0[i][2][part] = (ok && tv3) ? pzs[sl][part][(ly + 1) * AW + lx + 1] : T(0);
+        Pp[l][q][0][part] = Pp[l][q][1][part] = Pp[l][q][2][part] = T(0);
+        Up[l][q][part] = V[l][q][part] = T(0);
       }
-    }
-    __syncthreads();
-    if (z + 1 < nz) {
-      commit(z + 1, R);
-      __syncthreads();
-      form_u(z + 1);
-      if (z + 2 < nz) fetch(z + 2, R);   // in flight while this plane is computed
-    }
-    __syncthreads();
-    // first step: p'(z) on the p' region
-    const bool hz1 = tv3 && z + 1 < nz;
+  T C[Q][3][NP];
 #pragma unroll
-    for (int i = 0; i < NBR; ++i) {
-      const int k = threadIdx.x + i * NT;
-      if (k >= BA) continue;
-      const int lx = k % BW - 1, ly = k / BW - 1, gx = x0 + lx, gy = y0 + ly;
-      const int ku = (ly + 1) * AW + lx + 1;
-      T q[3][NP];
+  for (int q = 0; q < Q; ++q)
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+      for (int part = 0; part < NP; ++part) C[q][d][part] = T(0);
+  // dual step at the plane held in Pp / Up, whose next plane's u is un (hz: it exists), into o
+  auto step = [&](int l, int par, bool hz, const T (&un)[Q][NP], T (&o)[Q][3][NP]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      T w[3][NP];
       T n2 = T(0);
 #pragma unroll
       for (int part = 0; part < NP; ++part) {
-        const T uc = us[sl][part][ku];
-        const T g[3] = {gx + 1 < nx ? us[sl][part][ku + 1] - uc : T(0), gy + 1 < ny ? us[sl][part][ku + AW] - uc : T(0),
-                        hz1 ? us[sl ^ 1][part][ku] - uc : T(0)};
+        const T u0 = Up[l][q][part];
+        const T ux = from_right(u0);
+        const T uy = q < Q - 1 ? Up[l][q < Q - 1 ? q + 1 : q][part] : s_ut[l][par ^ 1][part][wv < NW - 1 ? wv + 1 : wv][lane];
+        const T g[3] = {xhi ? ux - u0 : T(0), yhi[q] ? uy - u0 : T(0), (hz && tv3) ? un[q][part] - u0 : T(0)};
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-          q[d][part] = (d < 2 || tv3) ? fmaT(cc, g[d], p0[i][d][part]) : T(0);
-          n2 = fmaT(q[d][part], q[d][part], n2);
+          w[d][part] = fmaT(cc, g[d], Pp[l][q][d][part]);
+          n2 = fmaT(w[d][part], w[d][part], n2);
         }
       }
-      const bool in = inside(gx, gy);
-      const T sc = n2 > T(1) ? sqrtT(n2) : T(1);
+      const T sc = proj_scale(n2);
 #pragma unroll
-      for (int part = 0; part < NP; ++part) {
-        qxs[part][k] = in ? q[0][part] / sc : T(0);
-        qys[part][k] = in ? q[1][part] / sc : T(0);
-        qzs[sl][part][k] = in ? q[2][part] / sc : T(0);
+      for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int part = 0; part < NP; ++part) o[q][d][part] = w[d][part] * sc;
+    }
+  };
+  Plane P;
+  load_plane(P, zs);
+  const int nsteps = zl - zs + L;   // the last output leaves at s = nsteps - 1
+  for (int s = 0; s < nsteps; ++s) {
+    const int par = s & 1, a1 = zs + s;
+    if (a1 < zl) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int part = 0; part < NP; ++part) {
+          V[0][q][part] = kept_copy(P.v[q][part]);
+#pragma unroll
+          for (int d = 0; d < 3; ++d) C[q][d][part] = kept_copy(P.p[q][d][part]);
+        }
+      if (a1 + 1 < zl) load_plane(P, a1 + 1);
+    }
+#pragma unroll
+    for (int l = 0; l < LV; ++l) {
+      const int z = a1 - l;   // plane of step l
+      if (l >= L) continue;
+      const bool arrives = z >= zs && z < zl;
+#pragma unroll
+      for (int part = 0; part < NP; ++part) s_py[l][par][part][wv][lane] = C[Q - 1][1][part];
+      __syncthreads();
+      if (arrives) {
+        T un[Q][NP];
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+          for (int part = 0; part < NP; ++part) {
+            const T cx = C[q][0][part], cy = C[q][1][part];
+            const T pxm = from_left(cx);
+            const T pym = q > 0 ? C[q > 0 ? q - 1 : 0][1][part] : s_py[l][par][part][wv > 0 ? wv - 1 : 0][lane];
+            T d = (xhi ? cx : T(0)) - (xlo ? pxm : T(0));
+            d += (yhi[q] ? cy : T(0)) - (ylo[q] ? pym : T(0));
+            d += C[q][2][part] - Pp[l][q][2][part];
+            un[q][part] = fmaT(tau, d, V[l][q][part]);
+          }
+        T O[Q][3][NP];
+        step(l, par, true, un, O);
+#pragma unroll
+        for (int part = 0; part < NP; ++part) s_ut[l][par][part][wv][lane] = un[0][part];
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+          for (int part = 0; part < NP; ++part) {
+            Up[l][q][part] = un[q][part];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+              Pp[l][q][d][part] = C[q][d][part];
+              C[q][d][part] = O[q][d][part];   // (of no plane when z == zs: not used)
+            }
+          }
+      } else if (z == zl) {   // the last plane: no plane above it
+        step(l, par, false, Up[l], C);
       }
     }
-    __syncthreads();
-    // u'(z) = v - tau D^T p' on the u' region
+    const int m = a1 - L;
+    const bool on = m >= zb && m < ze;
 #pragma unroll
-    for (int i = 0; i < NCR; ++i) {
-      const int k = threadIdx.x + i * NT;
-      if (k >= CA) continue;
-      const int lx = k % CW, ly = k / CW, gx = x0 + lx, gy = y0 + ly;
-      const int kb = (ly + 1) * BW + lx + 1;
-      const bool in = inside(gx, gy);
+    for (int part = 0; part < NP; ++part)
 #pragma unroll
-      for (int part = 0; part < NP; ++part) {
-        T d = (gx + 1 < nx ? qxs[part][kb] : T(0)) - (gx > 0 ? qxs[part][kb - 1] : T(0));
-        d += (gy + 1 < ny ? qys[part][kb] : T(0)) - (gy > 0 ? qys[part][kb - BW] : T(0));
-        if (tv3) d += (z + 1 < nz ? qzs[sl][part][kb] : T(0)) - (z > 0 ? qzs[sl ^ 1][part][kb] : T(0));
-        ws[sl][part][k] = in ? fmaT(tau, d, vs[sl][part][(ly + 1) * AW + lx + 1]) : T(0);
+      for (int d = 0; d < 3; ++d) {
+        const __amdgpu_buffer_rsrc_t ro = gp_rsrc<T>(a.q[d], (size_t)part * nz + (on ? m : 0), sz, on && (d < 2 || tv3));
+#pragma unroll
+        for (int q = 0; q < Q; ++q) gp_st(C[q][d][part], ro, offs[q]);
       }
-    }
-    __syncthreads();
-    // second step for the plane below, whose u' is complete now
-    if (z > 0) step2_out(z - 1, tv3);
-    // p'(z) on the tile for the next second step
-    {
-      const int kb = (ty + 1) * BW + tx + 1;
 #pragma unroll
-      for (int part = 0; part < NP; ++part) {
-        pp1[0][part] = qxs[part][kb];
-        pp1[1][part] = qys[part][kb];
-        pp1[2][part] = qzs[sl][part][kb];
-      }
-    }
+    for (int l = LV - 1; l > 0; --l)
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int part = 0; part < NP; ++part) V[l][q][part] = V[l - 1][q][part];
+    __builtin_amdgcn_sched_barrier(0);
   }
-  step2_out(nz - 1, false);
+}
+
+template <class T, int NP, int LV>
+__global__ void __launch_bounds__((gp_waves<T, NP>() * 64), 4) k_gp_pass(GpArgs<T> a) {
+  constexpr int NW = gp_waves<T, NP>(), RY = gp_rows<T, NP>();
+  __shared__ T s_py[LV][2][NP][NW][64];   // bottom-row p_y of every wavefront, by step and parity
+  __shared__ T s_ut[LV][2][NP][NW][64];   // top-row u
+  if (done(a.st)) return;
+  const int tile = blockIdx.x % (a.gx * a.gy), zb = (int)(blockIdx.x / (a.gx * a.gy)) * a.zchunk;
+  const int bx = tile % a.gx, by = tile / a.gx;
+  const int x0 = bx * (64 - 2 * LV) - LV, y0 = by * (RY - 2 * LV) - LV;
+  const bool interior = x0 >= 1 && x0 + 64 <= a.nx - 1 && y0 >= 1 && y0 + RY <= a.ny - 1;
+  const int ze = min(a.nz, zb + a.zchunk);
+  if (interior) gp_pass_body<T, NP, LV, false>(a, bx, by, zb, ze, s_py, s_ut);
+  else gp_pass_body<T, NP, LV, true>(a, bx, by, zb, ze, s_py, s_ut);
 }
 
 // u once more, then the threshold and the flags.  In place is allowed (a
@@ -618,28 +446,41 @@ int ggrid(size_t n) {
   return (int)(b > 8192 ? 8192 : (b == 0 ? 1 : b));
 }
 
-// K steps alternating between the dual sets a.p and a.q, then the final
-// launch on the set the last step wrote.
+// Planes per block of a pass: the cut whose rounds of 2 `cus` blocks (two fit a
+// compute unit) times a block's march, its planes and 3 LV of margin and
+// pipeline, is shortest.
+int gp_zchunk(int tiles, int nz, int lv, int cus) {
+  const int slots = 2 * (cus > 0 ? cus : 256);
+  int best = nz;
+  long best_t = -1;
+  for (int nc = 1; nc <= nz; ++nc) {
+    const int zc = (nz + nc - 1) / nc;
+    const long blocks = (long)tiles * ((nz + zc - 1) / zc);
+    const long t = (blocks + slots - 1) / slots * (zc + 3 * lv);
+    if (best_t < 0 || t < best_t) {
+      best_t = t;
+      best = zc;
+    }
+  }
+  return best;
+}
+
+// K steps, LV a launch, alternating between the dual sets a.p and a.q, then the
+// final launch on the set the last one wrote.
 template <class T, int NP>
-hipError_t run_gp(GpArgs<T> a, int K, hipStream_t s, int* launches) {
+hipError_t run_gp(GpArgs<T> a, int K, int cus, hipStream_t s, int* launches) {
+  constexpr int LV = gp_levels<T>(), RY = gp_rows<T, NP>();
   const dim3 g(ggrid((size_t)a.nx * a.ny * a.nz)), b(kGThreads);
-  const dim3 gz((a.nx + kZX - 1) / kZX, (a.ny + zstep_rows<T>() - 1) / zstep_rows<T>()), bz(kZT);
-  // FP32: pairs of steps in one launch, an odd step last on its own
-  constexpr bool kPairs = sizeof(T) == 4;
-  const dim3 gz2((a.nx + kZX - 1) / kZX, (a.ny + kZT / kZX - 1) / (kZT / kZX));
-  (void)gz2;
+  a.gx = (a.nx + 64 - 2 * LV - 1) / (64 - 2 * LV);
+  a.gy = (a.ny + RY - 2 * LV - 1) / (RY - 2 * LV);
+  a.zchunk = gp_zchunk(a.gx * a.gy, a.nz, a.tv2 ? 0 : LV, cus);
+  const dim3 gz(a.gx * a.gy * ((a.nz + a.zchunk - 1) / a.zchunk));
   int nl = 0;
   for (int k = 0; k < K;) {
     a.first = k == 0 ? 1 : 0;
-    int steps = 1;
-    if constexpr (kPairs) {
-      if (K - k >= 2) {
-        hipLaunchKernelGGL((k_gp_zstep2<T, NP>), gz2, bz, 0, s, a);
-        steps = 2;
-      }
-    }
-    if (steps == 1) hipLaunchKernelGGL((k_gp_zstep<T, NP>), gz, bz, 0, s, a);
-    k += steps;
+    a.levels = K - k < LV ? K - k : LV;
+    hipLaunchKernelGGL((k_gp_pass<T, NP, LV>), gz, dim3(gp_waves<T, NP>() * 64), 0, s, a);
+    k += a.levels;
     for (int d = 0; d < 3; ++d) std::swap(a.p[d], a.q[d]);
     ++nl;
   }
@@ -672,7 +513,7 @@ hipError_t launch_cprox(const ProxArgs& pa, hipStream_t s, int* launches) {
   a.tau = (float)tau;
   a.c = K > 0 ? (float)(1.0 / ((a.tv2 ? 8.0 : 12.0) * tau)) : 0.f;
   a.thr = (float)(pa.step * pa.l1);
-  return run_gp<float, 2>(a, K, s, launches);
+  return run_gp<float, 2>(a, K, pa.cus, s, launches);
 }
 
 hipError_t launch_cobj(const ObjArgs& oa, int nblocks, hipStream_t s) {
@@ -709,7 +550,7 @@ hipError_t launch_prox64(const Prox64Args& pa, hipStream_t s) {
   a.tau = tau;
   a.c = K > 0 ? 1.0 / ((pa.tv2 ? 8.0 : 12.0) * tau) : 0.0;
   a.thr = pa.step * pa.l1;
-  return pa.parts == 2 ? run_gp<double, 2>(a, K, s, nullptr) : run_gp<double, 1>(a, K, s, nullptr);
+  return pa.parts == 2 ? run_gp<double, 2>(a, K, pa.cus, s, nullptr) : run_gp<double, 1>(a, K, pa.cus, s, nullptr);
 }
 
 hipError_t launch_obj64(const double* x, int nx, int ny, int nz, int parts, int tv2, double* psum, double* ptv,

@@ -383,11 +383,12 @@ hipError_t sqdist64(const double* x, const double* y, size_t n, double* part, in
 struct Prox64Args {
   const double* v; double* x;   // [parts][nz][ny][nx]; x may be v
   double* p[3];                 // dual components, as v (p[2] unused in 2D)
-  double* p2[3];                // the second dual set (the sets alternate step by step)
+  double* p2[3];                // the second dual set (the sets alternate launch by launch)
   int nx, ny, nz;               // nz: planes of one part
   int parts;                    // 1: real object, 2: complex object
   int tv2, nonneg, inner_iters;
   double step, l1, tv;
+  int cus;                      // compute units of the device (shapes the grid)
 };
 hipError_t launch_prox64(const Prox64Args& a, hipStream_t s);
 // per-block partials of sum |x| and TV(x) in psum / ptv [nblocks]
