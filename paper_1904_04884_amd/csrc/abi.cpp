@@ -575,7 +575,7 @@ static ri_status forward_f64(ri_plan* p, const void* xv, void* bv, void* ws, siz
   if (st != RI_OK) return st;
   if (overlaps(x, vb, b, hb)) return fail(RI_ERR_INVALID_ARG, "x and b_out overlap");
   const Layout64 L = layout64(p, RI_OP_FORWARD);
-  HIP_TRY(forward64(tables64(p), x, b, at<double2>(ws, L.X), at<double2>(ws, L.S), (hipStream_t)stream));
+  HIP_TRY(forward64(tables64(p), x, b, at<double2>(ws, L.X), at<double2>(ws, L.S), 0.0, nullptr, (hipStream_t)stream));
   return RI_OK;
 }
 
@@ -587,7 +587,8 @@ static ri_status adjoint_f64(ri_plan* p, const void* yv, void* xv, void* ws, siz
   if (st != RI_OK) return st;
   if (overlaps(y, hb, x, vb)) return fail(RI_ERR_INVALID_ARG, "y and x_out overlap");
   const Layout64 L = layout64(p, RI_OP_ADJOINT);
-  HIP_TRY(adjoint64(tables64(p), y, x, at<double2>(ws, L.X), at<double2>(ws, L.S), (hipStream_t)stream));
+  HIP_TRY(adjoint64(tables64(p), y, x, at<double2>(ws, L.X), at<double2>(ws, L.S), 1.0, 0.0, nullptr,
+                    (hipStream_t)stream));
   return RI_OK;
 }
 
@@ -658,7 +659,7 @@ static ri_status solve_f64(ri_plan* p, const ri_solve_params* sp, const double* 
   Prox64Args pa = prox64_args(p, L, ws, sp->nonneg ? 1 : 0, sp->inner_iters, tstep, sp->l1, sp->tv);
   std::vector<double> h(3 * (size_t)L.nblk);
   auto objective = [&](const double* xv, double* F) -> hipError_t {
-    hipError_t e = forward64(t, xv, hol, X, S, s);
+    hipError_t e = forward64(t, xv, hol, X, S, 0.0, nullptr, s);
     if (e == hipSuccess) e = sqdist64(hol, b, np, part, L.nblk, s);
     if (e == hipSuccess) e = launch_obj64(xv, p->g.nx, p->g.ny, nzq, parts, tv2, psum, ptv, L.nblk, s);
     if (e == hipSuccess) e = hipMemcpyAsync(h.data(), part, (size_t)L.nblk * sizeof(double), hipMemcpyDeviceToHost, s);
@@ -706,10 +707,8 @@ static ri_status solve_f64(ri_plan* p, const ri_solve_params* sp, const double* 
   double* xn = xb;   // x_{k+1} (held x_{k-1} until the prox writes it)
   double sk = 1.0;
   while (!stop && it < sp->max_iters) {
-    HIP_TRY(forward64(t, y, hol, X, S, s));
-    HIP_TRY(axpby64(hol, 1.0, hol, -1.0, b, np, s));          // r = A y - b
-    HIP_TRY(adjoint64(t, hol, v, X, S, s));                   // A^T r
-    HIP_TRY(axpby64(v, 1.0, y, -tstep, v, n, s));             // v = y - t A^T r
+    HIP_TRY(forward64(t, y, hol, X, S, -1.0, b, s));             // r = A y - b
+    HIP_TRY(adjoint64(t, hol, v, X, S, -tstep, 1.0, y, s));      // v = y - t A^T r
     pa.v = v;
     pa.x = xn;
     HIP_TRY(launch_prox64(pa, s));
@@ -741,20 +740,18 @@ static ri_status solve_f64(ri_plan* p, const ri_solve_params* sp, const double* 
     f_cur = F;
     f_min = std::min(f_min, F);
   }
-  std::vector<double> hx(n);
-  HIP_TRY(hipMemcpyAsync(hx.data(), x, n * sizeof(double), hipMemcpyDeviceToHost, s));
+  const int nrow = p->g.ny * p->g.nz;
+  uint8_t* flags = reinterpret_cast<uint8_t*>(X);   // the spectra are done with
+  HIP_TRY(rowflags64(x, p->g.nx, nrow, flags, s));
+  std::vector<uint8_t> hf(nrow);
+  HIP_TRY(hipMemcpyAsync(hf.data(), flags, (size_t)nrow, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   size_t empty_rows = 0, empty_planes = 0;
-  const int nrow = p->g.ny * p->g.nz;
-  for (int r = 0; r < nrow; ++r) {
-    bool any = false;
-    for (int i = 0; i < p->g.nx && !any; ++i) any = hx[(size_t)r * p->g.nx + i] != 0.0;
-    empty_rows += !any;
-  }
   for (int z = 0; z < p->g.nz; ++z) {
-    bool any = false;
-    for (size_t i = 0; i < np && !any; ++i) any = hx[(size_t)z * np + i] != 0.0;
-    empty_planes += !any;
+    int rows = 0;
+    for (int y_ = 0; y_ < p->g.ny; ++y_) rows += hf[(size_t)z * p->g.ny + y_];
+    empty_rows += p->g.ny - rows;
+    empty_planes += rows == 0;
   }
   std::memset(report, 0, sizeof(*report));
   report->iters = it;

@@ -371,11 +371,15 @@ struct Plan64Tables {
   int nx, ny, m, nzp;    // nzp: planes of every part together
 };
 size_t f64_spectra_bytes(const Plan64Tables& t);
-// b = A x (x: [nzp][ny][nx], b: [ny][nx]); X: [nzp][ny][nx] complex scratch,
-// S: [ny][nx] complex scratch.
-hipError_t forward64(const Plan64Tables& t, const double* x, double* b, double2* X, double2* S, hipStream_t s);
-// x = A^T y, same scratch.
-hipError_t adjoint64(const Plan64Tables& t, const double* y, double* x, double2* X, double2* S, hipStream_t s);
+// out = A x + cb base (x: [nzp][ny][nx]; out, base: [ny][nx]; base nullable);
+// X: [nzp][ny][nx] complex scratch, S: [ny][nx] complex scratch.
+hipError_t forward64(const Plan64Tables& t, const double* x, double* out, double2* X, double2* S, double cb,
+                     const double* base, hipStream_t s);
+// out = ca A^T y + cb base (out, base: [nzp][ny][nx]; base nullable), same scratch.
+hipError_t adjoint64(const Plan64Tables& t, const double* y, double* out, double2* X, double2* S, double ca, double cb,
+                     const double* base, hipStream_t s);
+// flags[row] = 1 where row `row` of x holds a value other than 0
+hipError_t rowflags64(const double* x, int nx, int nrow, uint8_t* flags, hipStream_t s);
 hipError_t axpby64(double* out, double a, const double* x, double b, const double* y, size_t n, hipStream_t s);
 hipError_t fill64(double* out, double v, size_t n, hipStream_t s);
 // per-block partials of sum (x - y)^2 in part[nblocks]
