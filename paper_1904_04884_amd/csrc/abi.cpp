@@ -70,7 +70,7 @@ struct GraphCache {
   const void* b = nullptr;
   const void* x = nullptr;
   double step = 0, l1 = 0, tv = 0;
-  int inner = -1, dense = -1, nonneg = -1, warm = -1;
+  int inner = -1, dense = -1, nonneg = -1, warm = -1, restart = -1;
   double store_frac = -1.0;
 };
 
@@ -963,6 +963,7 @@ struct SolveCtx {
   bool dense;
   int nonneg;
   bool warm;     // the TV dual carries over from one outer iteration to the next
+  bool restart;  // function-value restart of the momentum
   RowStores rs;  // row-compressed iterates (rs.on) or none
 };
 
@@ -1176,19 +1177,29 @@ static hipError_t enqueue_iteration(const SolveCtx& c, hipStream_t s, PhaseTimer
     e = (x);                         \
     if (e != hipSuccess) return e;   \
   } while (0)
-  if (tm) tm->begin(PH_OBJ);
-  LTRY(p->cplx ? launch_cobj(I.obj, c.L.n_obj, s) : launch_obj(I.obj, s));
-  if (tm) tm->end(1);
+  if (p->cplx) {   // (a real object: x_0 before the first iteration, then the final TV pass)
+    if (tm) tm->begin(PH_OBJ);
+    LTRY(launch_cobj(I.obj, c.L.n_obj, s));
+    if (tm) tm->end(1);
+  }
   if (tm) tm->begin(PH_FORWARD);
   LTRY(launch_rows_r2c(m, I.fwd_rows, s));
   LTRY(launch_fwd_cols(ny, c.L.nchunk, I.fwd_cols, s));
   if (tm) tm->end(2);
   if (tm) tm->begin(PH_HOLO);
   LTRY(launch_holo_cols_inv(ny, I.holo_inv, s));
-  LTRY(launch_rows_c2r(m, I.holo_c2r, s));
-  LTRY(launch_scalars(I.scal, s));
-  LTRY(launch_rows_r2c(m, I.resid, s));
-  if (tm) tm->end(4);
+  if (!c.restart) {
+    HoloRowsArgs ha{};
+    ha.c2r = I.holo_c2r;
+    ha.th = I.resid.out;
+    ha.scal = I.scal;
+    LTRY(launch_holo_rows(m, ha, s));
+  } else {   // the residual waits for the objective, which decides the momentum
+    LTRY(launch_rows_c2r(m, I.holo_c2r, s));
+    LTRY(launch_scalars(I.scal, s));
+    LTRY(launch_rows_r2c(m, I.resid, s));
+  }
+  if (tm) tm->end(c.restart ? 4 : 2);
   if (tm) tm->begin(PH_ADJOINT);
   LTRY(launch_adj_cols(ny, c.L.nchunk, I.adj_cols, s));
   LTRY(launch_adj_rows(m, I.adj_rows, s));
@@ -1303,7 +1314,7 @@ static ri_status get_graph(ri_plan* p, const SolveCtx& c, hipGraphExec_t* exec) 
   GraphCache& g = p->gc;
   if (g.exec && g.ws == c.ws && g.b == c.b && g.x == c.vol[0] && g.step == c.step && g.l1 == c.l1 &&
       g.tv == c.tv && g.inner == c.inner && g.dense == (int)c.dense && g.nonneg == c.nonneg &&
-      g.warm == (int)c.warm && g.store_frac == c.p->store_frac) {
+      g.warm == (int)c.warm && g.restart == (int)c.restart && g.store_frac == c.p->store_frac) {
     *exec = g.exec;
     return RI_OK;
   }
@@ -1322,6 +1333,7 @@ static ri_status get_graph(ri_plan* p, const SolveCtx& c, hipGraphExec_t* exec) 
   g.exec = ex;
   g.ws = c.ws; g.b = c.b; g.x = c.vol[0]; g.step = c.step; g.l1 = c.l1; g.tv = c.tv;
   g.inner = c.inner; g.dense = (int)c.dense; g.nonneg = c.nonneg; g.warm = (int)c.warm;
+  g.restart = (int)c.restart;
   g.store_frac = c.p->store_frac;
   *exec = ex;
   return RI_OK;
@@ -1383,6 +1395,7 @@ extern "C" ri_status ri_solve(ri_plan* p, const ri_solve_params* sp, const void*
   c.dense = (sp->flags & RI_SOLVE_DENSE) != 0;
   c.nonneg = sp->nonneg ? 1 : 0;
   c.warm = (sp->flags & RI_SOLVE_DUAL_WARM) != 0;
+  c.restart = (sp->flags & RI_SOLVE_RESTART) != 0;
   const bool timing = (sp->flags & RI_SOLVE_TIMING) != 0 && report != nullptr;
   const bool use_graph = !timing && !(sp->flags & RI_SOLVE_NO_GRAPH);
   PhaseTimer tm;
@@ -1392,6 +1405,11 @@ extern "C" ri_status ri_solve(ri_plan* p, const ri_solve_params* sp, const void*
   if (timing) tm.begin(PH_OTHER);
   HIP_TRY(enqueue_setup(c, sp, s));
   if (timing) tm.end(6);
+  if (!p->cplx) {   // objective pieces of x_0
+    if (timing) tm.begin(PH_OBJ);
+    HIP_TRY(launch_obj(iteration_args(c).obj, s));
+    if (timing) tm.end(1);
+  }
   hipGraphExec_t exec = nullptr;
   if (use_graph) {
     ri_status gs = get_graph(p, c, &exec);
@@ -1708,7 +1726,7 @@ extern "C" ri_status ri_solve_batched(int32_t n, ri_plan* const* plans, const ri
     hipError_t e = hipSuccess;
     bool cleared = false;
     for (const BatchLaunch& bl : launches) {
-      if (bl.nblocks == 0) continue;
+      if (bl.nblocks == 0 || bl.kind == BK_OBJ) continue;   // x_0's objective pieces: once, below
       BatchMap mp{reinterpret_cast<const uint32_t*>(tables + bl.offs_off), (int)bl.frames.size()};
       if (persistent && bl.kind == BK_TV) {
         mp.queue = reinterpret_cast<uint32_t*>(tables + bl.queue_off);
@@ -1716,7 +1734,6 @@ extern "C" ri_status ri_solve_batched(int32_t n, ri_plan* const* plans, const ri
       }
       const void* a = tables + bl.args_off;
       switch (bl.kind) {
-        case BK_OBJ: e = launch_obj_batched((const ObjArgs*)a, mp, bl.nblocks, q); break;
         case BK_FWD_ROWS: case BK_RESID:
           e = launch_rows_r2c_batched(bl.size, (const RowsR2CArgs*)a, mp, bl.nblocks, q); break;
         case BK_FWD_COLS: e = launch_fwd_cols_batched(bl.size, (const FwdColsArgs*)a, mp, bl.nblocks, q); break;
@@ -1745,6 +1762,11 @@ extern "C" ri_status ri_solve_batched(int32_t n, ri_plan* const* plans, const ri
   };
 
   for (int i = 0; i < n; ++i) HIP_TRY(enqueue_setup(ctx[i], &params[i], s));
+  for (const BatchLaunch& bl : launches)
+    if (bl.kind == BK_OBJ && bl.nblocks > 0)
+      HIP_TRY(launch_obj_batched((const ObjArgs*)(tables + bl.args_off),
+                                 BatchMap{reinterpret_cast<const uint32_t*>(tables + bl.offs_off), (int)bl.frames.size()},
+                                 bl.nblocks, s));
   const bool use_graph = !(params[0].flags & RI_SOLVE_NO_GRAPH);
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;

@@ -102,6 +102,49 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 // ---------------------------------------------------------------------------
 // Packed R2C of real rows.  Block: ROWS rows x T threads; each row in LDS.
 // ---------------------------------------------------------------------------
+// Two samples of A x (scaled) and of the residual (1 + beta) A x_it - beta A
+// x_{it-1} - b, in the same operations wherever they are compiled: a batch takes
+// them in two launches, a single solve in one, with the same bits.
+__device__ __forceinline__ float2 scaled(float2 v, float f) {
+#pragma clang fp contract(off)
+  return make_float2(v.x * f, v.y * f);
+}
+__device__ __forceinline__ float2 residual(float2 ax, float2 axp, float2 b, float beta) {
+#pragma clang fp contract(off)
+  return make_float2(fmaf(beta, ax.x - axp.x, ax.x) - b.x, fmaf(beta, ax.y - axp.y, ax.y) - b.y);
+}
+
+// Transform of a real row (its samples 2 e, 2 e + 1 in element e) and store of
+// its packed spectrum.  Every thread of the block (wave) calls it.
+template <int M, bool WAVE>
+__device__ __forceinline__ void r2c_store(float2 (&v)[points_per_thread(M)], float2* buf, int t,
+                                          const float2* __restrict__ tw, bool active, float2* __restrict__ dst) {
+  constexpr int P = points_per_thread(M), T = M / P;
+  fft_reg<M, P, 1, 2, false, WAVE>(v, buf, t, tw);
+  // the partner Z[M - k] of every k comes through LDS
+  lds_sync<WAVE>();
+#pragma unroll
+  for (int s = 0; s < P; ++s) buf[t + s * T] = v[s];
+  lds_sync<WAVE>();
+  if (!active) return;
+#pragma unroll
+  for (int s = 0; s < P; ++s) {
+    const int k = t + s * T;
+    const float2 zk = v[s];
+    float2 o;
+    if (k == 0) {
+      o = make_float2(zk.x + zk.y, zk.x - zk.y);
+    } else {
+      const float2 zm = cconj(buf[M - k]);
+      const float2 e = cscale(cadd(zk, zm), 0.5f);
+      const float2 d = csub(zk, zm);
+      const float2 od = make_float2(0.5f * d.y, -0.5f * d.x);  // (zk - zm) / (2i)
+      o = cadd(e, cmul(tw[k], od));
+    }
+    dst[k] = o;
+  }
+}
+
 template <int M>
 __device__ __forceinline__ void rows_r2c_body(const RowsR2CArgs& a, int bx, int by) {
   const float2* __restrict__ tw = a.pt.tw_row;
@@ -142,36 +185,11 @@ __device__ __forceinline__ void rows_r2c_body(const RowsR2CArgs& a, int bx, int 
       const int e = t + s * T;
       v[s] = make_float2(0.f, 0.f);
       if (active) {
-        float2 xc = c0[e], xp = c1[e], bv = bb[e];
-        v[s].x = xc.x + beta * (xc.x - xp.x) - bv.x;
-        v[s].y = xc.y + beta * (xc.y - xp.y) - bv.y;
+        v[s] = residual(c0[e], c1[e], bb[e], beta);
       }
     }
   }
-  fft_reg<M, P, 1, 2, false, WAVE>(v, buf, t, tw);
-  // the partner Z[M - k] of every k comes through LDS
-  lds_sync<WAVE>();
-#pragma unroll
-  for (int s = 0; s < P; ++s) buf[t + s * T] = v[s];
-  lds_sync<WAVE>();
-  if (!active) return;  // no barriers below
-  float2* dst = a.out + (size_t)row * M;
-#pragma unroll
-  for (int s = 0; s < P; ++s) {
-    const int k = t + s * T;
-    const float2 zk = v[s];
-    float2 o;
-    if (k == 0) {
-      o = make_float2(zk.x + zk.y, zk.x - zk.y);
-    } else {
-      const float2 zm = cconj(buf[M - k]);
-      const float2 e = cscale(cadd(zk, zm), 0.5f);
-      const float2 d = csub(zk, zm);
-      const float2 od = make_float2(0.5f * d.y, -0.5f * d.x);  // (zk - zm) / (2i)
-      o = cadd(e, cmul(tw[k], od));
-    }
-    dst[k] = o;
-  }
+  r2c_store<M, WAVE>(v, buf, t, tw, active, a.out + (size_t)row * M);
 }
 
 // ---------------------------------------------------------------------------
@@ -753,7 +771,15 @@ __device__ __forceinline__ void obj_body(const ObjArgs& a, int bx, int) {
 // ---------------------------------------------------------------------------
 // FISTA scalars (one block).
 // ---------------------------------------------------------------------------
-constexpr int kScalarThreads = 1024;
+constexpr int kScalarThreads = 256;   // a block of the row kernels, one of which also runs this
+
+// FISTA momentum of iterate `it` (s_k before it): beta and the next s.
+__device__ __forceinline__ double fista_beta(int it, double s, double* sn) {
+  *sn = s;
+  if (it == 0) return 0.0;
+  *sn = 0.5 * (1.0 + sqrt(1.0 + 4.0 * s * s));
+  return (s - 1.0) / *sn;
+}
 
 __device__ __forceinline__ void scalars_body(const ScalarArgs& a, int, int) {
   __shared__ double red[3][16];
@@ -815,15 +841,12 @@ __device__ __forceinline__ void scalars_body(const ScalarArgs& a, int, int) {
     st->done = 1;
     return;
   }
-  double beta = 0.0;
-  if (it > 0) {
-    const double sn = 0.5 * (1.0 + sqrt(1.0 + 4.0 * st->s * st->s));
-    beta = (st->s - 1.0) / sn;
-    st->s = sn;
-    if (st->restart && F > st->f_prev) {
-      st->s = 1.0;
-      beta = 0.0;
-    }
+  double sn;
+  double beta = fista_beta(it, st->s, &sn);
+  st->s = sn;
+  if (it > 0 && st->restart && F > st->f_prev) {
+    st->s = 1.0;
+    beta = 0.0;
   }
   st->beta = beta;
   st->f_prev = F;
@@ -839,6 +862,7 @@ __global__ void k_state_init(SolveState* st, StateInit in) {
   s.cur = 0; s.prev = 2; s.next = 1;
   s.scur = 0;
   s.rows_peak = 0;
+  s.ticket = 0;
   s.ax_cur = 0; s.ax_prev = 1;
   s.max_iters = in.max_iters;
   s.restart = in.restart;
@@ -1054,6 +1078,72 @@ hipError_t launch_lipschitz(const PlanTables& pt, int m, int ny, int nz, double*
 }
 
 // ---------------------------------------------------------------------------
+// Hologram rows of an iteration in one launch.  The momentum does not wait for
+// the objective (but in restarted solves), so the residual row follows its A x
+// row in the same registers, and the block that finishes last runs the scalars:
+// two launches and a pass over the hologram fewer per iteration (128^2: 15.3 us and
+// two gaps in three launches, 12.1 us in one).
+// ---------------------------------------------------------------------------
+template <int M>
+__device__ __forceinline__ void holo_rows_body(const HoloRowsArgs& h, int bx) {
+  const RowsC2RArgs& a = h.c2r;
+  const float2* __restrict__ tw = a.pt.tw_row;
+  constexpr int P = points_per_thread(M), T = M / P, ROWS = kRowsPerBlock(M), NT = ROWS * T;
+  static_assert(NT == kScalarThreads, "the scalars run in a row block");
+  constexpr bool WAVE = kRowWave(M);
+  __shared__ float2 lds[ROWS][fft_buf_len(M, P)];
+  __shared__ double red[16];
+  __shared__ uint32_t s_last;
+  SolveState* st = h.scal.st;
+  if (solve_done(st)) return;
+  const int r = threadIdx.x / T, t = threadIdx.x % T;
+  const int row = bx * ROWS + r;
+  const bool active = row < a.nrows;
+  const int it = st->it;
+  double sn;
+  const float beta = (float)fista_beta(it, st->s, &sn);
+  float2* buf = lds[r];
+  const float2* src = a.in + (size_t)row * M;
+  float2 v[P];
+#pragma unroll
+  for (int s = 0; s < P; ++s) v[s] = active ? src[t + s * T] : make_float2(0.f, 0.f);
+  c2r_prepare<M, WAVE>(v, buf, t, tw);
+  fft_reg<M, P, 1, 2, true, WAVE>(v, buf, t, tw);
+  double acc = 0.0;
+  if (active) {
+    // A x_it goes to slot it & 1; A x_{it-1} is in the other
+    float2* dst = reinterpret_cast<float2*>((it & 1) ? a.ax1 : a.ax0) + (size_t)row * M;
+    const float2* axp = reinterpret_cast<const float2*>((it & 1) ? a.ax0 : a.ax1) + (size_t)row * M;
+    const float2* bb = reinterpret_cast<const float2*>(a.b) + (size_t)row * M;
+#pragma unroll
+    for (int s = 0; s < P; ++s) {
+      const int e = t + s * T;
+      const float2 ax = scaled(v[s], a.scale);
+      dst[e] = ax;
+      const float2 bv = bb[e];
+      const double dx = (double)ax.x - (double)bv.x, dy = (double)ax.y - (double)bv.y;
+      acc += dx * dx + dy * dy;
+      v[s] = residual(ax, axp[e], bv, beta);
+    }
+  }
+  r2c_store<M, WAVE>(v, buf, t, tw, active, h.th + (size_t)row * M);
+  acc = block_sum<NT>(acc, red);
+  if (threadIdx.x == 0) {
+    a.partial[bx] = 0.5 * acc;
+    __threadfence();   // the partial before the ticket
+    s_last = atomicAdd(&st->ticket, 1u) == gridDim.x - 1 ? 1u : 0u;
+  }
+  __syncthreads();
+  if (s_last == 0) return;
+  // every block has read the state and written its partial
+  __threadfence();
+  if (threadIdx.x == 0) atomicExch(&st->ticket, 0u);
+  scalars_body(h.scal, 0, 0);
+}
+template <int M>
+__global__ void __launch_bounds__(kScalarThreads) k_holo_rows(HoloRowsArgs h) { holo_rows_body<M>(h, blockIdx.x); }
+
+// ---------------------------------------------------------------------------
 // Single-frame and batched entry kernels
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void batch_find(BatchMap map, int& frame, int& local) {
@@ -1197,6 +1287,13 @@ hipError_t launch_rows_c2r(int m, RowsC2RArgs a, hipStream_t s) {
   const dim3 g = grid_rows(m, a.nrows);
   a.gx = g.x; a.gy = g.y;
 #define C(M) case M: hipLaunchKernelGGL(k_rows_c2r<M>, g, dim3(row_threads(M)), 0, s, a); return hipGetLastError();
+  RIHVR_DISPATCH(RIHVR_ROW_SIZES, m, C)
+#undef C
+}
+hipError_t launch_holo_rows(int m, HoloRowsArgs h, hipStream_t s) {
+  const dim3 g = grid_rows(m, h.c2r.nrows);
+  h.c2r.gx = g.x; h.c2r.gy = g.y;
+#define C(M) case M: hipLaunchKernelGGL(k_holo_rows<M>, g, dim3(kScalarThreads), 0, s, h); return hipGetLastError();
   RIHVR_DISPATCH(RIHVR_ROW_SIZES, m, C)
 #undef C
 }

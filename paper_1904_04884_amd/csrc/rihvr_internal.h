@@ -54,6 +54,7 @@ struct SolveState {
   int32_t restart;
   int32_t scur;        // row store holding x_it (the other one: x_{it-1}, then x_{it+1})
   int32_t rows_peak;   // row stores: most pool rows any iterate took so far
+  uint32_t ticket;     // blocks of the hologram rows launch that have finished (0 between launches)
   double s;            // FISTA s_k
   double beta;         // momentum of the current extrapolation
   double f_prev;       // objective of the previous iterate
@@ -259,6 +260,17 @@ struct ScalarArgs {
   int gx, gy;
 };
 hipError_t launch_scalars(ScalarArgs a, hipStream_t s);
+
+// The hologram rows of an iteration in one launch: A x_it (mode 1 of RowsC2R),
+// the packed row spectrum th of the residual r = (1 + beta) A x_it - beta A x_{it-1}
+// - b, and the scalars, by the last block to finish.  Not for restarted solves,
+// whose beta waits for the objective.
+struct HoloRowsArgs {
+  RowsC2RArgs c2r;
+  float2* th;
+  ScalarArgs scal;
+};
+hipError_t launch_holo_rows(int m, HoloRowsArgs a, hipStream_t s);
 hipError_t launch_scalars_batched(const ScalarArgs* args, BatchMap map, int nblocks, hipStream_t s);
 
 // Number of frames of a batch whose solve has stopped -> *out (one block).
