@@ -446,8 +446,8 @@ static Layout make_layout(const ri_plan* p, ri_op op, int col_blocks = 0, bool d
     L.ptv = take((size_t)L.n_obj * sizeof(double));
     L.n_prox = plane_group(p) ? tv_group_blocks_bound((int)nx, (int)ny, (int)nz, p->dual_planes, p->cus)
                               : tv_blocks_bound((int)nx, (int)ny, (int)nz, p->cus);
-    L.qsum = take((size_t)L.n_prox * sizeof(double));
-    L.qtv = take((size_t)L.n_prox * sizeof(double));
+    L.qsum = take((size_t)L.n_prox * 2 * sizeof(double));
+    L.qtv = take((size_t)L.n_prox * 2 * sizeof(double));
     L.hist = take((size_t)kHistCap * sizeof(double));
     L.state = take(sizeof(SolveState));
   }
@@ -510,6 +510,7 @@ static void prox_duals(const ri_plan* p, const Layout& L, void* ws, ProxArgs* a)
   a->dual_bf16 = (p->g.flags & RI_TV_DUAL_BF16) ? 1 : 0;
   a->fgp = (p->g.flags & RI_TV_FGP) ? 1 : 0;
   a->cus = a->fill = p->cus;
+  a->low = 1;
   a->group_planes = plane_group(p) ? p->dual_planes : 0;
 }
 
@@ -1032,12 +1033,14 @@ struct IterArgs {
   ProxArgs prox;
 };
 
-// Objective partials of a solve's final TV pass, whose grid is cut to reach `fill` blocks.
-static int final_partials(const ri_plan* p, int fill) {
+// Objective partials of a solve's final TV pass, whose grid is cut to reach
+// `fill` blocks (may: low tiles are allowed).
+static int final_partials(const ri_plan* p, int fill, bool may) {
   const int nx = p->g.nx, ny = p->g.ny, nz = p->g.nz;
   const ri_tuning& t = p->tune;
-  return plane_group(p) ? tv_group_final_blocks(nx, ny, nz, p->dual_planes, t.tv_levels, t.tv_blocks, p->cus, fill)
-                        : tv_final_blocks(nx, ny, nz, t.tv_levels, t.tv_blocks, p->cus, fill);
+  const int low = !may || (p->g.flags & (RI_TV_DUAL_BF16 | RI_TV_FGP)) ? 0 : ((p->g.flags & RI_TV2D) ? 2 : 1);
+  return plane_group(p) ? tv_group_final_blocks(nx, ny, nz, p->dual_planes, t.tv_levels, t.tv_blocks, p->cus, fill, low)
+                        : tv_final_blocks(nx, ny, nz, t.tv_levels, t.tv_blocks, p->cus, fill, low);
 }
 
 static IterArgs iteration_args(const SolveCtx& c) {
@@ -1106,7 +1109,7 @@ static IterArgs iteration_args(const SolveCtx& c) {
   sa.n_obj = L.n_obj;
   sa.qsum = at<double>(c.ws, L.qsum);
   sa.qtv = at<double>(c.ws, L.qtv);
-  sa.n_prox = final_partials(p, p->cus);
+  sa.n_prox = final_partials(p, p->cus, !c.rs.on);
   sa.hist = at<double>(c.ws, L.hist);
   if (p->cplx) sa.qsum = sa.qtv = nullptr;   // the objective kernel runs every iteration
   sa.overflow = c.rs.on ? c.rs.overflow : nullptr;
@@ -1638,7 +1641,8 @@ extern "C" ri_status ri_solve_batched(int32_t n, ri_plan* const* plans, const ri
   for (int i = 0; i < n; ++i) {
     it[i] = iteration_args(ctx[i]);
     it[i].prox.fill = std::max(1, plans[i]->cus / n);   // the frames fill the device together
-    it[i].scal.n_prox = final_partials(plans[i], it[i].prox.fill);
+    it[i].prox.low = 0;
+    it[i].scal.n_prox = final_partials(plans[i], it[i].prox.fill, false);
     const ri_plan* p = plans[i];
     const int ny = p->g.ny, nz = p->g.nz, m = p->m;
     dim3 g;

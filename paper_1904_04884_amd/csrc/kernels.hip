@@ -98,6 +98,27 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   }
   return v;
 }
+// The same of hi + lo, where lo is what the additions to hi dropped.
+template <int NT>
+__device__ __forceinline__ double block_sum_exact(double hi, double lo, double* red) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const double oh = __shfl_xor(hi, off, 64);
+    lo += __shfl_xor(lo, off, 64);
+    add_exact(hi, lo, oh);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[2 * (threadIdx.x >> 6)] = hi;
+    red[2 * (threadIdx.x >> 6) + 1] = lo;
+  }
+  __syncthreads();
+  double s = 0.0, l = 0.0;
+  for (int w = 0; w < NT / 64; ++w) {
+    l += red[2 * w + 1];
+    add_exact(s, l, red[2 * w]);
+  }
+  return isfinite(s) ? s + l : s;
+}
 
 // ---------------------------------------------------------------------------
 // Packed R2C of real rows.  Block: ROWS rows x T threads; each row in LDS.
@@ -792,15 +813,25 @@ __device__ __forceinline__ void scalars_body(const ScalarArgs& a, int, int) {
   const double* ps = from_prox ? a.qsum : a.psum;
   const double* pt = from_prox ? a.qtv : a.ptv;
   const int n_obj = from_prox ? a.n_prox : a.n_obj;
-  for (int i = threadIdx.x; i < n_obj; i += kScalarThreads) {
-    s += ps[i];
-    t += pt[i];
+  double sl = 0.0, tl = 0.0;
+  if (from_prox) {
+    for (int i = threadIdx.x; i < n_obj; i += kScalarThreads) {
+      sl += ps[2 * i + 1];
+      tl += pt[2 * i + 1];
+      add_exact(s, sl, ps[2 * i]);
+      add_exact(t, tl, pt[2 * i]);
+    }
+  } else {
+    for (int i = threadIdx.x; i < n_obj; i += kScalarThreads) {
+      s += ps[i];
+      t += pt[i];
+    }
   }
   d = block_sum<kScalarThreads>(d, red[0]);
   __syncthreads();
-  s = block_sum<kScalarThreads>(s, red[1]);
+  s = block_sum_exact<kScalarThreads>(s, sl, red[1]);
   __syncthreads();
-  t = block_sum<kScalarThreads>(t, red[2]);
+  t = block_sum_exact<kScalarThreads>(t, tl, red[2]);
   if (threadIdx.x != 0) return;
   const double F = d + st->l1 * s + st->tv * t;
   const int it = st->it;

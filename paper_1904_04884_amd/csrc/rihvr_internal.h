@@ -43,6 +43,18 @@ __device__ __forceinline__ T* pick3(T* a, T* b, T* c, int i) {
 // Solver state that lives in device memory for the duration of a solve.  All
 // control decisions (momentum, stop, buffer rotation) are taken on the device
 // so that one iteration can be replayed as a HIP graph.
+#ifdef __HIPCC__
+// Sums whose rounding does not depend on how the terms are grouped: the running
+// sum and what its additions dropped.  A frame's objective must not change with
+// the grid that its passes ran on (alone, or sharing the device with a batch).
+template <class L>
+__device__ __forceinline__ void add_exact(double& hi, L& lo, double v) {
+  const double s = hi + v, b = s - hi;
+  lo += (L)((hi - (s - b)) + (v - b));
+  hi = s;
+}
+#endif
+
 struct SolveState {
   int32_t it;          // index of the iterate evaluated by the next objective kernel
   int32_t done;        // 1: every kernel of the solve returns immediately
@@ -326,6 +338,7 @@ struct ProxArgs {
   int blocks;            // target blocks per pass (<= 0: the default)
   int tv2;               // per-plane 2D TV (pa[2], pb[2] unused)
   int cus;               // compute units of the device (shapes the final pass's grid; <= 0: uniform)
+  int low;               // a launch of its own: the passes may take low tiles (depth 3, FP32 dual, no row store)
   int fill;              // blocks that a pass's grid is cut to reach (cus; a frame of a batch: its share)
   int dual_bf16;         // dual buffers hold bfloat16
   int fgp;               // accelerated dual iteration (one step per pass; pa2 / pb2 hold p)
@@ -343,15 +356,14 @@ int prox_passes(int inner_iters, double tau, int levels, bool fgp);
 int prox_levels(int levels, bool fgp);
 // Planes per block of a pass for the given tuning (distinct values = distinct grids).
 int tv_pass_zchunk(int nx, int ny, int nz, int levels, int blocks, int fill);
-// Blocks of a dual pass and of the final pass (its tiles have a halo one
-// wider) for the given tuning, and a bound over every tuning and pass.
-int tv_pass_blocks(int nx, int ny, int nz, int levels, int blocks, int fill);
-int tv_final_blocks(int nx, int ny, int nz, int levels, int blocks, int cus, int fill);
+// Blocks of the final pass for the given tuning (low: 1 in 3D, 2 in 2D where
+// low tiles may be taken), and a bound over every tuning and pass.
+int tv_final_blocks(int nx, int ny, int nz, int levels, int blocks, int cus, int fill, int low);
 int tv_blocks_bound(int nx, int ny, int nz, int cus);
 // Grouped per-plane prox: final-pass blocks of all groups of G planes (the
 // objective partials of group g start at the sum over the groups before it),
 // and a bound over every tuning.
-int tv_group_final_blocks(int nx, int ny, int nz, int G, int levels, int blocks, int cus, int fill);
+int tv_group_final_blocks(int nx, int ny, int nz, int G, int levels, int blocks, int cus, int fill, int low);
 int tv_group_blocks_bound(int nx, int ny, int nz, int G, int cus);
 
 // Batched prox: the argument structs of every pass of every frame are built on

@@ -23,13 +23,20 @@ extern template void launch_tv_depth<4>(const TvSelect&, dim3, const TvPassArgs*
 // seven passes 498 -> 378 us).
 // `halo` is the tile halo of the pass (H on dual passes, H + 1 on the final).
 struct TvGrid {
-  int gx, gy, zchunk, nfull, zchunk2, nblocks;
+  int gx, gy, zchunk, nfull, zchunk2, nblocks, low;
 };
 
-static TvGrid pass_grid(int nx, int ny, int nz, int halo, int want, int fill) {
+// `low` (1: 3D, 2: 2D TV): tiles of 24 rows (two a lane instead of four) may be
+// used.  They redo more halo but take about 0.6 of the time for a plane, so they
+// are taken where their blocks still fit one round of `fill` and that outweighs
+// the longer chunks.  Depth 3, 48 rows and 24: 64^2 x 8 (march 11 planes and 11)
+// 55 -> 36 us, 128^2 x 32 (11, 13) 123 -> 90, 192^2 x 48 (13, 19) 142 -> 120, but
+// 256^2 x 64 (19, 31) 370 -> 376; in 2D 128 x 96 x 8 (4, 4) 27 -> 22, but 128^2 x 32
+// (5, 7) 42 -> 44: lines at 0.65 and 0.75 of the march.
+static TvGrid grid_of(int nx, int ny, int nz, int halo, int rows, int want, int fill) {
   TvGrid g{};
   g.gx = (nx + (kTvRX - 2 * halo) - 1) / (kTvRX - 2 * halo);
-  g.gy = (ny + (kTvRY - 2 * halo) - 1) / (kTvRY - 2 * halo);
+  g.gy = (ny + (rows - 2 * halo) - 1) / (rows - 2 * halo);
   const int tiles = g.gx * g.gy;
   const int nzc = std::max(1, std::min(nz / 16, (want + tiles - 1) / tiles));
   g.zchunk = (nz + nzc - 1) / nzc;
@@ -42,16 +49,26 @@ static TvGrid pass_grid(int nx, int ny, int nz, int halo, int want, int fill) {
   g.nblocks = tiles * ((nz + g.zchunk - 1) / g.zchunk);
   return g;
 }
+static TvGrid pass_grid(int nx, int ny, int nz, int halo, int want, int fill, int low) {
+  const TvGrid g = grid_of(nx, ny, nz, halo, kTvRY, want, fill);
+  if (!low || g.nblocks > fill) return g;
+  TvGrid h = grid_of(nx, ny, nz, halo, kTvWaves * kTvSmallQ, want, fill);
+  // planes a block marches over: its own and up to 3 halos of margin and pipeline
+  auto march = [&](const TvGrid& t) { return std::min(nz, t.zchunk + (low == 2 ? 0 : 2 * halo)) + halo; };
+  if (h.nblocks > fill || 100 * march(g) < (low == 2 ? 75 : 65) * march(h)) return g;
+  h.low = 1;
+  return h;
+}
 
 // The final pass runs one 12-wave block per compute unit, so its time is
 // whole rounds of `cus` blocks.  Its tiles are one voxel smaller than those of
 // the dual passes; when they fill whole rounds but for a few (at 1024^2 one
 // tile beyond 512), the leftover tiles are cut into thin z chunks that run
 // side by side in one short extra round instead of a full one.
-static TvGrid final_grid(int nx, int ny, int nz, int H, int want, int cus, int fill) {
-  TvGrid g = pass_grid(nx, ny, nz, H + 1, want, fill);
+static TvGrid final_grid(int nx, int ny, int nz, int H, int want, int cus, int fill, int low) {
+  TvGrid g = pass_grid(nx, ny, nz, H + 1, want, fill, low);
   const int tiles = g.gx * g.gy;
-  if (cus <= 0 || g.zchunk < nz || tiles <= cus) return g;
+  if (cus <= 0 || g.low || g.zchunk < nz || tiles <= cus) return g;
   const int r = tiles % cus;
   const int k = r > 0 ? std::min(nz, cus / r) : 1;
   if (k < 2) return g;
@@ -75,12 +92,9 @@ int prox_levels(int levels, bool fgp) { return fgp ? 2 : clamp_levels(levels); }
 
 size_t tv_pass_args_size() { return sizeof(TvPassArgs); }
 
-int tv_pass_blocks(int nx, int ny, int nz, int levels, int blocks, int fill) {
-  return pass_grid(nx, ny, nz, clamp_levels(levels), blocks > 0 ? blocks : kTvDefaultBlocks, fill).nblocks;
-}
-
-int tv_final_blocks(int nx, int ny, int nz, int levels, int blocks, int cus, int fill) {
-  return final_grid(nx, ny, nz, clamp_levels(levels), blocks > 0 ? blocks : kTvDefaultBlocks, cus, fill).nblocks;
+int tv_final_blocks(int nx, int ny, int nz, int levels, int blocks, int cus, int fill, int low) {
+  return final_grid(nx, ny, nz, clamp_levels(levels), blocks > 0 ? blocks : kTvDefaultBlocks, cus, fill,
+                    clamp_levels(levels) == kTvDefaultLevels ? low : 0).nblocks;
 }
 
 int tv_blocks_bound(int nx, int ny, int nz, int cus) {
@@ -93,9 +107,9 @@ int tv_blocks_bound(int nx, int ny, int nz, int cus) {
   return tx * ty * std::max(1, nz / 16) + std::max(cus, 0);
 }
 
-int tv_group_final_blocks(int nx, int ny, int nz, int G, int levels, int blocks, int cus, int fill) {
+int tv_group_final_blocks(int nx, int ny, int nz, int G, int levels, int blocks, int cus, int fill, int low) {
   int total = 0;
-  for (int z0 = 0; z0 < nz; z0 += G) total += tv_final_blocks(nx, ny, std::min(G, nz - z0), levels, blocks, cus, fill);
+  for (int z0 = 0; z0 < nz; z0 += G) total += tv_final_blocks(nx, ny, std::min(G, nz - z0), levels, blocks, cus, fill, low);
   return total;
 }
 
@@ -105,7 +119,7 @@ int tv_group_blocks_bound(int nx, int ny, int nz, int G, int cus) {
 }
 
 int tv_pass_zchunk(int nx, int ny, int nz, int levels, int blocks, int fill) {
-  return pass_grid(nx, ny, nz, clamp_levels(levels), blocks > 0 ? blocks : kTvDefaultBlocks, fill).zchunk;
+  return pass_grid(nx, ny, nz, clamp_levels(levels), blocks > 0 ? blocks : kTvDefaultBlocks, fill, 0).zchunk;
 }
 
 // Argument structs of every pass of one prox application.  Every pass takes
@@ -119,6 +133,7 @@ int prox_pass_args(const ProxArgs& pa, void* out, int* blocks_per_pass) {
   const bool fgp = pa.fgp != 0;
   const int H = prox_levels(pa.levels, fgp);
   const int npass = prox_passes(K, tau, H, fgp);
+  const int low = H == kTvDefaultLevels && pa.low && !fgp && !pa.dual_bf16 && !pa.rs.on ? (pa.tv2 ? 2 : 1) : 0;
   TvPassArgs a{};
   a.v = pa.v;
   a.x = pa.x;
@@ -142,8 +157,9 @@ int prox_pass_args(const ProxArgs& pa, void* out, int* blocks_per_pass) {
   double tk = 1.0;   // FGP: t_k of the step a pass takes
   for (int p = 0; p < npass; ++p) {
     const bool fin = p == npass - 1;
-    const TvGrid g = fin ? final_grid(pa.nx, pa.ny, pa.nz, H, want, pa.cus, pa.fill)
-                         : pass_grid(pa.nx, pa.ny, pa.nz, H, want, pa.fill);
+    const TvGrid g = fin ? final_grid(pa.nx, pa.ny, pa.nz, H, want, pa.cus, pa.fill, low)
+                         : pass_grid(pa.nx, pa.ny, pa.nz, H, want, pa.fill, low);
+    a.low = g.low;
     a.gx = g.gx;
     a.gy = g.gy;
     a.zchunk = g.zchunk;
@@ -185,7 +201,7 @@ static void launch_any(const TvSelect& k, int H, dim3 g, const TvPassArgs* a, co
   else launch_tv_depth<4>(k, g, a, map, s);
 }
 static TvSelect select_of(const TvPassArgs& a) {
-  return TvSelect{false, a.final_ != 0, a.tv2 != 0, a.fgp != 0, a.dual_bf16 != 0, a.rs.on != 0};
+  return TvSelect{false, a.final_ != 0, a.tv2 != 0, a.fgp != 0, a.dual_bf16 != 0, a.rs.on != 0, a.low != 0};
 }
 
 // The per-plane 2D TV couples no planes, so its prox can run on groups of G
@@ -205,8 +221,8 @@ static hipError_t launch_prox_grouped(const ProxArgs& pa, int K, int H, int np, 
     q.group_planes = 0;
     q.rowflag = pa.rowflag ? pa.rowflag + (size_t)z0 * pa.ny : nullptr;
     q.planeflag = pa.planeflag ? pa.planeflag + z0 : nullptr;
-    q.psum = pa.psum ? pa.psum + off : nullptr;
-    q.ptv = pa.ptv ? pa.ptv + off : nullptr;
+    q.psum = pa.psum ? pa.psum + 2 * off : nullptr;
+    q.ptv = pa.ptv ? pa.ptv + 2 * off : nullptr;
     if (pa.stage_group) q.x = pa.stage_group;
     const int npass = prox_pass_args(q, args.data(), nb.data());
     for (int p = 0; p < npass; ++p) {

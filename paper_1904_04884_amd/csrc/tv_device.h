@@ -71,6 +71,9 @@ constexpr int kTvWaves = 12;
 constexpr int kTvQ = 4;                 // rows per lane
 constexpr int kTvRX = 64;               // tile width (lanes)
 constexpr int kTvRY = kTvWaves * kTvQ;  // tile height
+constexpr int kTvSmallQ = 2;            // rows per lane of the low tiles (see pass_grid)
+template <int Q>
+using TvVec = float __attribute__((ext_vector_type(Q)));
 
 struct TvPassArgs {
   const float* v;                 // nullptr: vol[st->prev]
@@ -79,7 +82,7 @@ struct TvPassArgs {
   const float* pin[3];            // dual read by the first step (ignored when first)
   float* pout[3];                 // dual written by the last step (unless final)
   uint8_t* rowflag; uint8_t* planeflag;  // final pass: set where x != 0 (nullable)
-  double* psum; double* ptv;      // final pass: per-block sum(x) and TV(x) of the stored x (nullable)
+  double* psum; double* ptv;      // final pass: per-block sum(x) and TV(x) of the stored x, two words each (nullable)
   const SolveState* st;
   int nx, ny, nz;
   int levels;                     // fused dual steps in this pass (<= H)
@@ -100,6 +103,7 @@ struct TvPassArgs {
   int nblocks;                    // blocks of the pass (the objective partials are per block)
   float tau, c, thr;
   int gx, gy;                     // tiles along x and y (the grid of one frame)
+  int low;                        // tiles of kTvSmallQ rows a lane
   size_t zoff_v, zoff_x;          // grouped per-plane prox: first plane of the group in v and x (elements)
 };
 
@@ -197,13 +201,13 @@ __host__ __device__ constexpr int tv_ring() { return FINAL ? tv_delay(LV) + 1 : 
 // (about 2^20 * 128 clocks; the publisher needs a few hundred).
 constexpr int kStoreSpinLimit = 1 << 20;
 
-template <int H, int LV, bool EDGE, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
+template <int H, int LV, int Q, bool EDGE, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
 __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by, int zb, int ze, int blk,
                                              float (*s_py)[tv_py_slots(LV)][kTvWaves][64], float (*s_ut)[2][kTvWaves][64],
-                                             float4* s_v, float (*s_x)[kTvWaves][64], double (*s_red)[kTvWaves],
+                                             TvVec<Q>* s_v, float (*s_x)[kTvWaves][64], double (*s_red)[kTvWaves],
                                              float* s_fin, double* s_sum) {
-  constexpr int Q = kTvQ, NW = kTvWaves, NT = NW * 64;
-  constexpr int IX = kTvRX - 2 * H, IY = kTvRY - 2 * H;  // interior (stored) extent
+  constexpr int NW = kTvWaves, NT = NW * 64, RY = NW * Q;
+  constexpr int IX = kTvRX - 2 * H, IY = RY - 2 * H;  // interior (stored) extent
   constexpr int PYM = tv_py_slots(LV) - 1;
   constexpr bool LEAN = tv_lean(LV);
   const float* __restrict__ v =
@@ -247,9 +251,9 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
     ylo[q] = !EDGE || y > 0;
     yhi[q] = !EDGE || y + 1 < ny;
     const int r = wv * Q + q;
-    ys[q] = ix_store && iny && r >= H && r < kTvRY - H;
+    ys[q] = ix_store && iny && r >= H && r < RY - H;
     rowl[q] = iny ? (unsigned)(y * nx) * 4u : kTvOff;
-    rows[q] = iny && r >= H && r < kTvRY - H ? rowl[q] : kTvOff;
+    rows[q] = iny && r >= H && r < RY - H ? rowl[q] : kTvOff;
   }
   // (lean: the empty statement keeps the sums out of registers that live through the march)
   auto load_off = [&](int q) __attribute__((always_inline)) {
@@ -284,16 +288,22 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
       Xp(q) = 0.f;
     }
   }
-  // ||x||_1 and TV(x) of the thread's voxels (objective pieces)
+  // ||x||_1 and TV(x) of the thread's voxels (objective pieces), and what their
+  // additions dropped
   constexpr bool SUMS = FINAL && LEAN;
   double r_sum[2];
+  float r_lo[2];
   double& x_sum = *(SUMS ? s_sum + threadIdx.x : r_sum);
   double& tv_sum = *(SUMS ? s_sum + NT + threadIdx.x : r_sum + 1);
+  float* const s_lo = reinterpret_cast<float*>(s_sum + 2 * NT);
+  float& x_lo = *(SUMS ? s_lo + threadIdx.x : r_lo);
+  float& tv_lo = *(SUMS ? s_lo + NT + threadIdx.x : r_lo + 1);
   x_sum = tv_sum = 0.0;
+  x_lo = tv_lo = 0.f;
   // terms of the plane held in Xp; xn: the next plane (hz: it exists), slot:
   // the LDS slot holding the first row of every wave of the Xp plane
   auto accumulate = [&](const float* xn, bool hz, int slot) __attribute__((always_inline)) {
-    float ss = 0.f, tt = 0.f;
+    float xq[Q], tq[Q], any = 0.f;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       const float x0 = Xp(q);
@@ -305,11 +315,22 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
       // per-voxel norm in FP32 (the hardware square root, within 1 ulp, not
       // the correctly rounded sequence), running sums in FP64
       const float t = __builtin_amdgcn_sqrtf(fmaf(gx, gx, fmaf(gy, gy, gz * gz)));
-      ss += ys[q] ? fabsf(x0) : 0.f;   // ||x||_1
-      tt += ys[q] ? t : 0.f;
+      xq[q] = ys[q] ? fabsf(x0) : 0.f;   // ||x||_1
+      tq[q] = ys[q] ? t : 0.f;
+      any += xq[q] + tq[q];
     }
-    x_sum += (double)ss;
-    tv_sum += (double)tt;
+    if (__ballot(any != 0.f) == 0) return;   // nothing but zeros in the wave's rows (most planes of a sparse volume)
+    double xs = x_sum, ts = tv_sum;
+    float xl = x_lo, tl = tv_lo;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      add_exact(xs, xl, (double)xq[q]);
+      add_exact(ts, tl, (double)tq[q]);
+    }
+    x_sum = xs;
+    tv_sum = ts;
+    x_lo = xl;
+    tv_lo = tl;
   };
 
   // Input planes are prefetched one ahead (a plane takes about 4 us).  v of
@@ -355,15 +376,16 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
     }
   };
   constexpr int NS = tv_ring<LV, FINAL>();
-  auto vring = [&](int a) __attribute__((always_inline)) -> float4& { return s_v[(a % NS) * NT + threadIdx.x]; };
+  auto vring = [&](int a) __attribute__((always_inline)) -> TvVec<Q>& { return s_v[(a % NS) * NT + threadIdx.x]; };
 
   // Arrival of the previous dual c3 at plane a for fused step l: u(a), then
   // the dual step at plane a - 1 (which needs u(a) for its z-difference) into
   // c3.  arrive_pre publishes the row the wave above needs and fetches v;
   // a barrier separates the two halves.
   auto arrive_pre = [&](int l, int a, int par, const float (&c3)[Q][3], float (&un)[Q]) __attribute__((always_inline)) {
-    const float4 v4 = vring(a);  // thread-private: read before the barrier
-    un[0] = v4.x; un[1] = v4.y; un[2] = v4.z; un[3] = v4.w;
+    const TvVec<Q> vq = vring(a);  // thread-private: read before the barrier
+#pragma unroll
+    for (int q = 0; q < Q; ++q) un[q] = vq[q];
     s_py[l][par & PYM][wv][lane] = c3[Q - 1][1];
   };
   auto arrive_post = [&](int l, bool start, int par, float (&c3)[Q][3], float (&un)[Q]) __attribute__((always_inline)) {
@@ -529,8 +551,7 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
       store_dual(m, c3, zstore);
     } else {
       if (A.keep_dual) store_dual(m, c3, zstore);
-      const float4 v4 = vring(m);  // thread-private: read before the barrier
-      const float vm[Q] = {v4.x, v4.y, v4.z, v4.w};
+      const TvVec<Q> vm = vring(m);  // thread-private: read before the barrier
       s_py[LV][par & PYM][wv][lane] = c3[Q - 1][1];
       __syncthreads();
       const __amdgpu_buffer_rsrc_t rx = dual_rsrc(xo, m, sz, false, !zstore);
@@ -602,9 +623,10 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
     const int a1 = zs + s;
     float ppa[Q][3];   // FGP: p_prev of plane a1 (one step: output of a1 comes at the next arrival)
     if (!EACH || a1 < zl) {
-      float4 v4;
-      v4.x = vcopy(P.v[0]); v4.y = vcopy(P.v[1]); v4.z = vcopy(P.v[2]); v4.w = vcopy(P.v[3]);
-      vring(a1) = v4;
+      TvVec<Q> vq;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) vq[q] = vcopy(P.v[q]);
+      vring(a1) = vq;
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
         C[q][0] = vcopy(P.p[q][0]);
@@ -710,25 +732,33 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
         __syncthreads();
         accumulate(nullptr, false, (nsteps - 1) & 1);
       }
-      double s_acc = x_sum, t_acc = tv_sum;
+      double acc[2] = {x_sum, tv_sum}, lo[2] = {(double)x_lo, (double)tv_lo};
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        s_acc += __shfl_xor(s_acc, off, 64);
-        t_acc += __shfl_xor(t_acc, off, 64);
-      }
-      if (lane == 0) {
-        s_red[0][wv] = s_acc;
-        s_red[1][wv] = t_acc;
+      for (int k = 0; k < 2; ++k) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+          const double oh = __shfl_xor(acc[k], off, 64);
+          lo[k] += __shfl_xor(lo[k], off, 64);
+          add_exact(acc[k], lo[k], oh);
+        }
+        if (lane == 0) {
+          s_red[2 * k][wv] = acc[k];
+          s_red[2 * k + 1][wv] = lo[k];
+        }
       }
       __syncthreads();
       if (threadIdx.x == 0) {
-        double s = 0.0, t = 0.0;
-        for (int w = 0; w < NW; ++w) {
-          s += s_red[0][w];
-          t += s_red[1][w];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          double s = 0.0, l = 0.0;
+          for (int w = 0; w < NW; ++w) {
+            l += s_red[2 * k + 1][w];
+            add_exact(s, l, s_red[2 * k][w]);
+          }
+          double* dst = (k == 0 ? A.psum : A.ptv) + 2 * (size_t)blk;
+          dst[0] = s;
+          dst[1] = l;
         }
-        A.psum[blk] = s;
-        A.ptv[blk] = t;
       }
     }
   }
@@ -736,24 +766,24 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
 
 // HT: tile halo, LV: fused-step register slots.  Dual passes use HT = LV = H;
 // the final pass HT = H + 1, LV = H.
-template <int HT, int LV, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
+template <int HT, int LV, int Q, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
 __device__ __forceinline__ void tv_pass_entry(const TvPassArgs& A, int bx, int by, int zb, int ze, int blk) {
   __shared__ float s_py[LV + 1][tv_py_slots(LV)][kTvWaves][64];  // bottom-row p_y per wave, per step (+ final)
   __shared__ float s_ut[LV][2][kTvWaves][64];      // top-row u per wave, per step, parity
-  __shared__ float4 s_v[tv_ring<LV, FINAL>() * kTvWaves * 64];  // v ring, thread-private
+  __shared__ TvVec<Q> s_v[tv_ring<LV, FINAL>() * kTvWaves * 64];  // v ring, thread-private
   __shared__ float s_x[FINAL ? 2 : 1][kTvWaves][64];     // final pass: first-row x per wave, parity
-  __shared__ double s_red[2][kTvWaves];            // final pass: per-wave sums
-  __shared__ float s_fin[FINAL ? 2 * kTvQ * kTvWaves * 64 : 1];    // final pass: PzF, Xp (thread-private)
-  __shared__ double s_sum[FINAL && tv_lean(LV) ? 2 * kTvWaves * 64 : 1];   // final pass: sums (thread-private)
+  __shared__ double s_red[4][kTvWaves];            // final pass: per-wave sums
+  __shared__ float s_fin[FINAL ? 2 * Q * kTvWaves * 64 : 1];    // final pass: PzF, Xp (thread-private)
+  __shared__ double s_sum[FINAL && tv_lean(LV) ? 3 * kTvWaves * 64 : 1];   // final pass: sums (thread-private)
   // the stop flag read once per wave (a wave-uniform branch)
   if (A.st != nullptr && __builtin_amdgcn_readfirstlane(A.st->done)) return;
-  constexpr int IX = kTvRX - 2 * HT, IY = kTvRY - 2 * HT;
+  constexpr int RY = kTvWaves * Q, IX = kTvRX - 2 * HT, IY = RY - 2 * HT;
   const int x0 = bx * IX - HT, y0 = by * IY - HT;
   // interior tile: every point of the region and its +-1 neighbours lie inside
-  const bool interior = x0 >= 1 && x0 + kTvRX <= A.nx - 1 && y0 >= 1 && y0 + kTvRY <= A.ny - 1;
+  const bool interior = x0 >= 1 && x0 + kTvRX <= A.nx - 1 && y0 >= 1 && y0 + RY <= A.ny - 1;
   auto* sx = reinterpret_cast<float (*)[kTvWaves][64]>(&s_x[0][0][0]);
 #define RIHVR_TV_BODY(E) \
-  tv_pass_body<HT, LV, E, FINAL, TV2, FGP, BF, SP>(A, bx, by, zb, ze, blk, s_py, s_ut, s_v, sx, s_red, s_fin, s_sum)
+  tv_pass_body<HT, LV, Q, E, FINAL, TV2, FGP, BF, SP>(A, bx, by, zb, ze, blk, s_py, s_ut, s_v, sx, s_red, s_fin, s_sum)
   if (interior) RIHVR_TV_BODY(false);
   else RIHVR_TV_BODY(true);
 #undef RIHVR_TV_BODY
@@ -794,13 +824,13 @@ __device__ __forceinline__ TvWork tv_work(const TvPassArgs& A, uint32_t t) {
 // The first part of the grid (whole rounds of tiles) takes the XCD-contiguous
 // order; the thin chunks of the split tiles, dispatched last, keep the
 // hardware order so that they spread over every XCD.
-template <int H, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
+template <int H, bool FINAL, bool TV2, bool FGP, bool BF, bool SP, int Q = kTvQ>
 __global__ void __launch_bounds__(kTvWaves * 64, kTvWavesPerSimd) k_tv_pass(TvPassArgs A) {
   const uint32_t hw = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
   const uint32_t n1 = (uint32_t)A.nfull * (uint32_t)((A.nz + A.zchunk - 1) / A.zchunk);
   const uint32_t t = hw < n1 ? xcd_tile(hw, n1) : hw;
   const TvWork w = tv_work(A, t);
-  tv_pass_entry<FINAL ? H + 1 : H, H, FINAL, TV2, FGP, BF, SP>(A, w.bx, w.by, w.zb, w.ze, (int)t);
+  tv_pass_entry<FINAL ? H + 1 : H, H, Q, FINAL, TV2, FGP, BF, SP>(A, w.bx, w.by, w.zb, w.ze, (int)t);
 }
 
 // Work item b of a batched launch: the frame f with offs[f] <= b < offs[f+1]
@@ -819,7 +849,7 @@ __device__ __forceinline__ void tv_batch_item(const TvPassArgs* __restrict__ arg
   const TvPassArgs& A = args[lo];
   const int lb = (int)(b - (uint32_t)__builtin_amdgcn_readfirstlane(map.offs[lo]));
   const TvWork w = tv_work(A, (uint32_t)lb);
-  tv_pass_entry<FINAL ? H + 1 : H, H, FINAL, TV2, FGP, BF, SP>(A, w.bx, w.by, w.zb, w.ze, lb);
+  tv_pass_entry<FINAL ? H + 1 : H, H, kTvQ, FINAL, TV2, FGP, BF, SP>(A, w.bx, w.by, w.zb, w.ze, lb);
 }
 
 template <int H, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
@@ -889,7 +919,7 @@ static void launch_batched(dim3 g, const TvPassArgs* a, const BatchMap& map, hip
 // (final passes with an FP32 dual only), single or batched form.  One source
 // file per depth instantiates it.
 struct TvSelect {
-  bool batch, final_pass, tv2, fgp, bf16, sparse;
+  bool batch, final_pass, tv2, fgp, bf16, sparse, low;   // low: tiles of kTvSmallQ rows a lane
 };
 template <int H, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
 static void launch_tv_kernel(bool batch, dim3 g, const TvPassArgs* a, const BatchMap& map, hipStream_t s) {
@@ -898,6 +928,14 @@ static void launch_tv_kernel(bool batch, dim3 g, const TvPassArgs* a, const Batc
 }
 template <int H, bool TV2>
 static void launch_tv_dim(const TvSelect& k, dim3 g, const TvPassArgs* a, const BatchMap& map, hipStream_t s) {
+  if constexpr (H == kTvDefaultLevels) {
+    if (k.low) {   // (single launches with an FP32 dual only)
+      const dim3 b(kTvWaves * 64);
+      if (k.final_pass) hipLaunchKernelGGL((k_tv_pass<H, true, TV2, false, false, false, kTvSmallQ>), g, b, 0, s, *a);
+      else hipLaunchKernelGGL((k_tv_pass<H, false, TV2, false, false, false, kTvSmallQ>), g, b, 0, s, *a);
+      return;
+    }
+  }
   if (k.final_pass) {
     if (k.sparse && !k.bf16) launch_tv_kernel<H, true, TV2, false, false, true>(k.batch, g, a, map, s);
     else if (k.bf16) launch_tv_kernel<H, true, TV2, false, true, false>(k.batch, g, a, map, s);

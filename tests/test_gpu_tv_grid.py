@@ -59,7 +59,7 @@ def test_chunks_give_the_same_bits(torch_cuda, levels):
 
 def test_batch_of_small_frames(torch_cuda):
     """A frame of a batch gets its share of the device, so its chunks differ from
-    the single solve's: x has the same bits, the objective sums other partials."""
+    the single solve's: x and the objective have the same bits all the same."""
     torch = torch_cuda
     g = scenes.Geometry(nx=64, ny=64, nz=24, pixel_um=5.0, wavelength_um=0.532, z0_um=5000.0, dz_um=50.0)
     rng = np.random.default_rng(5)
@@ -82,4 +82,21 @@ def test_batch_of_small_frames(torch_cuda):
             p.close()
     for (x, r), xb, rb in zip(single, xs, reps):
         assert torch.equal(x, xb)
-        assert rb.objective == pytest.approx(r["objective"], rel=1e-9)
+        assert rb.objective == r["objective"]
+
+
+@pytest.mark.parametrize("dims", (2, 3))
+@pytest.mark.parametrize("shape", ((64, 64, 8), (128, 128, 32), (192, 192, 48), (96, 48, 1)))
+def test_low_tiles_give_the_same_bits(torch_cuda, shape, dims):
+    """Depth 3 takes low tiles on these volumes; depth 2 and 4 the full ones."""
+    torch = torch_cuda
+    plan = plan_of(*shape, dims)
+    v = torch.randn(plan.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(shape[2]))
+    try:
+        outs = []
+        for levels in (2, 3, 4):
+            plan.tuning = {**plan.tuning, "tv_levels": levels}
+            outs.append(plan.prox(v, 0.6, 0.05, 0.3, 7, nonneg=False))
+    finally:
+        plan.close()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
