@@ -1033,14 +1033,14 @@ struct IterArgs {
   ProxArgs prox;
 };
 
-// Objective partials of a solve's final TV pass, whose grid is cut to reach
-// `fill` blocks (may: low tiles are allowed).
+// Objective partials of a solve's final TV pass (fill: blocks of a round; may: low tiles are allowed).
 static int final_partials(const ri_plan* p, int fill, bool may) {
-  const int nx = p->g.nx, ny = p->g.ny, nz = p->g.nz;
+  const int nx = p->g.nx, ny = p->g.ny, nz = p->g.nz, tv2 = (p->g.flags & RI_TV2D) ? 1 : 0;
   const ri_tuning& t = p->tune;
-  const int low = !may || (p->g.flags & (RI_TV_DUAL_BF16 | RI_TV_FGP)) ? 0 : ((p->g.flags & RI_TV2D) ? 2 : 1);
-  return plane_group(p) ? tv_group_final_blocks(nx, ny, nz, p->dual_planes, t.tv_levels, t.tv_blocks, p->cus, fill, low)
-                        : tv_final_blocks(nx, ny, nz, t.tv_levels, t.tv_blocks, p->cus, fill, low);
+  const bool low = may && !(p->g.flags & (RI_TV_DUAL_BF16 | RI_TV_FGP));
+  return plane_group(p)
+             ? tv_group_final_blocks(nx, ny, nz, p->dual_planes, t.tv_levels, t.tv_blocks, p->cus, fill, tv2, low)
+             : tv_final_blocks(nx, ny, nz, t.tv_levels, t.tv_blocks, p->cus, fill, tv2, low);
 }
 
 static IterArgs iteration_args(const SolveCtx& c) {
@@ -2076,7 +2076,7 @@ extern "C" ri_status ri_plan_autotune(ri_plan* p, int32_t inner_iters, const cha
   for (int H = kTvLevelsMin; H <= kTvLevelsMax; ++H) {
     for (int b : kTvBlockCands) {
       const bool is_dflt = H == dflt.tv_levels && b == dflt.tv_blocks;
-      const std::pair<int, int> g{H, tv_pass_zchunk(nx, ny, nz, H, b, p->cus)};
+      const std::pair<int, int> g{H, tv_pass_zchunk(nx, ny, nz, H, b, p->cus, (p->g.flags & RI_TV2D) ? 1 : 0)};
       if (std::find(seen_tv.begin(), seen_tv.end(), g) != seen_tv.end() && !is_dflt) continue;
       seen_tv.push_back(g);
       ProxArgs a{};

@@ -339,7 +339,7 @@ struct ProxArgs {
   int tv2;               // per-plane 2D TV (pa[2], pb[2] unused)
   int cus;               // compute units of the device (shapes the final pass's grid; <= 0: uniform)
   int low;               // a launch of its own: the passes may take low tiles (depth 3, FP32 dual, no row store)
-  int fill;              // blocks that a pass's grid is cut to reach (cus; a frame of a batch: its share)
+  int fill;              // blocks of a round of the passes (cus; a frame of a batch: its share)
   int dual_bf16;         // dual buffers hold bfloat16
   int fgp;               // accelerated dual iteration (one step per pass; pa2 / pb2 hold p)
   RowStores rs;          // solver with rs.on: v from rs.v, x_{k+1} into store st->scur ^ 1
@@ -355,15 +355,17 @@ hipError_t launch_prox(const ProxArgs& a, hipStream_t s, int* launches);
 int prox_passes(int inner_iters, double tau, int levels, bool fgp);
 int prox_levels(int levels, bool fgp);
 // Planes per block of a pass for the given tuning (distinct values = distinct grids).
-int tv_pass_zchunk(int nx, int ny, int nz, int levels, int blocks, int fill);
-// Blocks of the final pass for the given tuning (low: 1 in 3D, 2 in 2D where
-// low tiles may be taken), and a bound over every tuning and pass.
-int tv_final_blocks(int nx, int ny, int nz, int levels, int blocks, int cus, int fill, int low);
+int tv_pass_zchunk(int nx, int ny, int nz, int levels, int blocks, int cus, int tv2);
+// Blocks of the final pass for the given tuning (low: where low tiles may be
+// taken), and a bound over every tuning and pass.
+int tv_final_blocks(int nx, int ny, int nz, int levels, int blocks, int cus, int fill, int tv2,
+                    bool low);
 int tv_blocks_bound(int nx, int ny, int nz, int cus);
 // Grouped per-plane prox: final-pass blocks of all groups of G planes (the
 // objective partials of group g start at the sum over the groups before it),
 // and a bound over every tuning.
-int tv_group_final_blocks(int nx, int ny, int nz, int G, int levels, int blocks, int cus, int fill, int low);
+int tv_group_final_blocks(int nx, int ny, int nz, int G, int levels, int blocks, int cus, int fill, int tv2,
+                    bool low);
 int tv_group_blocks_bound(int nx, int ny, int nz, int G, int cus);
 
 // Batched prox: the argument structs of every pass of every frame are built on

@@ -13,49 +13,66 @@ extern template void launch_tv_depth<2>(const TvSelect&, dim3, const TvPassArgs*
 extern template void launch_tv_depth<3>(const TvSelect&, dim3, const TvPassArgs*, const BatchMap&, hipStream_t);
 extern template void launch_tv_depth<4>(const TvSelect&, dim3, const TvPassArgs*, const BatchMap&, hipStream_t);
 
-// Blocks of one pass: x tiles, y tiles, z chunks.  The z-range is cut into
-// chunks of at least 16 planes until the grid holds about `want` blocks.  A
-// grid that this leaves below `fill` blocks (one per compute unit; for a frame
-// of a batch its share of them) is cut on, below 16 planes, until it gets
-// there: the chunks' margins are then redone by units that would idle, and a
-// block's march, which is the pass's time, gets shorter (depth 3: 128^2 x 32
-// from 24 blocks to 192, four passes 208 -> 118 us; 256^2 x 64 from 140 to 245,
-// seven passes 498 -> 378 us).
+// Blocks of one pass: x tiles, y tiles, z chunks.  A compute unit holds one
+// block, so a pass takes rounds of `fill` blocks (the units; for a frame of a
+// batch its share of them) times a block's march: its planes, the margins and
+// the pipeline's depth.  Of the cuts into chunks of 16 planes or more, up to
+// `want` blocks, and those that still fit one round, the one of least rounds
+// times march is taken; a single round counts 5/4 (its blocks run in step and
+// start cold).  Prox of 20 steps at depth 3, always cutting for `want` = 1536 and
+// so: 512^2 x 128 3D 2187 us (936 blocks, 4 rounds of 28 planes) and 2003 (234,
+// one of 76); 256^2 x 160 920 (350, 2 of 28) and 671 (245, one of 35); 1024^2 x 64
+// 4159 (1800) and 3477 (450); 512^2 x 128 in 2D stays at 936 blocks, 1242 us (one
+// round of 234: 1342).  128^2 x 32, 10 steps: 24 blocks of 16 planes 208 us, 192 of
+// 2 planes 118.  In a batch the frames fill the rounds together: no whole rounds,
+// but a march more for the tail.
 // `halo` is the tile halo of the pass (H on dual passes, H + 1 on the final).
+//
+// Low tiles, of 24 rows (two a lane instead of four), redo more halo but take
+// about 0.6 of the time for a plane.  They are taken where their blocks fit one
+// round and that outweighs the longer chunks.  Depth 3, 48 rows and 24: 64^2 x 8
+// (march 11 planes and 11) 55 -> 36 us, 128^2 x 32 (11, 13) 123 -> 90, 192^2 x 48
+// (13, 19) 142 -> 120, but 256^2 x 64 (19, 31) 370 -> 376; in 2D 128 x 96 x 8 (4, 4)
+// 27 -> 22, but 128^2 x 32 (5, 7) 42 -> 44: lines at 0.65 and 0.75 of the march.
 struct TvGrid {
   int gx, gy, zchunk, nfull, zchunk2, nblocks, low;
+  double cost;
+};
+// What shapes the grids of a prox's passes.
+struct TvCut {
+  int want, fill;
+  bool alone;   // not one of several frames in a launch
+  bool tv2;
+  bool low;     // low tiles may be taken
 };
 
-// `low` (1: 3D, 2: 2D TV): tiles of 24 rows (two a lane instead of four) may be
-// used.  They redo more halo but take about 0.6 of the time for a plane, so they
-// are taken where their blocks still fit one round of `fill` and that outweighs
-// the longer chunks.  Depth 3, 48 rows and 24: 64^2 x 8 (march 11 planes and 11)
-// 55 -> 36 us, 128^2 x 32 (11, 13) 123 -> 90, 192^2 x 48 (13, 19) 142 -> 120, but
-// 256^2 x 64 (19, 31) 370 -> 376; in 2D 128 x 96 x 8 (4, 4) 27 -> 22, but 128^2 x 32
-// (5, 7) 42 -> 44: lines at 0.65 and 0.75 of the march.
-static TvGrid grid_of(int nx, int ny, int nz, int halo, int rows, int want, int fill) {
+static TvGrid grid_of(int nx, int ny, int nz, int halo, int rows, const TvCut& c) {
   TvGrid g{};
   g.gx = (nx + (kTvRX - 2 * halo) - 1) / (kTvRX - 2 * halo);
   g.gy = (ny + (rows - 2 * halo) - 1) / (rows - 2 * halo);
-  const int tiles = g.gx * g.gy;
-  const int nzc = std::max(1, std::min(nz / 16, (want + tiles - 1) / tiles));
-  g.zchunk = (nz + nzc - 1) / nzc;
-  if (tiles * ((nz + g.zchunk - 1) / g.zchunk) < fill) {
-    const int most = std::max(1, std::min(nz, fill / tiles));
-    g.zchunk = std::min(g.zchunk, (nz + most - 1) / most);
+  const int tiles = g.gx * g.gy, fill = std::max(1, c.fill);
+  const int most = std::max(1, std::min(nz / 16, (c.want + tiles - 1) / tiles));
+  const int once = std::max(1, std::min(nz, fill / tiles));
+  g.cost = -1.0;
+  for (int n = 1; n <= std::max(most, once); ++n) {
+    const int zc = (nz + n - 1) / n, blocks = tiles * ((nz + zc - 1) / zc);
+    const int march = std::min(nz, zc + (c.tv2 ? 0 : 2 * halo)) + halo;
+    const int rounds = (blocks + fill - 1) / fill;
+    const double cost = !c.alone ? ((double)blocks / fill + 1.0) * march : rounds == 1 ? 1.25 * march : (double)rounds * march;
+    if (g.cost >= 0.0 && cost >= g.cost) continue;
+    g.cost = cost;
+    g.zchunk = zc;
+    g.nblocks = blocks;
   }
   g.nfull = tiles;
   g.zchunk2 = g.zchunk;
-  g.nblocks = tiles * ((nz + g.zchunk - 1) / g.zchunk);
   return g;
 }
-static TvGrid pass_grid(int nx, int ny, int nz, int halo, int want, int fill, int low) {
-  const TvGrid g = grid_of(nx, ny, nz, halo, kTvRY, want, fill);
-  if (!low || g.nblocks > fill) return g;
-  TvGrid h = grid_of(nx, ny, nz, halo, kTvWaves * kTvSmallQ, want, fill);
-  // planes a block marches over: its own and up to 3 halos of margin and pipeline
-  auto march = [&](const TvGrid& t) { return std::min(nz, t.zchunk + (low == 2 ? 0 : 2 * halo)) + halo; };
-  if (h.nblocks > fill || 100 * march(g) < (low == 2 ? 75 : 65) * march(h)) return g;
+static TvGrid pass_grid(int nx, int ny, int nz, int halo, const TvCut& c) {
+  const TvGrid g = grid_of(nx, ny, nz, halo, kTvRY, c);
+  if (!c.low) return g;
+  TvGrid h = grid_of(nx, ny, nz, halo, kTvWaves * kTvSmallQ, c);
+  if (g.nblocks > c.fill || h.nblocks > c.fill || 100 * g.cost < (c.tv2 ? 75 : 65) * h.cost) return g;
   h.low = 1;
   return h;
 }
@@ -65,8 +82,8 @@ static TvGrid pass_grid(int nx, int ny, int nz, int halo, int want, int fill, in
 // the dual passes; when they fill whole rounds but for a few (at 1024^2 one
 // tile beyond 512), the leftover tiles are cut into thin z chunks that run
 // side by side in one short extra round instead of a full one.
-static TvGrid final_grid(int nx, int ny, int nz, int H, int want, int cus, int fill, int low) {
-  TvGrid g = pass_grid(nx, ny, nz, H + 1, want, fill, low);
+static TvGrid final_grid(int nx, int ny, int nz, int H, int cus, const TvCut& c) {
+  TvGrid g = pass_grid(nx, ny, nz, H + 1, c);
   const int tiles = g.gx * g.gy;
   if (cus <= 0 || g.low || g.zchunk < nz || tiles <= cus) return g;
   const int r = tiles % cus;
@@ -92,9 +109,13 @@ int prox_levels(int levels, bool fgp) { return fgp ? 2 : clamp_levels(levels); }
 
 size_t tv_pass_args_size() { return sizeof(TvPassArgs); }
 
-int tv_final_blocks(int nx, int ny, int nz, int levels, int blocks, int cus, int fill, int low) {
-  return final_grid(nx, ny, nz, clamp_levels(levels), blocks > 0 ? blocks : kTvDefaultBlocks, cus, fill,
-                    clamp_levels(levels) == kTvDefaultLevels ? low : 0).nblocks;
+static TvCut cut_of(int blocks, int cus, int fill, int tv2, bool low) {
+  return TvCut{blocks > 0 ? blocks : kTvDefaultBlocks, fill, fill >= cus, tv2 != 0, low};
+}
+
+int tv_final_blocks(int nx, int ny, int nz, int levels, int blocks, int cus, int fill, int tv2, bool low) {
+  const int H = clamp_levels(levels);
+  return final_grid(nx, ny, nz, H, cus, cut_of(blocks, cus, fill, tv2, low && H == kTvDefaultLevels)).nblocks;
 }
 
 int tv_blocks_bound(int nx, int ny, int nz, int cus) {
@@ -107,9 +128,10 @@ int tv_blocks_bound(int nx, int ny, int nz, int cus) {
   return tx * ty * std::max(1, nz / 16) + std::max(cus, 0);
 }
 
-int tv_group_final_blocks(int nx, int ny, int nz, int G, int levels, int blocks, int cus, int fill, int low) {
+int tv_group_final_blocks(int nx, int ny, int nz, int G, int levels, int blocks, int cus, int fill, int tv2,
+                          bool low) {
   int total = 0;
-  for (int z0 = 0; z0 < nz; z0 += G) total += tv_final_blocks(nx, ny, std::min(G, nz - z0), levels, blocks, cus, fill, low);
+  for (int z0 = 0; z0 < nz; z0 += G) total += tv_final_blocks(nx, ny, std::min(G, nz - z0), levels, blocks, cus, fill, tv2, low);
   return total;
 }
 
@@ -118,8 +140,8 @@ int tv_group_blocks_bound(int nx, int ny, int nz, int G, int cus) {
   return groups * tv_blocks_bound(nx, ny, std::min(G, nz), cus);
 }
 
-int tv_pass_zchunk(int nx, int ny, int nz, int levels, int blocks, int fill) {
-  return pass_grid(nx, ny, nz, clamp_levels(levels), blocks > 0 ? blocks : kTvDefaultBlocks, fill, 0).zchunk;
+int tv_pass_zchunk(int nx, int ny, int nz, int levels, int blocks, int cus, int tv2) {
+  return pass_grid(nx, ny, nz, clamp_levels(levels), cut_of(blocks, cus, cus, tv2, false)).zchunk;
 }
 
 // Argument structs of every pass of one prox application.  Every pass takes
@@ -133,7 +155,8 @@ int prox_pass_args(const ProxArgs& pa, void* out, int* blocks_per_pass) {
   const bool fgp = pa.fgp != 0;
   const int H = prox_levels(pa.levels, fgp);
   const int npass = prox_passes(K, tau, H, fgp);
-  const int low = H == kTvDefaultLevels && pa.low && !fgp && !pa.dual_bf16 && !pa.rs.on ? (pa.tv2 ? 2 : 1) : 0;
+  const bool low = H == kTvDefaultLevels && pa.low && !fgp && !pa.dual_bf16 && !pa.rs.on;
+  const TvCut cut = cut_of(pa.blocks, pa.cus, pa.fill, pa.tv2, low);
   TvPassArgs a{};
   a.v = pa.v;
   a.x = pa.x;
@@ -151,14 +174,12 @@ int prox_pass_args(const ProxArgs& pa, void* out, int* blocks_per_pass) {
   a.rs = pa.rs;
   a.c = use_tv ? (float)(1.0 / ((pa.tv2 ? 8.0 : 12.0) * tau)) : 0.f;
   a.thr = (float)thr;
-  const int want = pa.blocks > 0 ? pa.blocks : kTvDefaultBlocks;
   TvPassArgs* o = static_cast<TvPassArgs*>(out);
   int done = 0;
   double tk = 1.0;   // FGP: t_k of the step a pass takes
   for (int p = 0; p < npass; ++p) {
     const bool fin = p == npass - 1;
-    const TvGrid g = fin ? final_grid(pa.nx, pa.ny, pa.nz, H, want, pa.cus, pa.fill, low)
-                         : pass_grid(pa.nx, pa.ny, pa.nz, H, want, pa.fill, low);
+    const TvGrid g = fin ? final_grid(pa.nx, pa.ny, pa.nz, H, pa.cus, cut) : pass_grid(pa.nx, pa.ny, pa.nz, H, cut);
     a.low = g.low;
     a.gx = g.gx;
     a.gy = g.gy;
