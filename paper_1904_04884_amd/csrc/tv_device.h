@@ -320,13 +320,17 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
       any += xq[q] + tq[q];
     }
     if (__ballot(any != 0.f) == 0) return;   // nothing but zeros in the wave's rows (most planes of a sparse volume)
-    double xs = x_sum, ts = tv_sum;
-    float xl = x_lo, tl = tv_lo;
+    // (a few FP32 terms add up exactly in FP64 unless they span 2^27)
+    double xp = 0.0, tp = 0.0;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      add_exact(xs, xl, (double)xq[q]);
-      add_exact(ts, tl, (double)tq[q]);
+      xp += (double)xq[q];
+      tp += (double)tq[q];
     }
+    double xs = x_sum, ts = tv_sum;
+    float xl = x_lo, tl = tv_lo;
+    add_exact(xs, xl, xp);
+    add_exact(ts, tl, tp);
     x_sum = xs;
     tv_sum = ts;
     x_lo = xl;
