@@ -334,7 +334,12 @@ __global__ void __launch_bounds__((gp_waves<T, NP>() * 64), 4) k_gp_pass(GpArgs<
   __shared__ T s_py[LV][2][NP][NW][64];   // bottom-row p_y of every wavefront, by step and parity
   __shared__ T s_ut[LV][2][NP][NW][64];   // top-row u
   if (done(a.st)) return;
-  const int tile = blockIdx.x % (a.gx * a.gy), zb = (int)(blockIdx.x / (a.gx * a.gy)) * a.zchunk;
+  // Where a plane's tiles alone occupy the units, neighbouring ones meet in one
+  // XCD's L2 (prox, 20 steps: 1024^2 x 256 complex 48.8 -> 41.5 ms, 512 x 384 x 48
+  // 1587 -> 1514 us, 1024^2 x 64 9.19 -> 9.39 ms); smaller planes, cut into many
+  // chunks, take the hardware's order (128^2 x 16: 104 us, 123 the other way).
+  const int t = (int)(a.gx * a.gy >= 256 ? xcd_tile(blockIdx.x, gridDim.x) : blockIdx.x);
+  const int tile = t % (a.gx * a.gy), zb = t / (a.gx * a.gy) * a.zchunk;
   const int bx = tile % a.gx, by = tile / a.gx;
   const int x0 = bx * (64 - 2 * LV) - LV, y0 = by * (RY - 2 * LV) - LV;
   const bool interior = x0 >= 1 && x0 + 64 <= a.nx - 1 && y0 >= 1 && y0 + RY <= a.ny - 1;
