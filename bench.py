@@ -51,14 +51,15 @@ def measured_traffic(tuning):
     or the plan runs the TV pass with another launch shape than the profiled run."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "k_tv_pass_c2_hbm_counters.md")
-    src = os.path.join(ROOT, "paper_1904_04884_amd", "csrc", "tv.hip")
+    csrc = os.path.join(ROOT, "paper_1904_04884_amd", "csrc")
     try:
         kv = {}
         for line in open(path):
             if " = " in line:
                 k, v = line.split(" = ", 1)
                 kv[k.strip()] = v.strip()
-        digest = hashlib.sha256(open(src, "rb").read()).hexdigest()
+        digest = hashlib.sha256(b"".join(open(os.path.join(csrc, f), "rb").read()
+                                         for f in ("tv_device.h", "tv.hip"))).hexdigest()   # kernels and grids
         if kv.get("tv_source_sha256") != digest:
             return None
         want = "%d,%d" % (tuning["tv_levels"], tuning["tv_blocks"])   # the TV pass's launch shape
@@ -525,11 +526,11 @@ def complex_leg(torch, rihvr, scenes, g, cfg, sc, iters=8):
         dt = time.perf_counter() - t0
         _, rt, _ = p.solve(b, cfg.l1, cfg.tv, iters, cfg.inner_iters, nonneg=False, flags=rihvr.RI_SOLVE_TIMING)
         ph_ms = {k: v / iters for k, v in rt["phase_ms"].items()}
-        step_launches = cfg.inner_iters // 2 + cfg.inner_iters % 2
+        step_launches = -(-cfg.inner_iters // 3)
         prox_bytes = (56.0 * step_launches + 40.0) * nvox
         out = {"iters": iters, "ms_per_iter": 1000.0 * dt / iters, "phase_ms_per_iter": ph_ms,
                "prox_GB_per_s": prox_bytes / (ph_ms["prox"] * 1e-3) / 1e9,
-               "prox_bytes_model": "56 B per complex voxel per launch of two dual steps + 40 B final",
+               "prox_bytes_model": "56 B per complex voxel per launch of up to three dual steps + 40 B final",
                "objective": rep["objective"]}
         log(f"complex object: {out['ms_per_iter']:.1f} ms per iteration (prox {ph_ms['prox']:.1f} ms, "
             f"{out['prox_GB_per_s']:.0f} GB/s by the two-steps-per-launch byte model)")
