@@ -212,7 +212,7 @@ __global__ void __launch_bounds__(256) k_gather_gemm(GatherGemmArgs a) {
 // that volume, first with one box per block, 64-bit addresses formed per load
 // and 2-byte stores (64 -> 32 and wider: gathered from global memory): 1 -> 16
 // channels 1.08 -> 0.45 ms, 16 -> 16 1.59 -> 0.59, 32 -> 16 3.81 -> 1.04,
-// 64 -> 32 (256 x 256 x 64) 2.32 -> 1.06, 128 -> 64 (128 x 128 x 32) 1.15 -> 0.90.
+// 64 -> 32 (256 x 256 x 64) 2.32 -> 0.83, 128 -> 64 (128 x 128 x 32) 1.15 -> 0.75.
 // ---------------------------------------------------------------------------
 constexpr int kHbX = 18, kHbY = 6;  // halo box extent in x and y
 
@@ -862,7 +862,12 @@ static int ew_grid(size_t n) {
 }
 
 // Blocks and z run of a 3x3x3 layer.  Big grids take boxes of RT planes and
-// march along z in runs that leave about 2048 blocks; grids of fewer boxes than
+// march along z in runs that leave about 2048 blocks.  Where the weights are
+// streamed (64 channels and more) the box is as high as LDS allows, as each
+// fragment then serves more rows: 64 -> 32 at 256 x 256 x 64 1.11 ms with 4 planes,
+// 0.83 with 8 (1.71 with 2); 64 -> 64 0.30 -> 0.19; 128 -> 64 at 128 x 128 x 32 0.97
+// with 2, 0.75 with 3.  Where they stay in registers (32 -> 16) 4 planes leave
+// three blocks a unit: 1.09 ms, 1.38 with 5, 1.49 with 8; grids of fewer boxes than
 // compute units (the coarse levels of a training crop) take one plane and 16
 // output channels per block, which spreads them over more of the chip.
 template <int C, int NT, int NH, int RT, bool IN32>
@@ -892,14 +897,14 @@ hipError_t launch_conv3(ConvArgs a, hipStream_t s) {
   const long boxes = (long)((a.W + 15) / 16) * ((a.H + 3) / 4) * ((a.D + rt - 1) / rt) * ((nt + 3) / 4);
   const bool small = boxes < 256;
   if (in32) {
-    if (small || nt == 1) return small ? launch_conv3_t<8, 1, 1, 1, true>(a, s) : launch_conv3_t<8, 1, 1, 4, true>(a, s);
+    if (small || nt == 1) return small ? launch_conv3_t<8, 1, 1, 1, true>(a, s) : launch_conv3_t<8, 1, 1, 8, true>(a, s);
     return nt == 2 ? launch_conv3_t<8, 2, 1, 4, true>(a, s) : launch_conv3_t<8, 2, 2, 4, true>(a, s);
   }
   switch (a.C) {
     case 8: return small || nt > 1 ? launch_conv3_t<8, 1, 1, 1, false>(a, s) : launch_conv3_t<8, 1, 1, 4, false>(a, s);
     case 16:
       if (!small && nt == 1) return launch_conv3_t<16, 1, 1, 4, false>(a, s);
-      if (!small && nt == 2) return launch_conv3_t<16, 2, 1, 4, false>(a, s);
+      if (!small && nt == 2) return launch_conv3_t<16, 2, 1, 8, false>(a, s);
       return launch_conv3_t<16, 1, 1, 1, false>(a, s);
     case 32:
       if (!small && nt == 1) return launch_conv3_t<32, 1, 1, 4, false>(a, s);
@@ -907,11 +912,11 @@ hipError_t launch_conv3(ConvArgs a, hipStream_t s) {
       if (!small && nt % 4 == 0) return launch_conv3_t<32, 2, 2, 4, false>(a, s);
       return launch_conv3_t<32, 1, 1, 1, false>(a, s);
     case 64:
-      if (!small && nt == 2) return launch_conv3_t<64, 2, 1, 4, false>(a, s);
-      if (!small && nt % 4 == 0) return launch_conv3_t<64, 2, 2, 4, false>(a, s);
+      if (!small && nt == 2) return launch_conv3_t<64, 2, 1, 8, false>(a, s);
+      if (!small && nt % 4 == 0) return launch_conv3_t<64, 2, 2, 8, false>(a, s);
       return launch_conv3_t<64, 1, 1, 1, false>(a, s);
     case 128:
-      if (!small && nt % 4 == 0) return launch_conv3_t<128, 2, 2, 2, false>(a, s);
+      if (!small && nt % 4 == 0) return launch_conv3_t<128, 2, 2, 3, false>(a, s);
       return launch_conv3_t<128, 1, 1, 1, false>(a, s);
     default: return hipErrorInvalidValue;
   }
