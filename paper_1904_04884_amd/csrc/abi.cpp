@@ -1033,16 +1033,6 @@ struct IterArgs {
   ProxArgs prox;
 };
 
-// Objective partials of a solve's final TV pass (fill: blocks of a round; may: low tiles are allowed).
-static int final_partials(const ri_plan* p, int fill, bool may) {
-  const int nx = p->g.nx, ny = p->g.ny, nz = p->g.nz, tv2 = (p->g.flags & RI_TV2D) ? 1 : 0;
-  const ri_tuning& t = p->tune;
-  const bool low = may && !(p->g.flags & (RI_TV_DUAL_BF16 | RI_TV_FGP));
-  return plane_group(p)
-             ? tv_group_final_blocks(nx, ny, nz, p->dual_planes, t.tv_levels, t.tv_blocks, p->cus, fill, tv2, low)
-             : tv_final_blocks(nx, ny, nz, t.tv_levels, t.tv_blocks, p->cus, fill, tv2, low);
-}
-
 static IterArgs iteration_args(const SolveCtx& c) {
   ri_plan* p = c.p;
   const Layout& L = c.L;
@@ -1109,7 +1099,6 @@ static IterArgs iteration_args(const SolveCtx& c) {
   sa.n_obj = L.n_obj;
   sa.qsum = at<double>(c.ws, L.qsum);
   sa.qtv = at<double>(c.ws, L.qtv);
-  sa.n_prox = final_partials(p, p->cus, !c.rs.on);
   sa.hist = at<double>(c.ws, L.hist);
   if (p->cplx) sa.qsum = sa.qtv = nullptr;   // the objective kernel runs every iteration
   sa.overflow = c.rs.on ? c.rs.overflow : nullptr;
@@ -1166,6 +1155,7 @@ static IterArgs iteration_args(const SolveCtx& c) {
   pa.blocks = p->tune.tv_blocks;
   pa.rs = c.rs;
   if (c.rs.on) pa.v = c.rs.v;   // v is the dense gradient-step output; x_{k+1} goes to a row store
+  sa.n_prox = prox_partials(pa);
   return I;
 }
 
@@ -1642,7 +1632,7 @@ extern "C" ri_status ri_solve_batched(int32_t n, ri_plan* const* plans, const ri
     it[i] = iteration_args(ctx[i]);
     it[i].prox.fill = std::max(1, plans[i]->cus / n);   // the frames fill the device together
     it[i].prox.low = 0;
-    it[i].scal.n_prox = final_partials(plans[i], it[i].prox.fill, false);
+    it[i].scal.n_prox = prox_partials(it[i].prox);
     const ri_plan* p = plans[i];
     const int ny = p->g.ny, nz = p->g.nz, m = p->m;
     dim3 g;

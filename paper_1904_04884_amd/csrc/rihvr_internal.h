@@ -356,16 +356,13 @@ int prox_passes(int inner_iters, double tau, int levels, bool fgp);
 int prox_levels(int levels, bool fgp);
 // Planes per block of a pass for the given tuning (distinct values = distinct grids).
 int tv_pass_zchunk(int nx, int ny, int nz, int levels, int blocks, int cus, int tv2);
-// Blocks of the final pass for the given tuning (low: where low tiles may be
-// taken), and a bound over every tuning and pass.
-int tv_final_blocks(int nx, int ny, int nz, int levels, int blocks, int cus, int fill, int tv2,
-                    bool low);
+// Objective partials that a prox writes: the blocks of its final pass, from the
+// same shape and grid as the launch (grouped per-plane prox: of all groups, whose
+// partials start at the sum over the groups before).
+int prox_partials(const ProxArgs& a);
+// Bounds on them, and on the blocks of any pass, over every tuning: a whole
+// volume, and groups of G planes.
 int tv_blocks_bound(int nx, int ny, int nz, int cus);
-// Grouped per-plane prox: final-pass blocks of all groups of G planes (the
-// objective partials of group g start at the sum over the groups before it),
-// and a bound over every tuning.
-int tv_group_final_blocks(int nx, int ny, int nz, int G, int levels, int blocks, int cus, int fill, int tv2,
-                    bool low);
 int tv_group_blocks_bound(int nx, int ny, int nz, int G, int cus);
 
 // Batched prox: the argument structs of every pass of every frame are built on

@@ -113,9 +113,32 @@ static TvCut cut_of(int blocks, int cus, int fill, int tv2, bool low) {
   return TvCut{blocks > 0 ? blocks : kTvDefaultBlocks, fill, fill >= cus, tv2 != 0, low};
 }
 
-int tv_final_blocks(int nx, int ny, int nz, int levels, int blocks, int cus, int fill, int tv2, bool low) {
-  const int H = clamp_levels(levels);
-  return final_grid(nx, ny, nz, H, cus, cut_of(blocks, cus, fill, tv2, low && H == kTvDefaultLevels)).nblocks;
+// Fusion depth, dual steps and cut of a prox's passes.
+struct TvProxShape {
+  int H, K;
+  TvCut cut;
+};
+static TvProxShape shape_of(const ProxArgs& a) {
+  const bool fgp = a.fgp != 0;
+  const int H = prox_levels(a.levels, fgp);
+  const bool low = H == kTvDefaultLevels && a.low && !fgp && !a.dual_bf16 && !a.rs.on;
+  return TvProxShape{H, a.step * a.tv > 0.0 && a.inner_iters > 0 ? a.inner_iters : 0,
+                     cut_of(a.blocks, a.cus, a.fill, a.tv2, low)};
+}
+static TvGrid final_grid_of(const ProxArgs& a, const TvProxShape& h) {
+  return final_grid(a.nx, a.ny, a.nz, h.H, a.cus, h.cut);
+}
+static bool grouped(const ProxArgs& a) { return a.tv2 && a.group_planes > 0 && a.group_planes < a.nz; }
+
+int prox_partials(const ProxArgs& pa) {
+  if (!grouped(pa)) return final_grid_of(pa, shape_of(pa)).nblocks;
+  ProxArgs q = pa;
+  int total = 0;
+  for (int z0 = 0; z0 < pa.nz; z0 += pa.group_planes) {
+    q.nz = std::min(pa.group_planes, pa.nz - z0);
+    total += final_grid_of(q, shape_of(q)).nblocks;
+  }
+  return total;
 }
 
 int tv_blocks_bound(int nx, int ny, int nz, int cus) {
@@ -126,13 +149,6 @@ int tv_blocks_bound(int nx, int ny, int nz, int cus) {
   const int tx = (nx + (kTvRX - 2 * h) - 1) / (kTvRX - 2 * h);
   const int ty = (ny + (kTvRY - 2 * h) - 1) / (kTvRY - 2 * h);
   return tx * ty * std::max(1, nz / 16) + std::max(cus, 0);
-}
-
-int tv_group_final_blocks(int nx, int ny, int nz, int G, int levels, int blocks, int cus, int fill, int tv2,
-                          bool low) {
-  int total = 0;
-  for (int z0 = 0; z0 < nz; z0 += G) total += tv_final_blocks(nx, ny, std::min(G, nz - z0), levels, blocks, cus, fill, tv2, low);
-  return total;
 }
 
 int tv_group_blocks_bound(int nx, int ny, int nz, int G, int cus) {
@@ -150,13 +166,10 @@ int tv_pass_zchunk(int nx, int ny, int nz, int levels, int blocks, int cus, int 
 int prox_pass_args(const ProxArgs& pa, void* out, int* blocks_per_pass) {
   const double tau = pa.step * pa.tv;
   const double thr = pa.step * pa.l1;
-  const bool use_tv = tau > 0.0 && pa.inner_iters > 0;
-  const int K = use_tv ? pa.inner_iters : 0;
-  const bool fgp = pa.fgp != 0;
-  const int H = prox_levels(pa.levels, fgp);
+  const TvProxShape shape = shape_of(pa);
+  const int H = shape.H, K = shape.K;
+  const bool use_tv = K > 0, fgp = pa.fgp != 0;
   const int npass = prox_passes(K, tau, H, fgp);
-  const bool low = H == kTvDefaultLevels && pa.low && !fgp && !pa.dual_bf16 && !pa.rs.on;
-  const TvCut cut = cut_of(pa.blocks, pa.cus, pa.fill, pa.tv2, low);
   TvPassArgs a{};
   a.v = pa.v;
   a.x = pa.x;
@@ -179,7 +192,7 @@ int prox_pass_args(const ProxArgs& pa, void* out, int* blocks_per_pass) {
   double tk = 1.0;   // FGP: t_k of the step a pass takes
   for (int p = 0; p < npass; ++p) {
     const bool fin = p == npass - 1;
-    const TvGrid g = fin ? final_grid(pa.nx, pa.ny, pa.nz, H, pa.cus, cut) : pass_grid(pa.nx, pa.ny, pa.nz, H, cut);
+    const TvGrid g = fin ? final_grid_of(pa, shape) : pass_grid(pa.nx, pa.ny, pa.nz, H, shape.cut);
     a.low = g.low;
     a.gx = g.gx;
     a.gy = g.gy;
@@ -230,7 +243,7 @@ static TvSelect select_of(const TvPassArgs& a) {
 // (the paper's plane-by-plane prox, with the memory of G planes instead of the
 // volume).  Each group's final pass writes its objective partials after the
 // previous groups' ones.
-static hipError_t launch_prox_grouped(const ProxArgs& pa, int K, int H, int np, hipStream_t s, int* launches) {
+static hipError_t launch_prox_grouped(const ProxArgs& pa, int H, int np, hipStream_t s, int* launches) {
   const int G = pa.group_planes;
   const size_t plane = (size_t)pa.nx * pa.ny;
   std::vector<TvPassArgs> args(np);
@@ -264,11 +277,10 @@ static hipError_t launch_prox_grouped(const ProxArgs& pa, int K, int H, int np, 
 }
 
 hipError_t launch_prox(const ProxArgs& pa, hipStream_t s, int* launches) {
-  const double tau = pa.step * pa.tv;
-  const int K = (tau > 0.0 && pa.inner_iters > 0) ? pa.inner_iters : 0;
-  const int H = prox_levels(pa.levels, pa.fgp != 0);
-  const int np = prox_passes(K, tau, H, pa.fgp != 0);
-  if (pa.tv2 && pa.group_planes > 0 && pa.group_planes < pa.nz) return launch_prox_grouped(pa, K, H, np, s, launches);
+  const TvProxShape shape = shape_of(pa);
+  const int H = shape.H;
+  const int np = prox_passes(shape.K, pa.step * pa.tv, H, pa.fgp != 0);
+  if (grouped(pa)) return launch_prox_grouped(pa, H, np, s, launches);
   std::vector<TvPassArgs> args(np);
   std::vector<int> nb(np);
   const int npass = prox_pass_args(pa, args.data(), nb.data());

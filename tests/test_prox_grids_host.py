@@ -1,0 +1,45 @@
+"""Objective partials of a solve: as many as the prox's final pass has blocks,
+for every size, depth, inner solver, dual storage, share of a batch and plane group (host code of the library, no GPU)."""
+import itertools
+import os
+import subprocess
+
+import pytest
+
+from paper_1904_04884_amd import build_lib, rihvr
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+TV2D, FGP, BF16, ROWS, LOW = 1, 2, 4, 8, 16
+
+
+@pytest.fixture(scope="module")
+def grids(tmp_path_factory):
+    if not rihvr.LIB_PATH.exists():
+        pytest.fail("librihvr.so is not built (run __graft_entry__.build())")
+    exe = tmp_path_factory.mktemp("grids") / "prox_grids"
+    lib = rihvr.LIB_PATH
+    obj = str(exe) + ".o"
+    hipcc = build_lib.hipcc()
+    subprocess.run([hipcc, "-x", "hip", "--cuda-host-only", "-std=c++17", f"--offload-arch={build_lib.ARCH}",
+                    "-I", str(build_lib.CSRC), "-c", os.path.join(HERE, "host_prox_grids.cpp"), "-o", obj], check=True)
+    subprocess.run([hipcc, obj, str(lib), f"-Wl,-rpath,{lib.parent}", "-o", str(exe)], check=True)
+
+    def run(rows):
+        text = "\n".join(" ".join(map(str, r)) for r in rows)
+        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout
+        return [tuple(map(int, line.split())) for line in out.splitlines()]
+    return run
+
+
+def test_partials_counted_are_those_written(grids):
+    xy = [(16, 16), (32, 48), (48, 32), (64, 64), (128, 128), (512, 64), (96, 512), (512, 512), (768, 384), (1024, 1024)]
+    kinds = [f | t for t in (0, TV2D) for f in (LOW, FGP | LOW, FGP | BF16, BF16, ROWS | LOW, LOW ^ LOW)]
+    rows = [(nx, ny, nz, lv, tb, fill, fl, 0)
+            for (nx, ny), nz, lv, (tb, fill), fl in itertools.product(
+                xy, (1, 4, 8, 17, 32, 128), (2, 3, 4), ((1536, 256), (64, 256), (6144, 85), (1536, 1)), kinds)]
+    rows += [(nx, ny, nz, lv, 1536, 256, TV2D | f, g)
+             for (nx, ny), (nz, g), lv, f in itertools.product(xy, ((17, 4), (32, 1), (8, 7)), (2, 3, 4), (LOW, BF16))]
+    out = grids(rows)
+    assert len(out) == len(rows)
+    for row, (counted, written, bound, _) in zip(rows, out):
+        assert counted == written <= bound, row
