@@ -180,7 +180,8 @@ typedef enum { RI_OP_FORWARD = 0, RI_OP_ADJOINT = 1, RI_OP_PROX = 2, RI_OP_SOLVE
  *               each pass recomputes a wider halo and uses more registers.
  *   tv_blocks   blocks per TV pass the z-range is cut for at most (64 ..
  *               65536; chunks keep at least 16 planes, fewer where the volume
- *               would otherwise fill only part of the device).
+ *               would otherwise fill only part of the device; per-plane passes
+ *               of a single step or none take up to twice as many).
  *   col_blocks  blocks of the per-plane column transforms of A and A^T the
  *               z-range is cut for (16 .. 8192).  More chunks mean more
  *               partial spectra: ri_workspace_size grows with it.

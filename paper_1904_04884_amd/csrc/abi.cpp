@@ -1451,6 +1451,7 @@ struct BatchLaunch {
   bool fgp = false;         // TV: accelerated-dual frames
   bool bf16 = false;        // TV: bfloat16-dual frames
   bool sparse = false;      // TV: frames with row-compressed iterates
+  bool partial = false;     // TV: passes of fewer steps than their depth
   std::vector<int> frames;
   size_t args_off = 0, offs_off = 0;
   size_t queue_off = 0;     // TV: claim counters of the persistent form
@@ -1470,6 +1471,11 @@ static size_t kind_args_size(int kind) {
     case BK_TV: return tv_pass_args_size();
   }
   return 0;
+}
+
+static TvPassShape prox_shape_of(const ri_plan* p, const ri_solve_params& sp, int pass) {
+  return prox_pass_shape(sp.inner_iters, (1.0 / p->lipschitz) * sp.tv, p->tune.tv_levels, (p->g.flags & RI_TV_FGP) != 0,
+                         pass);
 }
 
 static int prox_pass_count(const ri_plan* p, const ri_solve_params& sp) {
@@ -1513,7 +1519,7 @@ static std::vector<BatchLaunch> batch_launches(int n, ri_plan* const* plans, con
   for (int p = 0; p < maxpass; ++p) {
     for (int fin = 0; fin < 2; ++fin) {
       for (int t2 = 0; t2 < 2; ++t2) {
-        for (int fg = 0; fg < 8; ++fg) {   // bit 0: FGP, bit 1: bfloat16 dual, bit 2: row stores
+        for (int fg = 0; fg < 16; ++fg) {   // bit 0: FGP, bit 1: bfloat16 dual, bit 2: row stores, bit 3: partial pass
           for (int H = kTvLevelsMin; H <= kTvLevelsMax; ++H) {
             BatchLaunch b;
             b.kind = BK_TV;
@@ -1524,14 +1530,17 @@ static std::vector<BatchLaunch> batch_launches(int n, ri_plan* const* plans, con
             b.fgp = (fg & 1) != 0;
             b.bf16 = (fg & 2) != 0;
             b.sparse = (fg & 4) != 0;
+            b.partial = (fg & 8) != 0;
             for (int i = 0; i < n; ++i) {
               const int np = prox_pass_count(plans[i], params[i]);
               const bool f2 = (plans[i]->g.flags & RI_TV2D) != 0;
               const bool ff = (plans[i]->g.flags & RI_TV_FGP) != 0;
               const bool fb = (plans[i]->g.flags & RI_TV_DUAL_BF16) != 0;
               const bool fs = (p == np - 1) && plans[i]->store_frac > 0.0;   // only the final pass writes a store
-              if (prox_levels(plans[i]->tune.tv_levels, ff) == H && p < np && (p == np - 1) == (fin != 0) &&
-                  f2 == (t2 != 0) && ff == b.fgp && fb == b.bf16 && fs == b.sparse)
+              if (p >= np) continue;
+              const TvPassShape sh = prox_shape_of(plans[i], params[i], p);
+              if (sh.depth == H && sh.partial == b.partial && (p == np - 1) == (fin != 0) && f2 == (t2 != 0) &&
+                  ff == b.fgp && fb == b.bf16 && fs == b.sparse)
                 b.frames.push_back(i);
             }
             if (!b.frames.empty()) out.push_back(b);
@@ -1745,8 +1754,8 @@ extern "C" ri_status ri_solve_batched(int32_t n, ri_plan* const* plans, const ri
             cleared = true;
             if (e != hipSuccess) return e;
           }
-          e = launch_tv_pass_batched(bl.size, bl.final_pass, bl.tv2, bl.fgp, bl.bf16, bl.sparse, a, mp, bl.nblocks,
-                                     q);
+          e = launch_tv_pass_batched(bl.size, bl.partial, bl.final_pass, bl.tv2, bl.fgp, bl.bf16, bl.sparse, a, mp,
+                                     bl.nblocks, q);
           break;
       }
       if (e != hipSuccess) return e;

@@ -338,7 +338,8 @@ struct ProxArgs {
   int blocks;            // target blocks per pass (<= 0: the default)
   int tv2;               // per-plane 2D TV (pa[2], pb[2] unused)
   int cus;               // compute units of the device (shapes the final pass's grid; <= 0: uniform)
-  int low;               // a launch of its own: the passes may take low tiles (depth 3, FP32 dual, no row store)
+  int low;               // a launch of its own: the passes may take low tiles (depth 3, FP32 dual, no row
+                         // store) and the sequential form for being short of planes
   int fill;              // blocks of a round of the passes (cus; a frame of a batch: its share)
   int dual_bf16;         // dual buffers hold bfloat16
   int fgp;               // accelerated dual iteration (one step per pass; pa2 / pb2 hold p)
@@ -354,6 +355,13 @@ constexpr int kTvDefaultBlocks = 1536;
 hipError_t launch_prox(const ProxArgs& a, hipStream_t s, int* launches);
 int prox_passes(int inner_iters, double tau, int levels, bool fgp);
 int prox_levels(int levels, bool fgp);
+// Depth and steps of pass `pass` where its tiles are full ones (as in a batch); partial:
+// fewer steps than the depth.
+struct TvPassShape {
+  int depth, steps;
+  bool partial;
+};
+TvPassShape prox_pass_shape(int inner_iters, double tau, int levels, bool fgp, int pass);
 // Planes per block of a pass for the given tuning (distinct values = distinct grids).
 int tv_pass_zchunk(int nx, int ny, int nz, int levels, int blocks, int cus, int tv2);
 // Objective partials that a prox writes: the blocks of its final pass, from the
@@ -373,7 +381,7 @@ size_t tv_pass_args_size();
 // for one frame and returns the number of passes; blocks_per_pass (nullable,
 // npass entries) receives the frame's blocks of each pass.
 int prox_pass_args(const ProxArgs& a, void* out, int* blocks_per_pass);
-hipError_t launch_tv_pass_batched(int levels, bool final_pass, bool tv2, bool fgp, bool bf16, bool sparse,
+hipError_t launch_tv_pass_batched(int levels, bool seq, bool final_pass, bool tv2, bool fgp, bool bf16, bool sparse,
                                   const void* args, BatchMap map, int nblocks, hipStream_t s);
 
 // Complex-valued object (cplx.hip): volumes [2][nz/2][ny][nx] (real parts, then

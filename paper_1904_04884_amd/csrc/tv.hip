@@ -34,6 +34,15 @@ extern template void launch_tv_depth<4>(const TvSelect&, dim3, const TvPassArgs*
 // (march 11 planes and 11) 55 -> 36 us, 128^2 x 32 (11, 13) 123 -> 90, 192^2 x 48
 // (13, 19) 142 -> 120, but 256^2 x 64 (19, 31) 370 -> 376; in 2D 128 x 96 x 8 (4, 4)
 // 27 -> 22, but 128^2 x 32 (5, 7) 42 -> 44: lines at 0.65 and 0.75 of the march.
+//
+// Partial passes (fewer steps than the depth: the final pass of one step or none, every
+// pass of the accelerated dual) wait for their loads, not for their steps.  In 3D they
+// take the cut of least rounds times march with the margins of their own steps, a
+// single round at its face value, a sixteenth of the units kept free (a nearly full
+// round spills into another), and whole tiles where the leftovers of a round are split.
+// In 2D, with no margin to redo, chunks of 16 planes or less.  One step, z cuts 1, 2, 4,
+// 8: 512^2 x 128 3D 210, 114, 124, 135 us; 768^2 x 50 97, 129, 138, 170; 1024^2 x 64 233,
+// 234, 265, 307; in 2D 214, 190, 181, 193.
 struct TvGrid {
   int gx, gy, zchunk, nfull, zchunk2, nblocks, low;
   double cost;
@@ -44,7 +53,16 @@ struct TvCut {
   bool alone;   // not one of several frames in a launch
   bool tv2;
   bool low;     // low tiles may be taken
+  int partial;  // steps of a pass that takes fewer than its depth, else -1
+  bool last;    // the final pass
 };
+
+// Thin z chunks that final_grid cuts its leftover tiles into (0: it leaves them whole).
+static int leftover_chunks(int tiles, int nz, int cus) {
+  if (cus <= 0 || tiles <= cus || tiles % cus == 0) return 0;
+  const int k = std::min(nz, cus / (tiles % cus));
+  return k < 2 ? 0 : k;
+}
 
 static TvGrid grid_of(int nx, int ny, int nz, int halo, int rows, const TvCut& c) {
   TvGrid g{};
@@ -54,11 +72,26 @@ static TvGrid grid_of(int nx, int ny, int nz, int halo, int rows, const TvCut& c
   const int most = std::max(1, std::min(nz / 16, (c.want + tiles - 1) / tiles));
   const int once = std::max(1, std::min(nz, fill / tiles));
   g.cost = -1.0;
-  for (int n = 1; n <= std::max(most, once); ++n) {
+  const bool part = c.alone && c.partial >= 0;
+  int n0 = 1, n1 = std::max(most, once), units = fill;
+  int extra = c.tv2 ? 0 : 2 * halo, tail = halo;
+  if (part) {
+    extra = c.tv2 ? 0 : 2 * (c.partial + 1);
+    tail = c.partial + 2;
+    if (!c.tv2) {
+      units -= fill / 16;
+    } else if (tiles * most > fill) {
+      n0 = most;
+      n1 = std::min(nz, 2 * most);
+    }
+  }
+  for (int n = n0; n <= n1; ++n) {
     const int zc = (nz + n - 1) / n, blocks = tiles * ((nz + zc - 1) / zc);
-    const int march = std::min(nz, zc + (c.tv2 ? 0 : 2 * halo)) + halo;
-    const int rounds = (blocks + fill - 1) / fill;
-    const double cost = !c.alone ? ((double)blocks / fill + 1.0) * march : rounds == 1 ? 1.25 * march : (double)rounds * march;
+    const int march = std::min(nz, zc + extra) + tail;
+    const int rounds = (blocks + units - 1) / units;
+    double cost = !c.alone ? ((double)blocks / fill + 1.0) * march : (rounds == 1 && !part ? 1.25 : rounds) * (double)march;
+    if (const int k = part && n == 1 && c.last ? leftover_chunks(tiles, nz, fill) : 0)
+      cost = (double)(tiles / fill) * march + (nz + k - 1) / k + extra + tail;
     if (g.cost >= 0.0 && cost >= g.cost) continue;
     g.cost = cost;
     g.zchunk = zc;
@@ -85,10 +118,9 @@ static TvGrid pass_grid(int nx, int ny, int nz, int halo, const TvCut& c) {
 static TvGrid final_grid(int nx, int ny, int nz, int H, int cus, const TvCut& c) {
   TvGrid g = pass_grid(nx, ny, nz, H + 1, c);
   const int tiles = g.gx * g.gy;
-  if (cus <= 0 || g.low || g.zchunk < nz || tiles <= cus) return g;
+  const int k = g.low || g.zchunk < nz ? 0 : leftover_chunks(tiles, nz, cus);
+  if (k == 0) return g;
   const int r = tiles % cus;
-  const int k = r > 0 ? std::min(nz, cus / r) : 1;
-  if (k < 2) return g;
   g.nfull = tiles - r;
   g.zchunk2 = (nz + k - 1) / k;
   g.nblocks = g.nfull + r * ((nz + g.zchunk2 - 1) / g.zchunk2);
@@ -110,23 +142,49 @@ int prox_levels(int levels, bool fgp) { return fgp ? 2 : clamp_levels(levels); }
 size_t tv_pass_args_size() { return sizeof(TvPassArgs); }
 
 static TvCut cut_of(int blocks, int cus, int fill, int tv2, bool low) {
-  return TvCut{blocks > 0 ? blocks : kTvDefaultBlocks, fill, fill >= cus, tv2 != 0, low};
+  return TvCut{blocks > 0 ? blocks : kTvDefaultBlocks, fill, fill >= cus, tv2 != 0, low, -1, false};
 }
 
-// Fusion depth, dual steps and cut of a prox's passes.
+// A pass on full tiles: H steps at depth H, and for the final pass the steps that are
+// left at a depth of as many (2 at least).
+TvPassShape prox_pass_shape(int inner_iters, double tau, int levels, bool fgp, int pass) {
+  const int H = prox_levels(levels, fgp), np = prox_passes(inner_iters, tau, levels, fgp);
+  const int K = tau > 0.0 ? std::max(inner_iters, 0) : 0;
+  TvPassShape p{};
+  p.steps = fgp ? std::min(1, K) : std::min(H, K - pass * H);
+  p.depth = pass == np - 1 && !fgp ? std::max(kTvLevelsMin, p.steps) : H;
+  p.partial = p.steps < p.depth;
+  return p;
+}
+
+// Fusion depth, dual steps, passes and cut of a prox.
 struct TvProxShape {
-  int H, K;
+  int H, K, npass;
   TvCut cut;
 };
 static TvProxShape shape_of(const ProxArgs& a) {
   const bool fgp = a.fgp != 0;
   const int H = prox_levels(a.levels, fgp);
   const bool low = H == kTvDefaultLevels && a.low && !fgp && !a.dual_bf16 && !a.rs.on;
-  return TvProxShape{H, a.step * a.tv > 0.0 && a.inner_iters > 0 ? a.inner_iters : 0,
-                     cut_of(a.blocks, a.cus, a.fill, a.tv2, low)};
+  const double tau = a.step * a.tv;
+  const int np = prox_passes(a.inner_iters, tau, a.levels, fgp);
+  TvProxShape p{H, tau > 0.0 && a.inner_iters > 0 ? a.inner_iters : 0, np, cut_of(a.blocks, a.cus, a.fill, a.tv2, low)};
+  if (fgp) p.cut.partial = 1;
+  return p;
 }
-static TvGrid final_grid_of(const ProxArgs& a, const TvProxShape& h) {
-  return final_grid(a.nx, a.ny, a.nz, h.H, a.cus, h.cut);
+static TvGrid final_grid_of(const ProxArgs& a, const TvProxShape& h, int* depth = nullptr) {
+  if (depth) *depth = h.H;
+  TvCut cut = h.cut;
+  cut.last = true;
+  if (cut.low) {   // (low tiles exist at the default depth only, and are kept there)
+    const TvGrid g = final_grid(a.nx, a.ny, a.nz, h.H, a.cus, cut);
+    if (g.low) return g;
+    cut.low = false;
+  }
+  const TvPassShape p = prox_pass_shape(a.inner_iters, a.step * a.tv, a.levels, a.fgp != 0, h.npass - 1);
+  cut.partial = p.partial ? p.steps : -1;
+  if (depth) *depth = p.depth;
+  return final_grid(a.nx, a.ny, a.nz, p.depth, a.cus, cut);
 }
 static bool grouped(const ProxArgs& a) { return a.tv2 && a.group_planes > 0 && a.group_planes < a.nz; }
 
@@ -143,12 +201,12 @@ int prox_partials(const ProxArgs& pa) {
 
 int tv_blocks_bound(int nx, int ny, int nz, int cus) {
   // the most tiles (the final pass's halo at the deepest fusion) times the
-  // most z chunks pass_grid makes, or the split of final_grid (at most one
+  // most z chunks pass_grid makes (twice nz / 16 on partial passes), or the split of final_grid (at most one
   // thin chunk per compute unit beyond the tiles), or a grid cut to fill the device
   const int h = kTvLevelsMax + 1;
   const int tx = (nx + (kTvRX - 2 * h) - 1) / (kTvRX - 2 * h);
   const int ty = (ny + (kTvRY - 2 * h) - 1) / (kTvRY - 2 * h);
-  return tx * ty * std::max(1, nz / 16) + std::max(cus, 0);
+  return tx * ty * std::max(1, 2 * (nz / 16)) + std::max(cus, 0);
 }
 
 int tv_group_blocks_bound(int nx, int ny, int nz, int G, int cus) {
@@ -160,6 +218,17 @@ int tv_pass_zchunk(int nx, int ny, int nz, int levels, int blocks, int cus, int 
   return pass_grid(nx, ny, nz, clamp_levels(levels), cut_of(blocks, cus, cus, tv2, false)).zchunk;
 }
 
+// Whether a pass takes the sequential form (TvForm): where its steps do not fill the
+// pipeline of its kernel's depth, or its blocks are short of planes.  12 steps in 3D,
+// pipeline and sequential: 128^2 x 6 (6 planes) depth 3 59 and 54 us, 64^2 x 8 69 and
+// 66, but 128^2 x 32 (13 planes) 97 and 100, 192^2 x 48 127 and 140; at depth 4, whose
+// phases idle longer, 128^2 x 32 159 and 150, 192^2 x 48 (18 planes) 184 and 178.
+static bool pass_is_seq(const ProxArgs& a, bool fin, int depth, int steps, int zchunk) {
+  if (!tv_has_seq(depth, fin)) return false;
+  if (steps < depth) return true;
+  return a.low && std::min(a.nz, zchunk + (a.tv2 ? 0 : 2 * (steps + 1))) <= (depth > 3 ? 24 : 10);
+}
+
 // Argument structs of every pass of one prox application.  Every pass takes
 // up to H dual steps; the final pass (its own tile grid, halo H + 1) also
 // recovers the primal, thresholds and stores x.
@@ -169,7 +238,7 @@ int prox_pass_args(const ProxArgs& pa, void* out, int* blocks_per_pass) {
   const TvProxShape shape = shape_of(pa);
   const int H = shape.H, K = shape.K;
   const bool use_tv = K > 0, fgp = pa.fgp != 0;
-  const int npass = prox_passes(K, tau, H, fgp);
+  const int npass = shape.npass;
   TvPassArgs a{};
   a.v = pa.v;
   a.x = pa.x;
@@ -192,7 +261,8 @@ int prox_pass_args(const ProxArgs& pa, void* out, int* blocks_per_pass) {
   double tk = 1.0;   // FGP: t_k of the step a pass takes
   for (int p = 0; p < npass; ++p) {
     const bool fin = p == npass - 1;
-    const TvGrid g = fin ? final_grid_of(pa, shape) : pass_grid(pa.nx, pa.ny, pa.nz, H, shape.cut);
+    a.depth = H;
+    const TvGrid g = fin ? final_grid_of(pa, shape, &a.depth) : pass_grid(pa.nx, pa.ny, pa.nz, H, shape.cut);
     a.low = g.low;
     a.gx = g.gx;
     a.gy = g.gy;
@@ -202,6 +272,7 @@ int prox_pass_args(const ProxArgs& pa, void* out, int* blocks_per_pass) {
     a.nblocks = g.nblocks;
     if (blocks_per_pass) blocks_per_pass[p] = g.nblocks;
     const int lv = fgp ? std::min(1, K - done) : std::min(H, K - done);
+    a.seq = pass_is_seq(pa, fin, a.depth, lv, g.zchunk) ? 1 : 0;
     a.levels = lv;
     a.first = (done == 0 && !pa.warm) ? 1 : 0;   // a warm dual is read by the first pass
     a.final_ = fin ? 1 : 0;
@@ -235,7 +306,8 @@ static void launch_any(const TvSelect& k, int H, dim3 g, const TvPassArgs* a, co
   else launch_tv_depth<4>(k, g, a, map, s);
 }
 static TvSelect select_of(const TvPassArgs& a) {
-  return TvSelect{false, a.final_ != 0, a.tv2 != 0, a.fgp != 0, a.dual_bf16 != 0, a.rs.on != 0, a.low != 0};
+  return TvSelect{false, a.final_ != 0, a.tv2 != 0, a.fgp != 0, a.dual_bf16 != 0, a.rs.on != 0, a.low != 0,
+                  a.seq != 0};
 }
 
 // The per-plane 2D TV couples no planes, so its prox can run on groups of G
@@ -243,7 +315,7 @@ static TvSelect select_of(const TvPassArgs& a) {
 // (the paper's plane-by-plane prox, with the memory of G planes instead of the
 // volume).  Each group's final pass writes its objective partials after the
 // previous groups' ones.
-static hipError_t launch_prox_grouped(const ProxArgs& pa, int H, int np, hipStream_t s, int* launches) {
+static hipError_t launch_prox_grouped(const ProxArgs& pa, int np, hipStream_t s, int* launches) {
   const int G = pa.group_planes;
   const size_t plane = (size_t)pa.nx * pa.ny;
   std::vector<TvPassArgs> args(np);
@@ -262,7 +334,7 @@ static hipError_t launch_prox_grouped(const ProxArgs& pa, int H, int np, hipStre
     for (int p = 0; p < npass; ++p) {
       args[p].zoff_v = (size_t)z0 * plane;
       args[p].zoff_x = pa.stage_group ? 0 : (size_t)z0 * plane;
-      launch_any(select_of(args[p]), H, dim3(nb[p]), &args[p], BatchMap{nullptr, 0}, s);
+      launch_any(select_of(args[p]), args[p].depth, dim3(nb[p]), &args[p], BatchMap{nullptr, 0}, s);
     }
     nl += npass;
     if (pa.stage_group) {
@@ -277,23 +349,21 @@ static hipError_t launch_prox_grouped(const ProxArgs& pa, int H, int np, hipStre
 }
 
 hipError_t launch_prox(const ProxArgs& pa, hipStream_t s, int* launches) {
-  const TvProxShape shape = shape_of(pa);
-  const int H = shape.H;
-  const int np = prox_passes(shape.K, pa.step * pa.tv, H, pa.fgp != 0);
-  if (grouped(pa)) return launch_prox_grouped(pa, H, np, s, launches);
+  const int np = shape_of(pa).npass;
+  if (grouped(pa)) return launch_prox_grouped(pa, np, s, launches);
   std::vector<TvPassArgs> args(np);
   std::vector<int> nb(np);
   const int npass = prox_pass_args(pa, args.data(), nb.data());
   for (int p = 0; p < npass; ++p)
-    launch_any(select_of(args[p]), H, dim3(nb[p]), &args[p], BatchMap{nullptr, 0}, s);
+    launch_any(select_of(args[p]), args[p].depth, dim3(nb[p]), &args[p], BatchMap{nullptr, 0}, s);
   if (launches) *launches = npass;
   return hipGetLastError();
 }
 
-hipError_t launch_tv_pass_batched(int levels, bool final_pass, bool tv2, bool fgp, bool bf16, bool sparse,
+hipError_t launch_tv_pass_batched(int levels, bool seq, bool final_pass, bool tv2, bool fgp, bool bf16, bool sparse,
                                   const void* args, BatchMap map, int nblocks, hipStream_t s) {
-  launch_any(TvSelect{true, final_pass, tv2, fgp && !final_pass, bf16, sparse}, clamp_levels(levels), dim3(nblocks),
-             static_cast<const TvPassArgs*>(args), map, s);
+  launch_any(TvSelect{true, final_pass, tv2, fgp && !final_pass, bf16, sparse, false, seq}, clamp_levels(levels),
+             dim3(nblocks), static_cast<const TvPassArgs*>(args), map, s);
   return hipGetLastError();
 }
 

@@ -104,6 +104,8 @@ struct TvPassArgs {
   float tau, c, thr;
   int gx, gy;                     // tiles along x and y (the grid of one frame)
   int low;                        // tiles of kTvSmallQ rows a lane
+  int depth;                      // fusion depth of the kernel that runs the pass
+  int seq;                        // ... and its form (TvForm)
   size_t zoff_v, zoff_x;          // grouped per-plane prox: first plane of the group in v and x (elements)
 };
 
@@ -194,10 +196,18 @@ __host__ __device__ constexpr int tv_delay(int L) { return L + (L > 2 ? 1 : 0); 
 // LDS and the partial steps have one code path.  Depth 3 has the registers, and
 // there each of these costs (512^2 x 128, 20 steps: 2183 us without, 2270 with).
 __host__ __device__ constexpr bool tv_lean(int LV) { return LV > 3; }
-// Slots of s_py per step.  From depth 3 on an iteration has two barriers, so a
-// row is read long before it is replaced and one slot would do, which depth 4
-// takes (the sums' room); with one barrier the slots alternate.
-__host__ __device__ constexpr int tv_py_slots(int LV) { return tv_lean(LV) ? 1 : 2; }
+// Form of a pass: the pipeline above, or (SEQ) step l at plane a1 - l, every step
+// behind a barrier of its own, planes prefetched two ahead, FIRST known when
+// compiled.  A pass of one step or none, or over few planes, does not fill the
+// pipeline: its planes take less than their loads, and idle phases and the plane that
+// steps 2 and 3 wait are what it pays.  Prox of one step at 512^2 x 128 in 3D 214 ->
+// 112 us (with the z cut of such passes), none 135 -> 60; plane groups of one plane at
+// 768^2 x 50, 10 steps, 2.58 -> 1.95 ms; 64^2 x 8 in 2D, 10 steps, 24 -> 19 us.
+enum TvForm { TV_PIPE, TV_SEQ, TV_SEQ_FIRST };
+// Slots of s_py per step.  From depth 3 on an iteration of the pipeline has two
+// barriers, so a row is read long before it is replaced and one slot would do, which
+// depth 4 takes (the sums' room); with one barrier the slots alternate.
+__host__ __device__ constexpr int tv_py_slots(int LV, TvForm F) { return F == TV_PIPE && tv_lean(LV) ? 1 : 2; }
 // Slots of the v ring: back to the last step's plane, on the final pass to the
 // output plane.
 template <int LV, bool FINAL>
@@ -207,14 +217,15 @@ __host__ __device__ constexpr int tv_ring() { return FINAL ? tv_delay(LV) + 1 : 
 // (about 2^20 * 128 clocks; the publisher needs a few hundred).
 constexpr int kStoreSpinLimit = 1 << 20;
 
-template <int H, int LV, int Q, bool EDGE, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
+template <int H, int LV, int Q, TvForm F, bool EDGE, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
 __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by, int zb, int ze, int blk,
-                                             float (*s_py)[tv_py_slots(LV)][kTvWaves][64], float (*s_ut)[2][kTvWaves][64],
+                                             float (*s_py)[tv_py_slots(LV, F)][kTvWaves][64], float (*s_ut)[2][kTvWaves][64],
                                              TvVec<Q>* s_v, float (*s_x)[kTvWaves][64], double (*s_red)[kTvWaves],
                                              float* s_fin, double* s_sum) {
   constexpr int NW = kTvWaves, NT = NW * 64, RY = NW * Q;
   constexpr int IX = kTvRX - 2 * H, IY = RY - 2 * H;  // interior (stored) extent
-  constexpr int PYM = tv_py_slots(LV) - 1;
+  constexpr int PYM = tv_py_slots(LV, F) - 1;
+  constexpr bool SEQ = F != TV_PIPE, FIRST = F == TV_SEQ_FIRST;
   constexpr bool LEAN = tv_lean(LV);
   const float* __restrict__ v =
       uniform_ptr((A.v ? A.v : pick3(A.vol[0], A.vol[1], A.vol[2], A.st->prev)) + A.zoff_v);
@@ -343,8 +354,8 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
     tv_lo = tl;
   };
 
-  // Input planes are prefetched one ahead (a plane takes about 4 us).  v of
-  // recent planes lives in a thread-private LDS ring (slot = plane mod NS).
+  // Input planes are prefetched one ahead (a plane of the pipeline takes about 4 us),
+  // or two (SEQ).  v of recent planes lives in a thread-private LDS ring (slot = plane mod NS).
   struct InPlane {
     float v[Q];
     float p[Q][3];
@@ -357,6 +368,7 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
     const __amdgpu_buffer_rsrc_t rv = plane_rsrc(v, a, sz);
 #pragma unroll
     for (int q = 0; q < Q; ++q) P.v[q] = buf_ld(rv, off[q]);
+    if constexpr (FIRST) return;
     const __amdgpu_buffer_rsrc_t r0 = dual_rsrc(pin[0], a, sz, bf, first);
     const __amdgpu_buffer_rsrc_t r1 = dual_rsrc(pin[1], a, sz, bf, first);
 #pragma unroll
@@ -562,8 +574,10 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
     } else {
       if (A.keep_dual) store_dual(m, c3, zstore);
       const TvVec<Q> vm = vring(m);  // thread-private: read before the barrier
-      s_py[LV][par & PYM][wv][lane] = c3[Q - 1][1];
-      __syncthreads();
+      // no step, dual zero: nothing to exchange but the objective's rows
+      const bool still = FIRST && L == 0;
+      if (!still) s_py[LV][par & PYM][wv][lane] = c3[Q - 1][1];
+      if (!still || obj) __syncthreads();
       const __amdgpu_buffer_rsrc_t rx = dual_rsrc(xo, m, sz, false, !zstore);
       float xs[Q];
       unsigned nzm = 0;   // row-compressed store: segments holding a non-zero
@@ -572,7 +586,7 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
         float u = vm[q];
         if (tau != 0.f) {
           const float pxm = dpp_from_left(c3[q][0]);
-          const float pym = (q > 0) ? c3[q - 1][1] : s_py[LV][par & PYM][wv > 0 ? wv - 1 : 0][lane];
+          const float pym = (q > 0) ? c3[q - 1][1] : (still ? 0.f : s_py[LV][par & PYM][wv > 0 ? wv - 1 : 0][lane]);
           float d = (xhi ? c3[q][0] : 0.f) - (xlo ? pxm : 0.f);
           d += (yhi[q] ? c3[q][1] : 0.f) - (ylo[q] ? pym : 0.f);
           if constexpr (!TV2) d += c3[q][2] - PzF(q);
@@ -613,126 +627,192 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
     }
   };
 
-  // One plane of the pipeline: plane a1 = zs + s arrives (none past zl).  Steps 0
-  // and 2 run side by side between two barriers, then steps 1 and 3: step 2
-  // takes what step 1 left in the iteration before (its dual waits in D), so
-  // it sits one plane further back, step l at plane a1 - l - (l > 1).  Two
-  // independent steps per barrier fill the latencies of each other's exchange.
-  // A step is idle before its first plane, at plane zl it flushes, then idles
-  // again.  EACH = false: the steady part, where all LV steps are arrivals.
-  float C[Q][3], D[Q][3];   // duals after steps 0 / 1 and after steps 1 / 2 / 3
+  float C[Q][3];
 #pragma unroll
   for (int q = 0; q < Q; ++q)
 #pragma unroll
-    for (int k = 0; k < 3; ++k) C[q][k] = D[q][k] = 0.f;
-  const int delay = tv_delay(L);   // the output plane is a1 - delay
+    for (int k = 0; k < 3; ++k) C[q][k] = 0.f;
+  const int delay = SEQ ? L : tv_delay(L);   // the output plane is a1 - delay
+  const int nsteps = zl - zs + delay;        // the last output leaves at s = nsteps - 1
   InPlane P;
-  auto iterate = [&](auto each, int s) __attribute__((always_inline)) {
-    constexpr bool EACH = decltype(each)::value;
-    const int par = s & 1;
-    const int a1 = zs + s;
-    float ppa[Q][3];   // FGP: p_prev of plane a1 (one step: output of a1 comes at the next arrival)
-    if (!EACH || a1 < zl) {
+  if constexpr (SEQ) {
+    auto arrive = [&](int l, int a, int par) __attribute__((always_inline)) {
+      float un[Q];
+      arrive_pre(l, a, par, C, un);
+      __syncthreads();
+      arrive_post(l, a == zs, par, C, un);
+    };
+    auto step = [&](InPlane& P, int s) __attribute__((always_inline)) {
+      const int par = s & 1, a1 = zs + s;
+      float ppa[Q][3];   // FGP: p_prev of plane a1 (one step: output of a1 comes at the next arrival)
       TvVec<Q> vq;
 #pragma unroll
       for (int q = 0; q < Q; ++q) vq[q] = vcopy(P.v[q]);
       vring(a1) = vq;
 #pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        C[q][0] = dual_val(P.p[q][0], bf);
-        C[q][1] = dual_val(P.p[q][1], bf);
-        C[q][2] = TV2 ? 0.f : dual_val(P.p[q][2], bf);
-        if constexpr (FGP) {
-#pragma unroll
-          for (int k = 0; k < 3; ++k) ppa[q][k] = dual_val(P.pp[q][k], bf);
-        }
-      }
-      if (a1 + 1 < zl) load_plane(P, a1 + 1);
-    } else if constexpr (FGP) {
-#pragma unroll
-      for (int q = 0; q < Q; ++q) ppa[q][0] = ppa[q][1] = ppa[q][2] = 0.f;
-    }
-    auto arrives = [&](int l, int a) __attribute__((always_inline)) { return !EACH || (l < L && a >= zs && a < zl); };
-    auto flushes = [&](int l, int a) __attribute__((always_inline)) { return EACH && l < L && a == zl; };
-    // one phase: step l on x at plane a, and step m (if the kernel has it) on y at plane b
-    auto phase = [&](auto lc, auto mc, int a, float (&x)[Q][3], int b, float (&y)[Q][3]) __attribute__((always_inline)) {
-      constexpr int l = decltype(lc)::value, m = decltype(mc)::value;
-      float ul[Q], um[Q];
-      if (arrives(l, a)) arrive_pre(l, a, par, x, ul);
-      if constexpr (m < LV)
-        if (arrives(m, b)) arrive_pre(m, b, par, y, um);
-      __syncthreads();
-      if (arrives(l, a)) arrive_post(l, EACH && a == zs, par, x, ul);
-      else if (flushes(l, a)) flush(l, par, x);
-      if constexpr (m < LV) {
-        if (arrives(m, b)) arrive_post(m, EACH && b == zs, par, y, um);
-        else if (flushes(m, b)) flush(m, par, y);
-      }
-    };
-    using std::integral_constant;
-    phase(integral_constant<int, 0>{}, integral_constant<int, 2>{}, a1, C, a1 - 3, D);
-    const int m = a1 - delay;
-    const bool outs = !EACH || (m >= zs && m < zl);
-    // the output of C or D, chosen value by value (two branches that differ in
-    // the array alone would be merged and keep both arrays in memory)
-    auto output_of = [&](bool d) __attribute__((always_inline)) {
-      float O[Q][3];
-#pragma unroll
       for (int q = 0; q < Q; ++q)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) O[q][k] = d ? D[q][k] : C[q][k];
-      output(m, par, O);
-    };
-    if (EACH ? outs && (L < 2 || L == 3) : LV == 3) output_of(EACH ? L == 3 : true);
-    if (!EACH || L > 1) {
-      if constexpr (LV == 2) phase(integral_constant<int, 1>{}, integral_constant<int, LV>{}, a1 - 1, C, 0, D);
-      else phase(integral_constant<int, 1>{}, integral_constant<int, 3>{}, a1 - 1, C, a1 - 4, D);
-      if (EACH ? outs && (L == 2 || L == 4) : LV != 3) output_of(EACH ? L == 4 : LV == 4);
-      if constexpr (LV > 2) {
-        // the dual after step 1 waits for step 2
+        for (int k = 0; k < 3; ++k) {
+          C[q][k] = FIRST || (TV2 && k == 2) ? 0.f : dual_val(P.p[q][k], bf);
+          if constexpr (FGP) ppa[q][k] = FIRST || (TV2 && k == 2) ? 0.f : dual_val(P.pp[q][k], bf);
+        }
+      if (a1 + 2 < zl) load_plane(P, a1 + 2);
+#pragma unroll
+      for (int l = 0; l < LV; ++l) {
+        if (l >= L || a1 - l < zs) break;   // this and the later steps are idle
+        arrive(l, a1 - l, par);
+      }
+      if (a1 - L >= zs) output(a1 - L, par, C);
+      if constexpr (FGP) {
 #pragma unroll
         for (int q = 0; q < Q; ++q)
 #pragma unroll
-          for (int k = 0; k < 3; ++k) D[q][k] = C[q][k];
+          for (int k = 0; k < 3; ++k) PPv[q][k] = ppa[q][k];
       }
-    } else if constexpr (LEAN) {
-      __syncthreads();   // the iteration's second barrier (s_py)
+    };
+    InPlane R;
+    load_plane(P, zs);
+    if (zs + 1 < zl) load_plane(R, zs + 1);
+    for (int s = 0; s < zl - zs; s += 2) {   // (two register sets in turn)
+      step(P, s);
+      if (s + 1 < zl - zs) step(R, s + 1);
     }
-    if constexpr (FGP) {
+    // no plane arrives any more: step l flushes at s = zl - zs + l
+    for (int s = zl - zs; s < nsteps; ++s) {
+      const int par = s & 1, a1 = zs + s;
 #pragma unroll
-      for (int q = 0; q < Q; ++q)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) PPv[q][k] = ppa[q][k];
+      for (int l = 0; l < LV; ++l) {
+        const int a = a1 - l;
+        if (l >= L || a < zs) break;
+        if (a > zl) continue;
+        if (a == zl) {
+          __syncthreads();
+          flush(l, par, C);
+        } else {
+          arrive(l, a, par);
+        }
+      }
+      if (a1 - L >= zs) output(a1 - L, par, C);
     }
-    // the next plane's copies, and the waits for its loads, stay behind this
-    // plane's arithmetic
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  load_plane(P, zs);
-  const int nsteps = zl - zs + delay;   // the last output leaves at s = nsteps - 1
-  // steady part: every step has its first plane behind it, a1 < zl
-  const int s0 = tv_delay(LV) + 1;
-  const int s1 = L == LV && zl - zs > s0 ? zl - zs : 0;
-  if constexpr (LEAN) {
-    for (int s = 0; s < nsteps; ++s) {
-      if (s == s0) {
+  } else {
+    // One plane of the pipeline: plane a1 = zs + s arrives (none past zl).  Steps 0
+    // and 2 run side by side between two barriers, then steps 1 and 3: step 2
+    // takes what step 1 left in the iteration before (its dual waits in D), so
+    // it sits one plane further back, step l at plane a1 - l - (l > 1).  Two
+    // independent steps per barrier fill the latencies of each other's exchange.
+    // A step is idle before its first plane, at plane zl it flushes, then idles
+    // again.  EACH = false: the steady part, where all LV steps are arrivals.
+    float D[Q][3];   // dual after steps 1 / 2 / 3 (C: after steps 0 / 1)
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) D[q][k] = 0.f;
+    auto iterate = [&](auto each, int s) __attribute__((always_inline)) {
+      constexpr bool EACH = decltype(each)::value;
+      const int par = s & 1;
+      const int a1 = zs + s;
+      float ppa[Q][3];   // FGP: p_prev of plane a1 (one step: output of a1 comes at the next arrival)
+      if (!EACH || a1 < zl) {
+        TvVec<Q> vq;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) vq[q] = vcopy(P.v[q]);
+        vring(a1) = vq;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          C[q][0] = dual_val(P.p[q][0], bf);
+          C[q][1] = dual_val(P.p[q][1], bf);
+          C[q][2] = TV2 ? 0.f : dual_val(P.p[q][2], bf);
+          if constexpr (FGP) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) ppa[q][k] = dual_val(P.pp[q][k], bf);
+          }
+        }
+        if (a1 + 1 < zl) load_plane(P, a1 + 1);
+      } else if constexpr (FGP) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) ppa[q][0] = ppa[q][1] = ppa[q][2] = 0.f;
+      }
+      auto arrives = [&](int l, int a) __attribute__((always_inline)) { return !EACH || (l < L && a >= zs && a < zl); };
+      auto flushes = [&](int l, int a) __attribute__((always_inline)) { return EACH && l < L && a == zl; };
+      // one phase: step l on x at plane a, and step m (if the kernel has it) on y at plane b
+      auto phase = [&](auto lc, auto mc, int a, float (&x)[Q][3], int b, float (&y)[Q][3]) __attribute__((always_inline)) {
+        constexpr int l = decltype(lc)::value, m = decltype(mc)::value;
+        float ul[Q], um[Q];
+        if (arrives(l, a)) arrive_pre(l, a, par, x, ul);
+        if constexpr (m < LV)
+          if (arrives(m, b)) arrive_pre(m, b, par, y, um);
+        __syncthreads();
+        if (arrives(l, a)) arrive_post(l, EACH && a == zs, par, x, ul);
+        else if (flushes(l, a)) flush(l, par, x);
+        if constexpr (m < LV) {
+          if (arrives(m, b)) arrive_post(m, EACH && b == zs, par, y, um);
+          else if (flushes(m, b)) flush(m, par, y);
+        }
+      };
+      using std::integral_constant;
+      phase(integral_constant<int, 0>{}, integral_constant<int, 2>{}, a1, C, a1 - 3, D);
+      const int m = a1 - delay;
+      const bool outs = !EACH || (m >= zs && m < zl);
+      // the output of C or D, chosen value by value (two branches that differ in
+      // the array alone would be merged and keep both arrays in memory)
+      auto output_of = [&](bool d) __attribute__((always_inline)) {
+        float O[Q][3];
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) O[q][k] = d ? D[q][k] : C[q][k];
+        output(m, par, O);
+      };
+      if (EACH ? outs && (L < 2 || L == 3) : LV == 3) output_of(EACH ? L == 3 : true);
+      if (!EACH || L > 1) {
+        if constexpr (LV == 2) phase(integral_constant<int, 1>{}, integral_constant<int, LV>{}, a1 - 1, C, 0, D);
+        else phase(integral_constant<int, 1>{}, integral_constant<int, 3>{}, a1 - 1, C, a1 - 4, D);
+        if (EACH ? outs && (L == 2 || L == 4) : LV != 3) output_of(EACH ? L == 4 : LV == 4);
+        if constexpr (LV > 2) {
+          // the dual after step 1 waits for step 2
+#pragma unroll
+          for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) D[q][k] = C[q][k];
+        }
+      } else if constexpr (LEAN) {
+        __syncthreads();   // the iteration's second barrier (s_py)
+      }
+      if constexpr (FGP) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) PPv[q][k] = ppa[q][k];
+      }
+      // the next plane's copies, and the waits for its loads, stay behind this
+      // plane's arithmetic
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    load_plane(P, zs);
+    // steady part: every step has its first plane behind it, a1 < zl
+    const int s0 = tv_delay(LV) + 1;
+    const int s1 = L == LV && zl - zs > s0 ? zl - zs : 0;
+    if constexpr (LEAN) {
+      for (int s = 0; s < nsteps; ++s) {
+        if (s == s0) {
+          for (; s + 1 < s1; s += 2) {
+            iterate(std::false_type{}, s);
+            iterate(std::false_type{}, s + 1);
+          }
+        }
+        iterate(std::true_type{}, s);
+      }
+    } else {
+      int s = 0;
+      if (s1 > 0) {
+        for (; s < s0; ++s) iterate(std::true_type{}, s);
         for (; s + 1 < s1; s += 2) {
           iterate(std::false_type{}, s);
           iterate(std::false_type{}, s + 1);
         }
       }
-      iterate(std::true_type{}, s);
+      for (; s < nsteps; ++s) iterate(std::true_type{}, s);
     }
-  } else {
-    int s = 0;
-    if (s1 > 0) {
-      for (; s < s0; ++s) iterate(std::true_type{}, s);
-      for (; s + 1 < s1; s += 2) {
-        iterate(std::false_type{}, s);
-        iterate(std::false_type{}, s + 1);
-      }
-    }
-    for (; s < nsteps; ++s) iterate(std::true_type{}, s);
   }
   if constexpr (FINAL) {
     if (obj) {
@@ -776,9 +856,9 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
 
 // HT: tile halo, LV: fused-step register slots.  Dual passes use HT = LV = H;
 // the final pass HT = H + 1, LV = H.
-template <int HT, int LV, int Q, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
+template <int HT, int LV, int Q, bool SEQ, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
 __device__ __forceinline__ void tv_pass_entry(const TvPassArgs& A, int bx, int by, int zb, int ze, int blk) {
-  __shared__ float s_py[LV + 1][tv_py_slots(LV)][kTvWaves][64];  // bottom-row p_y per wave, per step (+ final)
+  __shared__ float s_py[LV + 1][tv_py_slots(LV, SEQ ? TV_SEQ : TV_PIPE)][kTvWaves][64];  // bottom-row p_y per wave, per step (+ final)
   __shared__ float s_ut[LV][2][kTvWaves][64];      // top-row u per wave, per step, parity
   __shared__ TvVec<Q> s_v[tv_ring<LV, FINAL>() * kTvWaves * 64];  // v ring, thread-private
   __shared__ float s_x[FINAL ? 2 : 1][kTvWaves][64];     // final pass: first-row x per wave, parity
@@ -792,10 +872,20 @@ __device__ __forceinline__ void tv_pass_entry(const TvPassArgs& A, int bx, int b
   // interior tile: every point of the region and its +-1 neighbours lie inside
   const bool interior = x0 >= 1 && x0 + kTvRX <= A.nx - 1 && y0 >= 1 && y0 + RY <= A.ny - 1;
   auto* sx = reinterpret_cast<float (*)[kTvWaves][64]>(&s_x[0][0][0]);
-#define RIHVR_TV_BODY(E) \
-  tv_pass_body<HT, LV, Q, E, FINAL, TV2, FGP, BF, SP>(A, bx, by, zb, ze, blk, s_py, s_ut, s_v, sx, s_red, s_fin, s_sum)
-  if (interior) RIHVR_TV_BODY(false);
-  else RIHVR_TV_BODY(true);
+#define RIHVR_TV_BODY(F, E) \
+  tv_pass_body<HT, LV, Q, F, E, FINAL, TV2, FGP, BF, SP>(A, bx, by, zb, ze, blk, s_py, s_ut, s_v, sx, s_red, s_fin, s_sum)
+  if constexpr (SEQ) {
+    if (A.first) {
+      if (interior) RIHVR_TV_BODY(TV_SEQ_FIRST, false);
+      else RIHVR_TV_BODY(TV_SEQ_FIRST, true);
+    } else {
+      if (interior) RIHVR_TV_BODY(TV_SEQ, false);
+      else RIHVR_TV_BODY(TV_SEQ, true);
+    }
+  } else {
+    if (interior) RIHVR_TV_BODY(TV_PIPE, false);
+    else RIHVR_TV_BODY(TV_PIPE, true);
+  }
 #undef RIHVR_TV_BODY
 }
 
@@ -834,18 +924,18 @@ __device__ __forceinline__ TvWork tv_work(const TvPassArgs& A, uint32_t t) {
 // The first part of the grid (whole rounds of tiles) takes the XCD-contiguous
 // order; the thin chunks of the split tiles, dispatched last, keep the
 // hardware order so that they spread over every XCD.
-template <int H, bool FINAL, bool TV2, bool FGP, bool BF, bool SP, int Q = kTvQ>
+template <int H, bool SEQ, bool FINAL, bool TV2, bool FGP, bool BF, bool SP, int Q = kTvQ>
 __global__ void __launch_bounds__(kTvWaves * 64, kTvWavesPerSimd) k_tv_pass(TvPassArgs A) {
   const uint32_t hw = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
   const uint32_t n1 = (uint32_t)A.nfull * (uint32_t)((A.nz + A.zchunk - 1) / A.zchunk);
   const uint32_t t = hw < n1 ? xcd_tile(hw, n1) : hw;
   const TvWork w = tv_work(A, t);
-  tv_pass_entry<FINAL ? H + 1 : H, H, Q, FINAL, TV2, FGP, BF, SP>(A, w.bx, w.by, w.zb, w.ze, (int)t);
+  tv_pass_entry<FINAL ? H + 1 : H, FGP ? 1 : H, Q, SEQ, FINAL, TV2, FGP, BF, SP>(A, w.bx, w.by, w.zb, w.ze, (int)t);
 }
 
 // Work item b of a batched launch: the frame f with offs[f] <= b < offs[f+1]
 // and block b - offs[f] of that frame's pass.
-template <int H, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
+template <int H, bool SEQ, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
 __device__ __forceinline__ void tv_batch_item(const TvPassArgs* __restrict__ args, const BatchMap& map, uint32_t b) {
   int lo = 0, hi = map.n;  // largest f with offs[f] <= b
   while (hi - lo > 1) {
@@ -859,13 +949,13 @@ __device__ __forceinline__ void tv_batch_item(const TvPassArgs* __restrict__ arg
   const TvPassArgs& A = args[lo];
   const int lb = (int)(b - (uint32_t)__builtin_amdgcn_readfirstlane(map.offs[lo]));
   const TvWork w = tv_work(A, (uint32_t)lb);
-  tv_pass_entry<FINAL ? H + 1 : H, H, kTvQ, FINAL, TV2, FGP, BF, SP>(A, w.bx, w.by, w.zb, w.ze, lb);
+  tv_pass_entry<FINAL ? H + 1 : H, FGP ? 1 : H, kTvQ, SEQ, FINAL, TV2, FGP, BF, SP>(A, w.bx, w.by, w.zb, w.ze, lb);
 }
 
-template <int H, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
+template <int H, bool SEQ, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
 __global__ void __launch_bounds__(kTvWaves * 64, kTvWavesPerSimd) k_tv_pass_b(const TvPassArgs* __restrict__ args,
                                                                                   BatchMap map) {
-  tv_batch_item<H, FINAL, TV2, FGP, BF, SP>(args, map, xcd_tile(blockIdx.x, gridDim.x));
+  tv_batch_item<H, SEQ, FINAL, TV2, FGP, BF, SP>(args, map, xcd_tile(blockIdx.x, gridDim.x));
 }
 
 // Persistent form of the batched pass: a grid of about one block per compute
@@ -886,7 +976,7 @@ __global__ void __launch_bounds__(kTvWaves * 64, kTvWavesPerSimd) k_tv_pass_b(co
 // the two across the loop's back edge and turn the item loop into an
 // exec-masked loop with the barriers inside, which waves leave after
 // different numbers of trips.
-template <int H, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
+template <int H, bool SEQ, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
 __global__ void __launch_bounds__(kTvWaves * 64, kTvWavesPerSimd) k_tv_pass_q(const TvPassArgs* __restrict__ args,
                                                                                   BatchMap map) {
   __shared__ uint32_t s_item;
@@ -907,7 +997,7 @@ __global__ void __launch_bounds__(kTvWaves * 64, kTvWavesPerSimd) k_tv_pass_q(co
       s_item = 0u;
       __syncthreads();  // ... and cleared before the next claim adds to it
       if (i >= len) break;
-      tv_batch_item<H, FINAL, TV2, FGP, BF, SP>(args, map, first + i);
+      tv_batch_item<H, SEQ, FINAL, TV2, FGP, BF, SP>(args, map, first + i);
     }
   }
   // every block passes here once, after its last claim on every counter
@@ -915,57 +1005,68 @@ __global__ void __launch_bounds__(kTvWaves * 64, kTvWavesPerSimd) k_tv_pass_q(co
     for (uint32_t k = 0; k <= kXcds; ++k) atomicExch(map.queue + k * kQueueStride, 0u);
 }
 
-template <int H, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
+template <int H, bool SEQ, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
 static void launch_batched(dim3 g, const TvPassArgs* a, const BatchMap& map, hipStream_t s) {
   const dim3 b(kTvWaves * 64);
   if (map.queue != nullptr)
-    hipLaunchKernelGGL((k_tv_pass_q<H, FINAL, TV2, FGP, BF, SP>), dim3(std::max(1, std::min<int>(g.x, map.grid))), b,
+    hipLaunchKernelGGL((k_tv_pass_q<H, SEQ, FINAL, TV2, FGP, BF, SP>), dim3(std::max(1, std::min<int>(g.x, map.grid))), b,
                        0, s, a, map);
-  else hipLaunchKernelGGL((k_tv_pass_b<H, FINAL, TV2, FGP, BF, SP>), g, b, 0, s, a, map);
+  else hipLaunchKernelGGL((k_tv_pass_b<H, SEQ, FINAL, TV2, FGP, BF, SP>), g, b, 0, s, a, map);
 }
 
-// Kernel selection for one fusion depth: final / dual pass, 2D or 3D TV, FGP
+// Kernel selection for one fusion depth: form, final / dual pass, 2D or 3D TV, FGP
 // (dual passes of depth-2 tiles only), bfloat16 dual, row-compressed output
 // (final passes with an FP32 dual only), single or batched form.  One source
 // file per depth instantiates it.
 struct TvSelect {
-  bool batch, final_pass, tv2, fgp, bf16, sparse, low;   // low: tiles of kTvSmallQ rows a lane
+  bool batch, final_pass, tv2, fgp, bf16, sparse, low, seq;   // low: tiles of kTvSmallQ rows a lane
 };
-template <int H, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
+template <int H, bool SEQ, bool FINAL, bool TV2, bool FGP, bool BF, bool SP>
 static void launch_tv_kernel(bool batch, dim3 g, const TvPassArgs* a, const BatchMap& map, hipStream_t s) {
-  if (batch) launch_batched<H, FINAL, TV2, FGP, BF, SP>(g, a, map, s);
-  else hipLaunchKernelGGL((k_tv_pass<H, FINAL, TV2, FGP, BF, SP>), g, dim3(kTvWaves * 64), 0, s, *a);
+  if (batch) launch_batched<H, SEQ, FINAL, TV2, FGP, BF, SP>(g, a, map, s);
+  else hipLaunchKernelGGL((k_tv_pass<H, SEQ, FINAL, TV2, FGP, BF, SP>), g, dim3(kTvWaves * 64), 0, s, *a);
 }
-template <int H, bool TV2>
+// Forms that exist: the final pass of depth 4 has no room for the second s_py slots of
+// SEQ, and a step of FGP never fills the pipeline.
+__host__ __device__ constexpr bool tv_has_seq(int H, bool final_pass) { return H < kTvLevelsMax || !final_pass; }
+
+template <int H, bool SEQ, bool TV2>
 static void launch_tv_dim(const TvSelect& k, dim3 g, const TvPassArgs* a, const BatchMap& map, hipStream_t s) {
   if constexpr (H == kTvDefaultLevels) {
     if (k.low) {   // (single launches with an FP32 dual only)
       const dim3 b(kTvWaves * 64);
-      if (k.final_pass) hipLaunchKernelGGL((k_tv_pass<H, true, TV2, false, false, false, kTvSmallQ>), g, b, 0, s, *a);
-      else hipLaunchKernelGGL((k_tv_pass<H, false, TV2, false, false, false, kTvSmallQ>), g, b, 0, s, *a);
+      if (k.final_pass) hipLaunchKernelGGL((k_tv_pass<H, SEQ, true, TV2, false, false, false, kTvSmallQ>), g, b, 0, s, *a);
+      else hipLaunchKernelGGL((k_tv_pass<H, SEQ, false, TV2, false, false, false, kTvSmallQ>), g, b, 0, s, *a);
       return;
     }
   }
   if (k.final_pass) {
-    if (k.sparse && !k.bf16) launch_tv_kernel<H, true, TV2, false, false, true>(k.batch, g, a, map, s);
-    else if (k.bf16) launch_tv_kernel<H, true, TV2, false, true, false>(k.batch, g, a, map, s);
-    else launch_tv_kernel<H, true, TV2, false, false, false>(k.batch, g, a, map, s);
+    if constexpr (!SEQ || tv_has_seq(H, true)) {
+      if (k.sparse && !k.bf16) launch_tv_kernel<H, SEQ, true, TV2, false, false, true>(k.batch, g, a, map, s);
+      else if (k.bf16) launch_tv_kernel<H, SEQ, true, TV2, false, true, false>(k.batch, g, a, map, s);
+      else launch_tv_kernel<H, SEQ, true, TV2, false, false, false>(k.batch, g, a, map, s);
+    }
     return;
   }
-  if constexpr (H == 2) {
+  if constexpr (H == 2 && SEQ) {
     if (k.fgp) {
-      if (k.bf16) launch_tv_kernel<H, false, TV2, true, true, false>(k.batch, g, a, map, s);
-      else launch_tv_kernel<H, false, TV2, true, false, false>(k.batch, g, a, map, s);
+      if (k.bf16) launch_tv_kernel<H, SEQ, false, TV2, true, true, false>(k.batch, g, a, map, s);
+      else launch_tv_kernel<H, SEQ, false, TV2, true, false, false>(k.batch, g, a, map, s);
       return;
     }
   }
-  if (k.bf16) launch_tv_kernel<H, false, TV2, false, true, false>(k.batch, g, a, map, s);
-  else launch_tv_kernel<H, false, TV2, false, false, false>(k.batch, g, a, map, s);
+  if (k.bf16) launch_tv_kernel<H, SEQ, false, TV2, false, true, false>(k.batch, g, a, map, s);
+  else launch_tv_kernel<H, SEQ, false, TV2, false, false, false>(k.batch, g, a, map, s);
 }
 template <int H>
 void launch_tv_depth(const TvSelect& k, dim3 g, const TvPassArgs* a, const BatchMap& map, hipStream_t s) {
-  if (k.tv2) launch_tv_dim<H, true>(k, g, a, map, s);
-  else launch_tv_dim<H, false>(k, g, a, map, s);
+  if (k.seq) {
+    if (k.tv2) launch_tv_dim<H, true, true>(k, g, a, map, s);
+    else launch_tv_dim<H, true, false>(k, g, a, map, s);
+  } else {
+    if (k.tv2) launch_tv_dim<H, false, true>(k, g, a, map, s);
+    else launch_tv_dim<H, false, false>(k, g, a, map, s);
+  }
 }
 
 }  // namespace rihvr
