@@ -9,6 +9,7 @@ import pytest
 
 from oracle import fista, prox
 from paper_1904_04884_amd import rihvr, scenes
+from test_prox_grids_host import CHUNKINGS
 
 pytestmark = pytest.mark.gpu
 
@@ -41,6 +42,23 @@ def test_depths_and_forms_give_the_same_bits(torch_cuda, shape, dims):
             if small:
                 ref = prox.prox_fused_lasso(v.cpu().numpy().astype(np.float64), 0.6, 0.05, 0.3, k, k % 2 == 0, dims=dims)
                 assert np.linalg.norm(outs[0].cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(ref), k
+    finally:
+        plan.close()
+
+
+@pytest.mark.parametrize("dims", (2, 3))
+@pytest.mark.parametrize("shape,levels,blocks", CHUNKINGS)
+def test_chunkings_give_the_same_bits(torch_cuda, shape, levels, blocks, dims):
+    torch = torch_cuda
+    plan = rihvr.Plan(geometry(*shape, dims))
+    v = volume(torch, plan, levels)
+    try:
+        ref = None
+        for b in blocks:
+            plan.tuning = {**plan.tuning, "tv_levels": levels, "tv_blocks": b}
+            out = plan.prox(v, 0.6, 0.05, 0.3, 2 * levels, nonneg=True)
+            ref = out if ref is None else ref
+            assert torch.equal(out, ref), b
     finally:
         plan.close()
 

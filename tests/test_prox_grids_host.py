@@ -43,3 +43,18 @@ def test_partials_counted_are_those_written(grids):
     assert len(out) == len(rows)
     for row, (counted, written, bound, _) in zip(rows, out):
         assert counted == written <= bound, row
+
+
+# volume, depth and three tv_blocks whose dual passes are cut into different chunks, one of
+# them ragged (tests/test_gpu_tv_forms.py compares their results)
+CHUNKINGS = [((512, 512, 200), 2, (64, 512, 1536)), ((768, 768, 120), 3, (64, 512, 65536)),
+             ((512, 512, 200), 4, (64, 512, 1536))]
+
+
+@pytest.mark.parametrize("dims", (0, TV2D))
+def test_chunkings_differ(grids, dims):
+    cuts = [grids([(*shape, lv, b, 256, dims | LOW, 0) for b in blocks]) for shape, lv, blocks in CHUNKINGS]
+    for (shape, _, _), out in zip(CHUNKINGS, cuts):
+        chunks = {o[3] for o in out}
+        assert len(chunks) == 3 and max(chunks) > min(chunks) >= 16, chunks
+    assert any(shape[2] % o[3] for (shape, _, _), out in zip(CHUNKINGS, cuts) for o in out)
