@@ -94,7 +94,8 @@ __device__ __forceinline__ T neg_div(const GpArgs<T>& a, size_t i, size_t o, int
 // planes are read through buffer descriptors (0 outside the volume), one plane
 // ahead.  State below the volume starts at zero and the dual's component along
 // an axis is exactly zero on that axis' last plane, so z needs no masks; x / y
-// masks are compiled only into tiles at the volume's edge (EDGE).
+// masks are compiled only into tiles at the volume's edge (EDGE), the z component into
+// the 3D form (TV3).
 //
 // Bound by the latency of its loads and of the exchange at each barrier, at
 // large sizes by memory: v and the dual in and out once per LV steps, 56 B per
@@ -104,8 +105,9 @@ __device__ __forceinline__ T neg_div(const GpArgs<T>& a, size_t i, size_t o, int
 // ms); one block of sixteen wavefronts and 32 rows 1613 (9.1 ms), LV = 4 spills
 // (2626).  FP64 has registers for LV = 2.  Against a pair of steps through LDS
 // with six stages and five barriers a plane (FP64: a step): 2934 us; FP64 real
-// 192 x 128 x 24, 10 steps, 450 -> 131 us; 256^2 x 48 complex FP64, 11 steps,
-// 1708 -> 725.
+// 192 x 128 x 24, 10 steps, 450 -> 123 us; 256^2 x 48 complex FP64, 10 steps, 1559 ->
+// 563, in 2D 1092 -> 333.  A single step takes tiles with a halo of one, and no dual is
+// loaded where it is zero: one step at 512^2 x 32 in 2D, complex FP64, 333 -> 193 us.
 constexpr unsigned kGpOff = 0x40000000u;   // past every plane, also when two are added
 
 __device__ __forceinline__ int dpp_left(int v) { return __builtin_amdgcn_mov_dpp(v, 0x138, 0xf, 0xf, true); }
@@ -170,15 +172,15 @@ constexpr int gp_rows() { return gp_q<T, NP>() * gp_waves<T, NP>(); }
 template <class T>
 constexpr int gp_levels() { return sizeof(T) == 4 ? 3 : 2; }
 
-template <class T, int NP, int LV, bool EDGE>
+template <class T, int NP, int LV, bool TV3, bool EDGE>
 __device__ __forceinline__ void gp_pass_body(const GpArgs<T>& a, int bx, int by, int zb, int ze,
                                              T (*s_py)[2][NP][gp_waves<T, NP>()][64],
                                              T (*s_ut)[2][NP][gp_waves<T, NP>()][64]) {
-  constexpr int NW = gp_waves<T, NP>(), Q = gp_q<T, NP>(), RY = gp_rows<T, NP>(), H = LV;
+  constexpr int NW = gp_waves<T, NP>(), Q = gp_q<T, NP>(), RY = gp_rows<T, NP>(), H = LV, ND = TV3 ? 3 : 2;
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   const size_t sz = (size_t)nx * ny;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool tv3 = !a.tv2, pre = !a.first;
+  const bool pre = !a.first;
   const int L = a.levels;
   const T tau = a.tau, cc = a.c;
   const T* v = in_of(a);
@@ -196,11 +198,11 @@ __device__ __forceinline__ void gp_pass_body(const GpArgs<T>& a, int bx, int by,
     offl[q] = inx && iny ? (unsigned)(y * nx + x) * (unsigned)sizeof(T) : kGpOff;
     offs[q] = inx && iny && lane >= H && lane < 64 - H && r >= H && r < RY - H ? offl[q] : kGpOff;
   }
-  const int M = tv3 ? L : 0;
+  const int M = TV3 ? L : 0;
   const int zs = max(0, zb - M), zl = min(nz, ze + M);
 
   struct Plane {
-    T v[Q][NP], p[Q][3][NP];
+    T v[Q][NP], p[Q][ND][NP];
   };
   auto load_plane = [&](Plane& r, int z) __attribute__((always_inline)) {
 #pragma unroll
@@ -208,58 +210,63 @@ __device__ __forceinline__ void gp_pass_body(const GpArgs<T>& a, int bx, int by,
       const __amdgpu_buffer_rsrc_t rv = gp_rsrc(v, (size_t)part * nz + z, sz, true);
 #pragma unroll
       for (int q = 0; q < Q; ++q) gp_ld(r.v[q][part], rv, offl[q]);
+    }
+    if (!pre) return;   // (r.p stays zero)
 #pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const __amdgpu_buffer_rsrc_t rp = gp_rsrc<T>(a.p[d], (size_t)part * nz + z, sz, pre && (d < 2 || tv3));
+    for (int part = 0; part < NP; ++part) {
+#pragma unroll
+      for (int d = 0; d < ND; ++d) {
+        const __amdgpu_buffer_rsrc_t rp = gp_rsrc<T>(a.p[d], (size_t)part * nz + z, sz, true);
 #pragma unroll
         for (int q = 0; q < Q; ++q) gp_ld(r.p[q][d][part], rp, offl[q]);
       }
     }
   };
   // per step: the previous plane's dual and u; v of the planes that steps 1.. are at
-  T Pp[LV][Q][3][NP], Up[LV][Q][NP], V[LV][Q][NP];
+  T Pp[LV][Q][ND][NP], Up[LV][Q][NP], V[LV][Q][NP];
 #pragma unroll
   for (int l = 0; l < LV; ++l)
 #pragma unroll
     for (int q = 0; q < Q; ++q)
 #pragma unroll
       for (int part = 0; part < NP; ++part) {
-        Pp[l][q][0][part] = Pp[l][q][1][part] = Pp[l][q][2][part] = T(0);
+#pragma unroll
+        for (int d = 0; d < ND; ++d) Pp[l][q][d][part] = T(0);
         Up[l][q][part] = V[l][q][part] = T(0);
       }
-  T C[Q][3][NP];
+  T C[Q][ND][NP];
+  Plane P;
 #pragma unroll
   for (int q = 0; q < Q; ++q)
 #pragma unroll
-    for (int d = 0; d < 3; ++d)
+    for (int d = 0; d < ND; ++d)
 #pragma unroll
-      for (int part = 0; part < NP; ++part) C[q][d][part] = T(0);
+      for (int part = 0; part < NP; ++part) C[q][d][part] = P.p[q][d][part] = T(0);
   // dual step at the plane held in Pp / Up, whose next plane's u is un (hz: it exists), into o
-  auto step = [&](int l, int par, bool hz, const T (&un)[Q][NP], T (&o)[Q][3][NP]) __attribute__((always_inline)) {
+  auto step = [&](int l, int par, bool hz, const T (&un)[Q][NP], T (&o)[Q][ND][NP]) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      T w[3][NP];
+      T w[ND][NP];
       T n2 = T(0);
 #pragma unroll
       for (int part = 0; part < NP; ++part) {
         const T u0 = Up[l][q][part];
         const T ux = from_right(u0);
         const T uy = q < Q - 1 ? Up[l][q < Q - 1 ? q + 1 : q][part] : s_ut[l][par ^ 1][part][wv < NW - 1 ? wv + 1 : wv][lane];
-        const T g[3] = {xhi ? ux - u0 : T(0), yhi[q] ? uy - u0 : T(0), (hz && tv3) ? un[q][part] - u0 : T(0)};
+        const T g[3] = {xhi ? ux - u0 : T(0), yhi[q] ? uy - u0 : T(0), hz ? un[q][part] - u0 : T(0)};
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
+        for (int d = 0; d < ND; ++d) {
           w[d][part] = fmaT(cc, g[d], Pp[l][q][d][part]);
           n2 = fmaT(w[d][part], w[d][part], n2);
         }
       }
       const T sc = proj_scale(n2);
 #pragma unroll
-      for (int d = 0; d < 3; ++d)
+      for (int d = 0; d < ND; ++d)
 #pragma unroll
         for (int part = 0; part < NP; ++part) o[q][d][part] = w[d][part] * sc;
     }
   };
-  Plane P;
   load_plane(P, zs);
   const int nsteps = zl - zs + L;   // the last output leaves at s = nsteps - 1
   for (int s = 0; s < nsteps; ++s) {
@@ -271,7 +278,7 @@ __device__ __forceinline__ void gp_pass_body(const GpArgs<T>& a, int bx, int by,
         for (int part = 0; part < NP; ++part) {
           V[0][q][part] = kept_copy(P.v[q][part]);
 #pragma unroll
-          for (int d = 0; d < 3; ++d) C[q][d][part] = kept_copy(P.p[q][d][part]);
+          for (int d = 0; d < ND; ++d) C[q][d][part] = kept_copy(P.p[q][d][part]);
         }
       if (a1 + 1 < zl) load_plane(P, a1 + 1);
     }
@@ -294,10 +301,10 @@ __device__ __forceinline__ void gp_pass_body(const GpArgs<T>& a, int bx, int by,
             const T pym = q > 0 ? C[q > 0 ? q - 1 : 0][1][part] : s_py[l][par][part][wv > 0 ? wv - 1 : 0][lane];
             T d = (xhi ? cx : T(0)) - (xlo ? pxm : T(0));
             d += (yhi[q] ? cy : T(0)) - (ylo[q] ? pym : T(0));
-            d += C[q][2][part] - Pp[l][q][2][part];
+            if constexpr (TV3) d += C[q][2][part] - Pp[l][q][2][part];
             un[q][part] = fmaT(tau, d, V[l][q][part]);
           }
-        T O[Q][3][NP];
+        T O[Q][ND][NP];
         step(l, par, true, un, O);
 #pragma unroll
         for (int part = 0; part < NP; ++part) s_ut[l][par][part][wv][lane] = un[0][part];
@@ -307,7 +314,7 @@ __device__ __forceinline__ void gp_pass_body(const GpArgs<T>& a, int bx, int by,
           for (int part = 0; part < NP; ++part) {
             Up[l][q][part] = un[q][part];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
+            for (int d = 0; d < ND; ++d) {
               Pp[l][q][d][part] = C[q][d][part];
               C[q][d][part] = O[q][d][part];   // (of no plane when z == zs: not used)
             }
@@ -321,8 +328,8 @@ __device__ __forceinline__ void gp_pass_body(const GpArgs<T>& a, int bx, int by,
 #pragma unroll
     for (int part = 0; part < NP; ++part)
 #pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const __amdgpu_buffer_rsrc_t ro = gp_rsrc<T>(a.q[d], (size_t)part * nz + (on ? m : 0), sz, on && (d < 2 || tv3));
+      for (int d = 0; d < ND; ++d) {
+        const __amdgpu_buffer_rsrc_t ro = gp_rsrc<T>(a.q[d], (size_t)part * nz + (on ? m : 0), sz, on);
 #pragma unroll
         for (int q = 0; q < Q; ++q) gp_st(C[q][d][part], ro, offs[q]);
       }
@@ -336,7 +343,7 @@ __device__ __forceinline__ void gp_pass_body(const GpArgs<T>& a, int bx, int by,
   }
 }
 
-template <class T, int NP, int LV>
+template <class T, int NP, int LV, bool TV3>
 __global__ void __launch_bounds__((gp_waves<T, NP>() * 64), 4) k_gp_pass(GpArgs<T> a) {
   constexpr int NW = gp_waves<T, NP>(), RY = gp_rows<T, NP>();
   __shared__ T s_py[LV][2][NP][NW][64];   // bottom-row p_y of every wavefront, by step and parity
@@ -352,8 +359,8 @@ __global__ void __launch_bounds__((gp_waves<T, NP>() * 64), 4) k_gp_pass(GpArgs<
   const int x0 = bx * (64 - 2 * LV) - LV, y0 = by * (RY - 2 * LV) - LV;
   const bool interior = x0 >= 1 && x0 + 64 <= a.nx - 1 && y0 >= 1 && y0 + RY <= a.ny - 1;
   const int ze = min(a.nz, zb + a.zchunk);
-  if (interior) gp_pass_body<T, NP, LV, false>(a, bx, by, zb, ze, s_py, s_ut);
-  else gp_pass_body<T, NP, LV, true>(a, bx, by, zb, ze, s_py, s_ut);
+  if (interior) gp_pass_body<T, NP, LV, TV3, false>(a, bx, by, zb, ze, s_py, s_ut);
+  else gp_pass_body<T, NP, LV, TV3, true>(a, bx, by, zb, ze, s_py, s_ut);
 }
 
 // u once more, then the threshold and the flags.  In place is allowed (a
@@ -459,17 +466,17 @@ int ggrid(size_t n) {
   return (int)(b > 8192 ? 8192 : (b == 0 ? 1 : b));
 }
 
-// Planes per block of a pass: the cut whose rounds of 2 `cus` blocks (two fit a
-// compute unit) times a block's march, its planes and 3 LV of margin and
-// pipeline, is shortest.
-int gp_zchunk(int tiles, int nz, int lv, int cus) {
-  const int slots = 2 * (cus > 0 ? cus : 256);
+// Planes per block of a pass: the cut whose rounds (16 wavefronts a compute unit: two
+// blocks of eight, one of sixteen) times a block's march, its planes and `extra` of
+// margin and pipeline (3 LV, in 2D without margin LV), is shortest.  FP64 in 2D, 10 steps,
+// without the LV: 1024^2 x 8 real 544 us, now 400; complex 1509 and 958.
+int gp_zchunk(int tiles, int nz, int extra, int slots) {
   int best = nz;
   long best_t = -1;
   for (int nc = 1; nc <= nz; ++nc) {
     const int zc = (nz + nc - 1) / nc;
     const long blocks = (long)tiles * ((nz + zc - 1) / zc);
-    const long t = (blocks + slots - 1) / slots * (zc + 3 * lv);
+    const long t = (blocks + slots - 1) / slots * (zc + extra);
     if (best_t < 0 || t < best_t) {
       best_t = t;
       best = zc;
@@ -478,21 +485,31 @@ int gp_zchunk(int tiles, int nz, int lv, int cus) {
   return best;
 }
 
-// K steps, LV a launch, alternating between the dual sets a.p and a.q, then the
-// final launch on the set the last one wrote.
-template <class T, int NP>
-hipError_t run_gp(GpArgs<T> a, int K, int cus, hipStream_t s, int* launches) {
-  constexpr int LV = gp_levels<T>(), RY = gp_rows<T, NP>();
-  const dim3 g(ggrid((size_t)a.nx * a.ny * a.nz)), b(kGThreads);
+// A launch of up to LV steps.
+template <class T, int NP, int LV>
+void launch_gp(GpArgs<T> a, int cus, hipStream_t s) {
+  constexpr int RY = gp_rows<T, NP>(), NW = gp_waves<T, NP>();
   a.gx = (a.nx + 64 - 2 * LV - 1) / (64 - 2 * LV);
   a.gy = (a.ny + RY - 2 * LV - 1) / (RY - 2 * LV);
-  a.zchunk = gp_zchunk(a.gx * a.gy, a.nz, a.tv2 ? 0 : LV, cus);
-  const dim3 gz(a.gx * a.gy * ((a.nz + a.zchunk - 1) / a.zchunk));
+  a.zchunk = gp_zchunk(a.gx * a.gy, a.nz, a.tv2 ? LV : 3 * LV, (cus > 0 ? cus : 256) * (16 / NW));
+  const dim3 g(a.gx * a.gy * ((a.nz + a.zchunk - 1) / a.zchunk)), b(NW * 64);
+  if (a.tv2) hipLaunchKernelGGL((k_gp_pass<T, NP, LV, false>), g, b, 0, s, a);
+  else hipLaunchKernelGGL((k_gp_pass<T, NP, LV, true>), g, b, 0, s, a);
+}
+
+// K steps, LV a launch (a single step left over on tiles with a halo of one),
+// alternating between the dual sets a.p and a.q, then the final launch on the set the
+// last one wrote.
+template <class T, int NP>
+hipError_t run_gp(GpArgs<T> a, int K, int cus, hipStream_t s, int* launches) {
+  constexpr int LV = gp_levels<T>();
+  const dim3 g(ggrid((size_t)a.nx * a.ny * a.nz)), b(kGThreads);
   int nl = 0;
   for (int k = 0; k < K;) {
     a.first = k == 0 ? 1 : 0;
     a.levels = K - k < LV ? K - k : LV;
-    hipLaunchKernelGGL((k_gp_pass<T, NP, LV>), gz, dim3(gp_waves<T, NP>() * 64), 0, s, a);
+    if (a.levels == 1) launch_gp<T, NP, 1>(a, cus, s);
+    else launch_gp<T, NP, LV>(a, cus, s);
     k += a.levels;
     for (int d = 0; d < 3; ++d) std::swap(a.p[d], a.q[d]);
     ++nl;
