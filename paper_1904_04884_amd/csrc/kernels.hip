@@ -37,8 +37,9 @@ __host__ __device__ constexpr int kRowsPerBlock(int m) {
 // passes order LDS within the wave, with no block barrier.
 __host__ __device__ constexpr bool kRowWave(int m) { return kRowThreads(m) <= 64; }
 // Column transforms: points per thread, and columns per tile such that a block
-// has at most 512 threads (256 VGPRs per lane available, no spills) and one
-// exchange buffer (padded), the twiddles and 4 KiB of flags fit the 160 KiB of LDS.
+// has at most 512 threads (256 VGPRs per lane available; with 8 points 128, for two
+// blocks a unit: no instance spills) and one exchange buffer (padded), the twiddles
+// and 4 KiB of flags fit the 160 KiB of LDS.
 __host__ __device__ constexpr int kColP(int ny) { return (ny % 3 == 0) ? 12 : (ny >= 2048 ? 16 : 8); }
 __host__ __device__ constexpr int kColW(int ny) {
   int w = 16;
@@ -295,8 +296,13 @@ __device__ __forceinline__ void rows_c2r_body(const RowsC2RArgs& a, int bx, int 
 constexpr unsigned kColOff = 0x80000000u;   // past every plane descriptor: reads 0
 constexpr int kColPlaneFlags = 2048;        // plane flags of a chunk staged in LDS
 
+// (The address is made uniform by hand: where the compiler keeps its factors in vector
+// registers, each load through the descriptor becomes a loop over the wave's values.)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t spec_rsrc(const float2* plane, size_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(plane), (short)0, (int)bytes, 0x00020000);
+  const uint64_t p = (uint64_t)(uintptr_t)plane;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p), hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((uintptr_t)((uint64_t)hi << 32 | lo)), (short)0,
+                                           __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
 }
 __device__ __forceinline__ float2 buf_ld2(__amdgpu_buffer_rsrc_t r, unsigned off) {
   const auto u = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
@@ -308,14 +314,16 @@ __device__ __forceinline__ float2 buf_ld2(__amdgpu_buffer_rsrc_t r, unsigned off
 // instead of evaluating them in the lanes of column 0, where every wavefront
 // would run a second phase for each of its points: the grid is only about two
 // blocks per CU, so these blocks set its end (A at 512^2 x 128: 156 us with the
-// second phase in the lanes, 148 shared out).  theta is read once into registers
-// (a global load in the loop would wait for the next plane's tile in flight:
-// 177 us).
+// second phase in the lanes, 148 shared out).  theta is read once (a global load in
+// the loop would wait for the next plane's tile in flight: 177 us), into LDS where 8
+// points a thread hold the block to 128 VGPRs, else into registers.
+__host__ __device__ constexpr bool kThetaLds(int ny) { return kColP(ny) <= 8; }
 template <int NY, int W>
 struct ColLds {
   float2 buf[fft_buf_len(NY, kColP(NY)) * W];
   float2 tw[NY];
   float2 c0[NY];
+  double thn[kThetaLds(NY) ? NY : 1];
   float cn[NY];
 };
 template <int NY, int W, bool INV>
@@ -334,26 +342,35 @@ __device__ __forceinline__ void col0_put(const float2 (&v)[kColP(NY)], ColLds<NY
 template <int NY, int W>
 struct NyquistShare {
   static constexpr int NT = W * NY / kColP(NY), N = (NY + NT - 1) / NT;
-  double th[N];
-  __device__ __forceinline__ void load(const PlanTables& pt, int m) {
+  static constexpr bool LDS = kThetaLds(NY);
+  double th[LDS ? 1 : N];
+  __device__ __forceinline__ void load(ColLds<NY, W>& l, const PlanTables& pt, int m) {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int y = threadIdx.x + i * NT;
-      th[i] = y < NY ? pt.theta[(size_t)y * (m + 1) + m] : 0.0;
+      const double v = y < NY ? pt.theta[(size_t)y * (m + 1) + m] : 0.0;
+      if constexpr (!LDS) th[i] = v;
+      else if (y < NY) l.thn[y] = v;
     }
   }
   __device__ __forceinline__ void put(ColLds<NY, W>& l, double2 zc) const {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int y = threadIdx.x + i * NT;
-      if (y < NY) l.cn[y] = phase_cos(zc.x, zc.y, th[i]);
+      if (y >= NY) continue;
+      double t;
+      if constexpr (LDS) t = l.thn[y];   // (written by this thread)
+      else t = th[i];
+      l.cn[y] = phase_cos(zc.x, zc.y, t);
     }
   }
 };
-// The filtered value of column 0 at y: c its own filter there.
+// The filtered value of column 0 at y = q + s TC: c its own filter there.  (Only y = 0
+// wraps at -y, so the other addresses are one register and a constant.)
 template <int NY, int W>
-__device__ __forceinline__ float2 col0_filter(const ColLds<NY, W>& l, int y, float c, float2 v) {
-  const float2 vn = cconj(l.c0[(NY - y) % NY]);
+__device__ __forceinline__ float2 col0_filter(const ColLds<NY, W>& l, int q, int s, float c, float2 v) {
+  const int y = q + s * (NY / kColP(NY));
+  const float2 vn = cconj(l.c0[s == 0 ? (NY - q) % NY : NY - y]);
   const float ca = 0.5f * (c + l.cn[y]), cb = 0.5f * (c - l.cn[y]);
   return make_float2(ca * v.x + cb * vn.x, ca * v.y + cb * vn.y);
 }
@@ -408,7 +425,7 @@ __device__ __forceinline__ void fwd_cols_planes(const FwdColsArgs& a, int bx, in
     for (int i = threadIdx.x; i < min(j1 - j0, kColPlaneFlags); i += blockDim.x) s_pf[i] = a.planeflag[j0 + i];
   stage_twiddles(l, pt.tw_col);
   NyquistShare<NY, W> ny;
-  if constexpr (COL0) ny.load(pt, m);
+  if constexpr (COL0) ny.load(l, pt, m);
   __syncthreads();
   auto next_plane = [&](int j) {
     if (pflags)
@@ -423,9 +440,11 @@ __device__ __forceinline__ void fwd_cols_planes(const FwdColsArgs& a, int bx, in
     const __amdgpu_buffer_rsrc_t r = spec_rsrc(a.t + (size_t)j * NY * m, plane_bytes);
     // offsets first (the flag bytes are read even when unused), then the loads
     unsigned o[P];
+    int qt = q;
+    if constexpr (COL0) asm volatile("" : "+v"(qt));   // the rows' addresses anew each plane: kept, they spill
 #pragma unroll
     for (int s = 0; s < P; ++s) {
-      const int y = q + s * TC;
+      const int y = qt + s * TC;
       const bool on = PF ? colok & (!flags | (fl8[y] != 0))
                          : colok && (!flags || a.rowflag[(size_t)j * NY + y] != 0);
       o[s] = on ? (unsigned)((y * m + kx) * sizeof(float2)) : kColOff;
@@ -446,7 +465,7 @@ __device__ __forceinline__ void fwd_cols_planes(const FwdColsArgs& a, int bx, in
     for (int s = 0; s < P; ++s) {
       const float c = phase_cos(zc.x, zc.y, th[s]);
       if (COL0 && kx == 0) {
-        const float2 f = col0_filter(l, q + s * TC, c, v[s]);
+        const float2 f = col0_filter(l, q, s, c, v[s]);
         acc[s].x += f.x;
         acc[s].y += f.y;
       } else {
@@ -510,11 +529,12 @@ __device__ __forceinline__ void fwd_cols_body(const FwdColsArgs& a, int bx, int 
 // ---------------------------------------------------------------------------
 // Sum of partial spectra and inverse column FFT (hologram sized).  A block
 // takes kHoloW columns; its G thread groups each add every G-th partial and
-// the groups' sums meet in LDS, where group 0 (the others on zeros) runs the
-// transform.  The sum of nchunk partials per point is the work here, so it
-// wants loads in flight: one thread per point of a 16-column tile, adding all
-// partials in turn, took 77 us at 128^2 (32 partials, 4 blocks), 74 us at
-// 768 x 384 (19 partials) and 207 us for frames of 256^2; now 10, 24 and 47 us.
+// the groups' sums meet in LDS, where group 0 adds them.  Every group then runs
+// the transform, whose barriers are the block's; only group 0's is stored.  The
+// sum of nchunk partials per point is the work here, so it wants loads in
+// flight: one thread per point of a 16-column tile, adding all partials in
+// turn, took 77 us at 128^2 (32 partials, 4 blocks), 74 us at 768 x 384 (19
+// partials) and 207 us for frames of 256^2; now 10, 24 and 47 us.
 // ---------------------------------------------------------------------------
 constexpr int kHoloW = 4;
 __host__ __device__ constexpr int kHoloG(int ny) {   // groups: blocks of up to 512 threads
@@ -580,7 +600,7 @@ __device__ __forceinline__ void adj_cols_planes(const AdjColsArgs& a, int bx, in
   const bool colok = kx < m;
   stage_twiddles(l, pt.tw_col);
   NyquistShare<NY, W> ny;
-  if constexpr (COL0) ny.load(pt, m);
+  if constexpr (COL0) ny.load(l, pt, m);
   float2 rh[P];
 #pragma unroll
   for (int s = 0; s < P; ++s) rh[s] = colok ? a.th[(size_t)(q + s * TC) * m + kx] : make_float2(0.f, 0.f);
@@ -602,7 +622,7 @@ __device__ __forceinline__ void adj_cols_planes(const AdjColsArgs& a, int bx, in
 #pragma unroll
     for (int s = 0; s < P; ++s) {
       const float c = phase_cos(zc.x, zc.y, th[s]);
-      v[s] = COL0 && kx == 0 ? col0_filter(l, q + s * TC, c, rh[s]) : cscale(rh[s], c);
+      v[s] = COL0 && kx == 0 ? col0_filter(l, q, s, c, rh[s]) : cscale(rh[s], c);
     }
     col_fft<NY, W, true>(v, l, w, q);
     float2* dst = a.u + (size_t)j * NY * m + kx;
