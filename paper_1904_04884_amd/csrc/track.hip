@@ -56,8 +56,11 @@ constexpr int kDetThreads = 256;
 constexpr int kDetBlocks = 2048;             // most blocks of the numbering passes
 constexpr int kDetMaxBlocks = 1024;          // most blocks of the maximum
 constexpr int kDetWords = 8;                 // words a wavefront masks at a time (loads in flight)
+constexpr uint32_t kDetSplitWords = 1u << 16;   // up to here a word's runs go to eight threads
+constexpr int kDetManyRuns = 8;              // from here on they go to a wavefront
 constexpr int kLinkMaxCand = 8;              // candidates kept per source
 constexpr int kLinkMaxSubnet = 8;            // sources per subnetwork
+constexpr int kLinkOver = 0x100;             // on a count of candidates: there were more
 
 __device__ __forceinline__ uint32_t find_root(const uint32_t* lab, uint32_t i) {
   uint32_t p = lab[i];
@@ -191,53 +194,94 @@ __global__ void __launch_bounds__(kDetThreads) k_det_mask(const float* __restric
   }
 }
 
-// Unites the runs of a word with those they touch in the word before and in the
-// four neighbour rows of smaller index.  Bound by chains of dependent loads, so
-// a word's rows go to four threads; most words are empty.
-__global__ void __launch_bounds__(kDetThreads) k_det_union(const uint64_t* __restrict__ mask, MaskGeom g, uint32_t* lab) {
-  const int k = threadIdx.x & 3;   // (z, y - 1), then (z - 1, y - 1 .. y + 1)
+// Unites the run of row `row` that starts at bit st of word m (word wx of the row) with
+// those it touches in a neighbour row of smaller index, k = (z, y - 1), then
+// (z - 1, y - 1 .. y + 1); k = 0 also with the word before.
+__device__ __forceinline__ void unite_run(const uint64_t* mask, const MaskGeom& g, uint32_t* lab, uint32_t row, uint32_t wx,
+                                          uint64_t m, int st, int k) {
   const int dy = k == 0 ? -1 : k - 2, dz = k == 0 ? 0 : -1;
-  for (uint64_t i = ((uint64_t)blockIdx.x * kDetThreads + threadIdx.x) >> 2; i < g.words;
-       i += (uint64_t)gridDim.x * (kDetThreads / 4)) {
-    const uint64_t m = mask[i];
-    if (m == 0) continue;
-    const uint32_t row = (uint32_t)i / g.wpr, wx = (uint32_t)i % g.wpr;
-    const int y = (int)(row % g.ny), z = (int)(row / g.ny);
-    const bool left = wx > 0, right = wx + 1 < g.wpr;
-    if (k == 0 && (m & 1ull) && left) {
-      const uint64_t a = mask[i - 1];
-      if (a >> 63) unite(lab, label_of(g, row, wx * 64), label_of(g, row, (wx - 1) * 64 + run_start(a, 63)));
+  const int y = (int)(row % g.ny), z = (int)(row / g.ny);
+  const uint64_t run = run_bits(m, st);
+  const uint32_t l = label_of(g, row, wx * 64 + st);
+  const bool left = wx > 0 && (run & 1ull), right = wx + 1 < g.wpr && (run >> 63);
+  if (k == 0 && left) {
+    const uint64_t a = mask[(size_t)row * g.wpr + wx - 1];
+    if (a >> 63) unite(lab, l, label_of(g, row, (wx - 1) * 64 + run_start(a, 63)));
+  }
+  if (z + dz < 0 || y + dy < 0 || y + dy >= g.ny) return;
+  const uint32_t nr = (uint32_t)((int64_t)row + (int64_t)dz * g.ny + dy);
+  const uint64_t* nb = mask + (size_t)nr * g.wpr + wx;
+  const uint64_t c = nb[0];
+  for (uint64_t h = (run | (run << 1) | (run >> 1)) & c; h != 0;) {
+    const int s = run_start(c, __ffsll((unsigned long long)h) - 1);
+    h &= ~run_bits(c, s);
+    unite(lab, l, label_of(g, nr, wx * 64 + s));
+  }
+  if (left) {
+    const uint64_t a = nb[-1];
+    if (a >> 63) unite(lab, l, label_of(g, nr, (wx - 1) * 64 + run_start(a, 63)));
+  }
+  if (right && (nb[1] & 1ull)) unite(lab, l, label_of(g, nr, (wx + 1) * 64));
+}
+
+// Unites every run with those it touches in the word before and in the four neighbour
+// rows of smaller index.  Bound by chains of dependent loads, so a word's rows go to four
+// threads, and where that leaves the device part empty (kDetSplitWords) the runs that
+// start in its eighths to 2^ps = 8; most words are empty.  A word of many runs is taken
+// by the whole wavefront, a lane for each: neighbouring labels in one load.  512^2 x 128
+// with every other column set: 2.85 ms with four threads a word, 0.8 now; 64^2 x 40:
+// 255 us, 35 now.
+__global__ void __launch_bounds__(kDetThreads) k_det_union(const uint64_t* __restrict__ mask, MaskGeom g, int ps,
+                                                           uint32_t* lab) {
+  const int lane = threadIdx.x & 63, k = threadIdx.x & 3;
+  const int part = (threadIdx.x >> 2) & ((1 << ps) - 1), bits = 64 >> ps;
+  const uint64_t mine = (~0ull >> (64 - bits)) << (part * bits);   // where this thread's runs start
+  const uint32_t per = kDetThreads >> (2 + ps);
+  for (uint64_t i0 = (uint64_t)blockIdx.x * per; i0 < g.words; i0 += (uint64_t)gridDim.x * per) {
+    const uint64_t i = i0 + (threadIdx.x >> (2 + ps));
+    const uint64_t m = i < g.words ? mask[i] : 0ull, starts = m & ~(m << 1);
+    const bool many = __popcll(starts) > kDetManyRuns;
+    if (!many) {
+      const uint32_t row = (uint32_t)i / g.wpr, wx = (uint32_t)i % g.wpr;
+      for (uint64_t q = starts & mine; q != 0; q &= q - 1)
+        unite_run(mask, g, lab, row, wx, m, __ffsll((unsigned long long)q) - 1, k);
     }
-    if (z + dz < 0 || y + dy < 0 || y + dy >= g.ny) continue;
-    const uint32_t nr = (uint32_t)((int64_t)row + (int64_t)dz * g.ny + dy);
-    const uint64_t* nb = mask + (size_t)nr * g.wpr + wx;
-    const uint64_t c = nb[0];
-    const uint64_t a = (left && (m & 1ull)) ? nb[-1] : 0, d = (right && (m >> 63)) ? nb[1] : 0;
-    if (((m | (m << 1) | (m >> 1)) & c) == 0 && !(a >> 63) && !(d & 1ull)) continue;
-    for (uint64_t q = m; q != 0;) {
-      const int st = __ffsll((unsigned long long)q) - 1;
-      const uint64_t run = run_bits(m, st);
-      q &= ~run;
-      const uint32_t l = label_of(g, row, wx * 64 + st);
-      for (uint64_t h = (run | (run << 1) | (run >> 1)) & c; h != 0;) {
-        const int s = run_start(c, __ffsll((unsigned long long)h) - 1);
-        h &= ~run_bits(c, s);
-        unite(lab, l, label_of(g, nr, wx * 64 + s));
-      }
-      if ((run & 1ull) && (a >> 63)) unite(lab, l, label_of(g, nr, (wx - 1) * 64 + run_start(a, 63)));
-      if ((run >> 63) && (d & 1ull)) unite(lab, l, label_of(g, nr, (wx + 1) * 64));
+    for (uint64_t h = __ballot(many && part == 0 && k == 0); h != 0; h &= h - 1) {
+      const uint32_t w = (uint32_t)__shfl((int)(uint32_t)i, __ffsll((unsigned long long)h) - 1, 64);
+      const uint64_t mw = mask[w];
+      if (((mw & ~(mw << 1)) >> lane) & 1ull)
+        for (int kk = 0; kk < 4; ++kk) unite_run(mask, g, lab, w / g.wpr, w % g.wpr, mw, lane, kk);
     }
+  }
+}
+
+// f(x, label, whether it is a root) for the runs of word i in order, four label loads in
+// flight.
+template <class F>
+__device__ __forceinline__ void for_runs(const uint64_t m, const MaskGeom& g, const uint32_t* lab, uint64_t i, F f) {
+  const uint32_t row = (uint32_t)i / g.wpr, wx = (uint32_t)i % g.wpr;
+  for (uint64_t q = m & ~(m << 1); q != 0;) {
+    uint32_t x[4], l[4];
+    bool on[4], root[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      on[k] = q != 0;
+      x[k] = wx * 64 + (on[k] ? __ffsll((unsigned long long)q) - 1 : 0);
+      l[k] = label_of(g, row, x[k]);
+      q &= q - 1;   // (0 stays 0)
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) root[k] = on[k] && lab[l[k]] == l[k];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (on[k]) f(x[k], l[k], root[k]);
   }
 }
 
 // Roots among the runs of word i.
 __device__ __forceinline__ uint32_t roots_of(const uint64_t* mask, const MaskGeom& g, const uint32_t* lab, uint64_t i) {
-  const uint64_t m = mask[i];
   uint32_t c = 0;
-  for (uint64_t q = m & ~(m << 1); q != 0; q &= q - 1) {
-    const uint32_t l = label_of(g, (uint32_t)i / g.wpr, ((uint32_t)i % g.wpr) * 64 + __ffsll((unsigned long long)q) - 1);
-    c += lab[l] == l ? 1u : 0u;
-  }
+  for_runs(mask[i], g, lab, i, [&](uint32_t, uint32_t, bool root) { c += root ? 1u : 0u; });
   return c;
 }
 
@@ -291,15 +335,13 @@ __global__ void __launch_bounds__(kDetThreads) k_det_number(const uint64_t* __re
       tot += wsum[w];
     }
     if (c != 0) {
-      const uint32_t row = (uint32_t)i / g.wpr, wx = (uint32_t)i % g.wpr;
-      const uint64_t m = mask[i];
-      for (uint64_t q = m & ~(m << 1); q != 0; q &= q - 1) {
-        const uint32_t x = wx * 64 + __ffsll((unsigned long long)q) - 1, l = label_of(g, row, x);
-        if (lab[l] != l) continue;
+      const uint32_t row = (uint32_t)i / g.wpr;
+      for_runs(mask[i], g, lab, i, [&](uint32_t x, uint32_t l, bool root) {
+        if (!root) return;
         lab[l] = kRootMark | id;
         if (id < max_comp) first[id] = (uint32_t)((size_t)row * g.nx + x);
         ++id;
-      }
+      });
     }
     run += tot;
     __syncthreads();
@@ -307,18 +349,41 @@ __global__ void __launch_bounds__(kDetThreads) k_det_number(const uint64_t* __re
   if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) *total = run;
 }
 
+// Sums of the objects.  A block adds its runs per object in LDS (a hash table, emptied
+// into the objects' sums once at the end): where many runs of one object follow each
+// other, global atomics on the same few words take turns.  512^2 x 128 with every other
+// column of x set: 53 ms with five global atomics a run, 2.0 now; two frames of 1500
+// particles segmented, linked and numbered: 402 -> 365 us.
+// A thread takes the runs that start in a word (its eighths, as k_det_union).
+constexpr int kDetSlots = 512, kDetProbes = 8;
+
 __global__ void __launch_bounds__(kDetThreads) k_det_stats(const float* __restrict__ x, const uint64_t* __restrict__ mask,
-                                                           MaskGeom g, const uint32_t* __restrict__ lab,
+                                                           MaskGeom g, int ps, const uint32_t* __restrict__ lab,
                                                            uint32_t max_comp, uint32_t* cnt,
                                                            double* sums /* [4][max_comp]: w, wz, wy, wx */) {
-  for (uint64_t i = (uint64_t)blockIdx.x * kDetThreads + threadIdx.x; i < g.words; i += (uint64_t)gridDim.x * kDetThreads) {
-    const uint64_t m = mask[i];
+  __shared__ uint32_t s_id[kDetSlots], s_cnt[kDetSlots];
+  __shared__ double s_sum[4][kDetSlots];
+  const int part = threadIdx.x & ((1 << ps) - 1), bits = 64 >> ps;
+  const uint64_t mine = (~0ull >> (64 - bits)) << (part * bits);
+  bool clean = false;   // the table is set up by the first words with a run
+  for (uint64_t i0 = (uint64_t)blockIdx.x * (kDetThreads >> ps); i0 < g.words; i0 += (uint64_t)gridDim.x * (kDetThreads >> ps)) {
+    const uint64_t i = i0 + (threadIdx.x >> ps);
+    const uint64_t m = i < g.words ? mask[i] : 0ull;
+    if (!__syncthreads_or(m != 0)) continue;
+    if (!clean) {
+      clean = true;
+      for (int e = threadIdx.x; e < kDetSlots; e += kDetThreads) {
+        s_id[e] = ~0u;
+        s_cnt[e] = 0u;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s_sum[k][e] = 0.0;
+      }
+      __syncthreads();
+    }
     const uint32_t row = (uint32_t)i / g.wpr, wx = (uint32_t)i % g.wpr;
-    for (uint64_t q = m; q != 0;) {
+    for (uint64_t q = m & ~(m << 1) & mine; q != 0; q &= q - 1) {
       const int st = __ffsll((unsigned long long)q) - 1;
-      const uint64_t bits = run_bits(m, st);
-      q &= ~bits;
-      const int len = __popcll(bits);
+      const int len = __popcll(run_bits(m, st));
       const uint32_t x0 = wx * 64 + st;
       uint32_t l = lab[label_of(g, row, x0)];
       while (!(l & kRootMark)) l = lab[l];
@@ -336,12 +401,38 @@ __global__ void __launch_bounds__(kDetThreads) k_det_stats(const float* __restri
           sx += (double)v[b] * (double)(x0 + b0 + b);
         }
       }
-      atomicAdd(&cnt[id], (uint32_t)len);
-      unsafeAtomicAdd(&sums[id], sw);
-      unsafeAtomicAdd(&sums[max_comp + id], sw * (double)(row / g.ny));
-      unsafeAtomicAdd(&sums[2 * (size_t)max_comp + id], sw * (double)(row % g.ny));
-      unsafeAtomicAdd(&sums[3 * (size_t)max_comp + id], sx);
+      const double sz = sw * (double)(row / g.ny), sy = sw * (double)(row % g.ny);
+      uint32_t h = (id * 2654435761u) >> 23;   // 9 bits: kDetSlots
+      static_assert(kDetSlots == 512, "slots of the hash");
+      bool held = false;
+      for (int t = 0; t < kDetProbes && !held; ++t) {
+        h = (h + (t > 0)) & (kDetSlots - 1);
+        const uint32_t was = atomicCAS(&s_id[h], ~0u, id);
+        held = was == ~0u || was == id;
+      }
+      if (held) {
+        atomicAdd(&s_cnt[h], (uint32_t)len);
+        unsafeAtomicAdd(&s_sum[0][h], sw);
+        unsafeAtomicAdd(&s_sum[1][h], sz);
+        unsafeAtomicAdd(&s_sum[2][h], sy);
+        unsafeAtomicAdd(&s_sum[3][h], sx);
+      } else {   // more objects than slots
+        atomicAdd(&cnt[id], (uint32_t)len);
+        unsafeAtomicAdd(&sums[id], sw);
+        unsafeAtomicAdd(&sums[max_comp + id], sz);
+        unsafeAtomicAdd(&sums[2 * (size_t)max_comp + id], sy);
+        unsafeAtomicAdd(&sums[3 * (size_t)max_comp + id], sx);
+      }
     }
+  }
+  if (!clean) return;
+  __syncthreads();
+  for (int e = threadIdx.x; e < kDetSlots; e += kDetThreads) {
+    const uint32_t id = s_id[e];
+    if (id == ~0u) continue;
+    atomicAdd(&cnt[id], s_cnt[e]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) unsafeAtomicAdd(&sums[k * (size_t)max_comp + id], s_sum[k][e]);
   }
 }
 
@@ -414,6 +505,7 @@ k_link_candidates(const ri_object* __restrict__ prev, const int32_t* n0p, int ma
                   const int32_t* n1p, int max_n1, double sz, double sy, double sx, double r2, LinkWs w, int32_t* link,
                   int32_t* status) {
   const int n0 = min(*n0p, max_n0), n1 = min(*n1p, max_n1);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *status = 0;   // (set by the launches that follow)
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < max_n0 + max_n1; i += gridDim.x * blockDim.x)
     w.parent[i] = (uint32_t)i;
   const int lane = threadIdx.x & 63;
@@ -458,17 +550,20 @@ k_link_candidates(const ri_object* __restrict__ prev, const int32_t* n0p, int ma
     w.cand[(size_t)i * kLinkMaxCand + lane] = cj;
     w.cand_d2[(size_t)i * kLinkMaxCand + lane] = cd;
   }
-  if (lane == 0) {
-    if (over) atomicOr(status, 2);
-    w.ncand[i] = nc;
-  }
+  if (lane == 0) w.ncand[i] = over ? nc | kLinkOver : nc;
 }
 
-__global__ void k_link_union(const int32_t* n0p, int max_n0, LinkWs w) {
+__global__ void k_link_union(const int32_t* n0p, int max_n0, LinkWs w, int32_t* status) {
   const int n0 = min(*n0p, max_n0);
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n0) return;
-  for (int k = 0; k < w.ncand[i]; ++k) unite(w.parent, (uint32_t)i, (uint32_t)(max_n0 + w.cand[(size_t)i * kLinkMaxCand + k]));
+  int nc = w.ncand[i];
+  if (nc & kLinkOver) {
+    atomicOr(status, 2);
+    nc &= ~kLinkOver;
+    w.ncand[i] = nc;
+  }
+  for (int k = 0; k < nc; ++k) unite(w.parent, (uint32_t)i, (uint32_t)(max_n0 + w.cand[(size_t)i * kLinkMaxCand + k]));
 }
 
 // Every source's subnetwork root (its smallest source) in its parent word.
@@ -639,7 +734,8 @@ DetLayout det_layout(int nx, int ny, int nz, size_t max_comp) {
   const size_t per = (words + kDetBlocks - 1) / kDetBlocks;
   L.chunk = (uint32_t)((per + kDetThreads - 1) / kDetThreads * kDetThreads);
   L.nblk = (unsigned)((words + L.chunk - 1) / L.chunk);
-  const size_t nb = (n + 16 * kDetThreads - 1) / (16 * kDetThreads);
+  // (it also clears the object sums, 9 words a component)
+  const size_t nb = (n + 9 * max_comp + 16 * kDetThreads - 1) / (16 * kDetThreads);
   L.nparts = (int)(nb < (size_t)kDetMaxBlocks ? nb : (size_t)kDetMaxBlocks);
   L.lab = take(rows * L.g.hx * 4);
   L.mask = take(words * 8);
@@ -706,13 +802,15 @@ extern "C" ri_status ri_detect(const ri_detect_params* prm, const float* x, int3
   hipStream_t s = (hipStream_t)stream;
   const uint32_t mc = (uint32_t)max_components;
   hipError_t e;
-  const dim3 b(kDetThreads), gw(grid_for(L.g.words)), gm(grid_for((size_t)L.g.words * (64 / kDetWords)));
+  const dim3 b(kDetThreads), gm(grid_for((size_t)L.g.words * (64 / kDetWords)));
   hipLaunchKernelGGL(k_det_max, dim3(L.nparts), b, 0, s, x, n, part, cnt, sums, (size_t)mc);
   hipLaunchKernelGGL(k_det_mask, gm, b, 0, s, x, L.g, part, L.nparts, prm->rel_threshold, mask, lab);
-  hipLaunchKernelGGL(k_det_union, dim3(grid_for((size_t)L.g.words * 4)), b, 0, s, mask, L.g, lab);
+  const int ps = L.g.words <= kDetSplitWords ? 3 : 0;
+  hipLaunchKernelGGL(k_det_union, dim3(grid_for((size_t)L.g.words << (2 + ps))), b, 0, s, mask, L.g, ps, lab);
   hipLaunchKernelGGL(k_det_count_roots, dim3(L.nblk), b, 0, s, mask, L.g, lab, L.chunk, bcounts);
   hipLaunchKernelGGL(k_det_number, dim3(L.nblk), b, 0, s, mask, L.g, lab, L.chunk, bcounts, mc, first, total);
-  hipLaunchKernelGGL(k_det_stats, gw, b, 0, s, x, mask, L.g, lab, mc, cnt, sums);
+  const dim3 gw(grid_for((size_t)L.g.words << ps));
+  hipLaunchKernelGGL(k_det_stats, gw, b, 0, s, x, mask, L.g, ps, lab, mc, cnt, sums);
   hipLaunchKernelGGL(k_det_finalize, dim3(1), dim3(kDetThreads), 0, s, cnt, sums, first, total, mc, prm->min_voxels,
                      objects, max_objects, counts);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "detect launch");
@@ -746,13 +844,12 @@ extern "C" ri_status ri_link(const ri_object* prev, const int32_t* n_prev, int32
   w.parent = reinterpret_cast<uint32_t*>(base + off);
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(status), (size_t)1, 0u);
   const double r2 = max_disp * max_disp;
   const int nbw = (max_prev + kDetThreads / 64 - 1) / (kDetThreads / 64);   // a wavefront per source
   hipLaunchKernelGGL(k_link_candidates, dim3(nbw), dim3(kDetThreads), 0, s, prev, n_prev, max_prev, cur, n_cur, max_cur,
                      spacing[0], spacing[1], spacing[2], r2, w, link, status);
   const int nb0 = (max_prev + kDetThreads - 1) / kDetThreads;
-  hipLaunchKernelGGL(k_link_union, dim3(nb0), dim3(kDetThreads), 0, s, n_prev, max_prev, w);
+  hipLaunchKernelGGL(k_link_union, dim3(nb0), dim3(kDetThreads), 0, s, n_prev, max_prev, w, status);
   hipLaunchKernelGGL(k_link_roots, dim3(nb0), dim3(kDetThreads), 0, s, n_prev, max_prev, w);
   hipLaunchKernelGGL(k_link_solve, dim3(nbw), dim3(kDetThreads), 0, s, n_prev, max_prev, r2, w, link, status);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "link launch");
