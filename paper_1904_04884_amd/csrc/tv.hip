@@ -222,11 +222,17 @@ int tv_pass_zchunk(int nx, int ny, int nz, int levels, int blocks, int cus, int 
 // pipeline of its kernel's depth, or its blocks are short of planes.  12 steps in 3D,
 // pipeline and sequential: 128^2 x 6 (6 planes) depth 3 59 and 54 us, 64^2 x 8 69 and
 // 66, but 128^2 x 32 (13 planes) 97 and 100, 192^2 x 48 127 and 140; at depth 4, whose
-// phases idle longer, 128^2 x 32 159 and 150, 192^2 x 48 (18 planes) 184 and 178.
+// phases idle longer, 128^2 x 32 159 and 150, 192^2 x 48 (18 planes) 184 and 178.  The
+// one pass of a prox of up to 3 steps gains more, as its dual is known to be zero: 3D, 2
+// steps, 512^2 x 24 49 and 43, 512^2 x 128 218 and 186, 1024^2 x 64 356 and 324; 3 steps
+// 83 and 75, 290 and 281, 396 and 376; in 2D, 3 steps, 768^2 x 30 94 and 89, 512^2 x 40 99
+// and 99, but 1024^2 x 64 318 and 328; 4 steps (depth 4) 512^2 x 40 162 and 170.
 static bool pass_is_seq(const ProxArgs& a, bool fin, int depth, int steps, int zchunk) {
-  if (!tv_has_seq(depth, fin)) return false;
+  if (!tv_has_seq(depth, fin, a.low && !a.rs.on)) return false;
   if (steps < depth) return true;
-  return a.low && std::min(a.nz, zchunk + (a.tv2 ? 0 : 2 * (steps + 1))) <= (depth > 3 ? 24 : 10);
+  int most = depth > 3 ? 24 : 10;
+  if (fin && depth < 4 && steps == a.inner_iters && !a.warm) most = a.tv2 ? 40 : a.nz;
+  return a.low && std::min(a.nz, zchunk + (a.tv2 ? 0 : 2 * (steps + 1))) <= most;
 }
 
 // Argument structs of every pass of one prox application.  Every pass takes

@@ -210,8 +210,8 @@ enum TvForm { TV_PIPE, TV_SEQ, TV_SEQ_FIRST };
 __host__ __device__ constexpr int tv_py_slots(int LV, TvForm F) { return F == TV_PIPE && tv_lean(LV) ? 1 : 2; }
 // Slots of the v ring: back to the last step's plane, on the final pass to the
 // output plane.
-template <int LV, bool FINAL>
-__host__ __device__ constexpr int tv_ring() { return FINAL ? tv_delay(LV) + 1 : tv_delay(LV); }
+template <int LV, bool FINAL, bool SEQ>
+__host__ __device__ constexpr int tv_ring() { return FINAL ? (SEQ ? LV : tv_delay(LV)) + 1 : tv_delay(LV); }
 
 // Bound on a wave's wait for another segment to publish a row-store index
 // (about 2^20 * 128 clocks; the publisher needs a few hundred).
@@ -307,14 +307,14 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
   }
   // ||x||_1 and TV(x) of the thread's voxels (objective pieces), and what their
   // additions dropped
-  constexpr bool SUMS = FINAL && LEAN;
+  constexpr bool SUMS = FINAL && LEAN, LOS = SUMS && !SEQ;   // (the second s_py slots of SEQ take the room)
   double r_sum[2];
   float r_lo[2];
   double& x_sum = *(SUMS ? s_sum + threadIdx.x : r_sum);
   double& tv_sum = *(SUMS ? s_sum + NT + threadIdx.x : r_sum + 1);
   float* const s_lo = reinterpret_cast<float*>(s_sum + 2 * NT);
-  float& x_lo = *(SUMS ? s_lo + threadIdx.x : r_lo);
-  float& tv_lo = *(SUMS ? s_lo + NT + threadIdx.x : r_lo + 1);
+  float& x_lo = *(LOS ? s_lo + threadIdx.x : r_lo);
+  float& tv_lo = *(LOS ? s_lo + NT + threadIdx.x : r_lo + 1);
   x_sum = tv_sum = 0.0;
   x_lo = tv_lo = 0.f;
   // terms of the plane held in Xp; xn: the next plane (hz: it exists), slot:
@@ -397,7 +397,7 @@ __device__ __forceinline__ void tv_pass_body(const TvPassArgs& A, int bx, int by
       }
     }
   };
-  constexpr int NS = tv_ring<LV, FINAL>();
+  constexpr int NS = tv_ring<LV, FINAL, SEQ>();
   auto vring = [&](int a) __attribute__((always_inline)) -> TvVec<Q>& { return s_v[(a % NS) * NT + threadIdx.x]; };
 
   // Arrival of the previous dual c3 at plane a for fused step l: u(a), then
@@ -860,11 +860,11 @@ template <int HT, int LV, int Q, bool SEQ, bool FINAL, bool TV2, bool FGP, bool 
 __device__ __forceinline__ void tv_pass_entry(const TvPassArgs& A, int bx, int by, int zb, int ze, int blk) {
   __shared__ float s_py[LV + 1][tv_py_slots(LV, SEQ ? TV_SEQ : TV_PIPE)][kTvWaves][64];  // bottom-row p_y per wave, per step (+ final)
   __shared__ float s_ut[LV][2][kTvWaves][64];      // top-row u per wave, per step, parity
-  __shared__ TvVec<Q> s_v[tv_ring<LV, FINAL>() * kTvWaves * 64];  // v ring, thread-private
+  __shared__ TvVec<Q> s_v[tv_ring<LV, FINAL, SEQ>() * kTvWaves * 64];  // v ring, thread-private
   __shared__ float s_x[FINAL ? 2 : 1][kTvWaves][64];     // final pass: first-row x per wave, parity
   __shared__ double s_red[4][kTvWaves];            // final pass: per-wave sums
   __shared__ float s_fin[FINAL ? 2 * Q * kTvWaves * 64 : 1];    // final pass: PzF, Xp (thread-private)
-  __shared__ double s_sum[FINAL && tv_lean(LV) ? 3 * kTvWaves * 64 : 1];   // final pass: sums (thread-private)
+  __shared__ double s_sum[FINAL && tv_lean(LV) ? (SEQ ? 2 : 3) * kTvWaves * 64 : 1];   // final pass: sums (thread-private)
   // the stop flag read once per wave (a wave-uniform branch)
   if (A.st != nullptr && __builtin_amdgcn_readfirstlane(A.st->done)) return;
   constexpr int RY = kTvWaves * Q, IX = kTvRX - 2 * HT, IY = RY - 2 * HT;
@@ -1026,9 +1026,12 @@ static void launch_tv_kernel(bool batch, dim3 g, const TvPassArgs* a, const Batc
   if (batch) launch_batched<H, SEQ, FINAL, TV2, FGP, BF, SP>(g, a, map, s);
   else hipLaunchKernelGGL((k_tv_pass<H, SEQ, FINAL, TV2, FGP, BF, SP>), g, dim3(kTvWaves * 64), 0, s, *a);
 }
-// Forms that exist: the final pass of depth 4 has no room for the second s_py slots of
-// SEQ, and a step of FGP never fills the pipeline.
-__host__ __device__ constexpr bool tv_has_seq(int H, bool final_pass) { return H < kTvLevelsMax || !final_pass; }
+// Forms that exist: a step of FGP never fills the pipeline, and the final pass of depth 4
+// takes SEQ only for few planes, in a launch of its own on dense iterates (a row store
+// would spill).
+__host__ __device__ constexpr bool tv_has_seq(int H, bool final_pass, bool single_dense) {
+  return H < kTvLevelsMax || !final_pass || single_dense;
+}
 
 template <int H, bool SEQ, bool TV2>
 static void launch_tv_dim(const TvSelect& k, dim3 g, const TvPassArgs* a, const BatchMap& map, hipStream_t s) {
@@ -1041,7 +1044,11 @@ static void launch_tv_dim(const TvSelect& k, dim3 g, const TvPassArgs* a, const 
     }
   }
   if (k.final_pass) {
-    if constexpr (!SEQ || tv_has_seq(H, true)) {
+    if constexpr (SEQ && H == kTvLevelsMax) {
+      const dim3 b(kTvWaves * 64);
+      if (k.bf16) hipLaunchKernelGGL((k_tv_pass<H, SEQ, true, TV2, false, true, false>), g, b, 0, s, *a);
+      else hipLaunchKernelGGL((k_tv_pass<H, SEQ, true, TV2, false, false, false>), g, b, 0, s, *a);
+    } else {
       if (k.sparse && !k.bf16) launch_tv_kernel<H, SEQ, true, TV2, false, false, true>(k.batch, g, a, map, s);
       else if (k.bf16) launch_tv_kernel<H, SEQ, true, TV2, false, true, false>(k.batch, g, a, map, s);
       else launch_tv_kernel<H, SEQ, true, TV2, false, false, false>(k.batch, g, a, map, s);
