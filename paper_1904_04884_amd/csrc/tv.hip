@@ -42,7 +42,12 @@ extern template void launch_tv_depth<4>(const TvSelect&, dim3, const TvPassArgs*
 // round spills into another), and whole tiles where the leftovers of a round are split.
 // In 2D, with no margin to redo, chunks of 16 planes or less.  One step, z cuts 1, 2, 4,
 // 8: 512^2 x 128 3D 210, 114, 124, 135 us; 768^2 x 50 97, 129, 138, 170; 1024^2 x 64 233,
-// 234, 265, 307; in 2D 214, 190, 181, 193.
+// 234, 265, 307; in 2D 214, 190, 181, 193.  So does the only pass of a prox, whose dual
+// is zero (2 steps in 2D, 1024^2 x 64: 275 us with the cut of full passes, 244).  With up
+// to 2 steps such passes run at depth 2 or, where that needs no longer march, at depth 3:
+// its tiles store 224 bytes of a row, whole 32-byte sectors, those of depth 2 232.  Two
+// steps, depth 2 and 3: 1024^2 x 16 3D 82 and 75 us, 2D 73 and 67; 768^2 x 30 3D 95 and
+// 89; but 512^2 x 24 (one round and two) 42 and 55.
 struct TvGrid {
   int gx, gy, zchunk, nfull, zchunk2, nblocks, low;
   double cost;
@@ -182,9 +187,19 @@ static TvGrid final_grid_of(const ProxArgs& a, const TvProxShape& h, int* depth 
     cut.low = false;
   }
   const TvPassShape p = prox_pass_shape(a.inner_iters, a.step * a.tv, a.levels, a.fgp != 0, h.npass - 1);
-  cut.partial = p.partial ? p.steps : -1;
+  const bool only = h.npass == 1 && !a.warm && p.depth < kTvLevelsMax;
+  cut.partial = p.partial || only ? p.steps : -1;
   if (depth) *depth = p.depth;
-  return final_grid(a.nx, a.ny, a.nz, p.depth, a.cus, cut);
+  const TvGrid g = final_grid(a.nx, a.ny, a.nz, p.depth, a.cus, cut);
+  if (a.fgp || p.depth != 2 || cut.partial < 0 || !cut.alone) return g;
+  const TvGrid g3 = final_grid(a.nx, a.ny, a.nz, 3, a.cus, cut);
+  auto march = [&](const TvGrid& t) {
+    const int rounds = (t.nblocks + cut.fill - 1) / std::max(1, cut.fill);
+    return (long)rounds * (std::min(a.nz, t.zchunk + (a.tv2 ? 0 : 2 * (p.steps + 1))) + p.steps + 2);
+  };
+  if (march(g3) > march(g)) return g;
+  if (depth) *depth = 3;
+  return g3;
 }
 static bool grouped(const ProxArgs& a) { return a.tv2 && a.group_planes > 0 && a.group_planes < a.nz; }
 
