@@ -35,7 +35,7 @@
  *     a status; on failure nothing has been launched and ri_last_error() holds
  *     a thread-local message.  HIP runtime failures map to RI_ERR_HIP.
  *   - Supported sizes: nx and ny of the form 2^a or 3 * 2^a, 16 <= nx <= 2048,
- *     16 <= ny <= 2048; nz >= 1.
+ *     16 <= ny <= 2048, but nx = 24; nz >= 1.
  */
 #ifndef RIHVR_H
 #define RIHVR_H
@@ -64,7 +64,7 @@ typedef enum {
  * defects from FP32 rounding (it agrees with the FP64 reference to ~1e-12):
  * the same model from the same FP64 tables, but with plain complex transforms
  * of whole planes (every plane's spectrum held in the workspace), the
- * gradient-projection prox one step per two passes over memory, and the FISTA
+ * gradient-projection prox up to two steps a pass over memory, and the FISTA
  * scalars, objective and stop tests on the host (ri_solve synchronises once
  * per outer iteration when a gap stop or the restart needs the objective, and
  * evaluates the objective of the returned iterate for the report; no graph,
@@ -95,7 +95,7 @@ typedef enum { RI_F32 = 0, RI_F64 = 1 } ri_dtype;
                                or with RI_TV2D per plane); prox = (1 - t l1/|u|)_+ u of the
                                complex TV prox u, computed by gradient projection on a
                                complex dual (one complex value per direction, projected
-                               jointly), one step per two passes over memory.  ||A||^2 = nz.
+                               jointly), up to three steps a pass over memory.  ||A||^2 = nz.
                                nonneg must be 0.  Not combinable with RI_TV_FGP or
                                RI_TV_DUAL_BF16; ri_solve rejects RI_SOLVE_DUAL_WARM and row
                                stores, ri_solve_batched and ri_plan_autotune reject the plan

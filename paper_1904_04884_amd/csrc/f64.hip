@@ -226,7 +226,7 @@ void launch_fft(Fft64Args f, int planes, hipStream_t s) {
   f.N = COL ? f.t.ny : f.t.nx;
   f.tw = COL ? f.t.tw_y : f.t.tw_x;
   const int lines = (COL ? f.t.nx : f.t.ny) * planes;
-  f.group = fft_group(f.N, lines);   // nx and ny are multiples of 16
+  f.group = fft_group(f.N, lines);   // divides lines: nx and ny are multiples of 8
   hipLaunchKernelGGL((k64_fft<COL, IN>), dim3(lines / f.group), dim3(kFThreads),
                      2 * (size_t)f.N * f.group * sizeof(double2), s, f);
 }

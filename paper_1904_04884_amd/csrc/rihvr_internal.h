@@ -44,9 +44,11 @@ __device__ __forceinline__ T* pick3(T* a, T* b, T* c, int i) {
 // control decisions (momentum, stop, buffer rotation) are taken on the device
 // so that one iteration can be replayed as a HIP graph.
 #ifdef __HIPCC__
-// Sums whose rounding does not depend on how the terms are grouped: the running
-// sum and what its additions dropped.  A frame's objective must not change with
-// the grid that its passes ran on (alone, or sharing the device with a batch).
+// Compensated sums: the running sum and what its additions dropped (kept in FP32 by the
+// threads, whose rounding is about 2^-24 of the dropped parts, 2^-77 of the sum).  A
+// frame's objective should not change with the grid that its passes ran on (alone, or
+// sharing the device with a batch): it has the same bits unless the sum lies that close
+// to a rounding boundary of FP64.
 template <class L>
 __device__ __forceinline__ void add_exact(double& hi, L& lo, double v) {
   const double s = hi + v, b = s - hi;
