@@ -315,15 +315,13 @@ __device__ __forceinline__ float2 buf_ld2(__amdgpu_buffer_rsrc_t r, unsigned off
 // would run a second phase for each of its points: the grid is only about two
 // blocks per CU, so these blocks set its end (A at 512^2 x 128: 156 us with the
 // second phase in the lanes, 148 shared out).  theta is read once (a global load in
-// the loop would wait for the next plane's tile in flight: 177 us), into LDS where 8
-// points a thread hold the block to 128 VGPRs, else into registers.
-__host__ __device__ constexpr bool kThetaLds(int ny) { return kColP(ny) <= 8; }
+// the loop would wait for the next plane's tile in flight: 177 us), by the forward pass
+// into LDS where 8 points a thread hold the block to 128 VGPRs, else into registers.
 template <int NY, int W>
 struct ColLds {
   float2 buf[fft_buf_len(NY, kColP(NY)) * W];
   float2 tw[NY];
   float2 c0[NY];
-  double thn[kThetaLds(NY) ? NY : 1];
   float cn[NY];
 };
 template <int NY, int W, bool INV>
@@ -339,27 +337,26 @@ __device__ __forceinline__ void col0_put(const float2 (&v)[kColP(NY)], ColLds<NY
     if (w == 0) l.c0[q + s * TC] = v[s];
 }
 // A thread's share of the Nyquist column: theta, and the filter of a plane.
-template <int NY, int W>
+template <int NY, int W, bool LDS>
 struct NyquistShare {
   static constexpr int NT = W * NY / kColP(NY), N = (NY + NT - 1) / NT;
-  static constexpr bool LDS = kThetaLds(NY);
   double th[LDS ? 1 : N];
-  __device__ __forceinline__ void load(ColLds<NY, W>& l, const PlanTables& pt, int m) {
+  __device__ __forceinline__ void load(double* thn, const PlanTables& pt, int m) {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int y = threadIdx.x + i * NT;
       const double v = y < NY ? pt.theta[(size_t)y * (m + 1) + m] : 0.0;
       if constexpr (!LDS) th[i] = v;
-      else if (y < NY) l.thn[y] = v;
+      else if (y < NY) thn[y] = v;
     }
   }
-  __device__ __forceinline__ void put(ColLds<NY, W>& l, double2 zc) const {
+  __device__ __forceinline__ void put(ColLds<NY, W>& l, const double* thn, double2 zc) const {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int y = threadIdx.x + i * NT;
       if (y >= NY) continue;
       double t;
-      if constexpr (LDS) t = l.thn[y];   // (written by this thread)
+      if constexpr (LDS) t = thn[y];   // (written by this thread)
       else t = th[i];
       l.cn[y] = phase_cos(zc.x, zc.y, t);
     }
@@ -400,7 +397,7 @@ __device__ __forceinline__ void stage_twiddles(ColLds<NY, W>& l, const float2* _
 // every row flag is read from global memory.  COL0: the block holding column 0.
 template <int NY, bool PF, bool COL0>
 __device__ __forceinline__ void fwd_cols_planes(const FwdColsArgs& a, int bx, int by, ColLds<NY, kColW(NY)>& l, uint32_t* lds_fl,
-                                                uint8_t* s_pf) {
+                                                uint8_t* s_pf, double* s_thn) {
   const PlanTables& pt = a.pt;
   constexpr int P = kColP(NY), TC = NY / P, W = kColW(NY);
   constexpr int NFW = NY / 4;          // dwords of row flags per plane
@@ -424,8 +421,8 @@ __device__ __forceinline__ void fwd_cols_planes(const FwdColsArgs& a, int bx, in
   if (pflags)
     for (int i = threadIdx.x; i < min(j1 - j0, kColPlaneFlags); i += blockDim.x) s_pf[i] = a.planeflag[j0 + i];
   stage_twiddles(l, pt.tw_col);
-  NyquistShare<NY, W> ny;
-  if constexpr (COL0) ny.load(l, pt, m);
+  NyquistShare<NY, W, PF> ny;
+  if constexpr (COL0) ny.load(s_thn, pt, m);
   __syncthreads();
   auto next_plane = [&](int j) {
     if (pflags)
@@ -441,7 +438,7 @@ __device__ __forceinline__ void fwd_cols_planes(const FwdColsArgs& a, int bx, in
     // offsets first (the flag bytes are read even when unused), then the loads
     unsigned o[P];
     int qt = q;
-    if constexpr (COL0) asm volatile("" : "+v"(qt));   // the rows' addresses anew each plane: kept, they spill
+    if constexpr (COL0 && PF) asm volatile("" : "+v"(qt));   // the rows' addresses anew each plane: kept, they spill
 #pragma unroll
     for (int s = 0; s < P; ++s) {
       const int y = qt + s * TC;
@@ -455,7 +452,7 @@ __device__ __forceinline__ void fwd_cols_planes(const FwdColsArgs& a, int bx, in
   // the plane's tile transformed, filtered, and added to the sums
   auto accumulate = [&](int j, float2 (&v)[P]) {
     const double2 zc = pt.zc[j];
-    if constexpr (COL0) ny.put(l, zc);   // the last reads are a barrier or more back
+    if constexpr (COL0) ny.put(l, s_thn, zc);   // the last reads are a barrier or more back
     col_fft<NY, W, false>(v, l, w, q);
     if constexpr (COL0) {
       col0_put(v, l, w, q);
@@ -521,9 +518,10 @@ __device__ __forceinline__ void fwd_cols_body(const FwdColsArgs& a, int bx, int 
   __shared__ ColLds<NY, kColW(NY)> l;
   __shared__ uint32_t lds_fl[PF ? NY / 4 : 1];
   __shared__ uint8_t s_pf[kColPlaneFlags];
+  __shared__ double s_thn[PF ? NY : 1];
   if (solve_done(a.st)) return;
-  if (bx == 0) fwd_cols_planes<NY, PF, true>(a, bx, by, l, lds_fl, s_pf);
-  else fwd_cols_planes<NY, PF, false>(a, bx, by, l, lds_fl, s_pf);
+  if (bx == 0) fwd_cols_planes<NY, PF, true>(a, bx, by, l, lds_fl, s_pf, s_thn);
+  else fwd_cols_planes<NY, PF, false>(a, bx, by, l, lds_fl, s_pf, s_thn);
 }
 
 // ---------------------------------------------------------------------------
@@ -599,8 +597,8 @@ __device__ __forceinline__ void adj_cols_planes(const AdjColsArgs& a, int bx, in
   const int kx = bx * W + w;
   const bool colok = kx < m;
   stage_twiddles(l, pt.tw_col);
-  NyquistShare<NY, W> ny;
-  if constexpr (COL0) ny.load(l, pt, m);
+  NyquistShare<NY, W, false> ny;
+  if constexpr (COL0) ny.load(nullptr, pt, m);
   float2 rh[P];
 #pragma unroll
   for (int s = 0; s < P; ++s) rh[s] = colok ? a.th[(size_t)(q + s * TC) * m + kx] : make_float2(0.f, 0.f);
@@ -615,7 +613,7 @@ __device__ __forceinline__ void adj_cols_planes(const AdjColsArgs& a, int bx, in
   for (int j = j0; j < j1; ++j) {
     const double2 zc = pt.zc[j];
     if constexpr (COL0) {
-      ny.put(l, zc);
+      ny.put(l, nullptr, zc);
       __syncthreads();   // (the next put comes after the transform's barriers)
     }
     float2 v[P];
