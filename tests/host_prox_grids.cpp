@@ -2,19 +2,21 @@
 // (flags: 1 per-plane 2D TV, 2 FGP, 4 bfloat16 dual, 8 row store, 16 low tiles
 // allowed; a device of 256 units), the partials that the scalars add up, the blocks
 // of the prox's final passes, the bound of both, and the planes per block of its
-// first pass.
+// first pass.  Argument: dual steps (7).
 #include <cstdio>
+#include <cstdlib>
 
 #include "tv_device.h"
 
 using namespace rihvr;
 
-int main() {
+int main(int argc, char** argv) {
+  const int steps = argc > 1 ? std::atoi(argv[1]) : 7;
   int nx, ny, nz, levels, blocks, fill, flags, group;
   while (std::scanf("%d %d %d %d %d %d %d %d", &nx, &ny, &nz, &levels, &blocks, &fill, &flags, &group) == 8) {
     ProxArgs a{};
     a.nx = nx; a.ny = ny; a.nz = nz;
-    a.inner_iters = 7;
+    a.inner_iters = steps;
     a.step = 0.5; a.tv = 0.5;
     a.levels = levels; a.blocks = blocks; a.cus = 256; a.fill = fill;
     a.tv2 = flags & 1; a.fgp = (flags >> 1) & 1; a.dual_bf16 = (flags >> 2) & 1;

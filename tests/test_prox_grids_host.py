@@ -24,9 +24,9 @@ def grids(tmp_path_factory):
                     "-I", str(build_lib.CSRC), "-c", os.path.join(HERE, "host_prox_grids.cpp"), "-o", obj], check=True)
     subprocess.run([hipcc, obj, str(lib), f"-Wl,-rpath,{lib.parent}", "-o", str(exe)], check=True)
 
-    def run(rows):
+    def run(rows, steps=7):
         text = "\n".join(" ".join(map(str, r)) for r in rows)
-        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout
+        out = subprocess.run([str(exe), str(steps)], input=text, capture_output=True, text=True, check=True).stdout
         return [tuple(map(int, line.split())) for line in out.splitlines()]
     return run
 
@@ -42,6 +42,23 @@ def test_partials_counted_are_those_written(grids):
     out = grids(rows)
     assert len(out) == len(rows)
     for row, (counted, written, bound, _) in zip(rows, out):
+        assert counted == written <= bound, row
+
+
+@pytest.mark.parametrize("steps", (0, 1, 2, 3, 4, 5, 8))
+def test_partials_of_short_proxes(grids, steps):
+    """Proxes of one pass, and of a last pass with few steps, which choose cut, depth and form
+    by rules of their own."""
+    xy = [(16, 16), (48, 32), (64, 64), (128, 128), (512, 64), (512, 512), (768, 384), (768, 768), (1024, 384),
+          (1024, 1024), (2048, 512), (2048, 2048)]
+    kinds = [f | t for t in (0, TV2D) for f in (LOW, FGP | LOW, BF16 | LOW, ROWS | LOW, 0)]
+    rows = [(nx, ny, nz, lv, tb, fill, fl, 0)
+            for (nx, ny), nz, lv, (tb, fill), fl in itertools.product(
+                xy, (1, 2, 8, 15, 16, 17, 24, 31, 64, 100, 256), (2, 3, 4),
+                ((1536, 256), (64, 256), (65536, 256), (1536, 85), (1536, 1)), kinds)]
+    rows += [(nx, ny, nz, lv, 1536, 256, TV2D | f, g)
+             for (nx, ny), (nz, g), lv, f in itertools.product(xy, ((17, 4), (32, 1), (100, 33)), (2, 3, 4), (LOW, BF16))]
+    for row, (counted, written, bound, _) in zip(rows, grids(rows, steps)):
         assert counted == written <= bound, row
 
 
