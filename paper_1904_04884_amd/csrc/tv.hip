@@ -43,11 +43,14 @@ extern template void launch_tv_depth<4>(const TvSelect&, dim3, const TvPassArgs*
 // In 2D, with no margin to redo, chunks of 16 planes or less.  One step, z cuts 1, 2, 4,
 // 8: 512^2 x 128 3D 210, 114, 124, 135 us; 768^2 x 50 97, 129, 138, 170; 1024^2 x 64 233,
 // 234, 265, 307; in 2D 214, 190, 181, 193.  So does the only pass of a prox, whose dual
-// is zero (2 steps in 2D, 1024^2 x 64: 275 us with the cut of full passes, 244).  With up
-// to 2 steps such passes run at depth 2 or, where that needs no longer march, at depth 3:
-// its tiles store 224 bytes of a row, whole 32-byte sectors, those of depth 2 232.  Two
-// steps, depth 2 and 3: 1024^2 x 16 3D 82 and 75 us, 2D 73 and 67; 768^2 x 30 3D 95 and
-// 89; but 512^2 x 24 (one round and two) 42 and 55.
+// is zero (2 steps in 2D, 1024^2 x 64: 275 us with the cut of full passes, 244).
+//
+// With up to 2 steps such passes run at depth 2 or, where that needs no longer march (in
+// 2D, where memory weighs more, a tenth longer), at depth 3: its tiles store 224 bytes of
+// a row, whole 32-byte sectors, those of depth 2 232.  Two steps, depth 2 and 3: 1024^2 x
+// 16 3D 82 and 75 us, 2D 73 and 67; 768^2 x 30 3D 95 and 89; but 512^2 x 24 (one round and
+// two) 42 and 55.  One step in 2D: 1024 x 384 x 100 129 and 117, 1024^2 x 64 188 and 178;
+// 512^2 x 128 (a march of 76 and 90) 95 and 105; without a step 1024^2 x 64 141 and 148.
 struct TvGrid {
   int gx, gy, zchunk, nfull, zchunk2, nblocks, low;
   double cost;
@@ -197,7 +200,7 @@ static TvGrid final_grid_of(const ProxArgs& a, const TvProxShape& h, int* depth 
     const int rounds = (t.nblocks + cut.fill - 1) / std::max(1, cut.fill);
     return (long)rounds * (std::min(a.nz, t.zchunk + (a.tv2 ? 0 : 2 * (p.steps + 1))) + p.steps + 2);
   };
-  if (march(g3) > march(g)) return g;
+  if (10 * march(g3) > (a.tv2 && p.steps > 0 ? 11 : 10) * march(g)) return g;
   if (depth) *depth = 3;
   return g3;
 }
