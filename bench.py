@@ -533,7 +533,7 @@ def complex_leg(torch, rihvr, scenes, g, cfg, sc, iters=8):
                "prox_bytes_model": "56 B per complex voxel per launch of up to three dual steps + 40 B final",
                "objective": rep["objective"]}
         log(f"complex object: {out['ms_per_iter']:.1f} ms per iteration (prox {ph_ms['prox']:.1f} ms, "
-            f"{out['prox_GB_per_s']:.0f} GB/s by the two-steps-per-launch byte model)")
+            f"{out['prox_GB_per_s']:.0f} GB/s by the byte model of three steps a launch)")
         return out
     finally:
         p.close()
